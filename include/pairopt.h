@@ -504,10 +504,10 @@ po_status po_timer_read(double* ms_total, int64_t* calls);
  * the launch on `stream`. */
 po_status po_probe_fp64_fma(int32_t waves_per_simd, int32_t chains, int64_t iters, double* d_sink, double* flop,
                             void* stream);
-/* Mode-steps evolved since the last read while timers were enabled, per series variant of the
- * second-order evolution kernel (chosen per block of 512 modes and chunk of 256 steps):
- * counts[0..7] = tan(theta)/theta polynomial of degree 4, 5, ..., 11; counts[8] = cos/sin series of
- * degree 7 with angle halving.
+/* Mode-steps evolved since the last read while timers were enabled, per step-size class of the
+ * second-order evolution (per block of 512 modes and chunk of 256 steps, from the bound on
+ * x = (omega dt)^2 that also selects the step's polynomial): counts[0..7] = x within the range of the
+ * tan(theta)/theta fit of degree 4, 5, ..., 11 and of no lower one; counts[8] = beyond.
  * Entries beyond 9 are set to 0.  Synchronises the device; clears the counts. */
 po_status po_timer_mode_steps(uint64_t* counts, int32_t n);
 

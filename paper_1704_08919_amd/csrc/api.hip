@@ -157,6 +157,7 @@ po_status build_batch(int32_t n, const po_pulse_spec* specs, const po_grid* grid
       }
       d.dv = dv;
       const int64_t m = int64_t(g.n[0]) * g.n[1] * g.n[2];
+      d.nmodes = m;
       d.nunits = int32_t((m + kUnit - 1) / kUnit);
       d.nitems = int32_t((m + kItem - 1) / kItem);
       modes += m;

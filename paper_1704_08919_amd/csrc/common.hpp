@@ -49,6 +49,7 @@ struct PulseDev {
   int32_t chk_off;    // first 256-step chunk of this pulse in the batch (table ranges per chunk)
   int32_t n[3];
   int64_t unit_off;   // first 64-mode reduction unit of this pulse in the batch
+  int64_t nmodes;
   int32_t nunits;
   int32_t item_off;   // first workgroup item of this pulse in the default evolution launch
   int32_t nitems;
@@ -157,7 +158,7 @@ po_status plan_evolve(const po_plan* plan, int32_t n, const po_pulse_spec* specs
 // Kernel timers (api.hip): start returns true (and records *e0) when timers are enabled;
 // timer_count enqueues the per-variant mode-step count of an evolution launch from its chunk
 // ranges (no-op when disabled).
-constexpr int kSeriesVariants = 9;  // T fits of degree 4..11 (tan_fit.hpp), then the angle-halving path
+constexpr int kSeriesVariants = 9;  // step-size classes: the ranges of the T fits of degree 4..11 (tan_fit.hpp), then beyond
 bool timer_start(hipStream_t s, hipEvent_t* e0);
 void timer_stop(hipStream_t s, hipEvent_t e0);
 po_status timer_count(int n_pulses, const PulseDev* d_desc, const double* d_ranges, hipStream_t s);

@@ -8,6 +8,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "cot_fit.hpp"
 #include "tan_fit.hpp"
 
 #pragma clang fp contract(off)
@@ -127,6 +128,149 @@ __device__ __forceinline__ void step_tan(State& v, double2 rec, double pxdt, dou
   const double qy = pydt + rec.y;
   const double x = fma(qx, qx, fma(qy, qy, qz2));
   rotate_tan(v, tan_ratio<V>(x, f), qx, qy, qz);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Cotangent form of the step.  With everything in units of e = e_perp, q' = (p - A)/e, y = |q'|^2
+// and z = (e dt)^2, x = (omega dt)^2 = z (1 + y), the step is a multiple of
+//     K' - i (q'_x tau_x + s q'_y tau_y + tau_z),   K' = sqrt(x) cot(sqrt x) / (e dt):
+// the tau_z coefficient is exactly 1, so its terms enter the FMA chains as addends and the three
+// products T q of the tangent form disappear; and K is smooth up to x = pi^2 (T only up to
+// pi^2/4), so its fits are a degree shorter at the same bound and reach x = 2.5 instead of 0.26.
+// Per mode-step: 2 FMAs (q'), 2 (y), n (K' as a polynomial in y), 24 (two blocks): 28 + n
+// instructions against 31 + n with a larger n.  The state grows by about 1/(e dt) per step and is
+// rescaled by an exact power of two every few steps (kGroupLong or kGroupShort).
+// ---------------------------------------------------------------------------------------------
+constexpr int kCotHalving = kNumCot;  // variant index beyond the fits: the angle-halving path
+// Steps between two rescalings.  A step multiplies the norm by sqrt(x)/sin(sqrt x)/(e dt), at most
+// 1.6/dt for x <= 2.5: 64 steps stay below 2^960 for dt >= 2^-14, 16 steps for dt >= 2^-59; a
+// smaller dt takes the angle-halving path (no halvings needed there, the state does not grow).
+constexpr int kGroupLong = 64, kGroupShort = 16;
+constexpr double kGroupLongMinDt = 0x1p-14, kGroupShortMinDt = 0x1p-59;
+
+// A mode in the cotangent form: -1/e, p/e and e; per chunk z = (e dt)^2 and 1/(e dt) as hi + lo (the
+// rounding of e dt and of the quotient would otherwise act as a fixed relative error of every
+// step's angle).
+struct CotMode {
+  double nie, px, py, e;
+};
+struct CotStep {
+  double z, ih, il;
+};
+
+__device__ __forceinline__ CotMode cot_mode(double px, double py, double e) {
+  const double ie = 1.0 / e;
+  return CotMode{-ie, px * ie, py * ie, e};
+}
+
+__device__ __forceinline__ CotStep cot_step_size(double e, double dt) {
+  const double qz = e * dt, ih = 1.0 / qz;
+  return CotStep{qz * qz, ih, ih * (fma(-ih, qz, 1.0) - ih * fma(e, dt, -qz))};
+}
+
+// K' for variant V.  Degrees up to kCotInline: per-lane coefficients of K(z (1 + y))/(e dt) in powers
+// of y (the fit's coefficients scaled by powers of z, a Taylor shift by 1, the division by e dt), n
+// FMAs per step.  Higher degrees, which large steps take, would need too many registers that way:
+// their fit stays in scalar registers and x = z (1 + y) and the division cost three more.
+constexpr int kCotInline = 8;
+
+template <int V, bool INLINE = (kCotDegree[V] <= kCotInline)>
+struct CotCoef {
+  double c[kCotDegree[V] + 1];
+};
+template <int V>
+struct CotCoef<V, false> {
+  double r[kCotDegree[V]];
+  CotStep s;
+};
+
+template <int V>
+__device__ __forceinline__ CotCoef<V> cot_coef(const CotStep& m) {
+  constexpr int n = kCotDegree[V];
+  CotCoef<V> k;
+  if constexpr (n <= kCotInline) {
+    k.c[0] = 1.0;
+    double zp = m.z;
+#pragma unroll
+    for (int j = 0; j < n; ++j) {
+      double r = kCotCoef[V][j];
+      asm volatile("" : "+s"(r));  // as load_fit: keeps the constants of other variants out of registers
+      k.c[j + 1] = r * zp;
+      zp *= m.z;
+    }
+#pragma unroll
+    for (int i = 0; i < n; ++i)
+#pragma unroll
+      for (int j = n - 1; j >= i; --j) k.c[j] += k.c[j + 1];
+    k.c[0] = fma(k.c[0], m.ih, k.c[0] * m.il);
+#pragma unroll
+    for (int j = 1; j <= n; ++j) k.c[j] *= m.ih;
+  } else {
+    k.s = m;
+#pragma unroll
+    for (int j = 0; j < n; ++j) {
+      k.r[j] = kCotCoef[V][j];
+      asm volatile("" : "+s"(k.r[j]));
+    }
+  }
+  return k;
+}
+
+template <int V>
+__device__ __forceinline__ double cot_K(double y, const CotCoef<V>& k) {
+  constexpr int n = kCotDegree[V];
+  if constexpr (n <= kCotInline) {
+    double K = k.c[n];
+#pragma unroll
+    for (int j = n - 1; j >= 0; --j) K = fma(K, y, k.c[j]);
+    return K;
+  } else {
+    const double x = fma(y, k.s.z, k.s.z);
+    double R = k.r[n - 1];
+#pragma unroll
+    for (int j = n - 2; j >= 0; --j) R = fma(R, x, k.r[j]);
+    const double K = fma(R, x, 1.0);
+    return fma(K, k.s.ih, K * k.s.il);
+  }
+}
+
+template <int V>
+__device__ __forceinline__ void step_cot(State& v, double2 A, const CotMode& m, const CotCoef<V>& k) {
+  const double qx = fma(A.x, m.nie, m.px), qy = fma(A.y, m.nie, m.py);
+  const double K = cot_K<V>(fma(qx, qx, qy * qy), k);
+  const double ar = fma(qx, v.bi, fma(-qy, v.br, fma(K, v.ar, v.ai)));
+  const double ai = fma(-qx, v.br, fma(-qy, v.bi, fma(K, v.ai, -v.ar)));
+  const double br = fma(qx, v.ai, fma(qy, v.ar, fma(K, v.br, -v.bi)));
+  const double bi = fma(-qx, v.ar, fma(qy, v.ai, fma(K, v.bi, v.br)));
+  const double cr = fma(qx, v.di, fma(qy, v.dr, fma(K, v.cr, v.ci)));
+  const double ci = fma(-qx, v.dr, fma(qy, v.di, fma(K, v.ci, -v.cr)));
+  const double dr = fma(qx, v.ci, fma(-qy, v.cr, fma(K, v.dr, -v.di)));
+  const double di = fma(-qx, v.cr, fma(-qy, v.ci, fma(K, v.di, v.dr)));
+  v = State{ar, ai, br, bi, cr, ci, dr, di};
+}
+
+// Rescales both blocks by one exact power of two so that the largest component of the first lies
+// in [1/2, 1) (no squares: the components may be near the ends of the exponent range).
+__device__ __forceinline__ void rescale(State& v) {
+  const double m = fmax(fmax(fabs(v.ar), fabs(v.ai)), fmax(fabs(v.br), fabs(v.bi)));
+  const int e = -__builtin_amdgcn_frexp_exp(m);
+  v.ar = ldexp(v.ar, e); v.ai = ldexp(v.ai, e); v.br = ldexp(v.br, e); v.bi = ldexp(v.bi, e);
+  v.cr = ldexp(v.cr, e); v.ci = ldexp(v.ci, e); v.dr = ldexp(v.dr, e); v.di = ldexp(v.di, e);
+}
+
+// psi <- P psi for both blocks, P given by its first column (a multiple of an SU(2) matrix is
+// [[a, -conj b], [b, conj a]]), then rescaled.
+__device__ __forceinline__ void apply_propagator(State& s, const State& p) {
+  const double ar = fma(-p.bi, s.bi, fma(-p.br, s.br, fma(-p.ai, s.ai, p.ar * s.ar)));
+  const double ai = fma(p.bi, s.br, fma(-p.br, s.bi, fma(p.ai, s.ar, p.ar * s.ai)));
+  const double br = fma(p.ai, s.bi, fma(p.ar, s.br, fma(-p.bi, s.ai, p.br * s.ar)));
+  const double bi = fma(-p.ai, s.br, fma(p.ar, s.bi, fma(p.bi, s.ar, p.br * s.ai)));
+  const double cr = fma(-p.di, s.di, fma(-p.dr, s.dr, fma(-p.ci, s.ci, p.cr * s.cr)));
+  const double ci = fma(p.di, s.dr, fma(-p.dr, s.di, fma(p.ci, s.cr, p.cr * s.ci)));
+  const double dr = fma(p.ci, s.di, fma(p.cr, s.dr, fma(-p.di, s.ci, p.dr * s.cr)));
+  const double di = fma(-p.ci, s.dr, fma(p.cr, s.di, fma(p.di, s.cr, p.dr * s.ci)));
+  s = State{ar, ai, br, bi, cr, ci, dr, di};
+  rescale(s);
 }
 
 // Large-step path: C, S at x / 4^h, then h double-angle steps; the step stays unitary.

@@ -13,19 +13,30 @@
 // q_z tau_z and x = |q|^2 = (omega dt)^2 (so Q_s^2 = x),
 //     U = C(x) 1 - i S(x) Q_s = C(x) [1 - i T(x) Q_s],
 //     C(x) = cos sqrt(x),  S(x) = sin sqrt(x) / sqrt(x),  T(x) = tan sqrt(x) / sqrt(x).
-// The scalar C is common to both blocks, and f is a ratio of squared norms, so the kernel
-// applies only 1 - i T Q_s (three FMAs per real component) and divides by the norms at the
-// end; the state is rescaled by an exact power of two once per LDS chunk to stay in range.
-// For any value of T, 1 - i T Q_s is a scalar multiple of a unitary matrix (its square modulus
-// is (1 + T^2 x) 1), so rounding in T perturbs only the rotation angle.  T is a polynomial in x
-// (a fit of (T - 1)/x whose error is below 2^-57) of the lowest degree that covers the whole
-// range of x of the 512-mode block the item belongs to in the 256-step chunk (a box of momenta
-// against the range of the table in the chunk); beyond the fits' range the large-step path
-// halves the angle and takes C and S from truncated Maclaurin series (remainder below 2^-56).
-// Either is shared by both blocks, because omega does not depend on s.
+// The scalar C is common to both blocks, and f is a ratio of squared norms, so any multiple of U will
+// do.  The second-order kernel divides by S e_perp dt instead: with P/e_perp = (P'_x, P'_y),
+//     U ~ K' - i (P'_x tau_x + s P'_y tau_y + tau_z),   K' = sqrt(x) cot(sqrt x) / (e_perp dt),
+// whose tau_z coefficient is 1 and enters the multiply-add chains as an addend: 24 FMAs for the two
+// blocks and no products to form first (the "cotangent form", dirac.hpp).  For any value of K' this
+// is a multiple of a unitary matrix, so rounding in K' perturbs only the rotation angle.  K' is a
+// polynomial (a fit of (sqrt x cot sqrt x - 1)/x whose error is below 2^-57, re-expanded per mode
+// about its smallest x) of the lowest degree that covers the whole range of x of the 512-mode block
+// the item belongs to in the 256-step chunk (a box of momenta against the range of the table in the
+// chunk); beyond the fits' range (x > 2.48) the large-step path halves the angle and takes C and S
+// from truncated Maclaurin series (remainder below 2^-56).  Either is shared by both blocks, because
+// omega does not depend on s.  The fourth-order and split-operator kernels below keep the multiple
+// 1 - i T Q_s with fits of T.
+//
+// What bounds it: FP64 issue, at the clock the power limit leaves (a chain of v_fma_f64 on distinct
+// registers runs at 1.85-1.95 GHz on this card, 0.73 of the 2.4 GHz peak at four waves per SIMD and
+// 0.77 at eight), so the time follows the number of FP64 instructions: 28 + n per mode-step with n =
+// 5.2 on average on the 64-pulse 64x64x16 nt = 16384 workload, against 31 + 6.2 for the tangent form
+// that this replaced there: 73.6 ms per generation against 80.9 (A/B on one card).  Five or six waves
+// per SIMD (96 or 80 VGPRs) measured 74.5 and 75.5 ms, two or one steps per loop iteration at four
+// waves 74.0 ms and slower.
 //
 // Work decomposition: a workgroup of THREADS lanes (64-wide waves) owns an item of
-// THREADS x MPL consecutive modes of one pulse, MPL modes per lane.  The pulse's table of -A dt
+// THREADS x MPL consecutive modes of one pulse, MPL modes per lane.  The pulse's table of A
 // is staged through LDS in chunks of 256 steps (double-buffered, one barrier per chunk) and
 // every lane reads the same record, an LDS broadcast.  The states (2 blocks x 2 complex
 // amplitudes per mode) stay in VGPRs for all nt steps.  f is summed per 64-mode unit by one
@@ -188,6 +199,8 @@ __global__ void __launch_bounds__(256) k_block_select(const PulseDev* __restrict
     bsel[d.blk_off + b] = choose_variant<1>(block_box(d, b), axl, axh, ayl, ayh, d.dt);
 }
 
+constexpr int kCotUnroll = 4;  // steps per iteration of the step loops
+
 struct EvolveArgs {
   const PulseDev* desc;
   int n_pulses;
@@ -198,65 +211,149 @@ struct EvolveArgs {
   double* units;
 };
 
-// Steps of one chunk (len records of buf) in series variant MODE for the MPL modes of a lane; the
-// tangent form (the variant's fit coefficients loaded once per chunk) then rescales the states by
-// exact powers of two.
-template <int MODE, int MPL>
-__device__ __forceinline__ void run_chunk(State (&v)[MPL], const double2* buf, int len, const double (&pxdt)[MPL],
-                                          const double (&pydt)[MPL], const double (&qz)[MPL], const double (&qz2)[MPL],
-                                          int h) {
-  if constexpr (MODE < kFineHalving) {
-    const Fit<MODE> f = load_fit<MODE>();
-    if (len == kChunk) {
-#pragma unroll(MPL == 1 ? 4 : 2)
-      for (int k = 0; k < kChunk; ++k) {
-        const double2 rec = buf[k];
+// A value that is equal in all lanes, in scalar registers.
+__device__ __forceinline__ double uniform(double v) {
+  return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
+                          __builtin_amdgcn_readfirstlane(__double2loint(v)));
+}
+
+// Upper 32 bits of a positive double (ordered as the doubles are).
+constexpr uint32_t high_word(double v) { return uint32_t(__builtin_bit_cast(uint64_t, v) >> 32); }
+
+// Variant of the cotangent form for a bound xb on x = (omega dt)^2: the lowest fit that covers it
+// (compared by the upper words, so a bound within 2^-20 of a fit's end takes the next one; NaN and
+// infinity compare above all), kCotHalving beyond, and for steps so small that even the short group
+// would overflow (dt < 2^-59), which need no halvings there.
+__device__ __forceinline__ int cot_variant(double xb, double dt) {
+  const uint32_t hi = __builtin_amdgcn_readfirstlane(__double2hiint(xb));
+  int mode = kCotHalving;
 #pragma unroll
-        for (int j = 0; j < MPL; ++j) step_tan<MODE>(v[j], rec, pxdt[j], pydt[j], qz[j], qz2[j], f);
-      }
-    } else {
-      for (int k = 0; k < len; ++k) {
-        const double2 rec = buf[k];
+  for (int k = kNumCot - 1; k >= 0; --k)
+    if (hi < high_word(kCotXmax[k])) mode = k;
+  return dt < kGroupShortMinDt ? kCotHalving : mode;
+}
+
+// The steps of one chunk (len table records of buf) for the MPL modes of a lane in fit variant V,
+// rescaled every `group` steps.
+template <int V, int MPL>
+__device__ __forceinline__ void run_cot(State (&v)[MPL], const double2* buf, int len, double dt,
+                                        const CotMode (&m)[MPL]) {
+  const int group = dt >= kGroupLongMinDt ? kGroupLong : kGroupShort;
+  CotCoef<V> k[MPL];
 #pragma unroll
-        for (int j = 0; j < MPL; ++j) step_tan<MODE>(v[j], rec, pxdt[j], pydt[j], qz[j], qz2[j], f);
-      }
+  for (int j = 0; j < MPL; ++j) {
+    double e = m[j].e;
+    asm volatile("" : "+v"(e));  // keeps this set-up inside the chunk loop, out of long-lived registers
+    k[j] = cot_coef<V>(cot_step_size(e, dt));
+  }
+  for (int n0 = 0; n0 < len; n0 += group) {
+    const int end = min(n0 + group, len);
+#pragma unroll kCotUnroll
+    for (int n = n0; n < end; ++n) {
+      const double2 rec = buf[n];
+#pragma unroll
+      for (int j = 0; j < MPL; ++j) step_cot<V>(v[j], rec, m[j], k[j]);
     }
 #pragma unroll
-    for (int j = 0; j < MPL; ++j) renormalise(v[j]);
-  } else {
-    const double inv4h = ldexp(1.0, -2 * h);
-    if (len == kChunk) {
-#pragma unroll(MPL == 1 ? 4 : 2)
-      for (int k = 0; k < kChunk; ++k) {
-        const double2 rec = buf[k];
+    for (int j = 0; j < MPL; ++j) rescale(v[j]);
+  }
+}
+
+// Coefficients of the degree-7 series of C and S, read from memory where they are used: as literals
+// the compiler sets them at kernel entry and spills them around the other variants' loops.
+__constant__ double2 kHalvingCoef[8] = {
+    {cos_coef(0), sinc_coef(0)}, {cos_coef(1), sinc_coef(1)}, {cos_coef(2), sinc_coef(2)}, {cos_coef(3), sinc_coef(3)},
+    {cos_coef(4), sinc_coef(4)}, {cos_coef(5), sinc_coef(5)}, {cos_coef(6), sinc_coef(6)}, {cos_coef(7), sinc_coef(7)}};
+
+// The chunk beyond the fits: C and S of degree 7 with angle halvings.
+template <int MPL>
+__device__ __forceinline__ void run_halving(State (&v)[MPL], const double2* buf, int len, double xb, double dt,
+                                            const CotMode (&m)[MPL]) {
+  int h = 0;
+  for (double x = xb; x > kCosSinXmax && h < kMaxHalvings; x *= 0.25) ++h;
+  h = __builtin_amdgcn_readfirstlane(h);
+  const double inv4h = ldexp(1.0, -2 * h);
+  const double2* cs = kHalvingCoef;
+  asm volatile("" : "+s"(cs));
+#pragma unroll 1
+  for (int n = 0; n < len; ++n) {
+    const double2 rec = buf[n];
 #pragma unroll
-        for (int j = 0; j < MPL; ++j) step_halving(v[j], rec, pxdt[j], pydt[j], qz[j], qz2[j], h, inv4h);
-      }
-    } else {
-      for (int k = 0; k < len; ++k) {
-        const double2 rec = buf[k];
+    for (int j = 0; j < MPL; ++j) {
+      // back to units of 1/dt: q = e dt q'
+      const double qz = m[j].e * dt;
+      const double qx = qz * fma(rec.x, m[j].nie, m[j].px), qy = qz * fma(rec.y, m[j].nie, m[j].py);
+      double xs = fma(qx, qx, fma(qy, qy, qz * qz)) * inv4h;
+      double C = cs[7].x, S = cs[7].y;
 #pragma unroll
-        for (int j = 0; j < MPL; ++j) step_halving(v[j], rec, pxdt[j], pydt[j], qz[j], qz2[j], h, inv4h);
+      for (int k = 6; k >= 0; --k) {
+        C = fma(C, xs, cs[k].x);
+        S = fma(S, xs, cs[k].y);
       }
+      for (int i = 0; i < h; ++i) {
+        const double c2 = fma(C, C, -(xs * S) * S);
+        S = S * C;
+        C = c2;
+        xs *= 4.0;
+      }
+      rotate(v[j], C, S, qx, qy, qz);
     }
   }
 }
 
-// The chunks of an item: table records staged through LDS (double-buffered, one barrier per
-// chunk) and the steps of each chunk in its variant (chunk_variant); HALVING: the block's own
-// variant is the angle-halving path.
-template <bool HALVING, int THREADS, int MPL>
-__device__ __forceinline__ void chunk_loop(State (&v)[MPL], const double2* tab, int nt, double dt, const double* rg,
-                                           const BlockBox& bb, int bmode, const double (&pxdt)[MPL],
-                                           const double (&pydt)[MPL], const double (&qz)[MPL],
-                                           const double (&qz2)[MPL], double2 (*lds)[kChunk]) {
+// The steps of one chunk, in the variant that the bound xb on its (omega dt)^2 selects.
+template <int MPL>
+__device__ __forceinline__ void run_chunk(State (&v)[MPL], const double2* buf, int len, double xb, double dt,
+                                          const CotMode (&m)[MPL]) {
+  switch (cot_variant(xb, dt)) {
+    case 0: run_cot<0, MPL>(v, buf, len, dt, m); break;
+    case 1: run_cot<1, MPL>(v, buf, len, dt, m); break;
+    case 2: run_cot<2, MPL>(v, buf, len, dt, m); break;
+    case 3: run_cot<3, MPL>(v, buf, len, dt, m); break;
+    case 4: run_cot<4, MPL>(v, buf, len, dt, m); break;
+    case 5: run_cot<5, MPL>(v, buf, len, dt, m); break;
+    case 6: run_cot<6, MPL>(v, buf, len, dt, m); break;
+    case 7: run_cot<7, MPL>(v, buf, len, dt, m); break;
+    case 8: run_cot<8, MPL>(v, buf, len, dt, m); break;
+    default: run_halving<MPL>(v, buf, len, xb, dt, m); break;
+  }
+}
+
+// Evolves the item of THREADS * MPL modes of pulse pi starting at mode `first`, writes f and the
+// 64-mode unit sums.  Every lane of the workgroup must call it (it contains barriers).  The table
+// is staged through LDS in chunks of 256 steps (double-buffered, one barrier per chunk).  The
+// series variant is chosen from the item's selection block (items never straddle blocks) and the
+// table ranges, so it depends only on the pulse, the block and the chunk, never on the launch.
+template <int THREADS, int MPL>
+__device__ __forceinline__ void process_item(const EvolveArgs& a, int pi, int first, double2 (*lds)[kChunk]) {
   constexpr int kPre = kChunk / THREADS;  // table records each lane stages per chunk
+  const PulseDev& d = a.desc[pi];
+  const int nt = d.nt;
+  const double dt = d.dt;
+  const double2* tab = reinterpret_cast<const double2*>(a.A) + d.tab_off;
+  const double2* edge = reinterpret_cast<const double2*>(a.Aedge) + 2 * pi;
+  const double2 ain = edge[0];
+  BlockBox bb = block_box(d, first / kSelBlock);
+  bb = BlockBox{uniform(bb.pxl), uniform(bb.pxh), uniform(bb.pyl), uniform(bb.pyh), uniform(bb.pz2)};
+  const double* rg = a.ranges + 4 * int64_t(d.chk_off);
+
+  State v[MPL];
+  CotMode mode[MPL];
+#pragma unroll
+  for (int j = 0; j < MPL; ++j) {
+    const int64_t m = int64_t(first) + j * THREADS + threadIdx.x;
+    double px, py, pz;
+    mode_momentum(d, m < d.nmodes ? m : 0, px, py, pz);
+    const double e = sqrt(fma(pz, pz, 1.0));
+    init_state(v[j], px - ain.x, py - ain.y, e);
+    mode[j] = cot_mode(px, py, e);
+  }
+
   const int nchunks = (nt + kChunk - 1) / kChunk;
 #pragma unroll
   for (int r = 0; r < kPre; ++r) {
     const int n = r * THREADS + threadIdx.x;
-    const double2 t = n < nt ? tab[n] : make_double2(0.0, 0.0);
-    lds[0][n] = make_double2(-t.x * dt, -t.y * dt);
+    lds[0][n] = n < nt ? tab[n] : make_double2(0.0, 0.0);
   }
   __syncthreads();
   for (int c = 0; c < nchunks; ++c) {
@@ -266,96 +363,24 @@ __device__ __forceinline__ void chunk_loop(State (&v)[MPL], const double2* tab, 
       const int n = (c + 1) * kChunk + r * THREADS + threadIdx.x;
       pre[r] = (c + 1 < nchunks && n < nt) ? tab[n] : make_double2(0.0, 0.0);
     }
-    const double2* buf = lds[c & 1];
-    const int len = min(kChunk, nt - c * kChunk);
-    const int2 cv = chunk_variant(bb, rg, c, bmode, dt);
-    const int mode = __builtin_amdgcn_readfirstlane(cv.x);
-    if constexpr (HALVING) {
-      if (mode == kFineHalving)
-        run_chunk<kFineHalving, MPL>(v, buf, len, pxdt, pydt, qz, qz2, __builtin_amdgcn_readfirstlane(cv.y));
-      else
-        run_chunk<kNumFine - 1, MPL>(v, buf, len, pxdt, pydt, qz, qz2, 0);
-    } else {
-      switch (mode) {
-        case 0: run_chunk<0, MPL>(v, buf, len, pxdt, pydt, qz, qz2, 0); break;
-        case 1: run_chunk<1, MPL>(v, buf, len, pxdt, pydt, qz, qz2, 0); break;
-        case 2: run_chunk<2, MPL>(v, buf, len, pxdt, pydt, qz, qz2, 0); break;
-        case 3: run_chunk<3, MPL>(v, buf, len, pxdt, pydt, qz, qz2, 0); break;
-        case 4: run_chunk<4, MPL>(v, buf, len, pxdt, pydt, qz, qz2, 0); break;
-        case 5: run_chunk<5, MPL>(v, buf, len, pxdt, pydt, qz, qz2, 0); break;
-        case 6: run_chunk<6, MPL>(v, buf, len, pxdt, pydt, qz, qz2, 0); break;
-        default: run_chunk<7, MPL>(v, buf, len, pxdt, pydt, qz, qz2, 0); break;
-      }
-    }
+    run_chunk<MPL>(v, lds[c & 1], min(kChunk, nt - c * kChunk),
+                   x_bound(bb, rg[4 * c], rg[4 * c + 1], rg[4 * c + 2], rg[4 * c + 3], dt), dt, mode);
 #pragma unroll
-    for (int r = 0; r < kPre; ++r)
-      lds[(c + 1) & 1][r * THREADS + threadIdx.x] = make_double2(-pre[r].x * dt, -pre[r].y * dt);
+    for (int r = 0; r < kPre; ++r) lds[(c + 1) & 1][r * THREADS + threadIdx.x] = pre[r];
     __syncthreads();
   }
-}
-
-// Evolves the item of THREADS * MPL modes of pulse pi starting at mode `first`, writes f and the
-// 64-mode unit sums.  Every lane of the workgroup must call it (it contains barriers).  The
-// series variant is chosen from the item's selection block (items never straddle blocks) and the
-// table ranges, so it depends only on the pulse, the block and the chunk, never on the launch.
-template <int THREADS, int MPL>
-__device__ __forceinline__ void process_item(const EvolveArgs& a, int pi, int first, double2 (*lds)[kChunk]) {
-  const PulseDev& d = a.desc[pi];
-  const int nt = d.nt;
-  const double dt = d.dt;
-  const int nx = d.n[0], ny = d.n[1];
-  const int64_t nmodes = int64_t(nx) * ny * d.n[2];
-  const double2* tab = reinterpret_cast<const double2*>(a.A) + d.tab_off;
-  const double2* edge = reinterpret_cast<const double2*>(a.Aedge) + 2 * pi;
-  const double2 ain = edge[0];
-  const BlockBox bb = block_box(d, first / kSelBlock);
-  const double* rg = a.ranges + 4 * int64_t(d.chk_off);
-
-  State v[MPL];
-  double pxdt[MPL], pydt[MPL], qz[MPL], qz2[MPL];
-#pragma unroll
-  for (int j = 0; j < MPL; ++j) {
-    const int64_t m = int64_t(first) + j * THREADS + threadIdx.x;
-    const int64_t mm = m < nmodes ? m : 0;
-    const int ix = int(mm % nx), iy = int((mm / nx) % ny), iz = int(mm / (int64_t(nx) * ny));
-    const double px = __dadd_rn(d.lo[0], __dmul_rn(double(ix) + 0.5, d.dp[0]));
-    const double py = __dadd_rn(d.lo[1], __dmul_rn(double(iy) + 0.5, d.dp[1]));
-    const double pz = __dadd_rn(d.lo[2], __dmul_rn(double(iz) + 0.5, d.dp[2]));
-    const double e = sqrt(fma(pz, pz, 1.0));
-    init_state(v[j], px - ain.x, py - ain.y, e);
-    pxdt[j] = px * dt;
-    pydt[j] = py * dt;
-    qz[j] = e * dt;
-    qz2[j] = qz[j] * qz[j];
-  }
-
-  // The block's variant for the whole table bounds its chunks' (chunk_variant).
-  const int bmode = __builtin_amdgcn_readfirstlane(block_variant(bb, rg, (nt + kChunk - 1) / kChunk, dt).x);
-  if (bmode == kFineHalving)
-    chunk_loop<true, THREADS, MPL>(v, tab, nt, dt, rg, bb, bmode, pxdt, pydt, qz, qz2, lds);
-  else
-    chunk_loop<false, THREADS, MPL>(v, tab, nt, dt, rg, bb, bmode, pxdt, pydt, qz, qz2, lds);
 
   const double2 aout = edge[1];
 #pragma unroll
   for (int j = 0; j < MPL; ++j) {
     const int64_t m = int64_t(first) + j * THREADS + threadIdx.x;
-    const bool active = m < nmodes;
     double fv = 0.0;
-    if (active) {
-      const int64_t mm = m;
-      const int ix = int(mm % nx), iy = int((mm / nx) % ny), iz = int(mm / (int64_t(nx) * ny));
-      const double px = __dadd_rn(d.lo[0], __dmul_rn(double(ix) + 0.5, d.dp[0]));
-      const double py = __dadd_rn(d.lo[1], __dmul_rn(double(iy) + 0.5, d.dp[1]));
-      const double pz = __dadd_rn(d.lo[2], __dmul_rn(double(iz) + 0.5, d.dp[2]));
+    if (m < d.nmodes) {
+      double px, py, pz;
+      mode_momentum(d, m, px, py, pz);
       fv = project(v[j], px - aout.x, py - aout.y, sqrt(fma(pz, pz, 1.0)));
-      if (a.f) a.f[d.mode_off + m] = fv;
     }
-    if (a.units) {
-      const double s = wave_sum(fv);
-      const int64_t base = int64_t(first) + j * THREADS + (threadIdx.x & ~63);
-      if ((threadIdx.x & 63) == 0 && base < nmodes) a.units[d.unit_off + base / kUnit] = s;
-    }
+    write_density(d, a.f, a.units, m, fv);
   }
 }
 
@@ -396,12 +421,8 @@ __global__ void __launch_bounds__(256) k_unit_sums(const PulseDev* __restrict__ 
   const int item = blockIdx.x;
   const int pi = find_pulse_item(desc, n_pulses, item);
   const PulseDev& d = desc[pi];
-  const int64_t nmodes = int64_t(d.n[0]) * d.n[1] * d.n[2];
   const int64_t m = int64_t(item - d.item_off) * kItem + threadIdx.x;
-  const double v = m < nmodes ? f[d.mode_off + m] : 0.0;
-  const double s = wave_sum(v);
-  const int64_t base = m - (threadIdx.x & 63);
-  if ((threadIdx.x & 63) == 0 && base < nmodes) units[d.unit_off + base / kUnit] = s;
+  write_unit(d, units, m, m < d.nmodes ? f[d.mode_off + m] : 0.0);
 }
 
 // J per pulse: each lane sums units t, t + 256, ... in order, then a fixed tree; times the cell volume.
@@ -416,7 +437,7 @@ __global__ void __launch_bounds__(256) k_yield(const PulseDev* __restrict__ desc
 }
 
 // Diagnostics: adds modes x steps of every (selection block, chunk) of every pulse to the count
-// of the variant the evolution chose for it (the same block_variant and chunk_variant).
+// of its step-size class (the ranges of the tangent fits, by block_variant and chunk_variant).
 // One workgroup per pulse, one thread per block.
 __global__ void __launch_bounds__(256) k_count_mode_steps(const PulseDev* __restrict__ desc,
                                                           const double* __restrict__ ranges,
@@ -585,12 +606,11 @@ __device__ __forceinline__ void process_item4(const Evolve4Args& a, int pi, int 
   const PulseDev& d = a.desc[pi];
   const int nt = d.nt;
   const double dt = d.dt;
-  const int64_t nmodes = int64_t(d.n[0]) * d.n[1] * d.n[2];
   const double4* tab = reinterpret_cast<const double4*>(a.Ag) + d.tab_off;
   const double2* edge = reinterpret_cast<const double2*>(a.Aedge) + 2 * pi;
   const int64_t m = int64_t(first) + threadIdx.x;
   double px, py, pz;
-  mode_momentum(d, m < nmodes ? m : 0, px, py, pz);
+  mode_momentum(d, m < d.nmodes ? m : 0, px, py, pz);
   const double ep = sqrt(fma(pz, pz, 1.0));
   State v;
   const double2 ain = edge[0];
@@ -605,12 +625,7 @@ __device__ __forceinline__ void process_item4(const Evolve4Args& a, int pi, int 
     chunk_loop4<false>(v, tab, nt, dt, rg, bb, bmode, pxdt, pydt, e, lds);
 
   const double2 aout = edge[1];
-  double fv = 0.0;
-  if (m < nmodes) {
-    fv = project(v, px - aout.x, py - aout.y, ep);
-    if (a.f) a.f[d.mode_off + m] = fv;
-  }
-  if (a.units) write_unit(d, a.units, m, nmodes, fv);
+  write_density(d, a.f, a.units, m, m < d.nmodes ? project(v, px - aout.x, py - aout.y, ep) : 0.0);
 }
 
 __global__ void __launch_bounds__(kItem) __attribute__((amdgpu_waves_per_eu(4))) k_evolve4(Evolve4Args a) {
@@ -782,12 +797,11 @@ __device__ __forceinline__ void process_item_split(const SplitArgs& a, int pi, i
   const int nt = d.nt;
   const double dt = d.dt;
   const double dtw = NSUB == 1 ? dt : -kTripleW0 * dt;  // the largest substep
-  const int64_t nmodes = int64_t(d.n[0]) * d.n[1] * d.n[2];
   const double2* tab = reinterpret_cast<const double2*>(a.At) + NSUB * d.tab_off;
   const double2* edge = reinterpret_cast<const double2*>(a.Aedge) + 2 * pi;
   const int64_t m = int64_t(first) + threadIdx.x;
   double px, py, pz;
-  mode_momentum(d, m < nmodes ? m : 0, px, py, pz);
+  mode_momentum(d, m < d.nmodes ? m : 0, px, py, pz);
   const double ep = sqrt(fma(pz, pz, 1.0));
   SplitMode<NSUB> k;
   double th0;
@@ -821,12 +835,7 @@ __device__ __forceinline__ void process_item_split(const SplitArgs& a, int pi, i
   phase_z(v, c0, -s0);
 
   const double2 aout = edge[1];
-  double fv = 0.0;
-  if (m < nmodes) {
-    fv = project(v, px - aout.x, py - aout.y, ep);
-    if (a.f) a.f[d.mode_off + m] = fv;
-  }
-  if (a.units) write_unit(d, a.units, m, nmodes, fv);
+  write_density(d, a.f, a.units, m, m < d.nmodes ? project(v, px - aout.x, py - aout.y, ep) : 0.0);
 }
 
 template <int NSUB>

@@ -443,7 +443,7 @@ __device__ __forceinline__ void grad_item(const GradArgs& a, int item, int pi, d
     for (int w = 1; w < kWaves; ++w) v += red[w][threadIdx.x].x;
     a.epart[int64_t(item) * 4 + threadIdx.x] = v;
   }
-  if (a.units) write_unit(d, a.units, m, nmodes, active ? f : 0.0);
+  if (a.units) write_unit(d, a.units, m, active ? f : 0.0);
 }
 
 __global__ void __launch_bounds__(kItem) __attribute__((amdgpu_waves_per_eu(3))) k_yield_grad(GradArgs a) {

@@ -135,14 +135,13 @@ __global__ void __launch_bounds__(kQPoints) k_qke(QkeArgs a) {
   const int nt = d.nt;
   const int64_t npts = 2 * int64_t(nt) + 1;
   const double dt = d.dt, hdt = 0.5 * d.dt;
-  const int64_t nmodes = int64_t(d.n[0]) * d.n[1] * d.n[2];
   const double2* E = reinterpret_cast<const double2*>(a.E) + d.tab_off;
   const double2* Ed = reinterpret_cast<const double2*>(a.Ed) + d.tab_off;
   const double2* A = reinterpret_cast<const double2*>(a.A) + d.tab_off;
 
   const int64_t m = int64_t(item - d.item_off) * kItem + threadIdx.x;
   double px, py, pz;
-  mode_momentum(d, m < nmodes ? m : 0, px, py, pz);
+  mode_momentum(d, m < d.nmodes ? m : 0, px, py, pz);
   const double e2 = fma(pz, pz, 1.0), ep = sqrt(e2);
 
   // chunk c holds the points h = 2 c kQChunk + 1 + i, i < kQPoints
@@ -169,12 +168,7 @@ __global__ void __launch_bounds__(kQPoints) k_qke(QkeArgs a) {
     __syncthreads();
   }
 
-  double fv = 0.0;
-  if (m < nmodes) {
-    fv = y.f;
-    if (a.f) a.f[d.mode_off + m] = fv;
-  }
-  if (a.units) write_unit(d, a.units, m, nmodes, fv);
+  write_density(d, a.f, a.units, m, m < d.nmodes ? y.f : 0.0);
 }
 
 }  // namespace

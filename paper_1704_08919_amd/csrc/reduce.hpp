@@ -54,12 +54,19 @@ __device__ __forceinline__ void mode_momentum(const PulseDev& d, int64_t m, doub
   pz = __dadd_rn(d.lo[2], __dmul_rn(double(iz) + 0.5, d.dp[2]));
 }
 
-// Writes the 64-mode unit sum of fv (lanes beyond the pulse's modes pass 0).
-__device__ __forceinline__ void write_unit(const PulseDev& d, double* __restrict__ units, int64_t lane_mode,
-                                           int64_t nmodes, double fv) {
-  const double s = wave_sum(fv);
+// Writes the 64-mode unit sum of v (lanes beyond the pulse's modes pass 0).
+__device__ __forceinline__ void write_unit(const PulseDev& d, double* __restrict__ units, int64_t lane_mode, double v) {
+  const double s = wave_sum(v);
   const int64_t base = lane_mode - (threadIdx.x & 63);
-  if ((threadIdx.x & 63) == 0 && base < nmodes) units[d.unit_off + base / kUnit] = s;
+  if ((threadIdx.x & 63) == 0 && base < d.nmodes) units[d.unit_off + base / kUnit] = s;
+}
+
+// Writes the density of mode m (lanes beyond the pulse's modes pass 0) to f and its 64-mode unit
+// sum to units (either may be NULL).
+__device__ __forceinline__ void write_density(const PulseDev& d, double* __restrict__ f, double* __restrict__ units,
+                                              int64_t m, double fv) {
+  if (f && m < d.nmodes) f[d.mode_off + m] = fv;
+  if (units) write_unit(d, units, m, fv);
 }
 
 }  // namespace po
