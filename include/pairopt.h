@@ -28,6 +28,9 @@
  *    lists also return PO_ERR_NUMERIC for non-finite results (and are then synchronous).
  *  - Results are bitwise reproducible: reductions use a fixed order that depends only on the
  *    sizes of the problem, not on launch shapes or scheduling.
+ *  - f depends on p_z only through p_z^2.  On a grid with n_z > 1 and lo_z = -hi_z the kernels evolve
+ *    the planes i_z < ceil(n_z / 2) and take each value for its mirror image (plane n_z - 1 - i_z)
+ *    too; J then sums f(p) + f(mirror image) over those planes.
  *
  * Packed multi-pulse layout: pulse i owns nt_i table rows, starting at row sum_{j<i} nt_j,
  * and M_i = n_x n_y n_z momentum modes, starting at sum_{j<i} M_j.  Coefficients of pulse i
@@ -249,9 +252,10 @@ po_status po_evolve_modes_split(int32_t n_pulses, const po_pulse_spec* specs, co
  *  d_J      out [n_pulses] or NULL.
  *  d_gA     out [sum nt][2]: dJ/dA at every step midpoint.
  *  d_gedge  out [n_pulses][2][2] or NULL: dJ/dA(t_i), dJ/dA(t_f) (initial state, projection).
- * Work buffers of ceil(modes / 256) x nt x 16 bytes per pulse (the per-step partial sums of each
- * 256-mode item, added in a fixed order by a second kernel) come from the stream-ordered pool: 64 MiB
- * for a 64x64x16 pulse at nt = 16384, 1 GiB for a 128x128x32 pulse at nt = 32768.  A batch whose
+ * Work buffers of ceil(distinct modes / 256) x nt x 16 bytes per pulse (the per-step partial sums of
+ * each 256-mode item, added in a fixed order by a second kernel) come from the stream-ordered pool:
+ * 32 MiB for a 64x64x16 pulse symmetric in p_z at nt = 16384, 512 MiB for a 128x128x32 one at nt =
+ * 32768.  A batch whose
  * work buffers do not fit in device memory returns PO_ERR_NOMEM before the gradient kernels are
  * enqueued; split it into several calls.
  *

@@ -157,13 +157,15 @@ po_status build_batch(int32_t n, const po_pulse_spec* specs, const po_grid* grid
       }
       d.dv = dv;
       const int64_t m = int64_t(g.n[0]) * g.n[1] * g.n[2];
-      d.nmodes = m;
-      d.nunits = int32_t((m + kUnit - 1) / kUnit);
-      d.nitems = int32_t((m + kItem - 1) / kItem);
+      d.mirror = g.n[2] > 1 && g.lo[2] == -g.hi[2] ? 1 : 0;
+      d.ndist = d.mirror ? int64_t(g.n[0]) * g.n[1] * ((g.n[2] + 1) / 2) : m;
+      d.nunits = int32_t((d.ndist + kUnit - 1) / kUnit);
+      d.nitems = int32_t((d.ndist + kItem - 1) / kItem);
+      b->total_units_all += (m + kUnit - 1) / kUnit;
       modes += m;
       units += d.nunits;
       items += d.nitems;
-      blocks += (m + kSelBlock - 1) / kSelBlock;
+      blocks += (d.ndist + kSelBlock - 1) / kSelBlock;
       if (i > 0 && std::memcmp(&g, &grids[0], sizeof g) != 0) b->uniform = false;
     }
     out[i] = d;
@@ -201,14 +203,15 @@ po_status upload(const std::vector<PulseDev>& h, Scratch& sc, hipStream_t s) {
   return PO_OK;
 }
 
-// Scratch of one evaluation (synthesis + evolution + yield), in elements.
+// Scratch of one evaluation (synthesis + evolution + yield), in elements (units: as if no grid were
+// mirror-symmetric, which keeps the allocation-free path's limit a matter of the grid's size).
 struct EvalSizes {
   size_t spec, part, scl, units, ranges;
 };
 
 EvalSizes eval_sizes(int32_t n, const Batch& b) {
   return EvalSizes{size_t(b.total_spec), size_t(std::max(1, b.max_stat_blocks)) * n, size_t(n),
-                   size_t(b.total_units), 4 * size_t(b.total_chunks)};
+                   size_t(b.total_units_all), 4 * size_t(b.total_chunks)};
 }
 
 po_status synth_into(const po_pulse_spec* specs, const double* d_coeff, double* d_A, double* d_E, double* d_A_edge,

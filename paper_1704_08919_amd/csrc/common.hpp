@@ -49,8 +49,13 @@ struct PulseDev {
   int32_t chk_off;    // first 256-step chunk of this pulse in the batch (table ranges per chunk)
   int32_t n[3];
   int64_t unit_off;   // first 64-mode reduction unit of this pulse in the batch
-  int64_t nmodes;
-  int32_t nunits;
+  // f depends on p_z only through p_z^2, so on a grid with lo_z = -hi_z the modes of planes iz and
+  // n_z - 1 - iz have equal f: the kernels evolve the distinct modes, a prefix of the mode index
+  // (planes iz < ceil(n_z / 2)), and write or count each value for its mirror image too.  On any
+  // other grid every mode is distinct.
+  int64_t ndist;
+  int32_t mirror;     // 1: mirror-symmetric grid with more than one plane
+  int32_t nunits;     // 64-mode units, 256-mode items and selection blocks of the distinct modes
   int32_t item_off;   // first workgroup item of this pulse in the default evolution launch
   int32_t nitems;
   int32_t blk_off;    // first series-selection block (kSelBlock modes) of this pulse in the batch
@@ -62,6 +67,7 @@ struct Batch {
   int32_t n_pulses = 0;
   int64_t total_rows = 0, total_modes = 0, total_coeff = 0, total_spec = 0;
   int64_t total_units = 0;
+  int64_t total_units_all = 0; // 64-mode units of all modes, mirror images included
   int32_t total_items = 0;     // workgroups of the default evolution launch
   int32_t total_blocks = 0;    // series-selection blocks (kSelBlock modes, per pulse)
   int32_t total_chunks = 0;    // kChunkSteps-step chunks of all pulses

@@ -57,15 +57,14 @@
 namespace po {
 namespace {
 
-// Box of cell-centred momenta of selection block b (kSelBlock consecutive modes) of a pulse:
-// [pxl, pxh] x [pyl, pyh] and the largest p_z^2.
+// Box of cell-centred momenta of selection block b (kSelBlock consecutive modes of the first nmodes)
+// of a pulse: [pxl, pxh] x [pyl, pyh] and the largest p_z^2.
 struct BlockBox {
   double pxl, pxh, pyl, pyh, pz2;
 };
 
-__device__ __forceinline__ BlockBox block_box(const PulseDev& d, int b) {
+__device__ __forceinline__ BlockBox block_box(const PulseDev& d, int b, int64_t nmodes) {
   const int nx = d.n[0], ny = d.n[1];
-  const int64_t nmodes = int64_t(nx) * ny * d.n[2];
   const int64_t m0 = int64_t(b) * kSelBlock, m1 = min(m0 + kSelBlock, nmodes) - 1;
   const int64_t r0 = m0 / nx, r1 = m1 / nx;  // rows (iy, iz)
   const int64_t z0 = r0 / ny, z1 = r1 / ny;
@@ -193,10 +192,9 @@ __global__ void __launch_bounds__(256) k_block_select(const PulseDev* __restrict
     __syncthreads();
   }
   const double axl = -red[0][0], axh = red[1][0], ayl = -red[2][0], ayh = red[3][0];
-  const int64_t nmodes = int64_t(d.n[0]) * d.n[1] * d.n[2];
-  const int nblk = int((nmodes + kSelBlock - 1) / kSelBlock);
+  const int nblk = int((d.ndist + kSelBlock - 1) / kSelBlock);
   for (int b = threadIdx.x; b < nblk; b += blockDim.x)
-    bsel[d.blk_off + b] = choose_variant<1>(block_box(d, b), axl, axh, ayl, ayh, d.dt);
+    bsel[d.blk_off + b] = choose_variant<1>(block_box(d, b, d.ndist), axl, axh, ayl, ayh, d.dt);
 }
 
 constexpr int kCotUnroll = 4;  // steps per iteration of the step loops
@@ -333,7 +331,7 @@ __device__ __forceinline__ void process_item(const EvolveArgs& a, int pi, int fi
   const double2* tab = reinterpret_cast<const double2*>(a.A) + d.tab_off;
   const double2* edge = reinterpret_cast<const double2*>(a.Aedge) + 2 * pi;
   const double2 ain = edge[0];
-  BlockBox bb = block_box(d, first / kSelBlock);
+  BlockBox bb = block_box(d, first / kSelBlock, d.ndist);
   bb = BlockBox{uniform(bb.pxl), uniform(bb.pxh), uniform(bb.pyl), uniform(bb.pyh), uniform(bb.pz2)};
   const double* rg = a.ranges + 4 * int64_t(d.chk_off);
 
@@ -343,7 +341,7 @@ __device__ __forceinline__ void process_item(const EvolveArgs& a, int pi, int fi
   for (int j = 0; j < MPL; ++j) {
     const int64_t m = int64_t(first) + j * THREADS + threadIdx.x;
     double px, py, pz;
-    mode_momentum(d, m < d.nmodes ? m : 0, px, py, pz);
+    mode_momentum(d, m < d.ndist ? m : 0, px, py, pz);
     const double e = sqrt(fma(pz, pz, 1.0));
     init_state(v[j], px - ain.x, py - ain.y, e);
     mode[j] = cot_mode(px, py, e);
@@ -375,7 +373,7 @@ __device__ __forceinline__ void process_item(const EvolveArgs& a, int pi, int fi
   for (int j = 0; j < MPL; ++j) {
     const int64_t m = int64_t(first) + j * THREADS + threadIdx.x;
     double fv = 0.0;
-    if (m < d.nmodes) {
+    if (m < d.ndist) {
       double px, py, pz;
       mode_momentum(d, m, px, py, pz);
       fv = project(v[j], px - aout.x, py - aout.y, sqrt(fma(pz, pz, 1.0)));
@@ -415,14 +413,21 @@ k_evolve_persistent(EvolveArgs a, const int2* __restrict__ queue, int n_items, i
   }
 }
 
-// Unit sums from a stored f array, in the same butterfly order as the fused reduction.
+// Unit sums from a stored f array, in the same butterfly order as the fused reduction (a mirror
+// image is added to its mode first: f + f there).
 __global__ void __launch_bounds__(256) k_unit_sums(const PulseDev* __restrict__ desc, int n_pulses,
                                                    const double* __restrict__ f, double* __restrict__ units) {
   const int item = blockIdx.x;
   const int pi = find_pulse_item(desc, n_pulses, item);
   const PulseDev& d = desc[pi];
   const int64_t m = int64_t(item - d.item_off) * kItem + threadIdx.x;
-  write_unit(d, units, m, m < d.nmodes ? f[d.mode_off + m] : 0.0);
+  double v = 0.0;
+  if (m < d.ndist) {
+    const int64_t mm = mirror_mode(d, m);
+    v = f[d.mode_off + m];
+    if (mm != m) v += f[d.mode_off + mm];
+  }
+  write_unit(d, units, m, v);
 }
 
 // J per pulse: each lane sums units t, t + 256, ... in order, then a fixed tree; times the cell volume.
@@ -437,7 +442,8 @@ __global__ void __launch_bounds__(256) k_yield(const PulseDev* __restrict__ desc
 }
 
 // Diagnostics: adds modes x steps of every (selection block, chunk) of every pulse to the count
-// of its step-size class (the ranges of the tangent fits, by block_variant and chunk_variant).
+// of its step-size class (the ranges of the tangent fits, by block_variant and chunk_variant); the
+// blocks here run over all modes of the grid, mirror images included.
 // One workgroup per pulse, one thread per block.
 __global__ void __launch_bounds__(256) k_count_mode_steps(const PulseDev* __restrict__ desc,
                                                           const double* __restrict__ ranges,
@@ -448,7 +454,7 @@ __global__ void __launch_bounds__(256) k_count_mode_steps(const PulseDev* __rest
   const int nch = (d.nt + kChunk - 1) / kChunk;
   const double* rg = ranges + 4 * int64_t(d.chk_off);
   for (int b = threadIdx.x; b < nblk; b += blockDim.x) {
-    const BlockBox bb = block_box(d, b);
+    const BlockBox bb = block_box(d, b, nmodes);
     const unsigned long long mb = (unsigned long long)min(int64_t(kSelBlock), nmodes - int64_t(b) * kSelBlock);
     unsigned long long local[kSeriesVariants] = {};
     const int bmode = block_variant(bb, rg, nch, d.dt).x;
@@ -610,13 +616,13 @@ __device__ __forceinline__ void process_item4(const Evolve4Args& a, int pi, int 
   const double2* edge = reinterpret_cast<const double2*>(a.Aedge) + 2 * pi;
   const int64_t m = int64_t(first) + threadIdx.x;
   double px, py, pz;
-  mode_momentum(d, m < d.nmodes ? m : 0, px, py, pz);
+  mode_momentum(d, m < d.ndist ? m : 0, px, py, pz);
   const double ep = sqrt(fma(pz, pz, 1.0));
   State v;
   const double2 ain = edge[0];
   init_state(v, px - ain.x, py - ain.y, ep);
   const double pxdt = px * dt, pydt = py * dt, e = ep * dt;
-  const BlockBox bb = block_box(d, first / kSelBlock);
+  const BlockBox bb = block_box(d, first / kSelBlock, d.ndist);
   const double* rg = a.ranges + 4 * int64_t(d.chk_off);
   const int bmode = __builtin_amdgcn_readfirstlane(block_variant<2>(bb, rg, (nt + kChunk - 1) / kChunk, dt).x);
   if (bmode == kFineHalving)
@@ -625,7 +631,7 @@ __device__ __forceinline__ void process_item4(const Evolve4Args& a, int pi, int 
     chunk_loop4<false>(v, tab, nt, dt, rg, bb, bmode, pxdt, pydt, e, lds);
 
   const double2 aout = edge[1];
-  write_density(d, a.f, a.units, m, m < d.nmodes ? project(v, px - aout.x, py - aout.y, ep) : 0.0);
+  write_density(d, a.f, a.units, m, m < d.ndist ? project(v, px - aout.x, py - aout.y, ep) : 0.0);
 }
 
 __global__ void __launch_bounds__(kItem) __attribute__((amdgpu_waves_per_eu(4))) k_evolve4(Evolve4Args a) {
@@ -801,7 +807,7 @@ __device__ __forceinline__ void process_item_split(const SplitArgs& a, int pi, i
   const double2* edge = reinterpret_cast<const double2*>(a.Aedge) + 2 * pi;
   const int64_t m = int64_t(first) + threadIdx.x;
   double px, py, pz;
-  mode_momentum(d, m < d.nmodes ? m : 0, px, py, pz);
+  mode_momentum(d, m < d.ndist ? m : 0, px, py, pz);
   const double ep = sqrt(fma(pz, pz, 1.0));
   SplitMode<NSUB> k;
   double th0;
@@ -825,7 +831,7 @@ __device__ __forceinline__ void process_item_split(const SplitArgs& a, int pi, i
   const double2 ain = edge[0];
   init_state(v, px - ain.x, py - ain.y, ep);
   phase_z(v, c0, s0);
-  const BlockBox bb = block_box(d, first / kSelBlock);
+  const BlockBox bb = block_box(d, first / kSelBlock, d.ndist);
   const double* rg = a.ranges + 4 * int64_t(d.chk_off);
   const int bmode = __builtin_amdgcn_readfirstlane(block_variant<1>(bb, rg, (nt + kChunk - 1) / kChunk, dtw).x);
   if (bmode == kFineHalving)
@@ -835,7 +841,7 @@ __device__ __forceinline__ void process_item_split(const SplitArgs& a, int pi, i
   phase_z(v, c0, -s0);
 
   const double2 aout = edge[1];
-  write_density(d, a.f, a.units, m, m < d.nmodes ? project(v, px - aout.x, py - aout.y, ep) : 0.0);
+  write_density(d, a.f, a.units, m, m < d.ndist ? project(v, px - aout.x, py - aout.y, ep) : 0.0);
 }
 
 template <int NSUB>

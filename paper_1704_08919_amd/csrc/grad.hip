@@ -303,10 +303,9 @@ __device__ __forceinline__ void grad_item(const GradArgs& a, int item, int pi, d
   const PulseDev& d = a.desc[pi];
   const int nt = d.nt;
   const double dt = d.dt;
-  const int64_t nmodes = int64_t(d.n[0]) * d.n[1] * d.n[2];
   const int li = item - d.item_off;
   const int64_t m = int64_t(li) * kItem + threadIdx.x;
-  const bool active = m < nmodes;
+  const bool active = m < d.ndist;
   const int h = a.sel[d.blk_off + li * kItem / kSelBlock].y;
   const double inv4h = ldexp(1.0, -2 * h);
   const auto fit = load_fit_of<MODE>();
@@ -342,6 +341,9 @@ __device__ __forceinline__ void grad_item(const GradArgs& a, int item, int pi, d
     if constexpr (MODE < kFineHalving) renormalise(psi);
   }
 
+  // modes that stand for a mirror image count twice: everything after t_f is linear in alpha_s^* psi
+  const double weight = !active ? 0.0 : mirror_mode(d, m) != m ? 2.0 : 1.0;
+
   // t_f: normalise each block, alpha_s = <+_s(P_out)|psi_s>, final-state terms, and
   // W_s = Im(conj(alpha_s) <+_s|tau|psi_s>), the start of the backward sweep (chi'_s = alpha_s |+_s>)
   WPair w;
@@ -359,8 +361,9 @@ __device__ __forceinline__ void grad_item(const GradArgs& a, int item, int pi, d
     p = Blk{p.ar * inv, p.ai * inv, p.br * inv, p.bi * inv};
     double al_r, al_i;
     inner(up_out, p, al_r, al_i);
-    if (!active) al_r = al_i = 0.0;
-    f += fma(al_r, al_r, al_i * al_i);
+    f += weight * fma(al_r, al_r, al_i * al_i);
+    al_r *= weight;
+    al_i *= weight;
     // d alpha = <+|dh|-><-|psi>/(2 w), dh = tau_x dP_x + s tau_y dP_y, dP = -dA(t_f)
     double xr, xi, yr, yi, mr, mi;
     tau_xy(up_out, dn_out, sg, xr, xi, yr, yi);
@@ -443,7 +446,7 @@ __device__ __forceinline__ void grad_item(const GradArgs& a, int item, int pi, d
     for (int w = 1; w < kWaves; ++w) v += red[w][threadIdx.x].x;
     a.epart[int64_t(item) * 4 + threadIdx.x] = v;
   }
-  if (a.units) write_unit(d, a.units, m, active ? f : 0.0);
+  if (a.units) write_unit(d, a.units, m, f);
 }
 
 __global__ void __launch_bounds__(kItem) __attribute__((amdgpu_waves_per_eu(3))) k_yield_grad(GradArgs a) {

@@ -78,8 +78,7 @@ po_status build_queue(po_plan* p, hipStream_t s) {
   std::stable_sort(order.begin(), order.end(), [&](int a, int c) { return p->specs[a].nt > p->specs[c].nt; });
   std::vector<int2> q;
   for (int i : order) {
-    const int64_t m = int64_t(p->grids[i].n[0]) * p->grids[i].n[1] * p->grids[i].n[2];
-    for (int64_t first = 0; first < m; first += per) q.push_back(make_int2(i, int(first)));
+    for (int64_t first = 0; first < p->h_desc[i].ndist; first += per) q.push_back(make_int2(i, int(first)));
   }
   p->n_items = int(q.size());
   if (p->d_queue) PO_HIP(hipFree(p->d_queue));

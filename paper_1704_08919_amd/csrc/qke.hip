@@ -141,7 +141,7 @@ __global__ void __launch_bounds__(kQPoints) k_qke(QkeArgs a) {
 
   const int64_t m = int64_t(item - d.item_off) * kItem + threadIdx.x;
   double px, py, pz;
-  mode_momentum(d, m < d.nmodes ? m : 0, px, py, pz);
+  mode_momentum(d, m < d.ndist ? m : 0, px, py, pz);
   const double e2 = fma(pz, pz, 1.0), ep = sqrt(e2);
 
   // chunk c holds the points h = 2 c kQChunk + 1 + i, i < kQPoints
@@ -168,7 +168,7 @@ __global__ void __launch_bounds__(kQPoints) k_qke(QkeArgs a) {
     __syncthreads();
   }
 
-  write_density(d, a.f, a.units, m, m < d.nmodes ? y.f : 0.0);
+  write_density(d, a.f, a.units, m, m < d.ndist ? y.f : 0.0);
 }
 
 }  // namespace

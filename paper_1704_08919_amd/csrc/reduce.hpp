@@ -54,19 +54,35 @@ __device__ __forceinline__ void mode_momentum(const PulseDev& d, int64_t m, doub
   pz = __dadd_rn(d.lo[2], __dmul_rn(double(iz) + 0.5, d.dp[2]));
 }
 
-// Writes the 64-mode unit sum of v (lanes beyond the pulse's modes pass 0).
+// Mode with the opposite p_z on a mirror-symmetric grid (the mode itself at p_z = 0 and on any other
+// grid): planes iz and n_z - 1 - iz.
+__device__ __forceinline__ int64_t mirror_mode(const PulseDev& d, int64_t m) {
+  if (!d.mirror) return m;
+  const int64_t plane = int64_t(d.n[0]) * d.n[1];
+  return m + (d.n[2] - 1 - 2 * (m / plane)) * plane;
+}
+
+// Writes the 64-mode unit sum of v (lanes beyond the pulse's distinct modes pass 0).
 __device__ __forceinline__ void write_unit(const PulseDev& d, double* __restrict__ units, int64_t lane_mode, double v) {
   const double s = wave_sum(v);
   const int64_t base = lane_mode - (threadIdx.x & 63);
-  if ((threadIdx.x & 63) == 0 && base < d.nmodes) units[d.unit_off + base / kUnit] = s;
+  if ((threadIdx.x & 63) == 0 && base < d.ndist) units[d.unit_off + base / kUnit] = s;
 }
 
-// Writes the density of mode m (lanes beyond the pulse's modes pass 0) to f and its 64-mode unit
-// sum to units (either may be NULL).
+// Writes the density of distinct mode m (lanes beyond them pass 0) to f and its 64-mode unit sum to
+// units (either may be NULL), in both places for its mirror image too.
 __device__ __forceinline__ void write_density(const PulseDev& d, double* __restrict__ f, double* __restrict__ units,
                                               int64_t m, double fv) {
-  if (f && m < d.nmodes) f[d.mode_off + m] = fv;
-  if (units) write_unit(d, units, m, fv);
+  double v = fv;
+  if (m < d.ndist) {
+    const int64_t mm = mirror_mode(d, m);
+    if (mm != m) v = fv + fv;
+    if (f) {
+      f[d.mode_off + m] = fv;
+      if (mm != m) f[d.mode_off + mm] = fv;
+    }
+  }
+  if (units) write_unit(d, units, m, v);
 }
 
 }  // namespace po
