@@ -171,6 +171,23 @@ po_status build_batch(int32_t n, const po_pulse_spec* specs, const po_grid* grid
     out[i] = d;
   }
   if (items > (int64_t(1) << 31) - 1) return set_error(PO_ERR_INVALID, "batch has too many modes");
+  int64_t slots = 0;
+  if (specs && grids)
+    for (int i = 0; i < n; ++i) {
+      // Few modes leave the chip idle along the mode axis, so they get more segments: 256 slots for a
+      // 1024-mode sheet (one workgroup per CU), 8 segments from 16384 modes on, where a batch of any
+      // size fills the chip and each further segment only costs its product with the state (32 of
+      // 33 x 64 instructions at the shortest length).  A matter of the pulse's own sizes: its result
+      // does not depend on the batch.
+      int want = 8;
+      while (want < 64 && want * out[i].nitems < 512) want *= 2;
+      const int units = (out[i].nt + kSegUnit - 1) / kSegUnit;
+      out[i].seg_len = (units + want - 1) / want * kSegUnit;
+      out[i].nseg = (out[i].nt + out[i].seg_len - 1) / out[i].seg_len;
+      out[i].slot_off = slots;
+      slots += int64_t(out[i].nitems) * out[i].nseg;
+    }
+  b->total_slots = slots;
   b->total_rows = tab;
   b->total_modes = modes;
   b->total_coeff = coeff;
@@ -240,12 +257,15 @@ unsigned long long* g_counts = nullptr;  // device: mode-steps per series varian
 
 // Evolution and yield into caller-provided scratch: d_units [total_units] (used when d_J is
 // non-NULL), d_ranges [4 total_chunks].  timed: bracket the evolution with the kernel timers.
+// d_prop: scratch of the time-split form, or NULL for the form without.
 po_status evolve_into(const Batch& b, const PulseDev* d_desc, const double* d_A, const double* d_A_edge, double* d_f,
-                      double* d_J, hipStream_t s, double* d_units, double* d_ranges, bool timed_ok) {
+                      double* d_J, hipStream_t s, double* d_units, double* d_ranges, double* d_prop, bool timed_ok) {
   hipEvent_t e0 = nullptr;
   const bool timed = timed_ok && timer_start(s, &e0);
   PO_TRY(launch_chunk_ranges(b, d_desc, d_A, d_ranges, s));
-  PO_TRY(launch_evolve_grid(b, d_desc, d_A, d_A_edge, d_ranges, d_f, d_J ? d_units : nullptr, s));
+  double* units = d_J ? d_units : nullptr;
+  if (d_prop) PO_TRY(launch_evolve_segments(b, d_desc, d_A, d_A_edge, d_ranges, d_prop, d_f, units, s));
+  else PO_TRY(launch_evolve_grid(b, d_desc, d_A, d_A_edge, d_ranges, d_f, units, s));
   if (timed) {
     timer_stop(s, e0);
     PO_TRY(timer_count(b.n_pulses, d_desc, d_ranges, s));
@@ -256,14 +276,16 @@ po_status evolve_into(const Batch& b, const PulseDev* d_desc, const double* d_A,
 
 po_status evolve_impl(const Batch& b, const PulseDev* d_desc, const double* d_A, const double* d_A_edge, double* d_f,
                       double* d_J, hipStream_t s) {
-  Scratch units, sel;
+  Scratch units, sel, prop;
   double* d_units = nullptr;
   if (d_J) {
     PO_TRY(units.alloc(sizeof(double) * size_t(b.total_units), s));
     d_units = static_cast<double*>(units.ptr);
   }
   PO_TRY(sel.alloc(sizeof(double) * 4 * size_t(b.total_chunks), s));
-  return evolve_into(b, d_desc, d_A, d_A_edge, d_f, d_J, s, d_units, static_cast<double*>(sel.ptr), true);
+  if (split_in_time(b)) PO_TRY(prop.alloc(sizeof(double) * kSlotDoubles * size_t(b.total_slots), s));
+  return evolve_into(b, d_desc, d_A, d_A_edge, d_f, d_J, s, d_units, static_cast<double*>(sel.ptr),
+                     static_cast<double*>(prop.ptr), true);
 }
 
 // Gradient of J with respect to the tables (forward + adjoint sweep per mode, fixed-order sums).
@@ -769,8 +791,12 @@ po_status po_evaluate_noalloc(int32_t n, const po_pulse_spec* specs, const po_gr
   PO_TRY(synth_into(specs, d_coeff, d_A, nullptr, d_A_edge, d_scale, s, b, d_desc,
                     reinterpret_cast<double*>(sc + o_spec), reinterpret_cast<double*>(sc + o_part),
                     reinterpret_cast<double*>(sc + o_scl)));
+  // what the scratch array has left serves the time-split form of a small batch
+  const size_t prop_bytes = sizeof(double) * kSlotDoubles * size_t(b.total_slots);
+  double* d_prop = split_in_time(b) && prop_bytes <= kNoAllocScratchBytes - need ? reinterpret_cast<double*>(sc + need)
+                                                                                  : nullptr;
   return evolve_into(b, d_desc, d_A, d_A_edge, d_f, d_J, s, reinterpret_cast<double*>(sc + o_units),
-                     reinterpret_cast<double*>(sc + o_ranges), false);
+                     reinterpret_cast<double*>(sc + o_ranges), d_prop, false);
 }
 
 po_status po_timer_enable(int on) {

@@ -35,6 +35,7 @@ constexpr int kUnit = 64;         // momentum modes per reduction unit, one wave
 constexpr int kItem = 256;        // modes per workgroup in the default (non-plan) evolution launch
 constexpr int kSelBlock = 512;    // modes per series-selection block: a multiple of every launch's item
 constexpr int kChunkSteps = 256;  // time steps per LDS chunk of the per-mode kernels (and per table range)
+constexpr int kSegUnit = 64;      // time segments of a pulse are multiples of this many steps
 constexpr int kMaxLines = 8192;   // spectral lines per pulse
 constexpr int kMaxNs = 64;        // B-spline coefficients per spectral function
 constexpr int kMaxSub = 8;        // sample points per step of po_field_samples
@@ -59,6 +60,11 @@ struct PulseDev {
   int32_t item_off;   // first workgroup item of this pulse in the default evolution launch
   int32_t nitems;
   int32_t blk_off;    // first series-selection block (kSelBlock modes) of this pulse in the batch
+  // Time segments of the second-order evolution: nseg of seg_len steps (the last may be shorter),
+  // each evolved from the identity and then applied to the state.  slot_off: first (item, segment)
+  // slot of the pulse in the batch, slots in the order item * nseg + segment.
+  int32_t nseg, seg_len;
+  int64_t slot_off;
   double T, dt, dw, wmin, wmax, norm_value, dv;
   double lo[3], dp[3];  // p_d = lo_d + (i + 1/2) dp_d; dp_d = 0 for a sheet (then p_d = lo_d)
 };
@@ -70,6 +76,7 @@ struct Batch {
   int64_t total_units_all = 0; // 64-mode units of all modes, mirror images included
   int32_t total_items = 0;     // workgroups of the default evolution launch
   int32_t total_blocks = 0;    // series-selection blocks (kSelBlock modes, per pulse)
+  int64_t total_slots = 0;     // (256-mode item, time segment) pairs of all pulses
   int32_t total_chunks = 0;    // kChunkSteps-step chunks of all pulses
   int32_t max_stat_blocks = 0; // largest per-pulse block count of the field statistics pass
   int32_t max_nt = 0;
@@ -133,6 +140,14 @@ po_status launch_chunk_ranges(const Batch& b, const PulseDev* d_desc, const doub
                               hipStream_t s);
 po_status launch_evolve_grid(const Batch& b, const PulseDev* d_desc, const double* d_A, const double* d_A_edge,
                              const double* d_ranges, double* d_f, double* d_units, hipStream_t s);
+// The same evolution with one workgroup per (item, segment) and a second kernel that applies each
+// mode's segments in order; d_prop holds kSlotDoubles per slot.  Bitwise equal to the other forms.
+constexpr int kSlotDoubles = 8 * kItem;
+bool split_in_time(const Batch& b);
+po_status launch_segments(const Batch& b, const PulseDev* d_desc, const double* d_A, const double* d_ranges,
+                          double* d_prop, hipStream_t s);
+po_status launch_evolve_segments(const Batch& b, const PulseDev* d_desc, const double* d_A, const double* d_A_edge,
+                                 const double* d_ranges, double* d_prop, double* d_f, double* d_units, hipStream_t s);
 // Persistent launch: items are {pulse, first mode} pairs of cfg.threads * cfg.mpl modes each,
 // taken in queue order through the counter (reset on the stream before the launch).
 po_status launch_evolve_persistent(const EvolveConfig& cfg, int n_pulses, const PulseDev* d_desc, const double* d_A,

@@ -331,6 +331,18 @@ __device__ __forceinline__ void renormalise(State& v) {
   v.cr = ldexp(v.cr, e); v.ci = ldexp(v.ci, e); v.dr = ldexp(v.dr, e); v.di = ldexp(v.di, e);
 }
 
+// A lane's state in slot `slot` of a propagator buffer [slot][8 components][256 lanes].
+__device__ __forceinline__ void store_state(double* __restrict__ buf, int64_t slot, const State& v) {
+  double* p = buf + slot * kSlotDoubles + threadIdx.x;
+  p[0] = v.ar; p[kItem] = v.ai; p[2 * kItem] = v.br; p[3 * kItem] = v.bi;
+  p[4 * kItem] = v.cr; p[5 * kItem] = v.ci; p[6 * kItem] = v.dr; p[7 * kItem] = v.di;
+}
+
+__device__ __forceinline__ State load_state(const double* __restrict__ buf, int64_t slot, int lane) {
+  const double* p = buf + slot * kSlotDoubles + lane;
+  return State{p[0], p[kItem], p[2 * kItem], p[3 * kItem], p[4 * kItem], p[5 * kItem], p[6 * kItem], p[7 * kItem]};
+}
+
 // Negative-energy eigenvector of h_s(P): (-(P_x - i s P_y), w + e) / sqrt(2 w (w + e)).
 __device__ __forceinline__ void init_state(State& v, double Px, double Py, double e) {
   const double w = sqrt(fma(Px, Px, fma(Py, Py, e * e)));

@@ -37,13 +37,16 @@
 //
 // Work decomposition: a workgroup of THREADS lanes (64-wide waves) owns an item of
 // THREADS x MPL consecutive modes of one pulse, MPL modes per lane.  The pulse's table of A
-// is staged through LDS in chunks of 256 steps (double-buffered, one barrier per chunk) and
-// every lane reads the same record, an LDS broadcast.  The states (2 blocks x 2 complex
-// amplitudes per mode) stay in VGPRs for all nt steps.  f is summed per 64-mode unit by one
+// is staged through LDS in chunks of 256 steps and every lane reads the same record, an LDS
+// broadcast.  The propagators (per block the first column, 2 complex amplitudes per mode) stay in
+// VGPRs.  f is summed per 64-mode unit by one
 // wave in a fixed butterfly order, and units per pulse in a fixed tree, so J does not depend on
-// the launch shape or on scheduling.  Two launch forms share the item code: one workgroup per
-// 256-mode item, or persistent workgroups that pull items (longest pulses first) from a device
-// queue through an atomic counter.
+// the launch shape or on scheduling.  Time is cut into segments (a multiple of 64 steps, 8 to 64 of
+// them by the pulse's own sizes); each is evolved from the identity and applied to the state.  Three
+// launch forms share this code and its results: one workgroup per 256-mode item that walks
+// through the segments, persistent workgroups that pull items (longest pulses first) from a device
+// queue through an atomic counter, and, for batches too small to fill the chip, one workgroup per
+// (item, segment) with a second kernel that applies the segments.
 #include <algorithm>
 
 #include "dirac.hpp"
@@ -317,78 +320,133 @@ __device__ __forceinline__ void run_chunk(State (&v)[MPL], const double2* buf, i
   }
 }
 
-// Evolves the item of THREADS * MPL modes of pulse pi starting at mode `first`, writes f and the
-// 64-mode unit sums.  Every lane of the workgroup must call it (it contains barriers).  The table
-// is staged through LDS in chunks of 256 steps (double-buffered, one barrier per chunk).  The
-// series variant is chosen from the item's selection block (items never straddle blocks) and the
-// table ranges, so it depends only on the pulse, the block and the chunk, never on the launch.
+// Per-item constants of the step loops.
+struct ItemTab {
+  const double2* tab;  // the pulse's table
+  const double* rg;    // its chunk ranges
+  BlockBox bb;
+  double dt;
+};
+
+__device__ __forceinline__ ItemTab item_tab(const EvolveArgs& a, const PulseDev& d, int first) {
+  const BlockBox bb = block_box(d, first / kSelBlock, d.ndist);
+  return ItemTab{reinterpret_cast<const double2*>(a.A) + d.tab_off, a.ranges + 4 * int64_t(d.chk_off),
+                 BlockBox{uniform(bb.pxl), uniform(bb.pxh), uniform(bb.pyl), uniform(bb.pyh), uniform(bb.pz2)}, d.dt};
+}
+
+// Propagators of steps [n0, n1) for the MPL modes of a lane: the first column per block of a multiple of
+// a unitary matrix.  Every lane of the workgroup must call it (barriers).  The table is staged
+// through LDS chunk by chunk; the series variant of each piece is chosen from the item's selection
+// block (items never straddle blocks) and the chunk's table range, so it depends only on the pulse,
+// the block and the chunk, never on the launch.
 template <int THREADS, int MPL>
-__device__ __forceinline__ void process_item(const EvolveArgs& a, int pi, int first, double2 (*lds)[kChunk]) {
-  constexpr int kPre = kChunk / THREADS;  // table records each lane stages per chunk
+__device__ __forceinline__ void propagate(State (&v)[MPL], const ItemTab& t, int n0, int n1, const CotMode (&mode)[MPL],
+                                          double2* lds) {
+#pragma unroll
+  for (int j = 0; j < MPL; ++j) v[j] = State{1.0, 0.0, 0.0, 0.0, 1.0, 0.0, 0.0, 0.0};
+  for (int n = n0; n < n1;) {
+    const int c = n / kChunk, len = min((c + 1) * kChunk, n1) - n;
+    __syncthreads();
+    for (int i = threadIdx.x; i < len; i += THREADS) lds[i] = t.tab[n + i];
+    __syncthreads();
+    const double* rg = t.rg + 4 * c;
+    run_chunk<MPL>(v, lds, len, x_bound(t.bb, rg[0], rg[1], rg[2], rg[3], t.dt), t.dt, mode);
+    n += len;
+  }
+}
+
+// Momentum of distinct mode m (mode 0 for lanes beyond them), its e_perp.
+__device__ __forceinline__ double lane_mode(const PulseDev& d, int64_t m, double& px, double& py) {
+  double pz;
+  mode_momentum(d, m < d.ndist ? m : 0, px, py, pz);
+  return sqrt(fma(pz, pz, 1.0));
+}
+
+// Evolves the item of THREADS * MPL modes of pulse pi starting at mode `first`, writes f and the
+// 64-mode unit sums.  Every lane of the workgroup must call it (it contains barriers).
+template <int THREADS, int MPL>
+__device__ __forceinline__ void process_item(const EvolveArgs& a, int pi, int first, double2* lds) {
   const PulseDev& d = a.desc[pi];
-  const int nt = d.nt;
-  const double dt = d.dt;
-  const double2* tab = reinterpret_cast<const double2*>(a.A) + d.tab_off;
   const double2* edge = reinterpret_cast<const double2*>(a.Aedge) + 2 * pi;
   const double2 ain = edge[0];
-  BlockBox bb = block_box(d, first / kSelBlock, d.ndist);
-  bb = BlockBox{uniform(bb.pxl), uniform(bb.pxh), uniform(bb.pyl), uniform(bb.pyh), uniform(bb.pz2)};
-  const double* rg = a.ranges + 4 * int64_t(d.chk_off);
+  const ItemTab t = item_tab(a, d, first);
 
-  State v[MPL];
+  State psi[MPL];
   CotMode mode[MPL];
 #pragma unroll
   for (int j = 0; j < MPL; ++j) {
-    const int64_t m = int64_t(first) + j * THREADS + threadIdx.x;
-    double px, py, pz;
-    mode_momentum(d, m < d.ndist ? m : 0, px, py, pz);
-    const double e = sqrt(fma(pz, pz, 1.0));
-    init_state(v[j], px - ain.x, py - ain.y, e);
+    double px, py;
+    const double e = lane_mode(d, int64_t(first) + j * THREADS + threadIdx.x, px, py);
+    init_state(psi[j], px - ain.x, py - ain.y, e);
     mode[j] = cot_mode(px, py, e);
   }
-
-  const int nchunks = (nt + kChunk - 1) / kChunk;
+  for (int n0 = 0; n0 < d.nt; n0 += d.seg_len) {
+    State v[MPL];
+    propagate<THREADS, MPL>(v, t, n0, min(n0 + d.seg_len, d.nt), mode, lds);
 #pragma unroll
-  for (int r = 0; r < kPre; ++r) {
-    const int n = r * THREADS + threadIdx.x;
-    lds[0][n] = n < nt ? tab[n] : make_double2(0.0, 0.0);
-  }
-  __syncthreads();
-  for (int c = 0; c < nchunks; ++c) {
-    double2 pre[kPre];
-#pragma unroll
-    for (int r = 0; r < kPre; ++r) {
-      const int n = (c + 1) * kChunk + r * THREADS + threadIdx.x;
-      pre[r] = (c + 1 < nchunks && n < nt) ? tab[n] : make_double2(0.0, 0.0);
-    }
-    run_chunk<MPL>(v, lds[c & 1], min(kChunk, nt - c * kChunk),
-                   x_bound(bb, rg[4 * c], rg[4 * c + 1], rg[4 * c + 2], rg[4 * c + 3], dt), dt, mode);
-#pragma unroll
-    for (int r = 0; r < kPre; ++r) lds[(c + 1) & 1][r * THREADS + threadIdx.x] = pre[r];
-    __syncthreads();
+    for (int j = 0; j < MPL; ++j) apply_propagator(psi[j], v[j]);
   }
 
   const double2 aout = edge[1];
 #pragma unroll
   for (int j = 0; j < MPL; ++j) {
     const int64_t m = int64_t(first) + j * THREADS + threadIdx.x;
-    double fv = 0.0;
-    if (m < d.ndist) {
-      double px, py, pz;
-      mode_momentum(d, m, px, py, pz);
-      fv = project(v[j], px - aout.x, py - aout.y, sqrt(fma(pz, pz, 1.0)));
-    }
-    write_density(d, a.f, a.units, m, fv);
+    double px, py;
+    const double e = lane_mode(d, m, px, py);
+    write_density(d, a.f, a.units, m, m < d.ndist ? project(psi[j], px - aout.x, py - aout.y, e) : 0.0);
   }
 }
 
 // One workgroup per 256-mode item; four waves per SIMD (the register budget of the variant
 // switch, met without spills).
 __global__ void __launch_bounds__(kItem) __attribute__((amdgpu_waves_per_eu(4))) k_evolve(EvolveArgs a) {
-  __shared__ double2 lds[2][kChunk];
+  __shared__ double2 lds[kChunk];
   const int item = xcd_item(blockIdx.x, gridDim.x);
   const int pi = find_pulse_item(a.desc, a.n_pulses, item);
   process_item<kItem, 1>(a, pi, (item - a.desc[pi].item_off) * kItem, lds);
+}
+
+// Time-split form, first kernel: one workgroup per (item, segment) slot; the segment's propagators go to
+// prop[slot][8 components][256 lanes].
+__global__ void __launch_bounds__(kItem) __attribute__((amdgpu_waves_per_eu(4)))
+k_segments(EvolveArgs a, double* __restrict__ prop) {
+  __shared__ double2 lds[kChunk];
+  const int64_t slot = blockIdx.x;
+  const int pi = find_pulse_slot(a.desc, a.n_pulses, slot);
+  const PulseDev& d = a.desc[pi];
+  const int rel = int(slot - d.slot_off), li = rel / d.nseg, seg = rel - li * d.nseg;
+  double px, py;
+  const double e = lane_mode(d, int64_t(li) * kItem + threadIdx.x, px, py);
+  const CotMode mode[1] = {cot_mode(px, py, e)};
+  State v[1];
+  propagate<kItem, 1>(v, item_tab(a, d, li * kItem), seg * d.seg_len, min((seg + 1) * d.seg_len, d.nt), mode, lds);
+  store_state(prop, slot, v[0]);
+}
+
+// Second kernel: one lane per mode applies its segments in order.  Wavefronts of 64 here (one per
+// workgroup) spread the few modes over as many CUs; the loads of four segments are in flight together.
+__global__ void __launch_bounds__(64) k_join_segments(EvolveArgs a, const double* __restrict__ prop) {
+  const int item = blockIdx.x / (kItem / 64), lane = (blockIdx.x % (kItem / 64)) * 64 + threadIdx.x;
+  const int pi = find_pulse_item(a.desc, a.n_pulses, item);
+  const PulseDev& d = a.desc[pi];
+  const int li = item - d.item_off;
+  const int64_t m = int64_t(li) * kItem + lane, slot = d.slot_off + int64_t(li) * d.nseg;
+  const double2* edge = reinterpret_cast<const double2*>(a.Aedge) + 2 * pi;
+  const double2 ain = edge[0], aout = edge[1];
+  double px, py;
+  const double e = lane_mode(d, m, px, py);
+  State psi;
+  init_state(psi, px - ain.x, py - ain.y, e);
+  for (int s0 = 0; s0 < d.nseg; s0 += 4) {
+    State v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (s0 + k < d.nseg) v[k] = load_state(prop, slot + s0 + k, lane);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (s0 + k < d.nseg) apply_propagator(psi, v[k]);
+  }
+  write_density(d, a.f, a.units, m, m < d.ndist ? project(psi, px - aout.x, py - aout.y, e) : 0.0);
 }
 
 __global__ void k_reset_counter(int* counter) { *counter = 0; }
@@ -400,7 +458,7 @@ __global__ void k_reset_counter(int* counter) { *counter = 0; }
 template <int THREADS, int MPL>
 __global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(MPL == 1 ? 4 : 2)))
 k_evolve_persistent(EvolveArgs a, const int2* __restrict__ queue, int n_items, int* __restrict__ counter) {
-  __shared__ double2 lds[2][kChunk];
+  __shared__ double2 lds[kChunk];
   __shared__ int s_item;
   for (;;) {
     if (threadIdx.x == 0) s_item = atomicAdd(counter, 1);
@@ -873,6 +931,32 @@ po_status launch_evolve_grid(const Batch& b, const PulseDev* d_desc, const doubl
                              const double* d_ranges, double* d_f, double* d_units, hipStream_t s) {
   EvolveArgs a{d_desc, b.n_pulses, d_A, d_A_edge, d_ranges, d_f, d_units};
   hipLaunchKernelGGL(k_evolve, dim3(b.total_items), dim3(kItem), 0, s, a);
+  PO_HIP(hipGetLastError());
+  return PO_OK;
+}
+
+// The batch is split in time when its items alone load the CUs thinly or unevenly.  Measured, one
+// pulse at nt = 4096, us per call split / not split: 16 items 75 / 357, 128 items 190 / 344, 256 items
+// 329 / 352, 320 items 402 / 581 (some CUs then hold two workgroups, the others one), 384 items
+// 480 / 594, 512 items 619 / 626 and, at nt = 1024, 194 / 177; 48 sheets of 1024 modes (192 items,
+// 12288 slots) 349 / 405, 64 of them 420 / 408.  At most 8192 slots (128 MiB of propagators).
+bool split_in_time(const Batch& b) {
+  return b.total_items <= 448 && b.total_slots > b.total_items && b.total_slots <= 8192;
+}
+
+po_status launch_segments(const Batch& b, const PulseDev* d_desc, const double* d_A, const double* d_ranges,
+                          double* d_prop, hipStream_t s) {
+  EvolveArgs a{d_desc, b.n_pulses, d_A, nullptr, d_ranges, nullptr, nullptr};
+  hipLaunchKernelGGL(k_segments, dim3(unsigned(b.total_slots)), dim3(kItem), 0, s, a, d_prop);
+  PO_HIP(hipGetLastError());
+  return PO_OK;
+}
+
+po_status launch_evolve_segments(const Batch& b, const PulseDev* d_desc, const double* d_A, const double* d_A_edge,
+                                 const double* d_ranges, double* d_prop, double* d_f, double* d_units, hipStream_t s) {
+  PO_TRY(launch_segments(b, d_desc, d_A, d_ranges, d_prop, s));
+  EvolveArgs a{d_desc, b.n_pulses, d_A, d_A_edge, d_ranges, d_f, d_units};
+  hipLaunchKernelGGL(k_join_segments, dim3(unsigned(b.total_items) * (kItem / 64)), dim3(64), 0, s, a, d_prop);
   PO_HIP(hipGetLastError());
   return PO_OK;
 }

@@ -27,6 +27,7 @@ struct po_plan {
   int* d_counter = nullptr;
   double* d_ranges = nullptr;  // table range per chunk
   double* d_units = nullptr;
+  double* d_prop = nullptr;    // segment propagators of a batch that is split in time (any launch shape)
   double* d_A = nullptr;
   double* d_edge = nullptr;
   double* d_spec = nullptr;
@@ -47,7 +48,7 @@ namespace {
 void free_all(po_plan* p) {
   if (p->exec) (void)hipGraphExecDestroy(p->exec);
   if (p->graph) (void)hipGraphDestroy(p->graph);
-  void* bufs[] = {p->d_desc, p->d_queue, p->d_counter, p->d_ranges, p->d_units, p->d_A, p->d_edge,
+  void* bufs[] = {p->d_desc, p->d_queue, p->d_counter, p->d_ranges, p->d_units, p->d_prop, p->d_A, p->d_edge,
                   p->d_spec, p->d_part, p->d_scale, p->d_probe, p->d_Jprobe};
   for (void* q : bufs)
     if (q) (void)hipFree(q);
@@ -103,7 +104,9 @@ po_status enqueue(po_plan* p, const double* d_coeff, const double* d_A, const do
   }
   PO_TRY(launch_chunk_ranges(p->b, p->d_desc, d_A, p->d_ranges, s));
   double* units = d_J ? p->d_units : nullptr;
-  if (p->cfg.persistent)
+  if (p->d_prop)
+    PO_TRY(launch_evolve_segments(p->b, p->d_desc, d_A, d_edge, p->d_ranges, p->d_prop, d_f, units, s));
+  else if (p->cfg.persistent)
     PO_TRY(launch_evolve_persistent(p->cfg, p->n, p->d_desc, d_A, d_edge, p->d_ranges, p->d_queue, p->n_items,
                                     p->workgroups, p->d_counter, d_f, units, s));
   else
@@ -221,6 +224,7 @@ po_status plan_create(int32_t n, const po_pulse_spec* specs, const po_grid* grid
   PO_TRY(dalloc(&p->d_counter, 1));
   PO_TRY(dalloc(&p->d_ranges, 4 * size_t(p->b.total_chunks)));
   PO_TRY(dalloc(&p->d_units, size_t(p->b.total_units)));
+  if (split_in_time(p->b)) PO_TRY(dalloc(&p->d_prop, size_t(kSlotDoubles) * size_t(p->b.total_slots)));
   PO_TRY(dalloc(&p->d_A, size_t(2 * p->b.total_rows)));
   PO_TRY(dalloc(&p->d_edge, size_t(4 * n)));
   PO_TRY(dalloc(&p->d_spec, size_t(p->b.total_spec)));

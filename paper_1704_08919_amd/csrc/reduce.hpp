@@ -36,6 +36,16 @@ __device__ __forceinline__ int find_pulse_item(const PulseDev* __restrict__ desc
   return lo;
 }
 
+// Pulse owning (item, segment) slot `slot`.
+__device__ __forceinline__ int find_pulse_slot(const PulseDev* __restrict__ desc, int n, int64_t slot) {
+  int lo = 0, hi = n - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (desc[mid].slot_off <= slot) lo = mid; else hi = mid - 1;
+  }
+  return lo;
+}
+
 // Workgroup IDs are dispatched round-robin over the 8 XCDs (each with its own L2), so block b runs
 // on XCD b % 8.  Give each XCD a contiguous range of items -- whole stretches of one pulse -- so a
 // pulse's table is fetched from HBM by one L2 rather than by all eight.  A bijection on [0, n).
