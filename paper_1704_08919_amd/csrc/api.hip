@@ -62,13 +62,59 @@ po_status check_device_range(const void* p, size_t bytes, size_t align, const ch
   return PO_OK;
 }
 
+namespace {
+
+// One memory pool per device for the calls' scratch.  The device's default pool hands everything back
+// at each synchronisation, so a call after one pays for mapping its scratch again (an evaluation with
+// 100 MB of it took 1.2 ms, 0.12 ms with the memory kept).  This pool keeps up to kPoolKeep bytes and
+// hands back what is beyond; all of it when an allocation fails for lack of memory.  The pool's
+// reuse is stream-ordered: memory freed on one stream serves another only behind its work.
+constexpr uint64_t kPoolKeep = uint64_t(512) << 20;
+constexpr int kMaxDevices = 64;
+std::mutex g_pool_mu;
+hipMemPool_t g_pool[kMaxDevices] = {};
+
+po_status scratch_pool(hipMemPool_t* out) {
+  int dev = -1;
+  PO_HIP(hipGetDevice(&dev));
+  if (dev < 0 || dev >= kMaxDevices) return set_error(PO_ERR_UNSUPPORTED, "device %d out of range", dev);
+  std::lock_guard<std::mutex> lk(g_pool_mu);
+  if (!g_pool[dev]) {
+    hipMemPoolProps props;
+    std::memset(&props, 0, sizeof props);
+    props.allocType = hipMemAllocationTypePinned;
+    props.location.type = hipMemLocationTypeDevice;
+    props.location.id = dev;
+    hipMemPool_t pool = nullptr;
+    PO_HIP(hipMemPoolCreate(&pool, &props));
+    uint64_t keep = kPoolKeep;
+    const hipError_t e = hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep);
+    if (e != hipSuccess) {
+      (void)hipMemPoolDestroy(pool);
+      return device_error(e, "hipMemPoolSetAttribute");
+    }
+    g_pool[dev] = pool;
+  }
+  *out = g_pool[dev];
+  return PO_OK;
+}
+
+}  // namespace
+
 po_status Scratch::alloc(size_t bytes, hipStream_t s) {
   stream = s;
   if (bytes == 0) bytes = 8;
-  hipError_t e = hipMallocAsync(&ptr, bytes, s);
+  hipMemPool_t pool = nullptr;
+  PO_TRY(scratch_pool(&pool));
+  hipError_t e = hipMallocFromPoolAsync(&ptr, bytes, pool, s);
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    (void)hipMemPoolTrimTo(pool, 0);
+    e = hipMallocFromPoolAsync(&ptr, bytes, pool, s);
+  }
   if (e != hipSuccess) {
     ptr = nullptr;
-    return device_error(e, "hipMallocAsync");
+    return device_error(e, "hipMallocFromPoolAsync");
   }
   return PO_OK;
 }
@@ -171,7 +217,7 @@ po_status build_batch(int32_t n, const po_pulse_spec* specs, const po_grid* grid
     out[i] = d;
   }
   if (items > (int64_t(1) << 31) - 1) return set_error(PO_ERR_INVALID, "batch has too many modes");
-  int64_t slots = 0;
+  int64_t slots = 0, part = 0;
   if (specs && grids)
     for (int i = 0; i < n; ++i) {
       // Few modes leave the chip idle along the mode axis, so they get more segments: 256 slots for a
@@ -186,8 +232,11 @@ po_status build_batch(int32_t n, const po_pulse_spec* specs, const po_grid* grid
       out[i].nseg = (out[i].nt + out[i].seg_len - 1) / out[i].seg_len;
       out[i].slot_off = slots;
       slots += int64_t(out[i].nitems) * out[i].nseg;
+      out[i].part_off = 2 * part;
+      part += int64_t(out[i].nitems) * out[i].nt;
     }
   b->total_slots = slots;
+  b->total_part = part;
   b->total_rows = tab;
   b->total_modes = modes;
   b->total_coeff = coeff;
@@ -213,10 +262,75 @@ po_status check_grids(int32_t n, const po_grid* grids) {
   return PO_OK;
 }
 
-// Uploads the descriptors into a stream-ordered buffer.
-po_status upload(const std::vector<PulseDev>& h, Scratch& sc, hipStream_t s) {
-  PO_TRY(sc.alloc(sizeof(PulseDev) * h.size(), s));
-  PO_HIP(hipMemcpyAsync(sc.ptr, h.data(), sizeof(PulseDev) * h.size(), hipMemcpyHostToDevice, s));
+// Descriptors of a few pulses as a kernel argument.
+constexpr int kArgPulses = 8;
+struct DescPack {
+  PulseDev d[kArgPulses];
+};
+
+__global__ void __launch_bounds__(64) k_put_desc(DescPack p, int n, PulseDev* __restrict__ out) {
+  for (int i = threadIdx.x; i < n; i += 64) out[i] = p.d[i];
+}
+
+// Descriptors of n pulses alike: pulse 0's, with the offsets of pulse i at i times pulse 1's.
+__global__ void __launch_bounds__(64) k_fill_desc(PulseDev d, PulseDev step, int n, PulseDev* __restrict__ out) {
+  const int i = blockIdx.x * 64 + threadIdx.x;
+  if (i >= n) return;
+  d.tab_off = i * step.tab_off;
+  d.mode_off = i * step.mode_off;
+  d.coeff_off = i * step.coeff_off;
+  d.spec_off = i * step.spec_off;
+  d.chk_off = i * step.chk_off;
+  d.unit_off = i * step.unit_off;
+  d.item_off = i * step.item_off;
+  d.slot_off = i * step.slot_off;
+  d.part_off = i * step.part_off;
+  out[i] = d;
+}
+
+// Puts the descriptors into device memory: by kernel arguments where they fit (a few pulses, or pulses
+// alike), which spares the copy from pageable host memory (it takes longer than these kernels, and
+// the host waits for it), else by that copy.
+po_status put_desc(const std::vector<PulseDev>& h, PulseDev* d_desc, hipStream_t s) {
+  static_assert(sizeof(DescPack) <= 3840, "kernel arguments are limited to 4 KiB");
+  const int n = int(h.size());
+  if (n <= kArgPulses) {
+    DescPack p;
+    std::memcpy(p.d, h.data(), sizeof(PulseDev) * h.size());
+    for (int i = n; i < kArgPulses; ++i) std::memset(&p.d[i], 0, sizeof(PulseDev));
+    hipLaunchKernelGGL(k_put_desc, dim3(1), dim3(64), 0, s, p, n, d_desc);
+    PO_HIP(hipGetLastError());
+    return PO_OK;
+  }
+  bool alike = true;
+  for (int i = 2; i < n && alike; ++i) {
+    PulseDev e;
+    std::memcpy(&e, &h[0], sizeof e);
+    const PulseDev& u = h[1];
+    e.tab_off = i * u.tab_off;
+    e.mode_off = i * u.mode_off;
+    e.coeff_off = i * u.coeff_off;
+    e.spec_off = i * u.spec_off;
+    e.chk_off = i * u.chk_off;
+    e.unit_off = i * u.unit_off;
+    e.item_off = i * u.item_off;
+    e.slot_off = i * u.slot_off;
+    e.part_off = i * u.part_off;
+    alike = std::memcmp(&e, &h[i], sizeof e) == 0;
+  }
+  if (alike) {
+    PulseDev e;
+    std::memcpy(&e, &h[1], sizeof e);
+    e.tab_off = e.mode_off = e.coeff_off = e.spec_off = e.unit_off = e.slot_off = e.part_off = 0;
+    e.chk_off = e.item_off = 0;
+    alike = std::memcmp(&e, &h[0], sizeof e) == 0;
+  }
+  if (alike) {
+    hipLaunchKernelGGL(k_fill_desc, dim3((n + 63) / 64), dim3(64), 0, s, h[0], h[1], n, d_desc);
+    PO_HIP(hipGetLastError());
+    return PO_OK;
+  }
+  PO_HIP(hipMemcpyAsync(d_desc, h.data(), sizeof(PulseDev) * h.size(), hipMemcpyHostToDevice, s));
   return PO_OK;
 }
 
@@ -231,22 +345,44 @@ EvalSizes eval_sizes(int32_t n, const Batch& b) {
                    size_t(b.total_units_all), 4 * size_t(b.total_chunks)};
 }
 
-po_status synth_into(const po_pulse_spec* specs, const double* d_coeff, double* d_A, double* d_E, double* d_A_edge,
-                     double* d_scale, hipStream_t s, const Batch& b, const PulseDev* d_desc, double* d_spec,
-                     double* d_part, double* d_scl) {
-  (void)specs;
-  return launch_synth(b, d_desc, d_coeff, d_spec, d_part, d_scl, d_A, d_E, d_A_edge, d_scale, s);
-}
+// Work buffers of the parts of a call: descriptors, synthesis, evolution (in the form the batch takes).
+struct DescWork {
+  size_t desc;
+  DescWork(Work& w, int32_t n) : desc(w.add(sizeof(PulseDev) * n)) {}
+};
+struct SynthWork {
+  size_t spec, part, scl;
+  SynthWork(Work& w, int32_t n, const Batch& b) {
+    const EvalSizes z = eval_sizes(n, b);
+    spec = w.add(sizeof(double) * z.spec);
+    part = w.add(sizeof(double) * z.part);
+    scl = w.add(sizeof(double) * z.scl);
+  }
+};
+struct AdjointWork {  // tables of the pulses and the line terms of the synthesis adjoint
+  size_t A, E, edge, scale, lines;
+  AdjointWork(Work& w, int32_t n, const Batch& b) {
+    A = w.add(sizeof(double) * 2 * size_t(b.total_rows));
+    E = w.add(sizeof(double) * 2 * size_t(b.total_rows));
+    edge = w.add(sizeof(double) * 4 * n);
+    scale = w.add(sizeof(double) * n);
+    lines = w.add(sizeof(double) * size_t(b.total_spec / 4) * 8 * size_t(b.max_ns));
+  }
+};
+struct EvolveWork {
+  size_t units, ranges, prop;
+  bool split;
+  EvolveWork(Work& w, const Batch& b) : split(split_in_time(b)) {
+    units = w.add(sizeof(double) * size_t(b.total_units));
+    ranges = w.add(sizeof(double) * 4 * size_t(b.total_chunks));
+    prop = split ? w.add(sizeof(double) * kSlotDoubles * size_t(b.total_slots)) : 0;
+  }
+};
 
-po_status synth_impl(int32_t n, const po_pulse_spec* specs, const double* d_coeff, double* d_A, double* d_E,
+po_status synth_impl(const Work& w, const SynthWork& z, const double* d_coeff, double* d_A, double* d_E,
                      double* d_A_edge, double* d_scale, hipStream_t s, const Batch& b, const PulseDev* d_desc) {
-  const EvalSizes z = eval_sizes(n, b);
-  Scratch spec, part, scl;
-  PO_TRY(spec.alloc(sizeof(double) * z.spec, s));
-  PO_TRY(part.alloc(sizeof(double) * z.part, s));
-  PO_TRY(scl.alloc(sizeof(double) * z.scl, s));
-  return synth_into(specs, d_coeff, d_A, d_E, d_A_edge, d_scale, s, b, d_desc, static_cast<double*>(spec.ptr),
-                    static_cast<double*>(part.ptr), static_cast<double*>(scl.ptr));
+  return launch_synth(b, d_desc, d_coeff, w.at<double>(z.spec), w.at<double>(z.part), w.at<double>(z.scl), d_A, d_E,
+                      d_A_edge, d_scale, s);
 }
 
 // Event pairs bracketing evolution launches while timers are enabled.
@@ -274,42 +410,29 @@ po_status evolve_into(const Batch& b, const PulseDev* d_desc, const double* d_A,
   return PO_OK;
 }
 
-po_status evolve_impl(const Batch& b, const PulseDev* d_desc, const double* d_A, const double* d_A_edge, double* d_f,
-                      double* d_J, hipStream_t s) {
-  Scratch units, sel, prop;
-  double* d_units = nullptr;
-  if (d_J) {
-    PO_TRY(units.alloc(sizeof(double) * size_t(b.total_units), s));
-    d_units = static_cast<double*>(units.ptr);
-  }
-  PO_TRY(sel.alloc(sizeof(double) * 4 * size_t(b.total_chunks), s));
-  if (split_in_time(b)) PO_TRY(prop.alloc(sizeof(double) * kSlotDoubles * size_t(b.total_slots), s));
-  return evolve_into(b, d_desc, d_A, d_A_edge, d_f, d_J, s, d_units, static_cast<double*>(sel.ptr),
-                     static_cast<double*>(prop.ptr), true);
+po_status evolve_impl(const Work& w, const EvolveWork& z, const Batch& b, const PulseDev* d_desc, const double* d_A,
+                      const double* d_A_edge, double* d_f, double* d_J, hipStream_t s) {
+  return evolve_into(b, d_desc, d_A, d_A_edge, d_f, d_J, s, w.at<double>(z.units), w.at<double>(z.ranges),
+                     z.split ? w.at<double>(z.prop) : nullptr, true);
 }
 
 // Gradient of J with respect to the tables (forward + adjoint sweep per mode, fixed-order sums).
-po_status yield_grad_impl(const Batch& b, const std::vector<PulseDev>& h, const PulseDev* d_desc, const double* d_A,
-                          const double* d_A_edge, double* d_J, double* d_gA, double* d_gedge, hipStream_t s) {
-  std::vector<int64_t> goff(b.n_pulses);
-  int64_t tot = 0;
-  for (int i = 0; i < b.n_pulses; ++i) {
-    goff[i] = tot;
-    tot += int64_t(h[i].nitems) * h[i].nt * 2;
+struct GradWork {
+  size_t part, epart, units, sel;
+  GradWork(Work& w, const Batch& b) {
+    part = w.add(sizeof(double) * 2 * size_t(b.total_part));
+    epart = w.add(sizeof(double) * 4 * size_t(b.total_items));
+    units = w.add(sizeof(double) * size_t(b.total_units));
+    sel = w.add(sizeof(int2) * size_t(b.total_blocks));
   }
-  Scratch sgoff, part, epart, units, sel, ged;
-  PO_TRY(part.alloc(sizeof(double) * size_t(tot), s));  // the large one first: fail before enqueueing work
-  PO_TRY(sgoff.alloc(sizeof(int64_t) * goff.size(), s));
-  PO_HIP(hipMemcpyAsync(sgoff.ptr, goff.data(), sizeof(int64_t) * goff.size(), hipMemcpyHostToDevice, s));
-  PO_TRY(epart.alloc(sizeof(double) * 4 * size_t(b.total_items), s));
-  PO_TRY(units.alloc(sizeof(double) * size_t(b.total_units), s));
-  PO_TRY(sel.alloc(sizeof(int2) * size_t(b.total_blocks), s));
-  int2* d_sel = static_cast<int2*>(sel.ptr);
-  double* d_units = static_cast<double*>(units.ptr);
-  PO_TRY(launch_block_select(b, d_desc, d_A, d_sel, s));
-  PO_TRY(launch_yield_grad(b, d_desc, d_A, d_A_edge, d_sel, static_cast<int64_t*>(sgoff.ptr),
-                           static_cast<double*>(part.ptr), static_cast<double*>(epart.ptr), d_units, d_gA, d_gedge, s));
-  if (d_J) PO_TRY(launch_yield_from_units(b, d_desc, d_units, d_J, s));
+};
+
+po_status yield_grad_impl(const Work& w, const GradWork& z, const Batch& b, const PulseDev* d_desc, const double* d_A,
+                          const double* d_A_edge, double* d_J, double* d_gA, double* d_gedge, hipStream_t s) {
+  PO_TRY(launch_block_select(b, d_desc, d_A, w.at<int2>(z.sel), s));
+  PO_TRY(launch_yield_grad(b, d_desc, d_A, d_A_edge, w.at<int2>(z.sel), w.at<double>(z.part), w.at<double>(z.epart),
+                           w.at<double>(z.units), d_gA, d_gedge, s));
+  if (d_J) PO_TRY(launch_yield_from_units(b, d_desc, w.at<double>(z.units), d_J, s));
   return PO_OK;
 }
 
@@ -459,9 +582,13 @@ po_status po_pulse_synth(int32_t n, const po_pulse_spec* specs, const double* d_
   PO_TRY(check_device_range(d_A_edge, sizeof(double) * 4 * n, 8, "d_A_edge"));
   if (d_scale) PO_TRY(check_device_range(d_scale, sizeof(double) * n, 8, "d_scale"));
   hipStream_t s = static_cast<hipStream_t>(stream);
-  Scratch desc;
-  PO_TRY(upload(h, desc, s));
-  PO_TRY(synth_impl(n, specs, d_coeff, d_A, d_E, d_A_edge, d_scale, s, b, static_cast<PulseDev*>(desc.ptr)));
+  Work w;
+  const DescWork dw(w, n);
+  const SynthWork sw(w, n, b);
+  PO_TRY(w.alloc(s));
+  PulseDev* d_desc = w.at<PulseDev>(dw.desc);
+  PO_TRY(put_desc(h, d_desc, s));
+  PO_TRY(synth_impl(w, sw, d_coeff, d_A, d_E, d_A_edge, d_scale, s, b, d_desc));
   return check_finite(d_A, 2 * b.total_rows, "d_A", s);
 }
 
@@ -486,9 +613,13 @@ po_status po_evolve_modes(int32_t n, const po_pulse_spec* specs, const po_grid* 
     if (timed) timer_stop(s, e0);
     return check_outputs(b, d_f, d_J, s);
   }
-  Scratch desc;
-  PO_TRY(upload(h, desc, s));
-  PO_TRY(evolve_impl(b, static_cast<PulseDev*>(desc.ptr), d_A, d_A_edge, d_f, d_J, s));
+  Work w;
+  const DescWork dw(w, n);
+  const EvolveWork ew(w, b);
+  PO_TRY(w.alloc(s));
+  PulseDev* d_desc = w.at<PulseDev>(dw.desc);
+  PO_TRY(put_desc(h, d_desc, s));
+  PO_TRY(evolve_impl(w, ew, b, d_desc, d_A, d_A_edge, d_f, d_J, s));
   return check_outputs(b, d_f, d_J, s);
 }
 
@@ -518,14 +649,14 @@ po_status po_field_samples(int32_t n, const po_pulse_spec* specs, const double* 
   if (d_A_edge) PO_TRY(check_device_range(d_A_edge, sizeof(double) * 4 * n, 8, "d_A_edge"));
   if (d_scale) PO_TRY(check_device_range(d_scale, sizeof(double) * n, 8, "d_scale"));
   hipStream_t s = static_cast<hipStream_t>(stream);
-  Scratch desc, spec, part, scl;
-  PO_TRY(upload(h, desc, s));
-  PO_TRY(spec.alloc(sizeof(double) * b.total_spec, s));
-  PO_TRY(part.alloc(sizeof(double) * size_t(std::max(1, b.max_stat_blocks)) * n, s));
-  PO_TRY(scl.alloc(sizeof(double) * n, s));
-  return launch_samples(b, static_cast<PulseDev*>(desc.ptr), d_coeff, static_cast<double*>(spec.ptr),
-                        static_cast<double*>(part.ptr), static_cast<double*>(scl.ptr), n_sub, offsets, with_end ? 1 : 0,
-                        d_E, d_Ed, d_A, d_A_edge, d_scale, s);
+  Work w;
+  const DescWork dw(w, n);
+  const SynthWork sw(w, n, b);
+  PO_TRY(w.alloc(s));
+  PulseDev* d_desc = w.at<PulseDev>(dw.desc);
+  PO_TRY(put_desc(h, d_desc, s));
+  return launch_samples(b, d_desc, d_coeff, w.at<double>(sw.spec), w.at<double>(sw.part), w.at<double>(sw.scl), n_sub,
+                        offsets, with_end ? 1 : 0, d_E, d_Ed, d_A, d_A_edge, d_scale, s);
 }
 
 po_status po_qke_modes(int32_t n, const po_pulse_spec* specs, const po_grid* grids, const double* d_E,
@@ -548,14 +679,13 @@ po_status po_qke_modes(int32_t n, const po_pulse_spec* specs, const po_grid* gri
   if (d_f) PO_TRY(check_device_range(d_f, sizeof(double) * b.total_modes, 8, "d_f"));
   if (d_J) PO_TRY(check_device_range(d_J, sizeof(double) * n, 8, "d_J"));
   hipStream_t s = static_cast<hipStream_t>(stream);
-  Scratch desc, units;
-  PO_TRY(upload(h, desc, s));
-  double* d_units = nullptr;
-  if (d_J) {
-    PO_TRY(units.alloc(sizeof(double) * size_t(b.total_units), s));
-    d_units = static_cast<double*>(units.ptr);
-  }
-  const PulseDev* d_desc = static_cast<PulseDev*>(desc.ptr);
+  Work w;
+  const DescWork dw(w, n);
+  const size_t o_units = w.add(sizeof(double) * size_t(b.total_units));
+  PO_TRY(w.alloc(s));
+  PulseDev* d_desc = w.at<PulseDev>(dw.desc);
+  PO_TRY(put_desc(h, d_desc, s));
+  double* d_units = d_J ? w.at<double>(o_units) : nullptr;
   PO_TRY(launch_qke_grid(b, d_desc, d_E, d_Ed, d_A, linear ? 1 : 0, d_f, d_units, s));
   if (d_J) PO_TRY(launch_yield_from_units(b, d_desc, d_units, d_J, s));
   return PO_OK;
@@ -575,16 +705,14 @@ po_status po_evolve_modes_m4(int32_t n, const po_pulse_spec* specs, const po_gri
   if (d_f) PO_TRY(check_device_range(d_f, sizeof(double) * b.total_modes, 8, "d_f"));
   if (d_J) PO_TRY(check_device_range(d_J, sizeof(double) * n, 8, "d_J"));
   hipStream_t s = static_cast<hipStream_t>(stream);
-  Scratch desc, units, sel;
-  PO_TRY(upload(h, desc, s));
-  double* d_units = nullptr;
-  if (d_J) {
-    PO_TRY(units.alloc(sizeof(double) * size_t(b.total_units), s));
-    d_units = static_cast<double*>(units.ptr);
-  }
-  PO_TRY(sel.alloc(sizeof(double) * 4 * size_t(b.total_chunks), s));
-  const PulseDev* d_desc = static_cast<PulseDev*>(desc.ptr);
-  double* d_ranges = static_cast<double*>(sel.ptr);
+  Work w;
+  const DescWork dw(w, n);
+  const size_t o_units = w.add(sizeof(double) * size_t(b.total_units));
+  const size_t o_ranges = w.add(sizeof(double) * 4 * size_t(b.total_chunks));
+  PO_TRY(w.alloc(s));
+  PulseDev* d_desc = w.at<PulseDev>(dw.desc);
+  PO_TRY(put_desc(h, d_desc, s));
+  double *d_units = d_J ? w.at<double>(o_units) : nullptr, *d_ranges = w.at<double>(o_ranges);
   PO_TRY(launch_chunk_ranges4(b, d_desc, d_Ag, d_ranges, s));
   PO_TRY(launch_evolve4_grid(b, d_desc, d_Ag, d_A_edge, d_ranges, d_f, d_units, s));
   if (d_J) PO_TRY(launch_yield_from_units(b, d_desc, d_units, d_J, s));
@@ -607,16 +735,15 @@ po_status po_evolve_modes_split(int32_t n, const po_pulse_spec* specs, const po_
   if (d_f) PO_TRY(check_device_range(d_f, sizeof(double) * b.total_modes, 8, "d_f"));
   if (d_J) PO_TRY(check_device_range(d_J, sizeof(double) * n, 8, "d_J"));
   hipStream_t s = static_cast<hipStream_t>(stream);
-  Scratch desc, units, sel;
-  PO_TRY(upload(h, desc, s));
-  double* d_units = nullptr;
-  if (d_J) {
-    PO_TRY(units.alloc(sizeof(double) * size_t(b.total_units), s));
-    d_units = static_cast<double*>(units.ptr);
-  }
-  PO_TRY(sel.alloc(sizeof(double) * 4 * size_t(b.total_chunks), s));
-  const PulseDev* d_desc = static_cast<PulseDev*>(desc.ptr);
-  PO_TRY(launch_evolve_split_grid(b, order, d_desc, d_At, d_A_edge, static_cast<double*>(sel.ptr), d_f, d_units, s));
+  Work w;
+  const DescWork dw(w, n);
+  const size_t o_units = w.add(sizeof(double) * size_t(b.total_units));
+  const size_t o_ranges = w.add(sizeof(double) * 4 * size_t(b.total_chunks));
+  PO_TRY(w.alloc(s));
+  PulseDev* d_desc = w.at<PulseDev>(dw.desc);
+  PO_TRY(put_desc(h, d_desc, s));
+  double *d_units = d_J ? w.at<double>(o_units) : nullptr, *d_ranges = w.at<double>(o_ranges);
+  PO_TRY(launch_evolve_split_grid(b, order, d_desc, d_At, d_A_edge, d_ranges, d_f, d_units, s));
   if (d_J) PO_TRY(launch_yield_from_units(b, d_desc, d_units, d_J, s));
   return PO_OK;
 }
@@ -635,9 +762,13 @@ po_status po_yield_gradient(int32_t n, const po_pulse_spec* specs, const po_grid
   if (d_gedge) PO_TRY(check_device_range(d_gedge, sizeof(double) * 4 * n, 8, "d_gedge"));
   if (d_J) PO_TRY(check_device_range(d_J, sizeof(double) * n, 8, "d_J"));
   hipStream_t s = static_cast<hipStream_t>(stream);
-  Scratch desc;
-  PO_TRY(upload(h, desc, s));
-  return yield_grad_impl(b, h, static_cast<PulseDev*>(desc.ptr), d_A, d_A_edge, d_J, d_gA, d_gedge, s);
+  Work w;
+  const DescWork dw(w, n);
+  const GradWork gw(w, b);
+  PO_TRY(w.alloc(s));
+  PulseDev* d_desc = w.at<PulseDev>(dw.desc);
+  PO_TRY(put_desc(h, d_desc, s));
+  return yield_grad_impl(w, gw, b, d_desc, d_A, d_A_edge, d_J, d_gA, d_gedge, s);
 }
 
 po_status po_synth_gradient(int32_t n, const po_pulse_spec* specs, const double* d_coeff, const double* d_gA,
@@ -655,19 +786,18 @@ po_status po_synth_gradient(int32_t n, const po_pulse_spec* specs, const double*
   if (d_U) PO_TRY(check_device_range(d_U, sizeof(double) * n, 8, "d_U"));
   if (d_gU) PO_TRY(check_device_range(d_gU, sizeof(double) * b.total_coeff, 8, "d_gU"));
   hipStream_t s = static_cast<hipStream_t>(stream);
-  Scratch desc, A, E, edge, scl, lines;
-  PO_TRY(upload(h, desc, s));
-  const PulseDev* d_desc = static_cast<PulseDev*>(desc.ptr);
-  PO_TRY(A.alloc(sizeof(double) * 2 * b.total_rows, s));
-  PO_TRY(E.alloc(sizeof(double) * 2 * b.total_rows, s));
-  PO_TRY(edge.alloc(sizeof(double) * 4 * n, s));
-  PO_TRY(scl.alloc(sizeof(double) * n, s));
-  PO_TRY(lines.alloc(sizeof(double) * size_t(b.total_spec / 4) * 8 * size_t(b.max_ns), s));
-  double *dA = static_cast<double*>(A.ptr), *dE = static_cast<double*>(E.ptr), *de = static_cast<double*>(edge.ptr);
-  double* dscale = static_cast<double*>(scl.ptr);
-  PO_TRY(synth_impl(n, specs, d_coeff, dA, dE, de, dscale, s, b, d_desc));
-  return launch_synth_adjoint(b, d_desc, d_coeff, d_gA, d_gedge, dA, de, dE, dscale, static_cast<double*>(lines.ptr),
-                              d_grad, d_U, d_gU, s);
+  Work w;
+  const DescWork dw(w, n);
+  const SynthWork sw(w, n, b);
+  const AdjointWork aw(w, n, b);
+  PO_TRY(w.alloc(s));
+  PulseDev* d_desc = w.at<PulseDev>(dw.desc);
+  PO_TRY(put_desc(h, d_desc, s));
+  double *dA = w.at<double>(aw.A), *dE = w.at<double>(aw.E), *de = w.at<double>(aw.edge);
+  double* dscale = w.at<double>(aw.scale);
+  PO_TRY(synth_impl(w, sw, d_coeff, dA, dE, de, dscale, s, b, d_desc));
+  return launch_synth_adjoint(b, d_desc, d_coeff, d_gA, d_gedge, dA, de, dE, dscale, w.at<double>(aw.lines), d_grad,
+                              d_U, d_gU, s);
 }
 
 po_status po_evaluate_gradient(int32_t n, const po_pulse_spec* specs, const po_grid* grids, const double* d_coeff,
@@ -685,23 +815,21 @@ po_status po_evaluate_gradient(int32_t n, const po_pulse_spec* specs, const po_g
   if (d_U) PO_TRY(check_device_range(d_U, sizeof(double) * n, 8, "d_U"));
   if (d_gU) PO_TRY(check_device_range(d_gU, sizeof(double) * b.total_coeff, 8, "d_gU"));
   hipStream_t s = static_cast<hipStream_t>(stream);
-  Scratch desc, A, E, edge, scl, gA, gedge, lines;
-  PO_TRY(upload(h, desc, s));
-  const PulseDev* d_desc = static_cast<PulseDev*>(desc.ptr);
-  PO_TRY(A.alloc(sizeof(double) * 2 * b.total_rows, s));
-  PO_TRY(E.alloc(sizeof(double) * 2 * b.total_rows, s));
-  PO_TRY(edge.alloc(sizeof(double) * 4 * n, s));
-  PO_TRY(scl.alloc(sizeof(double) * n, s));
-  PO_TRY(gA.alloc(sizeof(double) * 2 * b.total_rows, s));
-  PO_TRY(gedge.alloc(sizeof(double) * 4 * n, s));
-  PO_TRY(lines.alloc(sizeof(double) * size_t(b.total_spec / 4) * 8 * size_t(b.max_ns), s));
-  double *dA = static_cast<double*>(A.ptr), *dE = static_cast<double*>(E.ptr), *de = static_cast<double*>(edge.ptr);
-  double *dscale = static_cast<double*>(scl.ptr), *dgA = static_cast<double*>(gA.ptr);
-  double* dge = static_cast<double*>(gedge.ptr);
-  PO_TRY(synth_impl(n, specs, d_coeff, dA, dE, de, dscale, s, b, d_desc));
-  PO_TRY(yield_grad_impl(b, h, d_desc, dA, de, d_J, dgA, dge, s));
-  return launch_synth_adjoint(b, d_desc, d_coeff, dgA, dge, dA, de, dE, dscale, static_cast<double*>(lines.ptr),
-                              d_grad, d_U, d_gU, s);
+  Work w;
+  const DescWork dw(w, n);
+  const SynthWork sw(w, n, b);
+  const AdjointWork aw(w, n, b);
+  const GradWork gw(w, b);
+  const size_t o_gA = w.add(sizeof(double) * 2 * b.total_rows), o_ge = w.add(sizeof(double) * 4 * n);
+  PO_TRY(w.alloc(s));
+  PulseDev* d_desc = w.at<PulseDev>(dw.desc);
+  PO_TRY(put_desc(h, d_desc, s));
+  double *dA = w.at<double>(aw.A), *dE = w.at<double>(aw.E), *de = w.at<double>(aw.edge);
+  double *dscale = w.at<double>(aw.scale), *dgA = w.at<double>(o_gA), *dge = w.at<double>(o_ge);
+  PO_TRY(synth_impl(w, sw, d_coeff, dA, dE, de, dscale, s, b, d_desc));
+  PO_TRY(yield_grad_impl(w, gw, b, d_desc, dA, de, d_J, dgA, dge, s));
+  return launch_synth_adjoint(b, d_desc, d_coeff, dgA, dge, dA, de, dE, dscale, w.at<double>(aw.lines), d_grad, d_U,
+                              d_gU, s);
 }
 
 po_status po_pair_yield(int32_t n, const po_grid* grids, const double* d_f, double* d_J, void* stream) {
@@ -713,12 +841,14 @@ po_status po_pair_yield(int32_t n, const po_grid* grids, const double* d_f, doub
   PO_TRY(check_device_range(d_f, sizeof(double) * b.total_modes, 8, "d_f"));
   PO_TRY(check_device_range(d_J, sizeof(double) * n, 8, "d_J"));
   hipStream_t s = static_cast<hipStream_t>(stream);
-  Scratch desc, units;
-  PO_TRY(upload(h, desc, s));
-  PO_TRY(units.alloc(sizeof(double) * size_t(b.total_units), s));
-  const PulseDev* d_desc = static_cast<PulseDev*>(desc.ptr);
-  PO_TRY(launch_unit_sums_from_f(b, d_desc, d_f, static_cast<double*>(units.ptr), s));
-  PO_TRY(launch_yield_from_units(b, d_desc, static_cast<double*>(units.ptr), d_J, s));
+  Work w;
+  const DescWork dw(w, n);
+  const size_t o_units = w.add(sizeof(double) * size_t(b.total_units));
+  PO_TRY(w.alloc(s));
+  PulseDev* d_desc = w.at<PulseDev>(dw.desc);
+  PO_TRY(put_desc(h, d_desc, s));
+  PO_TRY(launch_unit_sums_from_f(b, d_desc, d_f, w.at<double>(o_units), s));
+  PO_TRY(launch_yield_from_units(b, d_desc, w.at<double>(o_units), d_J, s));
   return check_finite(d_J, n, "d_J", s);
 }
 
@@ -739,10 +869,14 @@ po_status po_evaluate(int32_t n, const po_pulse_spec* specs, const po_grid* grid
   if (d_f) PO_TRY(check_device_range(d_f, sizeof(double) * b.total_modes, 8, "d_f"));
   if (d_J) PO_TRY(check_device_range(d_J, sizeof(double) * n, 8, "d_J"));
   hipStream_t s = static_cast<hipStream_t>(stream);
-  Scratch desc;
-  PO_TRY(upload(h, desc, s));
-  const PulseDev* d_desc = static_cast<PulseDev*>(desc.ptr);
-  PO_TRY(synth_impl(n, specs, d_coeff, d_A, nullptr, d_A_edge, d_scale, s, b, d_desc));
+  Work w;
+  const DescWork dw(w, n);
+  const SynthWork sw(w, n, b);
+  const EvolveWork ew(w, plan ? Batch{} : b);  // a plan has its own
+  PO_TRY(w.alloc(s));
+  PulseDev* d_desc = w.at<PulseDev>(dw.desc);
+  PO_TRY(put_desc(h, d_desc, s));
+  PO_TRY(synth_impl(w, sw, d_coeff, d_A, nullptr, d_A_edge, d_scale, s, b, d_desc));
   PO_TRY(check_finite(d_A, 2 * b.total_rows, "d_A", s));
   if (plan) {
     hipEvent_t e0 = nullptr;
@@ -751,7 +885,7 @@ po_status po_evaluate(int32_t n, const po_pulse_spec* specs, const po_grid* grid
     if (timed) timer_stop(s, e0);
     return check_outputs(b, d_f, d_J, s);
   }
-  PO_TRY(evolve_impl(b, d_desc, d_A, d_A_edge, d_f, d_J, s));
+  PO_TRY(evolve_impl(w, ew, b, d_desc, d_A, d_A_edge, d_f, d_J, s));
   return check_outputs(b, d_f, d_J, s);
 }
 
@@ -788,9 +922,8 @@ po_status po_evaluate_noalloc(int32_t n, const po_pulse_spec* specs, const po_gr
   hipStream_t s = static_cast<hipStream_t>(stream);
   PulseDev* d_desc = reinterpret_cast<PulseDev*>(sc + o_desc);
   PO_HIP(hipMemcpyAsync(d_desc, g_noalloc_desc, sizeof(PulseDev) * size_t(n), hipMemcpyHostToDevice, s));
-  PO_TRY(synth_into(specs, d_coeff, d_A, nullptr, d_A_edge, d_scale, s, b, d_desc,
-                    reinterpret_cast<double*>(sc + o_spec), reinterpret_cast<double*>(sc + o_part),
-                    reinterpret_cast<double*>(sc + o_scl)));
+  PO_TRY(launch_synth(b, d_desc, d_coeff, reinterpret_cast<double*>(sc + o_spec), reinterpret_cast<double*>(sc + o_part),
+                      reinterpret_cast<double*>(sc + o_scl), d_A, nullptr, d_A_edge, d_scale, s));
   // what the scratch array has left serves the time-split form of a small batch
   const size_t prop_bytes = sizeof(double) * kSlotDoubles * size_t(b.total_slots);
   double* d_prop = split_in_time(b) && prop_bytes <= kNoAllocScratchBytes - need ? reinterpret_cast<double*>(sc + need)
@@ -900,16 +1033,18 @@ po_status po_de_generation(const po_de_params* prm, int64_t generation, const po
   Batch b;
   PO_TRY(build_batch(n, specs.data(), grids.data(), h.data(), &b));
   hipStream_t s = static_cast<hipStream_t>(stream);
-  Scratch desc, tab, edge;
-  PO_TRY(upload(h, desc, s));
-  PO_TRY(tab.alloc(sizeof(double) * 2 * b.total_rows, s));
-  PO_TRY(edge.alloc(sizeof(double) * 4 * n, s));
-  const PulseDev* d_desc = static_cast<PulseDev*>(desc.ptr);
-  double* d_A = static_cast<double*>(tab.ptr);
-  double* d_edge = static_cast<double*>(edge.ptr);
+  Work w;
+  const DescWork dw(w, n);
+  const SynthWork sw(w, n, b);
+  const EvolveWork ew(w, b);
+  const size_t o_A = w.add(sizeof(double) * 2 * b.total_rows), o_edge = w.add(sizeof(double) * 4 * n);
+  PO_TRY(w.alloc(s));
+  PulseDev* d_desc = w.at<PulseDev>(dw.desc);
+  PO_TRY(put_desc(h, d_desc, s));
+  double *d_A = w.at<double>(o_A), *d_edge = w.at<double>(o_edge);
   PO_TRY(launch_de_propose(*prm, generation, d_pop, d_trial, nullptr, s));
-  PO_TRY(synth_impl(n, specs.data(), d_trial, d_A, nullptr, d_edge, nullptr, s, b, d_desc));
-  PO_TRY(evolve_impl(b, d_desc, d_A, d_edge, nullptr, d_trial_fit, s));
+  PO_TRY(synth_impl(w, sw, d_trial, d_A, nullptr, d_edge, nullptr, s, b, d_desc));
+  PO_TRY(evolve_impl(w, ew, b, d_desc, d_A, d_edge, nullptr, d_trial_fit, s));
   PO_TRY(launch_de_select(*prm, d_pop, d_fit, d_trial, d_trial_fit, nullptr, s));
   return check_finite(d_trial_fit, n, "d_trial_fit", s);
 }
@@ -982,16 +1117,18 @@ po_status po_jde_generation(const po_jde_params* prm, int64_t generation, const 
   Batch b;
   PO_TRY(build_batch(n, specs.data(), grids.data(), h.data(), &b));
   hipStream_t s = static_cast<hipStream_t>(stream);
-  Scratch desc, tab, edge;
-  PO_TRY(upload(h, desc, s));
-  PO_TRY(tab.alloc(sizeof(double) * 2 * b.total_rows, s));
-  PO_TRY(edge.alloc(sizeof(double) * 4 * n, s));
-  const PulseDev* d_desc = static_cast<PulseDev*>(desc.ptr);
-  double* d_A = static_cast<double*>(tab.ptr);
-  double* d_edge = static_cast<double*>(edge.ptr);
+  Work w;
+  const DescWork dw(w, n);
+  const SynthWork sw(w, n, b);
+  const EvolveWork ew(w, b);
+  const size_t o_A = w.add(sizeof(double) * 2 * b.total_rows), o_edge = w.add(sizeof(double) * 4 * n);
+  PO_TRY(w.alloc(s));
+  PulseDev* d_desc = w.at<PulseDev>(dw.desc);
+  PO_TRY(put_desc(h, d_desc, s));
+  double *d_A = w.at<double>(o_A), *d_edge = w.at<double>(o_edge);
   PO_TRY(launch_jde_propose(*prm, generation, d_pop, d_fcr, d_trial, d_trial_fcr, nullptr, s));
-  PO_TRY(synth_impl(n, specs.data(), d_trial, d_A, nullptr, d_edge, nullptr, s, b, d_desc));
-  PO_TRY(evolve_impl(b, d_desc, d_A, d_edge, nullptr, d_trial_fit, s));
+  PO_TRY(synth_impl(w, sw, d_trial, d_A, nullptr, d_edge, nullptr, s, b, d_desc));
+  PO_TRY(evolve_impl(w, ew, b, d_desc, d_A, d_edge, nullptr, d_trial_fit, s));
   return launch_jde_select(*prm, d_pop, d_fit, d_fcr, d_trial, d_trial_fit, d_trial_fcr, nullptr, s);
 }
 

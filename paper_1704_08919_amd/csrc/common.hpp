@@ -65,6 +65,7 @@ struct PulseDev {
   // slot of the pulse in the batch, slots in the order item * nseg + segment.
   int32_t nseg, seg_len;
   int64_t slot_off;
+  int64_t part_off;   // first double of the pulse's gradient partials [items][nt][2]
   double T, dt, dw, wmin, wmax, norm_value, dv;
   double lo[3], dp[3];  // p_d = lo_d + (i + 1/2) dp_d; dp_d = 0 for a sheet (then p_d = lo_d)
 };
@@ -77,6 +78,7 @@ struct Batch {
   int32_t total_items = 0;     // workgroups of the default evolution launch
   int32_t total_blocks = 0;    // series-selection blocks (kSelBlock modes, per pulse)
   int64_t total_slots = 0;     // (256-mode item, time segment) pairs of all pulses
+  int64_t total_part = 0;      // sum of items x nt (rows of gradient partials)
   int32_t total_chunks = 0;    // kChunkSteps-step chunks of all pulses
   int32_t max_stat_blocks = 0; // largest per-pulse block count of the field statistics pass
   int32_t max_nt = 0;
@@ -91,7 +93,8 @@ po_status validate_grid(const po_grid& g, int i);
 po_status build_batch(int32_t n, const po_pulse_spec* specs, const po_grid* grids, PulseDev* out,
                       Batch* b);
 
-// Stream-ordered scratch buffer released on destruction (hipFreeAsync on the same stream).
+// Stream-ordered scratch buffer released on destruction (hipFreeAsync on the same stream), taken from
+// the library's memory pool of the current device.
 struct Scratch {
   void* ptr = nullptr;
   hipStream_t stream = nullptr;
@@ -99,6 +102,20 @@ struct Scratch {
     if (ptr) (void)hipFreeAsync(ptr, stream);
   }
   po_status alloc(size_t bytes, hipStream_t s);
+};
+
+// The work buffers of one call in one scratch allocation: add() each, alloc() once, then at().
+struct Work {
+  Scratch mem;
+  size_t bytes = 0;
+  size_t add(size_t n) {
+    const size_t o = bytes;
+    bytes += (n + 255) & ~size_t(255);
+    return o;
+  }
+  po_status alloc(hipStream_t s) { return mem.alloc(bytes, s); }
+  template <class T>
+  T* at(size_t o) const { return reinterpret_cast<T*>(static_cast<char*>(mem.ptr) + o); }
 };
 
 // --------------------------------------------------------------------- kernel launchers
@@ -117,9 +134,9 @@ po_status launch_synth_adjoint(const Batch& b, const PulseDev* d_desc, const dou
                                const double* d_gedge, const double* d_A, const double* d_A_edge, const double* d_E,
                                const double* d_scale, double* d_lines, double* d_grad, double* d_U, double* d_gU,
                                hipStream_t s);
-// Yield gradient (grad.hip): d_part [sum items_i nt_i][2] item partials at d_goff[i]; d_epart [items][4].
+// Yield gradient (grad.hip): d_part [sum items_i nt_i][2] item partials (at desc.part_off); d_epart [items][4].
 po_status launch_yield_grad(const Batch& b, const PulseDev* d_desc, const double* d_A, const double* d_A_edge,
-                            const int2* d_sel, const int64_t* d_goff, double* d_part, double* d_epart, double* d_units,
+                            const int2* d_sel, double* d_part, double* d_epart, double* d_units,
                             double* d_gA, double* d_gedge, hipStream_t s);
 // Launch shape of the evolution kernel.  threads: lanes per workgroup (64, 128, 256);
 // mpl: modes per lane (1, 2); persistent: workgroups pull items from a device queue.

@@ -286,7 +286,6 @@ struct GradArgs {
   const double* A;
   const double* Aedge;
   const int2* sel;      // per selection block (the evolution's k_block_select)
-  const int64_t* goff;  // per pulse: first double of its item partials
   double* part;         // [items of pulse][nt][2] per pulse
   double* epart;        // [total items][4]: dA(t_i) x, y, dA(t_f) x, y
   double* units;        // 64-mode sums of f
@@ -389,7 +388,7 @@ __device__ __forceinline__ void grad_item(const GradArgs& a, int item, int pi, d
   }
 
   // backward over the chunks in reverse, kGroup steps at a time (the last group of a chunk may be short)
-  double* part = a.part + a.goff[pi] + int64_t(li) * nt * 2;
+  double* part = a.part + d.part_off + int64_t(li) * nt * 2;
   double2 (*buf)[64] = bufs[wave];
   for (int c = nchunks - 1; c >= 0; --c) {
     const int n0 = c * kChunk, len = min(kChunk, nt - n0);
@@ -472,14 +471,13 @@ __global__ void __launch_bounds__(kItem) __attribute__((amdgpu_waves_per_eu(3)))
 
 // dJ/dA[n] = -2 dt dV sum over the pulse's items (in order) of the partials (the edge partials carry
 // their factors); one thread per (n, component).
-__global__ void __launch_bounds__(256) k_grad_reduce(const PulseDev* __restrict__ desc, const int64_t* __restrict__ goff,
-                                                     const double* __restrict__ part, const double* __restrict__ epart,
+__global__ void __launch_bounds__(256) k_grad_reduce(const PulseDev* __restrict__ desc, const double* __restrict__ part, const double* __restrict__ epart,
                                                      double* __restrict__ gA, double* __restrict__ gedge) {
   const PulseDev& d = desc[blockIdx.y];
   const int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x;
   const int64_t per = 2 * int64_t(d.nt);
   if (e < per) {
-    const double* p = part + goff[blockIdx.y];
+    const double* p = part + d.part_off;
     double v = 0.0;
     for (int i = 0; i < d.nitems; ++i) v += p[int64_t(i) * per + e];
     gA[2 * d.tab_off + e] = v * (-2.0 * d.dt) * d.dv;  // dq_x/dA_x = -dt; the factor 2 of 2 Re[...]
@@ -494,13 +492,13 @@ __global__ void __launch_bounds__(256) k_grad_reduce(const PulseDev* __restrict_
 }  // namespace
 
 po_status launch_yield_grad(const Batch& b, const PulseDev* d_desc, const double* d_A, const double* d_A_edge,
-                            const int2* d_sel, const int64_t* d_goff, double* d_part, double* d_epart, double* d_units,
+                            const int2* d_sel, double* d_part, double* d_epart, double* d_units,
                             double* d_gA, double* d_gedge, hipStream_t s) {
-  GradArgs a{d_desc, b.n_pulses, d_A, d_A_edge, d_sel, d_goff, d_part, d_epart, d_units};
+  GradArgs a{d_desc, b.n_pulses, d_A, d_A_edge, d_sel, d_part, d_epart, d_units};
   hipLaunchKernelGGL(k_yield_grad, dim3(b.total_items), dim3(kItem), 0, s, a);
   PO_HIP(hipGetLastError());
   hipLaunchKernelGGL(k_grad_reduce, dim3(unsigned((2 * int64_t(b.max_nt) + 255) / 256), b.n_pulses), dim3(256), 0, s,
-                     d_desc, d_goff, d_part, d_epart, d_gA, d_gedge);
+                     d_desc, d_part, d_epart, d_gA, d_gedge);
   PO_HIP(hipGetLastError());
   return PO_OK;
 }
