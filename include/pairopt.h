@@ -18,9 +18,9 @@
  *  - Host arrays (specs, grids, params) are read during the call only.
  *  - `stream` is a hipStream_t (NULL = the legacy default stream).  Every call is
  *    asynchronous on that stream; results are valid once the stream reaches them.
- *  - Work buffers that a call needs beyond its arguments are taken from the stream-ordered
- *    memory pool (hipMallocAsync / hipFreeAsync on `stream`), so calls on different streams
- *    never share scratch memory.
+ *  - Work buffers that a call needs beyond its arguments are taken, stream-ordered on `stream`, from
+ *    a memory pool of the library's own (one per device; it keeps up to 512 MiB between calls), so
+ *    calls on different streams never share scratch memory.
  *  - Errors: every argument is validated before anything is enqueued.  Invalid arguments
  *    return PO_ERR_INVALID, HIP failures PO_ERR_DEVICE; in both cases po_last_error() gives a
  *    message (thread-local).  No C++ exception crosses the ABI.  Nothing is enqueued when a
@@ -252,12 +252,12 @@ po_status po_evolve_modes_split(int32_t n_pulses, const po_pulse_spec* specs, co
  *  d_J      out [n_pulses] or NULL.
  *  d_gA     out [sum nt][2]: dJ/dA at every step midpoint.
  *  d_gedge  out [n_pulses][2][2] or NULL: dJ/dA(t_i), dJ/dA(t_f) (initial state, projection).
- * Work buffers of ceil(distinct modes / 256) x nt x 16 bytes per pulse (the per-step partial sums of
- * each 256-mode item, added in a fixed order by a second kernel) come from the stream-ordered pool:
- * 32 MiB for a 64x64x16 pulse symmetric in p_z at nt = 16384, 512 MiB for a 128x128x32 one at nt =
- * 32768.  A batch whose
- * work buffers do not fit in device memory returns PO_ERR_NOMEM before the gradient kernels are
- * enqueued; split it into several calls.
+ * Work buffers of ceil(distinct modes / 256) x (nt x 16 bytes + segments x 16 KiB) per pulse (the per-step
+ * partial sums of each 256-mode item and the propagators of its 8 to 64 time segments) come from the
+ * scratch pool: 48 MiB for a 64x64x16 pulse symmetric in p_z at nt = 16384, 640 MiB for a 128x128x32
+ * one at nt = 32768.  A batch that would need more than 2 GiB is worked through in groups of pulses,
+ * one after the other in the same buffers; a pulse whose buffers do not fit in device memory returns
+ * PO_ERR_NOMEM before the gradient kernels are enqueued.
  *
  * po_synth_gradient -- chain rule through the synthesis (Sec. III) of po_pulse_synth:
  *  d_gA, d_gedge  as produced above (d_gedge may be NULL: no end-point terms).

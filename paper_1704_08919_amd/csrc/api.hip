@@ -154,7 +154,7 @@ po_status build_batch(int32_t n, const po_pulse_spec* specs, const po_grid* grid
   *b = Batch{};
   b->n_pulses = n;
   int64_t tab = 0, modes = 0, coeff = 0, spec = 0;
-  int64_t units = 0, items = 0, blocks = 0, chunks = 0;
+  int64_t units = 0, items = 0, chunks = 0;
   for (int i = 0; i < n; ++i) {
     PulseDev d;
     std::memset(&d, 0, sizeof d);
@@ -164,7 +164,6 @@ po_status build_batch(int32_t n, const po_pulse_spec* specs, const po_grid* grid
     d.spec_off = spec;
     d.unit_off = units;
     d.item_off = int32_t(items);
-    d.blk_off = int32_t(blocks);
     d.chk_off = int32_t(chunks);
     if (specs) {
       const po_pulse_spec& s = specs[i];
@@ -211,7 +210,6 @@ po_status build_batch(int32_t n, const po_pulse_spec* specs, const po_grid* grid
       modes += m;
       units += d.nunits;
       items += d.nitems;
-      blocks += (d.ndist + kSelBlock - 1) / kSelBlock;
       if (i > 0 && std::memcmp(&g, &grids[0], sizeof g) != 0) b->uniform = false;
     }
     out[i] = d;
@@ -236,14 +234,12 @@ po_status build_batch(int32_t n, const po_pulse_spec* specs, const po_grid* grid
       part += int64_t(out[i].nitems) * out[i].nt;
     }
   b->total_slots = slots;
-  b->total_part = part;
   b->total_rows = tab;
   b->total_modes = modes;
   b->total_coeff = coeff;
   b->total_spec = spec;
   b->total_units = units;
   b->total_items = int32_t(items);
-  b->total_blocks = int32_t(blocks);
   b->total_chunks = int32_t(chunks);
   return PO_OK;
 }
@@ -416,22 +412,48 @@ po_status evolve_impl(const Work& w, const EvolveWork& z, const Batch& b, const 
                      z.split ? w.at<double>(z.prop) : nullptr, true);
 }
 
-// Gradient of J with respect to the tables (forward + adjoint sweep per mode, fixed-order sums).
+// Gradient of J with respect to the tables (forward and adjoint sweeps per mode, fixed-order sums).
+// The pulses are taken in groups whose segment propagators and partial sums stay within kGradGroup
+// bytes (a single pulse may need more), one group after the other in the same buffers.
+constexpr int64_t kGradGroup = int64_t(2) << 30;
+
 struct GradWork {
-  size_t part, epart, units, sel;
-  GradWork(Work& w, const Batch& b) {
-    part = w.add(sizeof(double) * 2 * size_t(b.total_part));
-    epart = w.add(sizeof(double) * 4 * size_t(b.total_items));
+  size_t prop, part, epart, units, ranges;
+  std::vector<GradRange> groups;
+  GradWork(Work& w, const std::vector<PulseDev>& h, const Batch& b) {
+    int64_t max_slots = 0, max_rows = 0, max_items = 0;
+    for (int i = 0; i < b.n_pulses;) {
+      GradRange r{i, i, h[i].slot_off, 0, h[i].part_off, h[i].item_off, 0, 0};
+      int64_t rows = 0;
+      for (; r.i1 < b.n_pulses; ++r.i1) {
+        const PulseDev& d = h[r.i1];
+        const int64_t ds = int64_t(d.nitems) * d.nseg, dr = int64_t(d.nitems) * d.nt;
+        if (r.i1 > i && (r.slots + ds) * kSlotDoubles * 8 + (rows + dr) * 16 > kGradGroup) break;
+        r.slots += ds;
+        rows += dr;
+        r.items += d.nitems;
+        r.max_nt = std::max(r.max_nt, d.nt);
+      }
+      max_slots = std::max(max_slots, r.slots);
+      max_rows = std::max(max_rows, rows);
+      max_items = std::max<int64_t>(max_items, r.items);
+      groups.push_back(r);
+      i = r.i1;
+    }
+    prop = w.add(sizeof(double) * kSlotDoubles * size_t(max_slots));
+    part = w.add(sizeof(double) * 2 * size_t(max_rows));
+    epart = w.add(sizeof(double) * 16 * size_t(max_items));
     units = w.add(sizeof(double) * size_t(b.total_units));
-    sel = w.add(sizeof(int2) * size_t(b.total_blocks));
+    ranges = w.add(sizeof(double) * 4 * size_t(b.total_chunks));
   }
 };
 
 po_status yield_grad_impl(const Work& w, const GradWork& z, const Batch& b, const PulseDev* d_desc, const double* d_A,
                           const double* d_A_edge, double* d_J, double* d_gA, double* d_gedge, hipStream_t s) {
-  PO_TRY(launch_block_select(b, d_desc, d_A, w.at<int2>(z.sel), s));
-  PO_TRY(launch_yield_grad(b, d_desc, d_A, d_A_edge, w.at<int2>(z.sel), w.at<double>(z.part), w.at<double>(z.epart),
-                           w.at<double>(z.units), d_gA, d_gedge, s));
+  PO_TRY(launch_chunk_ranges(b, d_desc, d_A, w.at<double>(z.ranges), s));
+  for (const GradRange& r : z.groups)
+    PO_TRY(launch_yield_grad(d_desc, r, d_A, d_A_edge, w.at<double>(z.ranges), w.at<double>(z.prop),
+                             w.at<double>(z.part), w.at<double>(z.epart), w.at<double>(z.units), d_gA, d_gedge, s));
   if (d_J) PO_TRY(launch_yield_from_units(b, d_desc, w.at<double>(z.units), d_J, s));
   return PO_OK;
 }
@@ -764,7 +786,7 @@ po_status po_yield_gradient(int32_t n, const po_pulse_spec* specs, const po_grid
   hipStream_t s = static_cast<hipStream_t>(stream);
   Work w;
   const DescWork dw(w, n);
-  const GradWork gw(w, b);
+  const GradWork gw(w, h, b);
   PO_TRY(w.alloc(s));
   PulseDev* d_desc = w.at<PulseDev>(dw.desc);
   PO_TRY(put_desc(h, d_desc, s));
@@ -819,7 +841,7 @@ po_status po_evaluate_gradient(int32_t n, const po_pulse_spec* specs, const po_g
   const DescWork dw(w, n);
   const SynthWork sw(w, n, b);
   const AdjointWork aw(w, n, b);
-  const GradWork gw(w, b);
+  const GradWork gw(w, h, b);
   const size_t o_gA = w.add(sizeof(double) * 2 * b.total_rows), o_ge = w.add(sizeof(double) * 4 * n);
   PO_TRY(w.alloc(s));
   PulseDev* d_desc = w.at<PulseDev>(dw.desc);

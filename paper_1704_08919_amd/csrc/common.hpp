@@ -59,7 +59,6 @@ struct PulseDev {
   int32_t nunits;     // 64-mode units, 256-mode items and selection blocks of the distinct modes
   int32_t item_off;   // first workgroup item of this pulse in the default evolution launch
   int32_t nitems;
-  int32_t blk_off;    // first series-selection block (kSelBlock modes) of this pulse in the batch
   // Time segments of the second-order evolution: nseg of seg_len steps (the last may be shorter),
   // each evolved from the identity and then applied to the state.  slot_off: first (item, segment)
   // slot of the pulse in the batch, slots in the order item * nseg + segment.
@@ -76,9 +75,7 @@ struct Batch {
   int64_t total_units = 0;
   int64_t total_units_all = 0; // 64-mode units of all modes, mirror images included
   int32_t total_items = 0;     // workgroups of the default evolution launch
-  int32_t total_blocks = 0;    // series-selection blocks (kSelBlock modes, per pulse)
   int64_t total_slots = 0;     // (256-mode item, time segment) pairs of all pulses
-  int64_t total_part = 0;      // sum of items x nt (rows of gradient partials)
   int32_t total_chunks = 0;    // kChunkSteps-step chunks of all pulses
   int32_t max_stat_blocks = 0; // largest per-pulse block count of the field statistics pass
   int32_t max_nt = 0;
@@ -134,9 +131,15 @@ po_status launch_synth_adjoint(const Batch& b, const PulseDev* d_desc, const dou
                                const double* d_gedge, const double* d_A, const double* d_A_edge, const double* d_E,
                                const double* d_scale, double* d_lines, double* d_grad, double* d_U, double* d_gU,
                                hipStream_t s);
-// Yield gradient (grad.hip): d_part [sum items_i nt_i][2] item partials (at desc.part_off); d_epart [items][4].
-po_status launch_yield_grad(const Batch& b, const PulseDev* d_desc, const double* d_A, const double* d_A_edge,
-                            const int2* d_sel, double* d_part, double* d_epart, double* d_units,
+// Yield gradient (grad.hip) of pulses [i0, i1) of the batch: d_prop holds their slots, d_part their item
+// partials [items][nt][2], d_epart 4 x [4] doubles per item of them.
+struct GradRange {
+  int i0, i1;
+  int64_t slot0, slots, part0;
+  int item0, items, max_nt;
+};
+po_status launch_yield_grad(const PulseDev* d_desc, const GradRange& r, const double* d_A, const double* d_A_edge,
+                            const double* d_ranges, double* d_prop, double* d_part, double* d_epart, double* d_units,
                             double* d_gA, double* d_gedge, hipStream_t s);
 // Launch shape of the evolution kernel.  threads: lanes per workgroup (64, 128, 256);
 // mpl: modes per lane (1, 2); persistent: workgroups pull items from a device queue.
@@ -145,10 +148,6 @@ struct EvolveConfig {
   int mpl = 1;
   int persistent = 0;
 };
-// Per-block series selection of the yield gradient: x = variant of kFitDegree (or kFineHalving),
-// y = number of angle halvings, one int2 per kSelBlock modes of each pulse (total_blocks).
-po_status launch_block_select(const Batch& b, const PulseDev* d_desc, const double* d_A, int2* d_bsel,
-                              hipStream_t s);
 // Range of the table per 256-step chunk of each pulse, d_ranges [total_chunks][4] = (min A_x,
 // max A_x, min A_y, max A_y); the second-order evolution picks its series variant per chunk and
 // selection block from it.  The evolution launches below take this array; d_units holds
@@ -161,8 +160,9 @@ po_status launch_evolve_grid(const Batch& b, const PulseDev* d_desc, const doubl
 // mode's segments in order; d_prop holds kSlotDoubles per slot.  Bitwise equal to the other forms.
 constexpr int kSlotDoubles = 8 * kItem;
 bool split_in_time(const Batch& b);
-po_status launch_segments(const Batch& b, const PulseDev* d_desc, const double* d_A, const double* d_ranges,
-                          double* d_prop, hipStream_t s);
+// First kernel of it for the slots [slot0, slot0 + slots), which belong to the n_pulses of d_desc.
+po_status launch_segments(const PulseDev* d_desc, int n_pulses, int64_t slot0, int64_t slots, const double* d_A,
+                          const double* d_ranges, double* d_prop, hipStream_t s);
 po_status launch_evolve_segments(const Batch& b, const PulseDev* d_desc, const double* d_A, const double* d_A_edge,
                                  const double* d_ranges, double* d_prop, double* d_f, double* d_units, hipStream_t s);
 // Persistent launch: items are {pulse, first mode} pairs of cfg.threads * cfg.mpl modes each,

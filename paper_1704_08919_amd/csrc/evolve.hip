@@ -51,6 +51,7 @@
 
 #include "dirac.hpp"
 #include "reduce.hpp"
+#include "select.hpp"
 
 // Every fused multiply-add below is written out: automatic contraction is off, so each mode's
 // arithmetic is the same instruction sequence in every launch shape (threads, modes per lane,
@@ -59,50 +60,6 @@
 
 namespace po {
 namespace {
-
-// Box of cell-centred momenta of selection block b (kSelBlock consecutive modes of the first nmodes)
-// of a pulse: [pxl, pxh] x [pyl, pyh] and the largest p_z^2.
-struct BlockBox {
-  double pxl, pxh, pyl, pyh, pz2;
-};
-
-__device__ __forceinline__ BlockBox block_box(const PulseDev& d, int b, int64_t nmodes) {
-  const int nx = d.n[0], ny = d.n[1];
-  const int64_t m0 = int64_t(b) * kSelBlock, m1 = min(m0 + kSelBlock, nmodes) - 1;
-  const int64_t r0 = m0 / nx, r1 = m1 / nx;  // rows (iy, iz)
-  const int64_t z0 = r0 / ny, z1 = r1 / ny;
-  const int ix0 = r0 == r1 ? int(m0 % nx) : 0, ix1 = r0 == r1 ? int(m1 % nx) : nx - 1;
-  const int iy0 = z0 == z1 ? int(r0 % ny) : 0, iy1 = z0 == z1 ? int(r1 % ny) : ny - 1;
-  const double px0 = d.lo[0] + (ix0 + 0.5) * d.dp[0], px1 = d.lo[0] + (ix1 + 0.5) * d.dp[0];
-  const double py0 = d.lo[1] + (iy0 + 0.5) * d.dp[1], py1 = d.lo[1] + (iy1 + 0.5) * d.dp[1];
-  const double pz0 = d.lo[2] + (z0 + 0.5) * d.dp[2], pz1 = d.lo[2] + (z1 + 0.5) * d.dp[2];
-  return BlockBox{fmin(px0, px1), fmax(px0, px1), fmin(py0, py1), fmax(py0, py1), fmax(pz0 * pz0, pz1 * pz1)};
-}
-
-// Series variant (x: index of the T fits or kFineHalving; y: angle halvings) for a bound xb on
-// the step angle squared.  For a block box against a range [lx, hx] x [ly, hy] of table values,
-// with the largest |p - A| per component,
-//   x = (omega dt)^2 <= dt^2 [ max|p_x - A_x|^2 + max|p_y - A_y|^2 + 1 + max p_z^2 ].
-__device__ __forceinline__ int2 variant_for_x(double xb) {
-  int mode = kFineHalving, h = 0;
-  for (int k = kNumFine - 1; k >= 0; --k)
-    if (xb <= kFitXmax[k]) mode = k;
-  if (mode == kFineHalving) {
-    double x = xb;
-    while (x > kCosSinXmax && h < kMaxHalvings) {
-      x *= 0.25;
-      ++h;
-    }
-  }
-  return make_int2(mode, h);
-}
-
-// Bound on (omega dt)^2 for a block box against a range [lx, hx] x [ly, hy] of table values.
-__device__ __forceinline__ double x_bound(const BlockBox& bb, double lx, double hx, double ly, double hy, double dt) {
-  const double X = fmax(fmax(bb.pxh - lx, hx - bb.pxl), 0.0);
-  const double Y = fmax(fmax(bb.pyh - ly, hy - bb.pyl), 0.0);
-  return (X * X + Y * Y + 1.0 + bb.pz2) * dt * dt * (1.0 + 1e-6);
-}
 
 // NODES = 1: the second-order step's angle.  NODES = 2: the fourth-order step's, from theta^2 the
 // bound above over both Gauss nodes, |w_s| <= theta + (sqrt3/6) theta^2.
@@ -173,33 +130,6 @@ __global__ void __launch_bounds__(256) k_chunk_ranges(const PulseDev* __restrict
   }
 }
 
-// Per block of kSelBlock consecutive modes of a pulse, the variant for the range of the whole
-// table (the yield gradient's choice).  Items of every launch shape lie inside one block.  One
-// workgroup per pulse: the table's extremes, then one thread per block.
-__global__ void __launch_bounds__(256) k_block_select(const PulseDev* __restrict__ desc, const double* __restrict__ A,
-                                                      int2* __restrict__ bsel) {
-  const PulseDev d = desc[blockIdx.x];
-  const double2* tab = reinterpret_cast<const double2*>(A) + d.tab_off;
-  double lx = INFINITY, hx = -INFINITY, ly = INFINITY, hy = -INFINITY;
-  for (int64_t n = threadIdx.x; n < d.nt; n += blockDim.x) {
-    const double2 a = tab[n];
-    lx = fmin(lx, a.x); hx = fmax(hx, a.x);
-    ly = fmin(ly, a.y); hy = fmax(hy, a.y);
-  }
-  __shared__ double red[4][256];
-  red[0][threadIdx.x] = -lx; red[1][threadIdx.x] = hx; red[2][threadIdx.x] = -ly; red[3][threadIdx.x] = hy;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (int(threadIdx.x) < w)
-      for (int k = 0; k < 4; ++k) red[k][threadIdx.x] = fmax(red[k][threadIdx.x], red[k][threadIdx.x + w]);
-    __syncthreads();
-  }
-  const double axl = -red[0][0], axh = red[1][0], ayl = -red[2][0], ayh = red[3][0];
-  const int nblk = int((d.ndist + kSelBlock - 1) / kSelBlock);
-  for (int b = threadIdx.x; b < nblk; b += blockDim.x)
-    bsel[d.blk_off + b] = choose_variant<1>(block_box(d, b, d.ndist), axl, axh, ayl, ayh, d.dt);
-}
-
 constexpr int kCotUnroll = 4;  // steps per iteration of the step loops
 
 struct EvolveArgs {
@@ -211,15 +141,6 @@ struct EvolveArgs {
   double* f;
   double* units;
 };
-
-// A value that is equal in all lanes, in scalar registers.
-__device__ __forceinline__ double uniform(double v) {
-  return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
-                          __builtin_amdgcn_readfirstlane(__double2loint(v)));
-}
-
-// Upper 32 bits of a positive double (ordered as the doubles are).
-constexpr uint32_t high_word(double v) { return uint32_t(__builtin_bit_cast(uint64_t, v) >> 32); }
 
 // Variant of the cotangent form for a bound xb on x = (omega dt)^2: the lowest fit that covers it
 // (compared by the upper words, so a bound within 2^-20 of a fit's end takes the next one; NaN and
@@ -355,13 +276,6 @@ __device__ __forceinline__ void propagate(State (&v)[MPL], const ItemTab& t, int
   }
 }
 
-// Momentum of distinct mode m (mode 0 for lanes beyond them), its e_perp.
-__device__ __forceinline__ double lane_mode(const PulseDev& d, int64_t m, double& px, double& py) {
-  double pz;
-  mode_momentum(d, m < d.ndist ? m : 0, px, py, pz);
-  return sqrt(fma(pz, pz, 1.0));
-}
-
 // Evolves the item of THREADS * MPL modes of pulse pi starting at mode `first`, writes f and the
 // 64-mode unit sums.  Every lane of the workgroup must call it (it contains barriers).
 template <int THREADS, int MPL>
@@ -409,9 +323,9 @@ __global__ void __launch_bounds__(kItem) __attribute__((amdgpu_waves_per_eu(4)))
 // Time-split form, first kernel: one workgroup per (item, segment) slot; the segment's propagators go to
 // prop[slot][8 components][256 lanes].
 __global__ void __launch_bounds__(kItem) __attribute__((amdgpu_waves_per_eu(4)))
-k_segments(EvolveArgs a, double* __restrict__ prop) {
+k_segments(EvolveArgs a, int64_t slot0, double* __restrict__ prop) {
   __shared__ double2 lds[kChunk];
-  const int64_t slot = blockIdx.x;
+  const int64_t slot = slot0 + blockIdx.x;
   const int pi = find_pulse_slot(a.desc, a.n_pulses, slot);
   const PulseDev& d = a.desc[pi];
   const int rel = int(slot - d.slot_off), li = rel / d.nseg, seg = rel - li * d.nseg;
@@ -420,7 +334,7 @@ k_segments(EvolveArgs a, double* __restrict__ prop) {
   const CotMode mode[1] = {cot_mode(px, py, e)};
   State v[1];
   propagate<kItem, 1>(v, item_tab(a, d, li * kItem), seg * d.seg_len, min((seg + 1) * d.seg_len, d.nt), mode, lds);
-  store_state(prop, slot, v[0]);
+  store_state(prop, slot - slot0, v[0]);
 }
 
 // Second kernel: one lane per mode applies its segments in order.  Wavefronts of 64 here (one per
@@ -912,13 +826,6 @@ __global__ void __launch_bounds__(kItem) k_evolve_split(SplitArgs a) {
 
 }  // namespace
 
-po_status launch_block_select(const Batch& b, const PulseDev* d_desc, const double* d_A, int2* d_bsel,
-                              hipStream_t s) {
-  hipLaunchKernelGGL(k_block_select, dim3(b.n_pulses), dim3(256), 0, s, d_desc, d_A, d_bsel);
-  PO_HIP(hipGetLastError());
-  return PO_OK;
-}
-
 po_status launch_chunk_ranges(const Batch& b, const PulseDev* d_desc, const double* d_A, double* d_ranges,
                               hipStream_t s) {
   const int max_chunks = (b.max_nt + kChunk - 1) / kChunk;
@@ -944,17 +851,17 @@ bool split_in_time(const Batch& b) {
   return b.total_items <= 448 && b.total_slots > b.total_items && b.total_slots <= 8192;
 }
 
-po_status launch_segments(const Batch& b, const PulseDev* d_desc, const double* d_A, const double* d_ranges,
-                          double* d_prop, hipStream_t s) {
-  EvolveArgs a{d_desc, b.n_pulses, d_A, nullptr, d_ranges, nullptr, nullptr};
-  hipLaunchKernelGGL(k_segments, dim3(unsigned(b.total_slots)), dim3(kItem), 0, s, a, d_prop);
+po_status launch_segments(const PulseDev* d_desc, int n_pulses, int64_t slot0, int64_t slots, const double* d_A,
+                          const double* d_ranges, double* d_prop, hipStream_t s) {
+  EvolveArgs a{d_desc, n_pulses, d_A, nullptr, d_ranges, nullptr, nullptr};
+  hipLaunchKernelGGL(k_segments, dim3(unsigned(slots)), dim3(kItem), 0, s, a, slot0, d_prop);
   PO_HIP(hipGetLastError());
   return PO_OK;
 }
 
 po_status launch_evolve_segments(const Batch& b, const PulseDev* d_desc, const double* d_A, const double* d_A_edge,
                                  const double* d_ranges, double* d_prop, double* d_f, double* d_units, hipStream_t s) {
-  PO_TRY(launch_segments(b, d_desc, d_A, d_ranges, d_prop, s));
+  PO_TRY(launch_segments(d_desc, b.n_pulses, 0, b.total_slots, d_A, d_ranges, d_prop, s));
   EvolveArgs a{d_desc, b.n_pulses, d_A, d_A_edge, d_ranges, d_f, d_units};
   hipLaunchKernelGGL(k_join_segments, dim3(unsigned(b.total_items) * (kItem / 64)), dim3(64), 0, s, a, d_prop);
   PO_HIP(hipGetLastError());

@@ -18,18 +18,19 @@
 // 2 Re <chi'_{n+1}| dU/dq_j |psi_n> with chi'_s = alpha_s chi_s, and it depends on the two states
 // only through W_s = Im <chi'_s|tau|psi_s>, a real 3-vector that the backward steps rotate.
 //
-// One workgroup of 256 lanes per 256-mode item, one mode per lane.  Forward: the evolution's own
-// step (tangent form or C, S with the pulse's angle halvings), states unit-normalised per block at
-// t_f.  Backward: the table is staged through LDS chunk by chunk in reverse; each step forms the
-// two derivative terms from W_{n+1} and rotates it to W_n (coefficients from the tangent form's
-// fit and a cos^2 series, or from the exact C, S on the angle-halving path).  Their sum over the
-// item's modes is taken per step in a fixed order: each lane stores its terms for 8 steps in LDS,
-// the wave reads them back transposed (lane (j, p) adds the lanes p, p + 8, ..., p + 56 of step
-// j), pairs up the 8 lanes of a step (DPP), and the four waves are added in order; the results are
-// written as item partials [item][n][2], and a second kernel sums the items of each pulse in
-// order.  So the gradient, like J, does not depend on scheduling.
+// Three kernels.  The forward sweep is the evolution's own segment kernel: per mode and time segment
+// the propagators of the two blocks.  k_grad_join, one lane per mode, applies them to the initial
+// state, takes f, the final-state terms and W at t_f, moves W back segment by segment (the
+// rotation a propagator induces) and leaves W at the end of each segment in the segment's slot.
+// k_grad_back then runs the backward steps of every (256-mode item, segment) at once: each step forms
+// the derivative terms and rotates W_{n+1} to W_n, and the terms are summed over the item's modes in a
+// fixed order: each lane stores its terms for 8 steps in LDS, the wave reads them back transposed
+// (lane (j, p) adds the lanes p, p + 8, ..., p + 56 of step j), pairs up the 8 lanes of a step (DPP), and
+// the four waves are added in order.  The results are item partials [item][n][2]; k_grad_reduce
+// sums the items of each pulse in order.  So the gradient, like J, does not depend on scheduling.
 #include "dirac.hpp"
 #include "reduce.hpp"
+#include "select.hpp"
 
 #pragma clang fp contract(off)
 
@@ -145,84 +146,82 @@ __device__ __forceinline__ double2 back_w(WPair& w, double qx, double qy, double
 }
 
 // Exact C, S form (the angle-halving path): l = 1, the products with 2 C S and S^2 are explicit.
-__device__ __forceinline__ double2 back_w_exact(WPair& w, double2 r, double pxdt, double pydt, double qz, double qz2,
-                                                int h, double inv4h) {
-  const double qx = pxdt + r.x, qy = pydt + r.y;
-  const double x = fma(qx, qx, fma(qy, qy, qz2));
+__device__ __forceinline__ double2 back_w_exact(WPair& w, double qx, double qy, double qz, int h, double inv4h) {
   double C, S, D;
+  const double x = fma(qx, qx, fma(qy, qy, qz * qz));
   csd(x, h, inv4h, C, S, D);
   const double S2 = S * S, cs = C * S;
   return back_w(w, qx, qy, qz, fma(-S2, x, C * C), S2 + S2, fma(C, D, S2), cs, 1.0, cs + cs, S2);
 }
 
-// Tangent form (steps within the fit's range): with S = C T and C D = -C^2 R, R = (T - 1)/x, the
-// coefficients are C^2 (1 - T^2 x), 2 C^2 T^2, C^2 (T^2 - R) and C^2 T; C^2 = cos^2 sqrt x comes
-// from its own series, R is the variant's fit (T = 1 + x R).  The cross products carry l = 2 C^2 T,
-// which the rotation takes as it is and the terms times S^2 / l = T / 2.
-// cos^2 sqrt x = 1 + sum_{k >= 1} (-1)^k 2^(2k-1) x^k / (2k)!, alternating with decreasing terms;
-// degree kFitCos2Degree[v] keeps the remainder below 2^-59 up to the variant's largest x.
-constexpr double pow2i(int n) { return n == 0 ? 1.0 : 2.0 * pow2i(n - 1); }
-constexpr double cos2_coef(int k) { return k == 0 ? 1.0 : (k % 2 ? -1.0 : 1.0) * pow2i(2 * k - 1) / factorial(2 * k); }
+// Within the fits' range.  In units of e_perp (q = e dt q', q'_z = 1, y = |q'|^2 - 1, z = (e dt)^2, x = z (1
+// + y)) with v = q' x W, T = tan(sqrt x)/sqrt x, R = (T - 1)/x, k = 2 C S = sin(2 sqrt x)/sqrt x, the rotation is
+//     W_n = W - k e dt (v - T e dt q' x v),
+// and since dU/dq_j U^+ = -i int_0^1 exp(-i s q.tau) tau_j exp(i s q.tau) ds, a term is the mean of the
+// rotating W over the step:
+//     2 Re <chi'_{n+1}| dU/dq_j |psi_n> = T (W_n + W_{n+1})_j - 2 R z q'_j (q'.W).
+// So beside the two cross products per block a step needs only T and R (one fit), k (a series of its own:
+// no cancellation), and the sums of W over the blocks: 48 + n + m FP64 instructions for degrees n and
+// m, against 63 + n + m when the terms are formed from C, S and D separately.
+// k = sum_j 2 (-4)^j x^j / (2 j + 1)!, alternating with decreasing terms; kFitCos2Degree[v] terms (of the
+// series of cos^2, whose terms are larger) keep its remainder below 2^-59 up to the variant's largest x.
+constexpr double pow4i(int n) { return n == 0 ? 1.0 : 4.0 * pow4i(n - 1); }
+constexpr double sin2_coef(int j) { return (j % 2 ? -2.0 : 2.0) * pow4i(j) / factorial(2 * j + 1); }
 
-template <int K>
-__device__ __forceinline__ void horner_cos2(double x, double& c) {
-  constexpr double ck = cos2_coef(K);
-  c = fma(c, x, ck);
-  if constexpr (K > 0) horner_cos2<K - 1>(x, c);
-}
+// Read from memory where a variant starts: as literals the compiler would set those that several
+// variants share at kernel entry.
+__constant__ double kSin2Coef[10] = {sin2_coef(0), sin2_coef(1), sin2_coef(2), sin2_coef(3), sin2_coef(4),
+                                     sin2_coef(5), sin2_coef(6), sin2_coef(7), sin2_coef(8), sin2_coef(9)};
 
-template <int M>
-__device__ __forceinline__ double cos2_series(double x) {
-  constexpr double cm = cos2_coef(M);
-  double c = cm;
-  horner_cos2<M - 1>(x, c);
-  return c;
-}
-
-template <int MODE>
-__device__ __forceinline__ double2 back_w_tan(WPair& w, double2 r, double pxdt, double pydt, double qz, double qz2,
-                                              const Fit<MODE>& f) {
-  constexpr int M = kFitCos2Degree[MODE];
-  const double qx = pxdt + r.x, qy = pydt + r.y;
-  const double x = fma(qx, qx, fma(qy, qy, qz2));
-  const double R = fit_R<MODE>(x, f);
-  const double T = fma(R, x, 1.0);
-  const double c2 = cos2_series<M>(x);
-  const double T2 = T * T;
-  const double cs = c2 * T, s2 = cs * T;
-  return back_w(w, qx, qy, qz, c2 * fma(-T2, x, 1.0), s2 + s2, c2 * (T2 - R), cs, cs + cs, 1.0, 0.5 * T);
-}
-
-// Coefficients of the fit for the tangent-form variants (an empty record for the halving path).
-template <int MODE, bool TAN = (MODE < kFineHalving)>
-struct FitOf {
-  using type = Fit<MODE>;
-};
-template <int MODE>
-struct FitOf<MODE, false> {
-  struct type {};
+struct BackMode {
+  double nie, px, py, qz, z, z2;  // -1/e, p/e, e dt, (e dt)^2, 2 (e dt)^2
 };
 
 template <int MODE>
-__device__ __forceinline__ typename FitOf<MODE>::type load_fit_of() {
-  if constexpr (MODE < kFineHalving) return load_fit<MODE>();
-  else return typename FitOf<MODE>::type{};
+struct BackFit {
+  Fit<MODE> f;
+  double k[kFitCos2Degree[MODE] + 1];
+};
+
+template <int MODE>
+__device__ __forceinline__ BackFit<MODE> load_back_fit() {
+  BackFit<MODE> b;
+  b.f = load_fit<MODE>();
+  const double* k = kSin2Coef;
+  asm volatile("" : "+s"(k));
+#pragma unroll
+  for (int j = 0; j <= kFitCos2Degree[MODE]; ++j) b.k[j] = k[j];
+  return b;
 }
 
-// One backward step in the form of the pulse's variant.
+// One backward step within the fits' range; s holds (ax + bx, ay - by) on entry and exit.  Returns twice
+// the terms summed over the blocks.
 template <int MODE>
-__device__ __forceinline__ double2 back_any(WPair& w, double2 r, double pxdt, double pydt, double qz, double qz2, int h,
-                                            double inv4h, const typename FitOf<MODE>::type& f) {
-  if constexpr (MODE < kFineHalving) return back_w_tan<MODE>(w, r, pxdt, pydt, qz, qz2, f);
-  else return back_w_exact(w, r, pxdt, pydt, qz, qz2, h, inv4h);
-}
-
-// Forward step of the evolution in the form the pulse's series choice selects.
-template <int MODE>
-__device__ __forceinline__ void fwd_step(State& v, double2 rec, double pxdt, double pydt, double qz, double qz2, int h,
-                                         double inv4h, const typename FitOf<MODE>::type& f) {
-  if constexpr (MODE < kFineHalving) step_tan<MODE>(v, rec, pxdt, pydt, qz, qz2, f);
-  else step_halving(v, rec, pxdt, pydt, qz, qz2, h, inv4h);
+__device__ __forceinline__ double2 back_step(WPair& w, double2& s, double2 A, const BackMode& m, const BackFit<MODE>& f) {
+  const double qx = fma(A.x, m.nie, m.px), qy = fma(A.y, m.nie, m.py);
+  const double x = fma(fma(qx, qx, qy * qy), m.z, m.z);
+  const double R = fit_R<MODE>(x, f.f), T = fma(R, x, 1.0);
+  double k = f.k[kFitCos2Degree[MODE]];
+#pragma unroll
+  for (int j = kFitCos2Degree[MODE] - 1; j >= 0; --j) k = fma(k, x, f.k[j]);
+  const double kq = k * m.qz, tz = T * m.qz, tx = tz * qx, ty = tz * qy;
+  {
+    const double vx = fma(qy, w.az, -w.ay), vy = fma(-qx, w.az, w.ax), vz = fma(qx, w.ay, -(qy * w.ax));
+    w.ax = fma(-kq, fma(tz, vy, fma(-ty, vz, vx)), w.ax);
+    w.ay = fma(-kq, fma(tx, vz, fma(-tz, vx, vy)), w.ay);
+    w.az = fma(-kq, fma(ty, vx, fma(-tx, vy, vz)), w.az);
+  }
+  {
+    const double vx = fma(-qy, w.bz, -w.by), vy = fma(-qx, w.bz, w.bx), vz = fma(qx, w.by, qy * w.bx);
+    w.bx = fma(-kq, fma(tz, vy, fma(ty, vz, vx)), w.bx);
+    w.by = fma(-kq, fma(tx, vz, fma(-tz, vx, vy)), w.by);
+    w.bz = fma(-kq, fma(-ty, vx, fma(-tx, vy, vz)), w.bz);
+  }
+  const double2 n = make_double2(w.ax + w.bx, w.ay - w.by);
+  const double rp = (R * m.z2) * fma(qx, n.x, fma(qy, n.y, w.az + w.bz));
+  const double2 g = make_double2(fma(T, s.x + n.x, -(rp * qx)), fma(T, s.y + n.y, -(rp * qy)));
+  s = n;
+  return g;
 }
 
 // Lane-to-lane moves inside rows of 16 (DPP): pairs (l, l^1), (l, l^2), l <-> 7 - l within 8 lanes and
@@ -281,67 +280,59 @@ __device__ __forceinline__ void group_store(double2 (*buf)[64], double2* red, in
 }
 
 struct GradArgs {
-  const PulseDev* desc;
+  const PulseDev* desc;  // of the group's pulses
   int n_pulses;
+  int64_t slot0, part0;  // first slot, first partial and first item of the group in the batch
+  int item0;
   const double* A;
   const double* Aedge;
-  const int2* sel;      // per selection block (the evolution's k_block_select)
+  const double* ranges;
+  double* prop;         // [slots][8][256]: propagators in, W at the segments' ends out (6 components)
   double* part;         // [items of pulse][nt][2] per pulse
-  double* epart;        // [total items][4]: dA(t_i) x, y, dA(t_f) x, y
+  double* epart;        // [items][4 waves][4]: dA(t_i) x, y, dA(t_f) x, y
   double* units;        // 64-mode sums of f
 };
 
 constexpr int kWaves = kItem / 64;
 
-// LDS: tab[kChunk] (-A dt of the chunk), red[kWaves][kChunk] (per-wave step sums of the chunk),
-// bufs[kWaves][kGroup][64] (lane values of kGroup steps, per wave); separate arrays, so the
-// compiler sees that the table reads do not depend on the buf stores.
-template <int MODE>
-__device__ __forceinline__ void grad_item(const GradArgs& a, int item, int pi, double2* tab, double2 (*red)[kChunk],
-                                          double2 (*bufs)[kGroup][64]) {
+// W <- R^T W for the rotation that the propagator (w - i v.tau) / |.| induces (its first column (a, b) of
+// a block: a = w - i v_z, b = v_y - i v_x): W + (2 / |.|^2) (v x t - w t) with t = v x W.
+__device__ __forceinline__ void rotate_back(double& wx, double& wy, double& wz, double ar, double ai, double br,
+                                            double bi) {
+  const double w = ar, vx = -bi, vy = br, vz = -ai;
+  const double s = 2.0 / fma(bi, bi, fma(br, br, fma(ai, ai, ar * ar)));
+  const double tx = fma(vy, wz, -(vz * wy)), ty = fma(vz, wx, -(vx * wz)), tz = fma(vx, wy, -(vy * wx));
+  const double dx = fma(vy, tz, fma(-vz, ty, -(w * tx))), dy = fma(vz, tx, fma(-vx, tz, -(w * ty))),
+               dz = fma(vx, ty, fma(-vy, tx, -(w * tz)));
+  wx = fma(s, dx, wx);
+  wy = fma(s, dy, wy);
+  wz = fma(s, dz, wz);
+}
+
+// One lane per mode, one wave per workgroup (as k_join_segments).
+__global__ void __launch_bounds__(64) k_grad_join(GradArgs a) {
+  const int rel = blockIdx.x / kWaves, wave = blockIdx.x % kWaves, lane = wave * 64 + threadIdx.x;
+  const int pi = find_pulse_item(a.desc, a.n_pulses, a.item0 + rel);
   const PulseDev& d = a.desc[pi];
-  const int nt = d.nt;
-  const double dt = d.dt;
-  const int li = item - d.item_off;
-  const int64_t m = int64_t(li) * kItem + threadIdx.x;
-  const bool active = m < d.ndist;
-  const int h = a.sel[d.blk_off + li * kItem / kSelBlock].y;
-  const double inv4h = ldexp(1.0, -2 * h);
-  const auto fit = load_fit_of<MODE>();
-  const double2* A = reinterpret_cast<const double2*>(a.A) + d.tab_off;
-  const double2 ain = reinterpret_cast<const double2*>(a.Aedge)[2 * pi];
-  const double2 aout = reinterpret_cast<const double2*>(a.Aedge)[2 * pi + 1];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-
-  double px, py, pz;
-  mode_momentum(d, active ? m : 0, px, py, pz);
-  const double e = sqrt(fma(pz, pz, 1.0));
-  const double pxdt = px * dt, pydt = py * dt, qz = e * dt, qz2 = qz * qz;
-
-  // forward: psi_s from |-_s(P_in)>, in the evolution's own step form (the tangent form drops the
-  // common factor C of every step; the blocks are normalised at t_f)
+  const int li = a.item0 + rel - d.item_off;
+  const int64_t m = int64_t(li) * kItem + lane, slot = d.slot_off - a.slot0 + int64_t(li) * d.nseg;
+  const double2* edge = reinterpret_cast<const double2*>(a.Aedge) + 2 * pi;
+  const double2 ain = edge[0], aout = edge[1];
+  // modes that stand for a mirror image count twice: everything after t_f is linear in alpha_s^* psi
+  const double weight = m >= d.ndist ? 0.0 : mirror_mode(d, m) != m ? 2.0 : 1.0;
+  double px, py;
+  const double e = lane_mode(d, m, px, py);
   State psi;
   init_state(psi, px - ain.x, py - ain.y, e);
-  const int nchunks = (nt + kChunk - 1) / kChunk;
-  for (int c = 0; c < nchunks; ++c) {
-    const int n0 = c * kChunk, len = min(kChunk, nt - n0);
-    __syncthreads();
-    if (int(threadIdx.x) < len) {
-      const double2 t = A[n0 + threadIdx.x];
-      tab[threadIdx.x] = make_double2(-t.x * dt, -t.y * dt);
-    }
-    __syncthreads();
-    if (len == kChunk) {
-#pragma unroll 4
-      for (int k = 0; k < kChunk; ++k) fwd_step<MODE>(psi, tab[k], pxdt, pydt, qz, qz2, h, inv4h, fit);
-    } else {
-      for (int k = 0; k < len; ++k) fwd_step<MODE>(psi, tab[k], pxdt, pydt, qz, qz2, h, inv4h, fit);
-    }
-    if constexpr (MODE < kFineHalving) renormalise(psi);
+  for (int s0 = 0; s0 < d.nseg; s0 += 4) {
+    State v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (s0 + k < d.nseg) v[k] = load_state(a.prop, slot + s0 + k, lane);
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (s0 + k < d.nseg) apply_propagator(psi, v[k]);
   }
-
-  // modes that stand for a mirror image count twice: everything after t_f is linear in alpha_s^* psi
-  const double weight = !active ? 0.0 : mirror_mode(d, m) != m ? 2.0 : 1.0;
 
   // t_f: normalise each block, alpha_s = <+_s(P_out)|psi_s>, final-state terms, and
   // W_s = Im(conj(alpha_s) <+_s|tau|psi_s>), the start of the backward sweep (chi'_s = alpha_s |+_s>)
@@ -387,42 +378,20 @@ __device__ __forceinline__ void grad_item(const GradArgs& a, int item, int pi, d
     }
   }
 
-  // backward over the chunks in reverse, kGroup steps at a time (the last group of a chunk may be short)
-  double* part = a.part + d.part_off + int64_t(li) * nt * 2;
-  double2 (*buf)[64] = bufs[wave];
-  for (int c = nchunks - 1; c >= 0; --c) {
-    const int n0 = c * kChunk, len = min(kChunk, nt - n0);
-    __syncthreads();
-    if (int(threadIdx.x) < len) {
-      const double2 t = A[n0 + threadIdx.x];
-      tab[threadIdx.x] = make_double2(-t.x * dt, -t.y * dt);
-    }
-    __syncthreads();
-    // a short group first (len not a multiple of kGroup), then full groups
-    int top = len - 1;
-    const int r = len % kGroup;
-    if (r != 0) {
-#pragma unroll 1
-      for (int j = 0; j < r; ++j) buf[j][lane] = back_any<MODE>(w, tab[top - j], pxdt, pydt, qz, qz2, h, inv4h, fit);
-      group_store(buf, red[wave], lane, top, r);
-      top -= r;
-    }
-    for (; top >= 0; top -= kGroup) {
+  for (int s1 = d.nseg; s1 > 0; s1 -= 4) {
+    State v[4];
 #pragma unroll
-      for (int j = 0; j < kGroup; ++j)
-        buf[j][lane] = back_any<MODE>(w, tab[top - j], pxdt, pydt, qz, qz2, h, inv4h, fit);
-      group_store(buf, red[wave], lane, top, kGroup);
-    }
-    __syncthreads();
-    if (int(threadIdx.x) < len) {
-      double2 v = red[0][threadIdx.x];
+    for (int k = 0; k < 4; ++k)
+      if (s1 - 1 - k >= 0) v[k] = load_state(a.prop, slot + s1 - 1 - k, lane);
 #pragma unroll
-      for (int w = 1; w < kWaves; ++w) {
-        v.x += red[w][threadIdx.x].x;
-        v.y += red[w][threadIdx.x].y;
+    for (int k = 0; k < 4; ++k)
+      if (s1 - 1 - k >= 0) {
+        double* o = a.prop + (slot + s1 - 1 - k) * kSlotDoubles + lane;
+        o[0] = w.ax; o[kItem] = w.ay; o[2 * kItem] = w.az;
+        o[3 * kItem] = w.bx; o[4 * kItem] = w.by; o[5 * kItem] = w.bz;
+        rotate_back(w.ax, w.ay, w.az, v[k].ar, v[k].ai, v[k].br, v[k].bi);
+        rotate_back(w.bx, w.by, w.bz, v[k].cr, v[k].ci, v[k].dr, v[k].di);
       }
-      reinterpret_cast<double2*>(part)[n0 + threadIdx.x] = v;
-    }
   }
 
   // t_i: d|-> = -|+><+|dh|->/(2 w), dP = -dA(t_i).  With chi'_0 = a |+> + b |->, the part of W_0
@@ -433,72 +402,163 @@ __device__ __forceinline__ void grad_item(const GradArgs& a, int item, int pi, d
   const double g_in_x = (fma(Py, w.az - w.bz, -(e * (w.ay + w.by)))) * inv_w2;
   const double g_in_y = (fma(e, w.ax - w.bx, -(Px * (w.az - w.bz)))) * inv_w2;
   const double e4[4] = {g_in_x, g_in_y, g_out_x, g_out_y};
-  __syncthreads();
+#pragma unroll
   for (int j = 0; j < 4; ++j) {
     const double sj = wave_sum(e4[j]);
-    if (lane == 0) red[wave][j] = make_double2(sj, 0.0);
+    if (threadIdx.x == 0) a.epart[(int64_t(rel) * kWaves + wave) * 4 + j] = sj;
   }
-  __syncthreads();
-  if (threadIdx.x < 4) {
-    double v = red[0][threadIdx.x].x;
-#pragma unroll
-    for (int w = 1; w < kWaves; ++w) v += red[w][threadIdx.x].x;
-    a.epart[int64_t(item) * 4 + threadIdx.x] = v;
-  }
-  if (a.units) write_unit(d, a.units, m, f);
+  write_unit(d, a.units, m, f);
 }
 
-__global__ void __launch_bounds__(kItem) __attribute__((amdgpu_waves_per_eu(3))) k_yield_grad(GradArgs a) {
+// Backward steps of a piece (len records of tab, last first) in fit variant MODE, kGroup steps at a time
+// (a short group first), with the per-wave step sums in red[wave].
+template <int MODE>
+__device__ __forceinline__ void back_piece(WPair& w, const double2* tab, int len, const BackMode& m, double xb,
+                                           double2 (*buf)[64], double2* red, int lane) {
+  int top = len - 1;
+  const int r = len % kGroup;
+  if constexpr (MODE < kFineHalving) {
+    const BackFit<MODE> f = load_back_fit<MODE>();
+    double2 s = make_double2(w.ax + w.bx, w.ay - w.by);
+    if (r != 0) {
+#pragma unroll 1
+      for (int j = 0; j < r; ++j) buf[j][lane] = back_step<MODE>(w, s, tab[top - j], m, f);
+      group_store(buf, red, lane, top, r);
+      top -= r;
+    }
+    for (; top >= 0; top -= kGroup) {
+#pragma unroll
+      for (int j = 0; j < kGroup; ++j) buf[j][lane] = back_step<MODE>(w, s, tab[top - j], m, f);
+      group_store(buf, red, lane, top, kGroup);
+    }
+  } else {
+    int h = 0;
+    for (double x = xb; x > kCosSinXmax && h < kMaxHalvings; x *= 0.25) ++h;
+    const double inv4h = ldexp(1.0, -2 * h);
+    for (int n = r != 0 ? r : kGroup; top >= 0; top -= n, n = kGroup) {
+#pragma unroll 1
+      for (int j = 0; j < n; ++j) {
+        const double2 A = tab[top - j];
+        const double2 g = back_w_exact(w, fma(A.x, m.nie, m.px) * m.qz, fma(A.y, m.nie, m.py) * m.qz, m.qz, h, inv4h);
+        buf[j][lane] = make_double2(g.x + g.x, g.y + g.y);
+      }
+      group_store(buf, red, lane, top, n);
+    }
+  }
+}
+
+// Lowest tangent fit that covers the bound xb, or kFineHalving (compared as in cot_variant).
+__device__ __forceinline__ int tan_variant(double xb) {
+  const uint32_t hi = __builtin_amdgcn_readfirstlane(__double2hiint(xb));
+  int mode = kFineHalving;
+#pragma unroll
+  for (int k = kNumFine - 1; k >= 0; --k)
+    if (hi < high_word(kFitXmax[k])) mode = k;
+  return mode;
+}
+
+// Backward steps of one (item, segment) slot, one mode per lane; a piece of the segment per 256-step
+// chunk, last first, each in its own variant.  Bound by FP64 issue at the clock the power limit
+// leaves.  10 pulses of 64x64x16 modes (32768 distinct) at nt = 4096: 3.27 ms here (4.1e11 mode-steps/s,
+// about 66 FP64 instructions each with the sums over modes) and 1.61 ms for the segments (8.3e11),
+// against 5.6 ms for one kernel that walked both sweeps item by item; 2 pulses of 512 distinct modes
+// at nt = 1000: 16 and 11 us against 274 us, which was 4 workgroups doing 2000 steps in a row.
+__global__ void __launch_bounds__(kItem) __attribute__((amdgpu_waves_per_eu(3))) k_grad_back(GradArgs a) {
   __shared__ double2 tab[kChunk];
   __shared__ double2 red[kWaves][kChunk];
   __shared__ double2 bufs[kWaves][kGroup][64];
-  const int item = xcd_item(blockIdx.x, gridDim.x);
-  const int pi = find_pulse_item(a.desc, a.n_pulses, item);
-  // the item's variant is that of the evolution's selection block holding it
+  const int64_t slot = a.slot0 + blockIdx.x;
+  const int pi = find_pulse_slot(a.desc, a.n_pulses, slot);
   const PulseDev& d = a.desc[pi];
-  switch (a.sel[d.blk_off + (item - d.item_off) * kItem / kSelBlock].x) {
-    case 0: grad_item<0>(a, item, pi, tab, red, bufs); break;
-    case 1: grad_item<1>(a, item, pi, tab, red, bufs); break;
-    case 2: grad_item<2>(a, item, pi, tab, red, bufs); break;
-    case 3: grad_item<3>(a, item, pi, tab, red, bufs); break;
-    case 4: grad_item<4>(a, item, pi, tab, red, bufs); break;
-    case 5: grad_item<5>(a, item, pi, tab, red, bufs); break;
-    case 6: grad_item<6>(a, item, pi, tab, red, bufs); break;
-    case 7: grad_item<7>(a, item, pi, tab, red, bufs); break;
-    default: grad_item<kFineHalving>(a, item, pi, tab, red, bufs); break;
+  const int rel = int(slot - d.slot_off), li = rel / d.nseg, seg = rel - li * d.nseg;
+  const double dt = d.dt;
+  const double2* A = reinterpret_cast<const double2*>(a.A) + d.tab_off;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  double px, py;
+  const double e = lane_mode(d, int64_t(li) * kItem + threadIdx.x, px, py);
+  BackMode m;
+  const double ie = 1.0 / e;
+  m.nie = -ie;
+  m.px = px * ie;
+  m.py = py * ie;
+  m.qz = e * dt;
+  m.z = m.qz * m.qz;
+  m.z2 = m.z + m.z;
+  const double* wp = a.prop + int64_t(blockIdx.x) * kSlotDoubles + threadIdx.x;
+  WPair w{wp[0], wp[kItem], wp[2 * kItem], wp[3 * kItem], wp[4 * kItem], wp[5 * kItem]};
+  const BlockBox b0 = block_box(d, li * kItem / kSelBlock, d.ndist);
+  const BlockBox bb{uniform(b0.pxl), uniform(b0.pxh), uniform(b0.pyl), uniform(b0.pyh), uniform(b0.pz2)};
+  const double* rg = a.ranges + 4 * int64_t(d.chk_off);
+  double2* part = reinterpret_cast<double2*>(a.part + (d.part_off - a.part0) + int64_t(li) * d.nt * 2);
+  const int n0 = seg * d.seg_len;
+  for (int n1 = min(n0 + d.seg_len, d.nt); n1 > n0;) {
+    const int c = (n1 - 1) / kChunk, beg = max(n0, c * kChunk), len = n1 - beg;
+    __syncthreads();
+    if (int(threadIdx.x) < len) tab[threadIdx.x] = A[beg + threadIdx.x];
+    __syncthreads();
+    const double xb = x_bound(bb, rg[4 * c], rg[4 * c + 1], rg[4 * c + 2], rg[4 * c + 3], dt);
+    switch (tan_variant(xb)) {
+      case 0: back_piece<0>(w, tab, len, m, xb, bufs[wave], red[wave], lane); break;
+      case 1: back_piece<1>(w, tab, len, m, xb, bufs[wave], red[wave], lane); break;
+      case 2: back_piece<2>(w, tab, len, m, xb, bufs[wave], red[wave], lane); break;
+      case 3: back_piece<3>(w, tab, len, m, xb, bufs[wave], red[wave], lane); break;
+      case 4: back_piece<4>(w, tab, len, m, xb, bufs[wave], red[wave], lane); break;
+      case 5: back_piece<5>(w, tab, len, m, xb, bufs[wave], red[wave], lane); break;
+      case 6: back_piece<6>(w, tab, len, m, xb, bufs[wave], red[wave], lane); break;
+      case 7: back_piece<7>(w, tab, len, m, xb, bufs[wave], red[wave], lane); break;
+      default: back_piece<kFineHalving>(w, tab, len, m, xb, bufs[wave], red[wave], lane); break;
+    }
+    __syncthreads();
+    if (int(threadIdx.x) < len) {
+      double2 v = red[0][threadIdx.x];
+#pragma unroll
+      for (int k = 1; k < kWaves; ++k) {
+        v.x += red[k][threadIdx.x].x;
+        v.y += red[k][threadIdx.x].y;
+      }
+      part[beg + threadIdx.x] = v;
+    }
+    n1 = beg;
   }
 }
 
-// dJ/dA[n] = -2 dt dV sum over the pulse's items (in order) of the partials (the edge partials carry
+// dJ/dA[n] = -dt dV sum over the pulse's items (in order) of the partials (the edge partials carry
 // their factors); one thread per (n, component).
-__global__ void __launch_bounds__(256) k_grad_reduce(const PulseDev* __restrict__ desc, const double* __restrict__ part, const double* __restrict__ epart,
-                                                     double* __restrict__ gA, double* __restrict__ gedge) {
-  const PulseDev& d = desc[blockIdx.y];
+__global__ void __launch_bounds__(256) k_grad_reduce(GradArgs a, double* __restrict__ gA, double* __restrict__ gedge) {
+  const PulseDev& d = a.desc[blockIdx.y];
   const int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x;
   const int64_t per = 2 * int64_t(d.nt);
   if (e < per) {
-    const double* p = part + d.part_off;
+    const double* p = a.part + (d.part_off - a.part0) + e;
     double v = 0.0;
-    for (int i = 0; i < d.nitems; ++i) v += p[int64_t(i) * per + e];
-    gA[2 * d.tab_off + e] = v * (-2.0 * d.dt) * d.dv;  // dq_x/dA_x = -dt; the factor 2 of 2 Re[...]
+#pragma unroll 8
+    for (int i = 0; i < d.nitems; ++i) v += p[int64_t(i) * per];
+    gA[2 * d.tab_off + e] = v * -d.dt * d.dv;  // dq_x/dA_x = -dt; the partials hold 2 Re[...]
   }
   if (gedge && blockIdx.x == 0 && threadIdx.x < 4) {
+    const double* p = a.epart + int64_t(d.item_off - a.item0) * kWaves * 4 + threadIdx.x;
     double v = 0.0;
-    for (int i = 0; i < d.nitems; ++i) v += epart[int64_t(d.item_off + i) * 4 + threadIdx.x];
+    for (int i = 0; i < d.nitems * kWaves; ++i) v += p[int64_t(i) * 4];
     gedge[4 * blockIdx.y + threadIdx.x] = v * d.dv;
   }
 }
 
 }  // namespace
 
-po_status launch_yield_grad(const Batch& b, const PulseDev* d_desc, const double* d_A, const double* d_A_edge,
-                            const int2* d_sel, double* d_part, double* d_epart, double* d_units,
+po_status launch_yield_grad(const PulseDev* d_desc, const GradRange& r, const double* d_A, const double* d_A_edge,
+                            const double* d_ranges, double* d_prop, double* d_part, double* d_epart, double* d_units,
                             double* d_gA, double* d_gedge, hipStream_t s) {
-  GradArgs a{d_desc, b.n_pulses, d_A, d_A_edge, d_sel, d_part, d_epart, d_units};
-  hipLaunchKernelGGL(k_yield_grad, dim3(b.total_items), dim3(kItem), 0, s, a);
+  const int n = r.i1 - r.i0;
+  const PulseDev* desc = d_desc + r.i0;
+  GradArgs a{desc,     n,      r.slot0, r.part0, r.item0, d_A,    d_A_edge + 4 * int64_t(r.i0),
+             d_ranges, d_prop, d_part,  d_epart, d_units};
+  PO_TRY(launch_segments(desc, n, r.slot0, r.slots, d_A, d_ranges, d_prop, s));
+  hipLaunchKernelGGL(k_grad_join, dim3(unsigned(r.items) * kWaves), dim3(64), 0, s, a);
   PO_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_grad_reduce, dim3(unsigned((2 * int64_t(b.max_nt) + 255) / 256), b.n_pulses), dim3(256), 0, s,
-                     d_desc, d_part, d_epart, d_gA, d_gedge);
+  hipLaunchKernelGGL(k_grad_back, dim3(unsigned(r.slots)), dim3(kItem), 0, s, a);
+  PO_HIP(hipGetLastError());
+  hipLaunchKernelGGL(k_grad_reduce, dim3(unsigned((2 * int64_t(r.max_nt) + 255) / 256), n), dim3(256), 0, s, a, d_gA,
+                     d_gedge ? d_gedge + 4 * int64_t(r.i0) : nullptr);
   PO_HIP(hipGetLastError());
   return PO_OK;
 }
