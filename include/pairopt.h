@@ -161,7 +161,7 @@ po_status po_evaluate(int32_t n_pulses, const po_pulse_spec* specs, const po_gri
  * HIP graph capture, tight serving loops, harnesses that forbid allocation.  Same kernels, same
  * results bit for bit; it calls no hipMalloc, hipFree or other allocating routine.  Its scratch
  * (pulse descriptors, spectra, normalisation partials, per-64-mode partial sums and per-chunk
- * table ranges) lives in one file-scope device array of 64 MiB that each device holds from
+ * table ranges) lives in one file-scope device array of 133 MiB that each device holds from
  * the library's first use there until the process ends; the caller passes inputs and outputs as
  * for po_evaluate.  Limits: at most 4096 pulses, and a batch whose scratch (about
  * 8 (sum 4 lines + pulses (statistic blocks + 1) + sum modes / 64 + 4 sum ceil(nt/256)) bytes
@@ -253,7 +253,7 @@ po_status po_evolve_modes_split(int32_t n_pulses, const po_pulse_spec* specs, co
  *  d_gA     out [sum nt][2]: dJ/dA at every step midpoint.
  *  d_gedge  out [n_pulses][2][2] or NULL: dJ/dA(t_i), dJ/dA(t_f) (initial state, projection).
  * Work buffers of ceil(distinct modes / 256) x (nt x 16 bytes + segments x 16 KiB) per pulse (the per-step
- * partial sums of each 256-mode item and the propagators of its 8 to 64 time segments) come from the
+ * partial sums of each 256-mode item and the propagators of its 8 to 32 time segments) come from the
  * scratch pool: 48 MiB for a 64x64x16 pulse symmetric in p_z at nt = 16384, 640 MiB for a 128x128x32
  * one at nt = 32768.  A batch that would need more than 2 GiB is worked through in groups of pulses,
  * one after the other in the same buffers; a pulse whose buffers do not fit in device memory returns

@@ -154,7 +154,7 @@ po_status build_batch(int32_t n, const po_pulse_spec* specs, const po_grid* grid
   *b = Batch{};
   b->n_pulses = n;
   int64_t tab = 0, modes = 0, coeff = 0, spec = 0;
-  int64_t units = 0, items = 0, chunks = 0;
+  int64_t units = 0, items = 0, chunks = 0, lines = 0, harm = 0;
   for (int i = 0; i < n; ++i) {
     PulseDev d;
     std::memset(&d, 0, sizeof d);
@@ -162,6 +162,8 @@ po_status build_batch(int32_t n, const po_pulse_spec* specs, const po_grid* grid
     d.mode_off = modes;
     d.coeff_off = coeff;
     d.spec_off = spec;
+    d.line_off = lines;
+    d.harm_off = harm;
     d.unit_off = units;
     d.item_off = int32_t(items);
     d.chk_off = int32_t(chunks);
@@ -183,7 +185,9 @@ po_status build_batch(int32_t n, const po_pulse_spec* specs, const po_grid* grid
       tab += s.nt;
       chunks += (s.nt + kChunkSteps - 1) / kChunkSteps;
       coeff += 4 * int64_t(s.n_s);
-      spec += 4 * int64_t(d.nlines);
+      spec += kSpecRec * (int64_t(spec_records(d.nlines)) + 1);
+      lines += d.nlines;
+      harm += d.nlines + 2;
       b->max_nt = std::max(b->max_nt, s.nt);
       b->max_lines = std::max(b->max_lines, d.nlines);
       b->max_ns = std::max(b->max_ns, d.ns);
@@ -218,13 +222,13 @@ po_status build_batch(int32_t n, const po_pulse_spec* specs, const po_grid* grid
   int64_t slots = 0, part = 0;
   if (specs && grids)
     for (int i = 0; i < n; ++i) {
-      // Few modes leave the chip idle along the mode axis, so they get more segments: 256 slots for a
-      // 1024-mode sheet (one workgroup per CU), 8 segments from 16384 modes on, where a batch of any
-      // size fills the chip and each further segment only costs its product with the state (32 of
-      // 33 x 64 instructions at the shortest length).  A matter of the pulse's own sizes: its result
-      // does not depend on the batch.
+      // Few modes leave the chip idle along the mode axis, so they get more segments: 128 slots for a
+      // 1024-mode sheet (62 us for the whole evaluation at nt = 4096; 67 us with 16 or 64 segments, the
+      // latter spent on applying them), 8 segments from 16384 modes on, where a batch of any size fills
+      // the chip and each further segment only costs its product with the state.  A matter of the
+      // pulse's own sizes: its result does not depend on the batch.
       int want = 8;
-      while (want < 64 && want * out[i].nitems < 512) want *= 2;
+      while (want < 32 && want * out[i].nitems < 512) want *= 2;
       const int units = (out[i].nt + kSegUnit - 1) / kSegUnit;
       out[i].seg_len = (units + want - 1) / want * kSegUnit;
       out[i].nseg = (out[i].nt + out[i].seg_len - 1) / out[i].seg_len;
@@ -238,6 +242,8 @@ po_status build_batch(int32_t n, const po_pulse_spec* specs, const po_grid* grid
   b->total_modes = modes;
   b->total_coeff = coeff;
   b->total_spec = spec;
+  b->total_lines = lines;
+  b->total_harm = harm;
   b->total_units = units;
   b->total_items = int32_t(items);
   b->total_chunks = int32_t(chunks);
@@ -276,6 +282,8 @@ __global__ void __launch_bounds__(64) k_fill_desc(PulseDev d, PulseDev step, int
   d.mode_off = i * step.mode_off;
   d.coeff_off = i * step.coeff_off;
   d.spec_off = i * step.spec_off;
+  d.line_off = i * step.line_off;
+  d.harm_off = i * step.harm_off;
   d.chk_off = i * step.chk_off;
   d.unit_off = i * step.unit_off;
   d.item_off = i * step.item_off;
@@ -307,6 +315,8 @@ po_status put_desc(const std::vector<PulseDev>& h, PulseDev* d_desc, hipStream_t
     e.mode_off = i * u.mode_off;
     e.coeff_off = i * u.coeff_off;
     e.spec_off = i * u.spec_off;
+    e.line_off = i * u.line_off;
+    e.harm_off = i * u.harm_off;
     e.chk_off = i * u.chk_off;
     e.unit_off = i * u.unit_off;
     e.item_off = i * u.item_off;
@@ -317,7 +327,7 @@ po_status put_desc(const std::vector<PulseDev>& h, PulseDev* d_desc, hipStream_t
   if (alike) {
     PulseDev e;
     std::memcpy(&e, &h[1], sizeof e);
-    e.tab_off = e.mode_off = e.coeff_off = e.spec_off = e.unit_off = e.slot_off = e.part_off = 0;
+    e.tab_off = e.mode_off = e.coeff_off = e.spec_off = e.line_off = e.harm_off = e.unit_off = e.slot_off = e.part_off = 0;
     e.chk_off = e.item_off = 0;
     alike = std::memcmp(&e, &h[0], sizeof e) == 0;
   }
@@ -356,13 +366,14 @@ struct SynthWork {
   }
 };
 struct AdjointWork {  // tables of the pulses and the line terms of the synthesis adjoint
-  size_t A, E, edge, scale, lines;
+  size_t A, E, edge, scale, harm, lines;
   AdjointWork(Work& w, int32_t n, const Batch& b) {
     A = w.add(sizeof(double) * 2 * size_t(b.total_rows));
     E = w.add(sizeof(double) * 2 * size_t(b.total_rows));
     edge = w.add(sizeof(double) * 4 * n);
     scale = w.add(sizeof(double) * n);
-    lines = w.add(sizeof(double) * size_t(b.total_spec / 4) * 8 * size_t(b.max_ns));
+    harm = w.add(sizeof(double) * 8 * size_t(b.total_harm));
+    lines = w.add(sizeof(double) * size_t(b.total_lines) * (8 + size_t(b.max_ns)));
   }
 };
 struct EvolveWork {
@@ -376,9 +387,10 @@ struct EvolveWork {
 };
 
 po_status synth_impl(const Work& w, const SynthWork& z, const double* d_coeff, double* d_A, double* d_E,
-                     double* d_A_edge, double* d_scale, hipStream_t s, const Batch& b, const PulseDev* d_desc) {
+                     double* d_A_edge, double* d_scale, double* d_ranges, hipStream_t s, const Batch& b,
+                     const PulseDev* d_desc) {
   return launch_synth(b, d_desc, d_coeff, w.at<double>(z.spec), w.at<double>(z.part), w.at<double>(z.scl), d_A, d_E,
-                      d_A_edge, d_scale, s);
+                      d_A_edge, d_scale, d_ranges, s);
 }
 
 // Event pairs bracketing evolution launches while timers are enabled.
@@ -389,12 +401,14 @@ unsigned long long* g_counts = nullptr;  // device: mode-steps per series varian
 
 // Evolution and yield into caller-provided scratch: d_units [total_units] (used when d_J is
 // non-NULL), d_ranges [4 total_chunks].  timed: bracket the evolution with the kernel timers.
-// d_prop: scratch of the time-split form, or NULL for the form without.
+// d_prop: scratch of the time-split form, or NULL for the form without; have_ranges: the synthesis has
+// already written d_ranges.
 po_status evolve_into(const Batch& b, const PulseDev* d_desc, const double* d_A, const double* d_A_edge, double* d_f,
-                      double* d_J, hipStream_t s, double* d_units, double* d_ranges, double* d_prop, bool timed_ok) {
+                      double* d_J, hipStream_t s, double* d_units, double* d_ranges, bool have_ranges, double* d_prop,
+                      bool timed_ok) {
   hipEvent_t e0 = nullptr;
   const bool timed = timed_ok && timer_start(s, &e0);
-  PO_TRY(launch_chunk_ranges(b, d_desc, d_A, d_ranges, s));
+  if (!have_ranges) PO_TRY(launch_chunk_ranges(b, d_desc, d_A, d_ranges, s));
   double* units = d_J ? d_units : nullptr;
   if (d_prop) PO_TRY(launch_evolve_segments(b, d_desc, d_A, d_A_edge, d_ranges, d_prop, d_f, units, s));
   else PO_TRY(launch_evolve_grid(b, d_desc, d_A, d_A_edge, d_ranges, d_f, units, s));
@@ -407,8 +421,8 @@ po_status evolve_into(const Batch& b, const PulseDev* d_desc, const double* d_A,
 }
 
 po_status evolve_impl(const Work& w, const EvolveWork& z, const Batch& b, const PulseDev* d_desc, const double* d_A,
-                      const double* d_A_edge, double* d_f, double* d_J, hipStream_t s) {
-  return evolve_into(b, d_desc, d_A, d_A_edge, d_f, d_J, s, w.at<double>(z.units), w.at<double>(z.ranges),
+                      const double* d_A_edge, bool have_ranges, double* d_f, double* d_J, hipStream_t s) {
+  return evolve_into(b, d_desc, d_A, d_A_edge, d_f, d_J, s, w.at<double>(z.units), w.at<double>(z.ranges), have_ranges,
                      z.split ? w.at<double>(z.prop) : nullptr, true);
 }
 
@@ -449,8 +463,9 @@ struct GradWork {
 };
 
 po_status yield_grad_impl(const Work& w, const GradWork& z, const Batch& b, const PulseDev* d_desc, const double* d_A,
-                          const double* d_A_edge, double* d_J, double* d_gA, double* d_gedge, hipStream_t s) {
-  PO_TRY(launch_chunk_ranges(b, d_desc, d_A, w.at<double>(z.ranges), s));
+                          const double* d_A_edge, bool have_ranges, double* d_J, double* d_gA, double* d_gedge,
+                          hipStream_t s) {
+  if (!have_ranges) PO_TRY(launch_chunk_ranges(b, d_desc, d_A, w.at<double>(z.ranges), s));
   for (const GradRange& r : z.groups)
     PO_TRY(launch_yield_grad(d_desc, r, d_A, d_A_edge, w.at<double>(z.ranges), w.at<double>(z.prop),
                              w.at<double>(z.part), w.at<double>(z.epart), w.at<double>(z.units), d_gA, d_gedge, s));
@@ -552,8 +567,11 @@ void timer_stop(hipStream_t s, hipEvent_t e0) {
 // is only a stand-in for the symbol: its device address comes from hipGetSymbolAddress, taken once
 // per device with that device current, and only that address is handed to kernels and copies.
 // ---------------------------------------------------------------------------------------------
-constexpr size_t kNoAllocScratchBytes = size_t(64) << 20;
 constexpr int kNoAllocMaxPulses = 4096;
+constexpr size_t kNoAllocLimitBytes = size_t(64) << 20;
+// Beyond the limit's own sizes: 32 bytes per line (at most 2^21 lines within the limit), up to 18 records
+// more per pulse and what a descriptor exceeds 208 bytes by.
+constexpr size_t kNoAllocScratchBytes = 2 * kNoAllocLimitBytes + kNoAllocMaxPulses * (18 * 8 * kSpecRec + sizeof(PulseDev) - 208) + 4096;
 constexpr int kNoAllocMaxDevices = 64;
 
 static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
@@ -610,7 +628,7 @@ po_status po_pulse_synth(int32_t n, const po_pulse_spec* specs, const double* d_
   PO_TRY(w.alloc(s));
   PulseDev* d_desc = w.at<PulseDev>(dw.desc);
   PO_TRY(put_desc(h, d_desc, s));
-  PO_TRY(synth_impl(w, sw, d_coeff, d_A, d_E, d_A_edge, d_scale, s, b, d_desc));
+  PO_TRY(synth_impl(w, sw, d_coeff, d_A, d_E, d_A_edge, d_scale, nullptr, s, b, d_desc));
   return check_finite(d_A, 2 * b.total_rows, "d_A", s);
 }
 
@@ -641,7 +659,7 @@ po_status po_evolve_modes(int32_t n, const po_pulse_spec* specs, const po_grid* 
   PO_TRY(w.alloc(s));
   PulseDev* d_desc = w.at<PulseDev>(dw.desc);
   PO_TRY(put_desc(h, d_desc, s));
-  PO_TRY(evolve_impl(w, ew, b, d_desc, d_A, d_A_edge, d_f, d_J, s));
+  PO_TRY(evolve_impl(w, ew, b, d_desc, d_A, d_A_edge, false, d_f, d_J, s));
   return check_outputs(b, d_f, d_J, s);
 }
 
@@ -790,7 +808,7 @@ po_status po_yield_gradient(int32_t n, const po_pulse_spec* specs, const po_grid
   PO_TRY(w.alloc(s));
   PulseDev* d_desc = w.at<PulseDev>(dw.desc);
   PO_TRY(put_desc(h, d_desc, s));
-  return yield_grad_impl(w, gw, b, d_desc, d_A, d_A_edge, d_J, d_gA, d_gedge, s);
+  return yield_grad_impl(w, gw, b, d_desc, d_A, d_A_edge, false, d_J, d_gA, d_gedge, s);
 }
 
 po_status po_synth_gradient(int32_t n, const po_pulse_spec* specs, const double* d_coeff, const double* d_gA,
@@ -817,8 +835,9 @@ po_status po_synth_gradient(int32_t n, const po_pulse_spec* specs, const double*
   PO_TRY(put_desc(h, d_desc, s));
   double *dA = w.at<double>(aw.A), *dE = w.at<double>(aw.E), *de = w.at<double>(aw.edge);
   double* dscale = w.at<double>(aw.scale);
-  PO_TRY(synth_impl(w, sw, d_coeff, dA, dE, de, dscale, s, b, d_desc));
-  return launch_synth_adjoint(b, d_desc, d_coeff, d_gA, d_gedge, dA, de, dE, dscale, w.at<double>(aw.lines), d_grad,
+  PO_TRY(synth_impl(w, sw, d_coeff, dA, dE, de, dscale, nullptr, s, b, d_desc));
+  return launch_synth_adjoint(b, d_desc, d_coeff, d_gA, d_gedge, dA, de, dE, dscale, w.at<double>(aw.harm),
+                              w.at<double>(aw.lines), d_grad,
                               d_U, d_gU, s);
 }
 
@@ -848,9 +867,10 @@ po_status po_evaluate_gradient(int32_t n, const po_pulse_spec* specs, const po_g
   PO_TRY(put_desc(h, d_desc, s));
   double *dA = w.at<double>(aw.A), *dE = w.at<double>(aw.E), *de = w.at<double>(aw.edge);
   double *dscale = w.at<double>(aw.scale), *dgA = w.at<double>(o_gA), *dge = w.at<double>(o_ge);
-  PO_TRY(synth_impl(w, sw, d_coeff, dA, dE, de, dscale, s, b, d_desc));
-  PO_TRY(yield_grad_impl(w, gw, b, d_desc, dA, de, d_J, dgA, dge, s));
-  return launch_synth_adjoint(b, d_desc, d_coeff, dgA, dge, dA, de, dE, dscale, w.at<double>(aw.lines), d_grad, d_U,
+  PO_TRY(synth_impl(w, sw, d_coeff, dA, dE, de, dscale, w.at<double>(gw.ranges), s, b, d_desc));
+  PO_TRY(yield_grad_impl(w, gw, b, d_desc, dA, de, true, d_J, dgA, dge, s));
+  return launch_synth_adjoint(b, d_desc, d_coeff, dgA, dge, dA, de, dE, dscale, w.at<double>(aw.harm),
+                              w.at<double>(aw.lines), d_grad, d_U,
                               d_gU, s);
 }
 
@@ -898,7 +918,8 @@ po_status po_evaluate(int32_t n, const po_pulse_spec* specs, const po_grid* grid
   PO_TRY(w.alloc(s));
   PulseDev* d_desc = w.at<PulseDev>(dw.desc);
   PO_TRY(put_desc(h, d_desc, s));
-  PO_TRY(synth_impl(w, sw, d_coeff, d_A, nullptr, d_A_edge, d_scale, s, b, d_desc));
+  PO_TRY(synth_impl(w, sw, d_coeff, d_A, nullptr, d_A_edge, d_scale, plan ? nullptr : w.at<double>(ew.ranges), s, b,
+                    d_desc));
   PO_TRY(check_finite(d_A, 2 * b.total_rows, "d_A", s));
   if (plan) {
     hipEvent_t e0 = nullptr;
@@ -907,7 +928,7 @@ po_status po_evaluate(int32_t n, const po_pulse_spec* specs, const po_grid* grid
     if (timed) timer_stop(s, e0);
     return check_outputs(b, d_f, d_J, s);
   }
-  PO_TRY(evolve_impl(w, ew, b, d_desc, d_A, d_A_edge, d_f, d_J, s));
+  PO_TRY(evolve_impl(w, ew, b, d_desc, d_A, d_A_edge, true, d_f, d_J, s));
   return check_outputs(b, d_f, d_J, s);
 }
 
@@ -922,6 +943,14 @@ po_status po_evaluate_noalloc(int32_t n, const po_pulse_spec* specs, const po_gr
   Batch b;
   PO_TRY(build_batch(n, specs, grids, g_noalloc_desc, &b));
   const EvalSizes z = eval_sizes(n, b);
+  // the documented limit: descriptors (208 bytes a pulse), 4 doubles a line, partials, scales, unit sums and
+  // ranges; the array also has room for the larger records that are laid out in it
+  const size_t limit = align256(208 * size_t(n)) + align256(32 * size_t(b.total_lines)) +
+                       align256(sizeof(double) * z.part) + align256(sizeof(double) * z.scl) +
+                       align256(sizeof(double) * z.units) + align256(sizeof(double) * z.ranges);
+  if (limit > kNoAllocLimitBytes)
+    return set_error(PO_ERR_INVALID, "batch needs %zu bytes of scratch, the allocation-free path holds %zu", limit,
+                     kNoAllocLimitBytes);
   const size_t o_desc = 0;
   const size_t o_spec = o_desc + align256(sizeof(PulseDev) * size_t(n));
   const size_t o_part = o_spec + align256(sizeof(double) * z.spec);
@@ -929,9 +958,7 @@ po_status po_evaluate_noalloc(int32_t n, const po_pulse_spec* specs, const po_gr
   const size_t o_units = o_scl + align256(sizeof(double) * z.scl);
   const size_t o_ranges = o_units + align256(sizeof(double) * z.units);
   const size_t need = o_ranges + align256(sizeof(double) * z.ranges);
-  if (need > kNoAllocScratchBytes)
-    return set_error(PO_ERR_INVALID, "batch needs %zu bytes of scratch, the allocation-free path holds %zu", need,
-                     kNoAllocScratchBytes);
+  if (need > kNoAllocScratchBytes) return set_error(PO_ERR_INVALID, "batch needs %zu bytes of scratch", need);
   PO_TRY(check_device_range(d_coeff, sizeof(double) * b.total_coeff, 8, "d_coeff"));
   PO_TRY(check_device_range(d_A, sizeof(double) * 2 * b.total_rows, 8, "d_A"));
   PO_TRY(check_device_range(d_A_edge, sizeof(double) * 4 * n, 8, "d_A_edge"));
@@ -945,13 +972,14 @@ po_status po_evaluate_noalloc(int32_t n, const po_pulse_spec* specs, const po_gr
   PulseDev* d_desc = reinterpret_cast<PulseDev*>(sc + o_desc);
   PO_HIP(hipMemcpyAsync(d_desc, g_noalloc_desc, sizeof(PulseDev) * size_t(n), hipMemcpyHostToDevice, s));
   PO_TRY(launch_synth(b, d_desc, d_coeff, reinterpret_cast<double*>(sc + o_spec), reinterpret_cast<double*>(sc + o_part),
-                      reinterpret_cast<double*>(sc + o_scl), d_A, nullptr, d_A_edge, d_scale, s));
+                      reinterpret_cast<double*>(sc + o_scl), d_A, nullptr, d_A_edge, d_scale,
+                      reinterpret_cast<double*>(sc + o_ranges), s));
   // what the scratch array has left serves the time-split form of a small batch
   const size_t prop_bytes = sizeof(double) * kSlotDoubles * size_t(b.total_slots);
   double* d_prop = split_in_time(b) && prop_bytes <= kNoAllocScratchBytes - need ? reinterpret_cast<double*>(sc + need)
                                                                                   : nullptr;
   return evolve_into(b, d_desc, d_A, d_A_edge, d_f, d_J, s, reinterpret_cast<double*>(sc + o_units),
-                     reinterpret_cast<double*>(sc + o_ranges), d_prop, false);
+                     reinterpret_cast<double*>(sc + o_ranges), true, d_prop, false);
 }
 
 po_status po_timer_enable(int on) {
@@ -1065,8 +1093,8 @@ po_status po_de_generation(const po_de_params* prm, int64_t generation, const po
   PO_TRY(put_desc(h, d_desc, s));
   double *d_A = w.at<double>(o_A), *d_edge = w.at<double>(o_edge);
   PO_TRY(launch_de_propose(*prm, generation, d_pop, d_trial, nullptr, s));
-  PO_TRY(synth_impl(w, sw, d_trial, d_A, nullptr, d_edge, nullptr, s, b, d_desc));
-  PO_TRY(evolve_impl(w, ew, b, d_desc, d_A, d_edge, nullptr, d_trial_fit, s));
+  PO_TRY(synth_impl(w, sw, d_trial, d_A, nullptr, d_edge, nullptr, w.at<double>(ew.ranges), s, b, d_desc));
+  PO_TRY(evolve_impl(w, ew, b, d_desc, d_A, d_edge, true, nullptr, d_trial_fit, s));
   PO_TRY(launch_de_select(*prm, d_pop, d_fit, d_trial, d_trial_fit, nullptr, s));
   return check_finite(d_trial_fit, n, "d_trial_fit", s);
 }
@@ -1149,8 +1177,8 @@ po_status po_jde_generation(const po_jde_params* prm, int64_t generation, const 
   PO_TRY(put_desc(h, d_desc, s));
   double *d_A = w.at<double>(o_A), *d_edge = w.at<double>(o_edge);
   PO_TRY(launch_jde_propose(*prm, generation, d_pop, d_fcr, d_trial, d_trial_fcr, nullptr, s));
-  PO_TRY(synth_impl(w, sw, d_trial, d_A, nullptr, d_edge, nullptr, s, b, d_desc));
-  PO_TRY(evolve_impl(w, ew, b, d_desc, d_A, d_edge, nullptr, d_trial_fit, s));
+  PO_TRY(synth_impl(w, sw, d_trial, d_A, nullptr, d_edge, nullptr, w.at<double>(ew.ranges), s, b, d_desc));
+  PO_TRY(evolve_impl(w, ew, b, d_desc, d_A, d_edge, true, nullptr, d_trial_fit, s));
   return launch_jde_select(*prm, d_pop, d_fit, d_fcr, d_trial, d_trial_fit, d_trial_fcr, nullptr, s);
 }
 

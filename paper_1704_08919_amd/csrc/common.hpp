@@ -36,15 +36,22 @@ constexpr int kItem = 256;        // modes per workgroup in the default (non-pla
 constexpr int kSelBlock = 512;    // modes per series-selection block: a multiple of every launch's item
 constexpr int kChunkSteps = 256;  // time steps per LDS chunk of the per-mode kernels (and per table range)
 constexpr int kSegUnit = 64;      // time segments of a pulse are multiples of this many steps
+constexpr int kSpecRec = 8;       // doubles per harmonic record (k_spectra); one more record ends a pulse's
+constexpr int kSpecPad = 16;      // records per exact phase evaluation; a pulse's are padded to a multiple
 constexpr int kMaxLines = 8192;   // spectral lines per pulse
 constexpr int kMaxNs = 64;        // B-spline coefficients per spectral function
 constexpr int kMaxSub = 8;        // sample points per step of po_field_samples
+
+__host__ __device__ constexpr int spec_records(int nlines) {
+  return (nlines + 2 + kSpecPad - 1) / kSpecPad * kSpecPad;
+}
 
 struct PulseDev {
   int64_t tab_off;    // first table row (rows of 2 doubles)
   int64_t mode_off;   // first mode in the packed f array
   int64_t coeff_off;  // first coefficient (doubles)
-  int64_t spec_off;   // first spectral record in the scratch spectra (4 doubles per line)
+  int64_t spec_off;   // first double of the pulse's harmonic records in the scratch spectra
+  int64_t line_off, harm_off;  // first line, first harmonic (nlines + 2 per pulse) in the batch
   int32_t nt, ns, order, nlines;
   int32_t nmin, norm, stat_blocks;
   int32_t chk_off;    // first 256-step chunk of this pulse in the batch (table ranges per chunk)
@@ -72,6 +79,7 @@ struct PulseDev {
 struct Batch {
   int32_t n_pulses = 0;
   int64_t total_rows = 0, total_modes = 0, total_coeff = 0, total_spec = 0;
+  int64_t total_lines = 0, total_harm = 0;
   int64_t total_units = 0;
   int64_t total_units_all = 0; // 64-mode units of all modes, mirror images included
   int32_t total_items = 0;     // workgroups of the default evolution launch
@@ -116,20 +124,21 @@ struct Work {
 };
 
 // --------------------------------------------------------------------- kernel launchers
+// Tables of a batch; d_ranges [total_chunks][4] (or NULL) as launch_chunk_ranges writes it.
 po_status launch_synth(const Batch& b, const PulseDev* d_desc, const double* d_coeff, double* d_spec,
                        double* d_part, double* d_scale_ws, double* d_A, double* d_E, double* d_A_edge,
-                       double* d_scale_out, hipStream_t s);
+                       double* d_scale_out, double* d_ranges, hipStream_t s);
 // Scaled field samples at t_i + (n + offsets[r]) dt (rows per pulse nt n_sub + with_end, from
 // desc.tab_off); any of d_E, d_Ed, d_A, d_A_edge may be NULL.
 po_status launch_samples(const Batch& b, const PulseDev* d_desc, const double* d_coeff, double* d_spec, double* d_part,
                          double* d_scale_ws, int n_sub, const double* offsets, int with_end, double* d_E,
                          double* d_Ed, double* d_A, double* d_A_edge, double* d_scale_out, hipStream_t s);
-// Adjoint of the synthesis: d_lines scratch [sum lines][8 max_ns]; d_A, d_A_edge, d_E the (scaled) tables of
+// Adjoint of the synthesis: d_harm scratch [sum (lines + 2)][8], d_lines [sum lines][8 + max_ns]; d_A, d_A_edge, d_E the (scaled) tables of
 // the pulses and d_scale their scale; d_gA [sum nt][2] and d_gedge [n][2][2] (or NULL) the gradient of
 // J with respect to the tables.  Writes dJ/dc, the energy U and dU/dc (NULL to skip).
 po_status launch_synth_adjoint(const Batch& b, const PulseDev* d_desc, const double* d_coeff, const double* d_gA,
                                const double* d_gedge, const double* d_A, const double* d_A_edge, const double* d_E,
-                               const double* d_scale, double* d_lines, double* d_grad, double* d_U, double* d_gU,
+                               const double* d_scale, double* d_harm, double* d_lines, double* d_grad, double* d_U, double* d_gU,
                                hipStream_t s);
 // Yield gradient (grad.hip) of pulses [i0, i1) of the batch: d_prop holds their slots, d_part their item
 // partials [items][nt][2], d_epart 4 x [4] doubles per item of them.

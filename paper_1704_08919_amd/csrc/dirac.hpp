@@ -259,7 +259,8 @@ __device__ __forceinline__ void rescale(State& v) {
 }
 
 // psi <- P psi for both blocks, P given by its first column (a multiple of an SU(2) matrix is
-// [[a, -conj b], [b, conj a]]), then rescaled.
+// [[a, -conj b], [b, conj a]]).  |P| is in [1/2, 2), so a few products may go by between two rescalings;
+// these are exact, so their places do not affect the result.
 __device__ __forceinline__ void apply_propagator(State& s, const State& p) {
   const double ar = fma(-p.bi, s.bi, fma(-p.br, s.br, fma(-p.ai, s.ai, p.ar * s.ar)));
   const double ai = fma(p.bi, s.br, fma(-p.br, s.bi, fma(p.ai, s.ar, p.ar * s.ai)));
@@ -270,7 +271,6 @@ __device__ __forceinline__ void apply_propagator(State& s, const State& p) {
   const double dr = fma(p.ci, s.di, fma(p.cr, s.dr, fma(-p.di, s.ci, p.dr * s.cr)));
   const double di = fma(-p.ci, s.dr, fma(p.cr, s.di, fma(p.di, s.cr, p.dr * s.ci)));
   s = State{ar, ai, br, bi, cr, ci, dr, di};
-  rescale(s);
 }
 
 // Large-step path: C, S at x / 4^h, then h double-angle steps; the step stays unitary.
@@ -341,6 +341,22 @@ __device__ __forceinline__ void store_state(double* __restrict__ buf, int64_t sl
 __device__ __forceinline__ State load_state(const double* __restrict__ buf, int64_t slot, int lane) {
   const double* p = buf + slot * kSlotDoubles + lane;
   return State{p[0], p[kItem], p[2 * kItem], p[3 * kItem], p[4 * kItem], p[5 * kItem], p[6 * kItem], p[7 * kItem]};
+}
+
+// Applies the n propagators from slot `slot` on to a lane's state, in order; the loads of four are in
+// flight together.
+constexpr int kApplyBatch = 4;
+
+__device__ __forceinline__ void apply_segments(State& psi, const double* __restrict__ buf, int64_t slot, int n, int lane) {
+  for (int s0 = 0; s0 < n; s0 += kApplyBatch) {
+    State v[kApplyBatch];
+#pragma unroll
+    for (int k = 0; k < kApplyBatch; ++k) v[k] = load_state(buf, slot + min(s0 + k, n - 1), lane);
+#pragma unroll
+    for (int k = 0; k < kApplyBatch; ++k)
+      if (s0 + k < n) apply_propagator(psi, v[k]);
+    rescale(psi);
+  }
 }
 
 // Negative-energy eigenvector of h_s(P): (-(P_x - i s P_y), w + e) / sqrt(2 w (w + e)).

@@ -41,7 +41,7 @@
 // broadcast.  The propagators (per block the first column, 2 complex amplitudes per mode) stay in
 // VGPRs.  f is summed per 64-mode unit by one
 // wave in a fixed butterfly order, and units per pulse in a fixed tree, so J does not depend on
-// the launch shape or on scheduling.  Time is cut into segments (a multiple of 64 steps, 8 to 64 of
+// the launch shape or on scheduling.  Time is cut into segments (a multiple of 64 steps, 8 to 32 of
 // them by the pulse's own sizes); each is evolved from the identity and applied to the state.  Three
 // launch forms share this code and its results: one workgroup per 256-mode item that walks
 // through the segments, persistent workgroups that pull items (longest pulses first) from a device
@@ -298,7 +298,10 @@ __device__ __forceinline__ void process_item(const EvolveArgs& a, int pi, int fi
     State v[MPL];
     propagate<THREADS, MPL>(v, t, n0, min(n0 + d.seg_len, d.nt), mode, lds);
 #pragma unroll
-    for (int j = 0; j < MPL; ++j) apply_propagator(psi[j], v[j]);
+    for (int j = 0; j < MPL; ++j) {
+      apply_propagator(psi[j], v[j]);
+      rescale(psi[j]);
+    }
   }
 
   const double2 aout = edge[1];
@@ -338,7 +341,7 @@ k_segments(EvolveArgs a, int64_t slot0, double* __restrict__ prop) {
 }
 
 // Second kernel: one lane per mode applies its segments in order.  Wavefronts of 64 here (one per
-// workgroup) spread the few modes over as many CUs; the loads of four segments are in flight together.
+// workgroup) spread the few modes over as many CUs.
 __global__ void __launch_bounds__(64) k_join_segments(EvolveArgs a, const double* __restrict__ prop) {
   const int item = blockIdx.x / (kItem / 64), lane = (blockIdx.x % (kItem / 64)) * 64 + threadIdx.x;
   const int pi = find_pulse_item(a.desc, a.n_pulses, item);
@@ -351,15 +354,7 @@ __global__ void __launch_bounds__(64) k_join_segments(EvolveArgs a, const double
   const double e = lane_mode(d, m, px, py);
   State psi;
   init_state(psi, px - ain.x, py - ain.y, e);
-  for (int s0 = 0; s0 < d.nseg; s0 += 4) {
-    State v[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (s0 + k < d.nseg) v[k] = load_state(prop, slot + s0 + k, lane);
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (s0 + k < d.nseg) apply_propagator(psi, v[k]);
-  }
+  apply_segments(psi, prop, slot, d.nseg, lane);
   write_density(d, a.f, a.units, m, m < d.ndist ? project(psi, px - aout.x, py - aout.y, e) : 0.0);
 }
 
@@ -845,8 +840,8 @@ po_status launch_evolve_grid(const Batch& b, const PulseDev* d_desc, const doubl
 // The batch is split in time when its items alone load the CUs thinly or unevenly.  Measured, one
 // pulse at nt = 4096, us per call split / not split: 16 items 75 / 357, 128 items 190 / 344, 256 items
 // 329 / 352, 320 items 402 / 581 (some CUs then hold two workgroups, the others one), 384 items
-// 480 / 594, 512 items 619 / 626 and, at nt = 1024, 194 / 177; 48 sheets of 1024 modes (192 items,
-// 12288 slots) 349 / 405, 64 of them 420 / 408.  At most 8192 slots (128 MiB of propagators).
+// 480 / 594, 512 items 619 / 626 and, at nt = 1024, 194 / 177.  At most 8192 slots (128 MiB of
+// propagators).
 bool split_in_time(const Batch& b) {
   return b.total_items <= 448 && b.total_slots > b.total_items && b.total_slots <= 8192;
 }

@@ -324,15 +324,7 @@ __global__ void __launch_bounds__(64) k_grad_join(GradArgs a) {
   const double e = lane_mode(d, m, px, py);
   State psi;
   init_state(psi, px - ain.x, py - ain.y, e);
-  for (int s0 = 0; s0 < d.nseg; s0 += 4) {
-    State v[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (s0 + k < d.nseg) v[k] = load_state(a.prop, slot + s0 + k, lane);
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (s0 + k < d.nseg) apply_propagator(psi, v[k]);
-  }
+  apply_segments(psi, a.prop, slot, d.nseg, lane);
 
   // t_f: normalise each block, alpha_s = <+_s(P_out)|psi_s>, final-state terms, and
   // W_s = Im(conj(alpha_s) <+_s|tau|psi_s>), the start of the backward sweep (chi'_s = alpha_s |+_s>)
@@ -378,13 +370,12 @@ __global__ void __launch_bounds__(64) k_grad_join(GradArgs a) {
     }
   }
 
-  for (int s1 = d.nseg; s1 > 0; s1 -= 4) {
-    State v[4];
+  for (int s1 = d.nseg; s1 > 0; s1 -= kApplyBatch) {
+    State v[kApplyBatch];
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (s1 - 1 - k >= 0) v[k] = load_state(a.prop, slot + s1 - 1 - k, lane);
+    for (int k = 0; k < kApplyBatch; ++k) v[k] = load_state(a.prop, slot + max(s1 - 1 - k, 0), lane);
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
+    for (int k = 0; k < kApplyBatch; ++k)
       if (s1 - 1 - k >= 0) {
         double* o = a.prop + (slot + s1 - 1 - k) * kSlotDoubles + lane;
         o[0] = w.ax; o[kItem] = w.ay; o[2 * kItem] = w.az;

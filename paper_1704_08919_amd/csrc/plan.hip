@@ -98,11 +98,12 @@ po_status enqueue(po_plan* p, const double* d_coeff, const double* d_A, const do
                   hipStream_t s) {
   if (d_coeff) {
     PO_TRY(launch_synth(p->b, p->d_desc, d_coeff, p->d_spec, p->d_part, p->d_scale, p->d_A, nullptr, p->d_edge,
-                        nullptr, s));
+                        nullptr, p->d_ranges, s));
     d_A = p->d_A;
     d_edge = p->d_edge;
+  } else {
+    PO_TRY(launch_chunk_ranges(p->b, p->d_desc, d_A, p->d_ranges, s));
   }
-  PO_TRY(launch_chunk_ranges(p->b, p->d_desc, d_A, p->d_ranges, s));
   double* units = d_J ? p->d_units : nullptr;
   if (p->d_prop)
     PO_TRY(launch_evolve_segments(p->b, p->d_desc, d_A, d_edge, p->d_ranges, p->d_prop, d_f, units, s));

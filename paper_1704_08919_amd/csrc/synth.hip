@@ -9,6 +9,20 @@
 // Every line frequency is an integer multiple k of dw, so the phase Omega_k t equals
 // pi k (h - nt) / nt exactly; it is reduced modulo 2 in integers and evaluated with sincospi,
 // which keeps all trig arguments in [0, 2) whatever T is.
+//
+// The window cos^2(pi t/T) = 1/2 + cos(dw t)/2 shifts lines by one, so the windowed field is itself a sum
+// over harmonics of dw with coefficients C_k = c_k/2 + (c_{k-1} + c_{k+1})/4 (S_k alike), and
+//     A(t) = A_0 - C_0 (t - t_f) - sum_k [P_k sin(k dw t) - Q_k cos(k dw t)],  (P, Q)_k = (C, S)_k / (k dw),
+// A_0 = -sum_k (-1)^k Q_k (A(t_f) = 0).  One pass over the harmonics therefore needs, per time and line,
+// a rotation of (cos, sin) to the next harmonic (4 operations; exact phase every 16th line) and two
+// FMAs per wanted component, E from the raw lines (times the window, so that it vanishes at the ends
+// to relative precision) and A from P and Q: 12 operations for E and A, against about 120 when the
+// three frequencies of every line are summed separately.  The records are equal for all lanes and come
+// through scalar loads, four records in flight.  Bound by FP64 issue on large batches: 256 pulses x
+// 16384 steps x 128 lines take 0.36 ms for A and E and 0.27 ms for the peak (2.06 and 0.47 ms when each
+// line's three frequencies and the divisions by them were formed per step; 134 MB of tables are 0.03
+// ms).  A single pulse (16 workgroups) is a chain of rotations and exact phases: 9 and 13 us for 66
+// harmonics, 72 and 11 us before.
 #include "common.hpp"
 
 namespace po {
@@ -56,193 +70,196 @@ __device__ void bspline_all(int k, int ns, double wmin, double wmax, double w, d
   }
 }
 
-// One block per pulse; each thread fills lines j.  Output per line: (E cos Phi, E sin Phi) for x
-// and y, i.e. spec[off + 4 j + {0,1,2,3}] = (cEx, sEx, cEy, sEy).
+// First index mu - k + 1 and values N[0..k) of the k basis functions that do not vanish at w, for order
+// k <= 4 (de Boor's triangular scheme on the clamped knots; the last span is closed at omega_max).
+__device__ __forceinline__ int bspline_local(int k, int ns, double wmin, double wmax, double w, double N[4]) {
+  const int nb = ns - k + 2;  // breakpoints
+  int mu = k - 1 + min(max(int((w - wmin) / (wmax - wmin) * double(nb - 1)), 0), nb - 2);
+  while (mu > k - 1 && w < knot(mu, k, ns, wmin, wmax)) --mu;
+  while (mu < ns - 1 && w >= knot(mu + 1, k, ns, wmin, wmax)) ++mu;
+  N[0] = 1.0;
+#pragma unroll
+  for (int j = 1; j < 4; ++j) {
+    if (j < k) {
+      double saved = 0.0;
+#pragma unroll
+      for (int r = 0; r < j; ++r) {
+        const double right = knot(mu + r + 1, k, ns, wmin, wmax) - w, left = w - knot(mu + 1 - (j - r), k, ns, wmin, wmax);
+        const double t = N[r] / (right + left);
+        N[r] = saved + right * t;
+        saved = left * t;
+      }
+      N[j] = saved;
+    }
+  }
+  return mu - k + 1;
+}
+
+// E and phase Phi of both components at line j, E = sum a b_i, Phi = sum pi (c + 1) b_i.
+__device__ void line_spectrum(const PulseDev& d, const double* __restrict__ a, int j, double E[2], double ph[2]) {
+  // basis at the line frequency clamped into the band: the end lines sample the end knots
+  // whatever the rounding of (N_min + j) dw
+  const double w = fmin(fmax(double(d.nmin + j) * d.dw, d.wmin), d.wmax);
+  E[0] = E[1] = ph[0] = ph[1] = 0.0;
+  if (d.order <= 4) {
+    double N[4];
+    const int i0 = bspline_local(d.order, d.ns, d.wmin, d.wmax, w, N);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (r < d.order)
+        for (int l = 0; l < 2; ++l) {
+          E[l] += a[(l * 2 + 0) * d.ns + i0 + r] * N[r];
+          ph[l] += M_PI * (a[(l * 2 + 1) * d.ns + i0 + r] + 1.0) * N[r];
+        }
+  } else {
+    double b[2 * kMaxNs + 2];
+    bspline_all(d.order, d.ns, d.wmin, d.wmax, w, b);
+    for (int i = 0; i < d.ns; ++i)
+      for (int l = 0; l < 2; ++l) {
+        E[l] += a[(l * 2 + 0) * d.ns + i] * b[i];
+        ph[l] += M_PI * (a[(l * 2 + 1) * d.ns + i] + 1.0) * b[i];
+      }
+  }
+}
+
+// Harmonic records of a pulse, kSpecRec doubles each for k = nmin - 1 + i, i = 0..nlines + 1 (padded with
+// zero records to a multiple of kSpecPad): the raw line
+// (cEx, sEx, cEy, sEy) (cE = E cos Phi, sE = E sin Phi; 0 for the two outer records) and (Px, Qx, Py,
+// Qy); then (A_0x, A_0y, C_0x, C_0y).  One workgroup per pulse, in tiles of kSpecTile harmonics.
+constexpr int kSpecTile = 126;
+
 __global__ void __launch_bounds__(128) k_spectra(const PulseDev* __restrict__ desc,
                                                  const double* __restrict__ coeff, double* __restrict__ spec) {
   const PulseDev d = desc[blockIdx.x];
   const double* a = coeff + d.coeff_off;
-  double b[2 * kMaxNs + 2];
-  for (int j = threadIdx.x; j < d.nlines; j += blockDim.x) {
-    // basis at the line frequency clamped into the band: the end lines sample the end knots
-    // whatever the rounding of (N_min + j) dw
-    const double w = fmin(fmax(double(d.nmin + j) * d.dw, d.wmin), d.wmax);
-    bspline_all(d.order, d.ns, d.wmin, d.wmax, w, b);
-    double out[4];
-    for (int l = 0; l < 2; ++l) {
-      double E = 0.0, ph = 0.0;
-      for (int i = 0; i < d.ns; ++i) {
-        E += a[(l * 2 + 0) * d.ns + i] * b[i];
-        ph += M_PI * (a[(l * 2 + 1) * d.ns + i] + 1.0) * b[i];
+  __shared__ double4 raw[128];
+  __shared__ double red[4][128];
+  __shared__ double c0[2];
+  const int t = threadIdx.x, nh = spec_records(d.nlines);
+  double* out = spec + d.spec_off;
+  double a0x = 0.0, a0y = 0.0;
+  if (t < 2) c0[t] = 0.0;
+  for (int i0 = 0; i0 < nh; i0 += kSpecTile) {
+    const int j = i0 + t - 2;  // raw line of this thread; harmonic i0 + t takes lines i0 + t - 2, ..., i0 + t
+    double4 q = make_double4(0.0, 0.0, 0.0, 0.0);
+    if (j >= 0 && j < d.nlines) {
+      double E[2], ph[2], sp, cp;
+      line_spectrum(d, a, j, E, ph);
+      sincos(ph[0], &sp, &cp);
+      q.x = E[0] * cp;
+      q.y = E[0] * sp;
+      sincos(ph[1], &sp, &cp);
+      q.z = E[1] * cp;
+      q.w = E[1] * sp;
+    }
+    __syncthreads();
+    raw[t] = q;
+    __syncthreads();
+    const int i = i0 + t;
+    if (t < kSpecTile && i < nh) {
+      const int k = d.nmin - 1 + i;
+      const double4 l = raw[t], m = raw[t + 1], u = raw[t + 2];
+      double4 w = make_double4(0.5 * m.x + 0.25 * (l.x + u.x), 0.5 * m.y + 0.25 * (l.y + u.y),
+                               0.5 * m.z + 0.25 * (l.z + u.z), 0.5 * m.w + 0.25 * (l.w + u.w));
+      if (k == 1 && d.nmin == 0) {  // cos(-x) = cos x, sin(-x) = -sin x: the side line k = -1 of k = 0 (= l)
+        w.x += 0.25 * l.x;
+        w.y -= 0.25 * l.y;
+        w.z += 0.25 * l.z;
+        w.w -= 0.25 * l.w;
       }
-      double sp, cp;
-      sincos(ph, &sp, &cp);
-      out[2 * l] = E * cp;
-      out[2 * l + 1] = E * sp;
-    }
-    double4* dst = reinterpret_cast<double4*>(spec + d.spec_off) + j;
-    *dst = make_double4(out[0], out[1], out[2], out[3]);
-  }
-}
-
-// sincos(pi k (h - nt) / nt) with the argument reduced exactly in integers.
-__device__ __forceinline__ void line_phase(int64_t k, int64_t hm, int64_t two_nt, double inv_nt, double* s, double* c) {
-  int64_t r = (k * hm) % two_nt;
-  if (r < 0) r += two_nt;
-  sincospi(double(r) * inv_nt, s, c);
-}
-
-// Unscaled field (want_E) and potential (want_A) at half-step index h.
-__device__ void field_at(const PulseDev& d, const double4* __restrict__ sp, int64_t h, bool want_E, bool want_A,
-                         double E[2], double A[2]) {
-  const int64_t nt = d.nt, two_nt = 2 * int64_t(d.nt);
-  const int64_t hm = h - nt;
-  const double inv_nt = 1.0 / double(d.nt);
-  double ex = 0.0, ey = 0.0, ax = 0.0, ay = 0.0;
-  double sd = 0.0, cd = 1.0;  // Delta omega t
-  if (want_A) line_phase(1, hm, two_nt, inv_nt, &sd, &cd);
-  const double tmf = double(h - two_nt) * (0.5 * d.dt);  // t - t_f
-  for (int j = 0; j < d.nlines; ++j) {
-    const int64_t k = int64_t(d.nmin) + j;
-    double s, c;
-    line_phase(k, hm, two_nt, inv_nt, &s, &c);
-    const double4 q = sp[j];  // (cEx, sEx, cEy, sEy)
-    if (want_E) {
-      ex += q.x * c + q.y * s;
-      ey += q.z * c + q.w * s;
-    }
-    if (want_A) {
-      // E_j [I(Om, -Phi)/2 + I(dw + Om, -Phi)/4 + I(dw - Om, +Phi)/4], I(w, phi; t) = int_{t_f}^t cos(w s + phi) ds
-      //   = [sin(w t + phi) - (-1)^k' sin(phi)] / w with w t_f = k' pi; (t - t_f) cos(phi) when w = 0.
-      const double sgn = (k & 1) ? -1.0 : 1.0;
-      const double cp = c * cd - s * sd, spp = s * cd + c * sd;  // (Om + dw) t
-      const double cm = cd * c + sd * s, smm = sd * c - cd * s;  // (dw - Om) t
-      const double om = double(k) * d.dw, wp = double(k + 1) * d.dw, wm = double(1 - k) * d.dw;
-      double tx, ty;
-      // main line
       if (k == 0) {
-        tx = 0.5 * tmf * q.x;
-        ty = 0.5 * tmf * q.z;
-      } else {
-        tx = 0.5 * (q.x * s - q.y * c + sgn * q.y) / om;
-        ty = 0.5 * (q.z * s - q.w * c + sgn * q.w) / om;
+        c0[0] = w.x;
+        c0[1] = w.z;
       }
-      // upper side line dw + Om (never zero)
-      tx += 0.25 * (q.x * spp - q.y * cp - sgn * q.y) / wp;
-      ty += 0.25 * (q.z * spp - q.w * cp - sgn * q.w) / wp;
-      // lower side line dw - Om
-      if (k == 1) {
-        tx += 0.25 * tmf * q.x;
-        ty += 0.25 * tmf * q.z;
-      } else {
-        tx += 0.25 * (q.x * smm + q.y * cm + sgn * q.y) / wm;
-        ty += 0.25 * (q.z * smm + q.w * cm + sgn * q.w) / wm;
-      }
-      ax -= tx;
-      ay -= ty;
+      const double iw = k >= 1 ? 1.0 / (double(k) * d.dw) : 0.0;  // k = 0: the (t - t_f) term; k = -1: folded into 1
+      w = make_double4(w.x * iw, w.y * iw, w.z * iw, w.w * iw);
+      const double sg = (k & 1) ? 1.0 : -1.0;
+      a0x += sg * w.y;
+      a0y += sg * w.w;
+      double4* o = reinterpret_cast<double4*>(out + int64_t(kSpecRec) * i);
+      o[0] = m;
+      o[1] = w;
     }
   }
-  if (want_E) {
-    const double g = cospi(double(hm) * (0.5 * inv_nt));  // cos(pi t / T)
-    E[0] = g * g * ex;
-    E[1] = g * g * ey;
+  red[0][t] = a0x;
+  red[1][t] = a0y;
+  __syncthreads();
+  for (int w = 64; w > 0; w >>= 1) {
+    if (t < w) {
+      red[0][t] += red[0][t + w];
+      red[1][t] += red[1][t + w];
+    }
+    __syncthreads();
   }
-  if (want_A) {
-    A[0] = ax;
-    A[1] = ay;
-  }
+  if (t == 0)
+    *reinterpret_cast<double4*>(out + int64_t(kSpecRec) * nh) = make_double4(red[0][0], red[1][0], c0[0], c0[1]);
 }
 
-// Line data of up to 256 lines of a pulse, staged in LDS by a workgroup: the spectral record and
-// the factors 1/(2 Om), 1/(4 (dw + Om)), 1/(4 (dw - Om)) of the three terms of A (0 where the
-// frequency vanishes and the term takes its t - t_f form instead).
-struct LineTile {
-  double4 q[256];
-  double f0[256], f1[256], f2[256];
+// Sums over the harmonics of a pulse at phase index hm = h - nt plus a fraction cf (in half-steps): the
+// raw field e (without its window), its derivative ed, and sum [P sin - Q cos] in a.  The phase is
+// evaluated exactly (sincospi of the reduced index) at every 16th harmonic and carried to the next 15
+// by rotating with the step angle (a few ulps).
+struct FieldSums {
+  double ex, ey, dx, dy, ax, ay;
 };
 
-// field_at for every lane of a workgroup at its own half-step index h (all lanes must call it:
-// the lines are staged tile by tile with barriers).  The phase index r = k (h - nt) mod 2 nt
-// advances by h - nt from one line to the next, so only the first line needs a division; the
-// phase itself is evaluated exactly (sincospi of the reduced index) on every 16th line and carried
-// to the next 15 by rotating with the step angle pi (h - nt) / nt (a few ulps per line).
-__device__ void field_tiled(const PulseDev& d, const double4* __restrict__ sp, int64_t h, bool want_E, bool want_A,
-                            LineTile& L, double E[2], double A[2]) {
-  const int64_t nt = d.nt, two_nt = 2 * int64_t(d.nt);
-  const int64_t hm = h - nt;
+template <bool WE, bool WD, bool WA>
+__device__ __forceinline__ FieldSums field_sums(const PulseDev& d, const double* __restrict__ rec, int64_t hm, double cf) {
+  const int64_t two_nt = 2 * int64_t(d.nt);
   const double inv_nt = 1.0 / double(d.nt);
-  double ex = 0.0, ey = 0.0, ax = 0.0, ay = 0.0;
-  double sd = 0.0, cd = 1.0;  // Delta omega t
-  if (want_A) line_phase(1, hm, two_nt, inv_nt, &sd, &cd);
-  const double tmf = double(h - two_nt) * (0.5 * d.dt);  // t - t_f
-  int64_t r = (int64_t(d.nmin) * hm) % two_nt;
+  const int nh = spec_records(d.nlines), k0 = d.nmin - 1;
+  int64_t r = (int64_t(k0) * hm) % two_nt, r16 = (kSpecPad * hm) % two_nt;
   if (r < 0) r += two_nt;
-  double sr, cr;  // rotation by one line: pi (h - nt) / nt
-  sincospi(double(hm < 0 ? hm + two_nt : hm) * inv_nt, &sr, &cr);
-  double s = 0.0, c = 1.0;
-  for (int j0 = 0; j0 < d.nlines; j0 += 256) {
-    const int cnt = min(256, d.nlines - j0);
-    __syncthreads();
-    if (int(threadIdx.x) < cnt) {
-      const int64_t k = int64_t(d.nmin) + j0 + threadIdx.x;
-      L.q[threadIdx.x] = sp[j0 + threadIdx.x];
-      L.f0[threadIdx.x] = k == 0 ? 0.0 : 0.5 / (double(k) * d.dw);
-      L.f1[threadIdx.x] = 0.25 / (double(k + 1) * d.dw);
-      L.f2[threadIdx.x] = k == 1 ? 0.0 : 0.25 / (double(1 - k) * d.dw);
+  if (r16 < 0) r16 += two_nt;
+  double sr, cr;  // rotation by one harmonic
+  sincospi((double(hm < 0 ? hm + two_nt : hm) + cf) * inv_nt, &sr, &cr);
+  FieldSums o{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  for (int i0 = 0; i0 < nh; i0 += kSpecPad) {
+    double s, c, u = double(r) * inv_nt;
+    if (cf != 0.0) {
+      u = fma(double(k0 + i0), cf * inv_nt, u);
+      u -= 2.0 * floor(0.5 * u);
     }
-    __syncthreads();
-    for (int t = 0; t < cnt; ++t) {
-      const int64_t k = int64_t(d.nmin) + j0 + t;
-      if (((j0 + t) & 15) == 0) {
-        sincospi(double(r) * inv_nt, &s, &c);
-      } else {
-        const double cn = fma(c, cr, -(s * sr));
-        s = fma(s, cr, c * sr);
-        c = cn;
+    sincospi(u, &s, &c);
+    r += r16;
+    if (r >= two_nt) r -= two_nt;
+#pragma unroll 4
+    for (int i = i0; i < i0 + kSpecPad; ++i) {  // (four records' scalar loads in flight)
+      const double* q = rec + int64_t(kSpecRec) * i;
+      if (WE || WD) {
+        o.ex = fma(q[0], c, fma(q[1], s, o.ex));
+        o.ey = fma(q[2], c, fma(q[3], s, o.ey));
       }
-      r += hm;
-      if (r >= two_nt) r -= two_nt;
-      if (r < 0) r += two_nt;
-      const double4 q = L.q[t];  // (cEx, sEx, cEy, sEy)
-      if (want_E) {
-        ex += q.x * c + q.y * s;
-        ey += q.z * c + q.w * s;
+      if (WD) {
+        const double om = double(k0 + i) * d.dw;
+        o.dx = fma(om, fma(q[1], c, -(q[0] * s)), o.dx);
+        o.dy = fma(om, fma(q[3], c, -(q[2] * s)), o.dy);
       }
-      if (want_A) {
-        const double sgn = (k & 1) ? -1.0 : 1.0;
-        const double cp = c * cd - s * sd, spp = s * cd + c * sd;  // (Om + dw) t
-        const double cm = cd * c + sd * s, smm = sd * c - cd * s;  // (dw - Om) t
-        double tx, ty;
-        if (k == 0) {
-          tx = 0.5 * tmf * q.x;
-          ty = 0.5 * tmf * q.z;
-        } else {
-          tx = L.f0[t] * (q.x * s - q.y * c + sgn * q.y);
-          ty = L.f0[t] * (q.z * s - q.w * c + sgn * q.w);
-        }
-        tx += L.f1[t] * (q.x * spp - q.y * cp - sgn * q.y);
-        ty += L.f1[t] * (q.z * spp - q.w * cp - sgn * q.w);
-        if (k == 1) {
-          tx += 0.25 * tmf * q.x;
-          ty += 0.25 * tmf * q.z;
-        } else {
-          tx += L.f2[t] * (q.x * smm + q.y * cm + sgn * q.y);
-          ty += L.f2[t] * (q.z * smm + q.w * cm + sgn * q.w);
-        }
-        ax -= tx;
-        ay -= ty;
+      if (WA) {
+        o.ax = fma(q[4], s, fma(-q[5], c, o.ax));
+        o.ay = fma(q[6], s, fma(-q[7], c, o.ay));
       }
+      const double cn = fma(c, cr, -(s * sr));
+      s = fma(s, cr, c * sr);
+      c = cn;
     }
   }
-  if (want_E) {
-    const double g = cospi(double(hm) * (0.5 * inv_nt));  // cos(pi t / T)
-    E[0] = g * g * ex;
-    E[1] = g * g * ey;
-  }
-  if (want_A) {
-    A[0] = ax;
-    A[1] = ay;
-  }
+  return o;
+}
+
+// A(t) from the sums, t - t_f = tmf.
+__device__ __forceinline__ double2 potential(const PulseDev& d, const double* __restrict__ rec, const FieldSums& o,
+                                             double tmf) {
+  const double* e = rec + int64_t(kSpecRec) * spec_records(d.nlines);
+  return make_double2(e[0] - (e[2] * tmf + o.ax), e[1] - (e[3] * tmf + o.ay));
+}
+
+// A(t_i) = C_0 T and A(t_f) = 0: all harmonics return to their values at t_f.
+__device__ __forceinline__ void write_edges(const PulseDev& d, const double* __restrict__ rec, double s,
+                                            double2* __restrict__ edge) {
+  const double* e = rec + int64_t(kSpecRec) * spec_records(d.nlines);
+  edge[0] = make_double2(s * (e[2] * d.T), s * (e[3] * d.T));
+  edge[1] = make_double2(0.0, 0.0);
 }
 
 // Per block: max |E| over step nodes (PEAK) or sum |E|^2 over midpoints (ENERGY) -> part[pulse][block].
@@ -251,17 +268,18 @@ __global__ void __launch_bounds__(256) k_field_stats(const PulseDev* __restrict_
                                                      double* __restrict__ part) {
   const PulseDev d = desc[blockIdx.y];
   if (d.norm == PO_NORM_NONE || int(blockIdx.x) >= d.stat_blocks) return;
-  const double4* sp = reinterpret_cast<const double4*>(spec + d.spec_off);
   __shared__ double red[256];
-  __shared__ LineTile L;
   const int64_t n = int64_t(blockIdx.x) * 256 + threadIdx.x;
   const bool peak = d.norm == PO_NORM_PEAK;
-  // nodes 0..nt (PEAK) or midpoints 0..nt-1 (ENERGY); every lane takes part in the line staging
-  const bool active = peak ? n <= d.nt : n < d.nt;
-  double E[2], A[2];
-  field_tiled(d, sp, active ? (peak ? 2 * n : 2 * n + 1) : 0, true, false, L, E, A);
+  // nodes 0..nt (PEAK) or midpoints 0..nt-1 (ENERGY)
   double v = 0.0;
-  if (active) v = peak ? sqrt(E[0] * E[0] + E[1] * E[1]) : E[0] * E[0] + E[1] * E[1];
+  if (peak ? n <= d.nt : n < d.nt) {
+    const int64_t hm = (peak ? 2 * n : 2 * n + 1) - d.nt;
+    const FieldSums o = field_sums<true, false, false>(d, spec + d.spec_off, hm, 0.0);
+    const double g = cospi(double(hm) * (0.5 / double(d.nt)));  // cos(pi t / T)
+    const double ex = g * g * o.ex, ey = g * g * o.ey;
+    v = peak ? sqrt(ex * ex + ey * ey) : ex * ex + ey * ey;
+  }
   red[threadIdx.x] = v;
   __syncthreads();
   for (int w = 128; w > 0; w >>= 1) {
@@ -274,18 +292,11 @@ __global__ void __launch_bounds__(256) k_field_stats(const PulseDev* __restrict_
   if (threadIdx.x == 0) part[size_t(blockIdx.y) * stride + blockIdx.x] = red[0];
 }
 
-// One block per pulse: fixed-order reduction of the partials -> scale.
-__global__ void __launch_bounds__(256) k_scale(const PulseDev* __restrict__ desc, const double* __restrict__ part,
-                                               int stride, double* __restrict__ scale_ws,
-                                               double* __restrict__ scale_out) {
-  const PulseDev d = desc[blockIdx.x];
-  __shared__ double red[256];
+// Scale of a pulse from its partials, by a 256-lane workgroup: fixed-order reduction, every lane gets it.
+__device__ __forceinline__ double pulse_scale(const PulseDev& d, const double* __restrict__ part, double* red) {
   const bool peak = d.norm == PO_NORM_PEAK;
   double v = 0.0;
-  for (int i = threadIdx.x; i < d.stat_blocks; i += 256) {
-    const double x = part[size_t(blockIdx.x) * stride + i];
-    v = peak ? fmax(v, x) : v + x;
-  }
+  for (int i = threadIdx.x; i < d.stat_blocks; i += 256) v = peak ? fmax(v, part[i]) : v + part[i];
   red[threadIdx.x] = v;
   __syncthreads();
   for (int w = 128; w > 0; w >>= 1) {
@@ -293,116 +304,84 @@ __global__ void __launch_bounds__(256) k_scale(const PulseDev* __restrict__ desc
                                                       : red[threadIdx.x] + red[threadIdx.x + w];
     __syncthreads();
   }
-  if (threadIdx.x == 0) {
-    double s = 1.0;
-    if (d.norm == PO_NORM_PEAK) s = red[0] > 0.0 ? d.norm_value / red[0] : 0.0;
-    else if (d.norm == PO_NORM_ENERGY) {
-      const double U = red[0] * d.dt;
-      s = U > 0.0 ? sqrt(d.norm_value / U) : 0.0;
-    }
-    scale_ws[blockIdx.x] = s;
-    if (scale_out) scale_out[blockIdx.x] = s;
+  double s = 1.0;
+  if (peak) {
+    s = red[0] > 0.0 ? d.norm_value / red[0] : 0.0;
+  } else if (d.norm == PO_NORM_ENERGY) {
+    const double U = red[0] * d.dt;
+    s = U > 0.0 ? sqrt(d.norm_value / U) : 0.0;
   }
+  return s;
 }
 
-// Scaled A (and E) at every step midpoint; block (0, pulse) also writes A(t_i), A(t_f).
+// One block per pulse: the scale.
+__global__ void __launch_bounds__(256) k_scale(const PulseDev* __restrict__ desc, const double* __restrict__ part,
+                                               int stride, double* __restrict__ scale_ws) {
+  __shared__ double red[256];
+  const double s = pulse_scale(desc[blockIdx.x], part + size_t(blockIdx.x) * stride, red);
+  if (threadIdx.x == 0) scale_ws[blockIdx.x] = s;
+}
+
+// The scale in the kernel that applies it: read (FUSED false) or reduced by every workgroup for itself,
+// which saves the launch of k_scale where there are few partials (kFusedStats).
+constexpr int kFusedStats = 512;
+
+template <bool FUSED>
+__device__ __forceinline__ double block_scale(const PulseDev& d, int pulse, const double* __restrict__ part, int stride,
+                                              const double* __restrict__ scale_ws, double* red) {
+  if constexpr (FUSED) return pulse_scale(d, part + size_t(pulse) * stride, red);
+  else return scale_ws[pulse];
+}
+
+// Scaled A (and E) at every step midpoint, the table's range over the workgroup's 256 steps (one chunk of
+// the per-mode kernels; NULL to skip); block (0, pulse) also writes A(t_i), A(t_f) and the scale.
+template <bool FUSED, bool WE>
 __global__ void __launch_bounds__(256) k_tables(const PulseDev* __restrict__ desc, const double* __restrict__ spec,
-                                                const double* __restrict__ scale, double* __restrict__ Aout,
-                                                double* __restrict__ Eout, double* __restrict__ Aedge) {
+                                                const double* __restrict__ part, int stride,
+                                                const double* __restrict__ scale_ws, double* __restrict__ Aout,
+                                                double* __restrict__ Eout, double* __restrict__ Aedge,
+                                                double* __restrict__ scale_out, double* __restrict__ ranges) {
+  static_assert(kChunkSteps == 256, "one workgroup per chunk");
   const PulseDev d = desc[blockIdx.y];
   if (int64_t(blockIdx.x) * 256 >= d.nt) return;  // whole workgroup: beyond this pulse's steps
+  __shared__ double red[256];
   const int64_t n = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  const double4* sp = reinterpret_cast<const double4*>(spec + d.spec_off);
-  const double s = scale[blockIdx.y];
-  __shared__ LineTile L;
-  {
-    double E[2], A[2];
-    field_tiled(d, sp, n < d.nt ? 2 * n + 1 : 1, Eout != nullptr, true, L, E, A);
-    if (n < d.nt) {
-      reinterpret_cast<double2*>(Aout)[d.tab_off + n] = make_double2(s * A[0], s * A[1]);
-      if (Eout) reinterpret_cast<double2*>(Eout)[d.tab_off + n] = make_double2(s * E[0], s * E[1]);
+  const double* rec = spec + d.spec_off;
+  const double s = block_scale<FUSED>(d, blockIdx.y, part, stride, scale_ws, red);
+  double lx = INFINITY, hx = -INFINITY, ly = INFINITY, hy = -INFINITY;
+  if (n < d.nt) {
+    const int64_t hm = 2 * n + 1 - d.nt;
+    const FieldSums o = field_sums<WE, false, true>(d, rec, hm, 0.0);
+    const double2 A = potential(d, rec, o, double(2 * n + 1 - 2 * int64_t(d.nt)) * (0.5 * d.dt));
+    const double ax = s * A.x, ay = s * A.y;
+    lx = hx = ax;
+    ly = hy = ay;
+    reinterpret_cast<double2*>(Aout)[d.tab_off + n] = make_double2(ax, ay);
+    if constexpr (WE) {
+      const double g = cospi(double(hm) * (0.5 / double(d.nt)));  // cos(pi t / T)
+      reinterpret_cast<double2*>(Eout)[d.tab_off + n] = make_double2(s * (g * g * o.ex), s * (g * g * o.ey));
     }
   }
-  if (blockIdx.x == 0 && threadIdx.x < 2) {
-    double E[2], A[2];
-    field_at(d, sp, threadIdx.x == 0 ? 0 : 2 * int64_t(d.nt), false, true, E, A);
-    reinterpret_cast<double2*>(Aedge)[2 * blockIdx.y + threadIdx.x] = make_double2(s * A[0], s * A[1]);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    write_edges(d, rec, s, reinterpret_cast<double2*>(Aedge) + 2 * blockIdx.y);
+    if (scale_out) scale_out[blockIdx.y] = s;
   }
-}
-
-// Unscaled E, dE/dt and A at t = t_i + (n + c) dt for any offset c (0 <= n <= nt).  The phase of
-// line k is pi [k (2n - nt) mod 2nt] / nt + 2 pi k c / nt: the step part is reduced exactly in
-// integers, the offset part (below 2 pi k / nt) is added in floating point.
-__device__ void field_sample(const PulseDev& d, const double4* __restrict__ sp, int64_t n, double c, bool want_E,
-                             bool want_Ed, bool want_A, double E[2], double Ed[2], double A[2]) {
-  const int64_t nt = d.nt, two_nt = 2 * nt, hm = 2 * n - nt;
-  const double inv_nt = 1.0 / double(nt), cfrac = 2.0 * c * inv_nt;
-  auto phase = [&](int64_t k, double* s, double* co) {
-    int64_t r = (k * hm) % two_nt;
-    if (r < 0) r += two_nt;
-    double u = fma(double(k), cfrac, double(r) * inv_nt);
-    if (u >= 2.0) u -= 2.0;
-    sincospi(u, s, co);
-  };
-  double ex = 0.0, ey = 0.0, dx = 0.0, dy = 0.0, ax = 0.0, ay = 0.0;
-  double sd = 0.0, cd = 1.0;
-  if (want_A) phase(1, &sd, &cd);
-  const double tmf = (double(n - nt) + c) * d.dt;  // t - t_f
-  for (int j = 0; j < d.nlines; ++j) {
-    const int64_t k = int64_t(d.nmin) + j;
-    double s, co;
-    phase(k, &s, &co);
-    const double4 q = sp[j];  // (cEx, sEx, cEy, sEy)
-    if (want_E || want_Ed) {
-      ex += q.x * co + q.y * s;
-      ey += q.z * co + q.w * s;
+  if (ranges) {
+    // NaN entries drop out of the range, as in k_chunk_ranges
+    double v[4] = {-lx, hx, -ly, hy};
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) v[k] = fmax(v[k], __shfl_xor(v[k], off, 64));
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0)
+      for (int k = 0; k < 4; ++k) red[(threadIdx.x >> 6) * 4 + k] = v[k];
+    __syncthreads();
+    if (threadIdx.x < 4) {
+      const int k = threadIdx.x;
+      const double m = fmax(fmax(red[k], red[4 + k]), fmax(red[8 + k], red[12 + k]));
+      ranges[4 * int64_t(d.chk_off + int(blockIdx.x)) + k] = (k % 2 == 0) ? -m : m;
     }
-    if (want_Ed) {
-      const double om = double(k) * d.dw;
-      dx += om * (q.y * co - q.x * s);
-      dy += om * (q.w * co - q.z * s);
-    }
-    if (want_A) {
-      // the line terms of field_at, at this phase
-      const double sgn = (k & 1) ? -1.0 : 1.0;
-      const double cp = co * cd - s * sd, spp = s * cd + co * sd;
-      const double cm = cd * co + sd * s, smm = sd * co - cd * s;
-      const double om = double(k) * d.dw, wp = double(k + 1) * d.dw, wm = double(1 - k) * d.dw;
-      double tx, ty;
-      if (k == 0) {
-        tx = 0.5 * tmf * q.x;
-        ty = 0.5 * tmf * q.z;
-      } else {
-        tx = 0.5 * (q.x * s - q.y * co + sgn * q.y) / om;
-        ty = 0.5 * (q.z * s - q.w * co + sgn * q.w) / om;
-      }
-      tx += 0.25 * (q.x * spp - q.y * cp - sgn * q.y) / wp;
-      ty += 0.25 * (q.z * spp - q.w * cp - sgn * q.w) / wp;
-      if (k == 1) {
-        tx += 0.25 * tmf * q.x;
-        ty += 0.25 * tmf * q.z;
-      } else {
-        tx += 0.25 * (q.x * smm + q.y * cm + sgn * q.y) / wm;
-        ty += 0.25 * (q.z * smm + q.w * cm + sgn * q.w) / wm;
-      }
-      ax -= tx;
-      ay -= ty;
-    }
-  }
-  const double arg = (double(hm) + 2.0 * c) * inv_nt;  // 2 t / T
-  const double g = cospi(0.5 * arg);                   // cos(pi t / T)
-  if (want_E) {
-    E[0] = g * g * ex;
-    E[1] = g * g * ey;
-  }
-  if (want_Ed) {
-    const double g2d = -(M_PI / d.T) * sinpi(arg);  // d cos^2(pi t/T) / dt
-    Ed[0] = g2d * ex + g * g * dx;
-    Ed[1] = g2d * ey + g * g * dy;
-  }
-  if (want_A) {
-    A[0] = ax;
-    A[1] = ay;
   }
 }
 
@@ -410,153 +389,132 @@ struct Offsets {
   double c[kMaxSub];
 };
 
-// Scaled samples: row r of pulse i is t_i + (r / n_sub + c_{r % n_sub}) dt; with_end adds t_f.
+// Scaled samples: row r of pulse i is t_i + (r / n_sub + c_{r % n_sub}) dt; with_end adds t_f.  The offset
+// part of a phase (below 2 pi k / nt) is added in floating point.
+template <bool FUSED, bool WE, bool WD, bool WA>
 __global__ void __launch_bounds__(256) k_samples(const PulseDev* __restrict__ desc, const double* __restrict__ spec,
-                                                 const double* __restrict__ scale, int n_sub, Offsets off,
+                                                 const double* __restrict__ part, int stride,
+                                                 const double* __restrict__ scale_ws, int n_sub, Offsets off,
                                                  int with_end, double* __restrict__ Eout, double* __restrict__ Edout,
-                                                 double* __restrict__ Aout, double* __restrict__ Aedge) {
+                                                 double* __restrict__ Aout, double* __restrict__ Aedge,
+                                                 double* __restrict__ scale_out) {
   const PulseDev d = desc[blockIdx.y];
+  __shared__ double red[256];
   const int64_t rows = int64_t(d.nt) * n_sub + (with_end ? 1 : 0);
+  if (int64_t(blockIdx.x) * 256 >= rows) return;  // whole workgroup
   const int64_t k = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  const double4* sp = reinterpret_cast<const double4*>(spec + d.spec_off);
-  const double s = scale[blockIdx.y];
+  const double* rec = spec + d.spec_off;
+  const double s = block_scale<FUSED>(d, blockIdx.y, part, stride, scale_ws, red);
   if (k < rows) {
     const bool end = k == int64_t(d.nt) * n_sub;
     const int64_t n = end ? d.nt : k / n_sub;
     const double c = end ? 0.0 : off.c[k % n_sub];
-    double E[2], Ed[2], A[2];
-    field_sample(d, sp, n, c, Eout != nullptr, Edout != nullptr, Aout != nullptr, E, Ed, A);
+    const int64_t hm = 2 * n - d.nt;
+    const double inv_nt = 1.0 / double(d.nt);
+    const FieldSums o = field_sums<WE, WD, WA>(d, rec, hm, 2.0 * c);
     const int64_t row = d.tab_off + k;
-    if (Eout) reinterpret_cast<double2*>(Eout)[row] = make_double2(s * E[0], s * E[1]);
-    if (Edout) reinterpret_cast<double2*>(Edout)[row] = make_double2(s * Ed[0], s * Ed[1]);
-    if (Aout) reinterpret_cast<double2*>(Aout)[row] = make_double2(s * A[0], s * A[1]);
+    const double arg = (double(hm) + 2.0 * c) * inv_nt;  // 2 t / T
+    const double g = cospi(0.5 * arg);                   // cos(pi t / T)
+    if constexpr (WE) reinterpret_cast<double2*>(Eout)[row] = make_double2(s * (g * g * o.ex), s * (g * g * o.ey));
+    if constexpr (WD) {
+      const double g2d = -(M_PI / d.T) * sinpi(arg);  // d cos^2(pi t/T) / dt
+      reinterpret_cast<double2*>(Edout)[row] = make_double2(s * (g2d * o.ex + g * g * o.dx), s * (g2d * o.ey + g * g * o.dy));
+    }
+    if constexpr (WA) {
+      const double2 A = potential(d, rec, o, (double(n - d.nt) + c) * d.dt);
+      reinterpret_cast<double2*>(Aout)[row] = make_double2(s * A.x, s * A.y);
+    }
   }
-  if (Aedge && blockIdx.x == 0 && threadIdx.x < 2) {
-    double E[2], A[2];
-    field_at(d, sp, threadIdx.x == 0 ? 0 : 2 * int64_t(d.nt), false, true, E, A);
-    reinterpret_cast<double2*>(Aedge)[2 * blockIdx.y + threadIdx.x] = make_double2(s * A[0], s * A[1]);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (Aedge) write_edges(d, rec, s, reinterpret_cast<double2*>(Aedge) + 2 * blockIdx.y);
+    if (scale_out) scale_out[blockIdx.y] = s;
   }
 }
 
 // ------------------------------------------------------------------------------------------
 // Adjoint of the synthesis (gradient of J and of the energy U with respect to the coefficients).
-// A_l(t) and E_l(t) are linear in the line values cE = E_j cos Phi_j, sE = E_j sin Phi_j of every
-// line: A_l(t) = -sum_j [cE_lj alpha_j(t) + sE_lj beta_j(t)] with alpha_j, beta_j the line terms
-// of field_at, E_l(t) = g(t)^2 sum_j [cE_lj cos(Om_j t) + sE_lj sin(Om_j t)].  Per line the kernel
-// forms G = sum_t gA(t) dA(t)/d(cE, sE) over the step midpoints and both ends, and
-// dU/d(cE, sE) = 2 dt sum_n E_l(t_n) g^2 (cos, sin)(Om_j t_n) over the midpoints.
+// A and the windowed E are linear in the harmonic coefficients C_k, S_k:
+//     dJ/dC_k = -sum_n g(t_n) sin(k dw t_n) / (k dw),  dJ/dS_k = sum_n g(t_n) (cos(k dw t_n) - (-1)^k) / (k dw),
+//     dJ/dC_0 = -sum_n g(t_n) (t_n - t_f) + g(t_i) T   (A(t_i) = C_0 T; A(t_f) = 0 depends on nothing),
+//     dU/dC_k = 2 dt sum_n E(t_n) cos(k dw t_n),  dU/dS_k with sin,
+// g = dJ/dA, per component.  The window's adjoint takes them to the lines (half of harmonic k, a quarter of
+// its neighbours), and the lines' E and Phi to the coefficients.
 // ------------------------------------------------------------------------------------------
 
-// Unscaled line terms (alpha, beta) of line k at half-step index hh (as in field_at).
-__device__ __forceinline__ void line_terms(const PulseDev& d, int64_t k, int64_t hh, double& al, double& be,
-                                           double& co, double& si) {
-  const int64_t nt = d.nt, two_nt = 2 * nt, hm = hh - nt;
-  const double inv_nt = 1.0 / double(nt);
-  double s, c, sd, cd;
-  line_phase(k, hm, two_nt, inv_nt, &s, &c);
-  line_phase(1, hm, two_nt, inv_nt, &sd, &cd);
-  co = c;
-  si = s;
-  const double tmf = double(hh - two_nt) * (0.5 * d.dt);
-  const double sgn = (k & 1) ? -1.0 : 1.0;
-  const double cp = c * cd - s * sd, spp = s * cd + c * sd;
-  const double cm = cd * c + sd * s, smm = sd * c - cd * s;
-  const double om = double(k) * d.dw, wp = double(k + 1) * d.dw, wm = double(1 - k) * d.dw;
-  if (k == 0) {
-    al = 0.5 * tmf;
-    be = 0.0;
-  } else {
-    al = 0.5 * s / om;
-    be = 0.5 * (sgn - c) / om;
-  }
-  al += 0.25 * spp / wp;
-  be += 0.25 * (-cp - sgn) / wp;
-  if (k == 1) {
-    al += 0.25 * tmf;
-  } else {
-    al += 0.25 * smm / wm;
-    be += 0.25 * (cm + sgn) / wm;
-  }
-}
-
-// One workgroup per (line, pulse).  The eight line sums G = sum_t gA(t) dA(t)/d(cE, sE) per component
-// and dU/d(cE, sE) (unscaled field) are formed with fixed-order block sums; then thread c < 4 n_s
-// chains them through cE = E cos Phi, sE = E sin Phi and the B-spline expansions of E and
-// Phi = pi (c + 1) for coefficient c, writing out[line][c] (dJ) and out[line][4 n_s + c] (dU),
-// line slots of `stride` = 8 max n_s doubles.
-__global__ void __launch_bounds__(256) k_adjoint_lines(const PulseDev* __restrict__ desc, const double* __restrict__ coeff,
-                                                       const double* __restrict__ gA, const double* __restrict__ gedge,
-                                                       const double* __restrict__ E, const double* __restrict__ scale,
-                                                       int stride, double* __restrict__ out) {
+// One workgroup per (harmonic, pulse): the eight sums, out[harmonic][8] = d/d(Cx, Sx, Cy, Sy) of J, then of
+// U (unscaled field).  A lane takes every 256th midpoint and rotates from one to the next, exact
+// phase every 16th.
+__global__ void __launch_bounds__(256) k_adjoint_harmonics(const PulseDev* __restrict__ desc,
+                                                           const double* __restrict__ gA,
+                                                           const double* __restrict__ gedge,
+                                                           const double* __restrict__ E,
+                                                           const double* __restrict__ scale, double* __restrict__ out) {
   const PulseDev d = desc[blockIdx.y];
-  const int j = blockIdx.x;
-  if (j >= d.nlines) return;
-  const int64_t k = int64_t(d.nmin) + j;
-  const double inv_s = scale[blockIdx.y] != 0.0 ? 1.0 / scale[blockIdx.y] : 0.0;
+  const int i = blockIdx.x;
+  if (i >= d.nlines + 2) return;
+  const int64_t k = int64_t(d.nmin) - 1 + i, two_nt = 2 * int64_t(d.nt);
+  const double inv_nt = 1.0 / double(d.nt), sgn = (k & 1) ? -1.0 : 1.0;
   const double2* g = reinterpret_cast<const double2*>(gA) + d.tab_off;
   const double2* Et = reinterpret_cast<const double2*>(E) + d.tab_off;
-  double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int64_t n = threadIdx.x; n < int64_t(d.nt) + 2; n += blockDim.x) {
-    double2 gv;
-    int64_t hh;
-    const bool mid = n < d.nt;
-    if (mid) {
-      gv = g[n];
-      hh = 2 * n + 1;
+  const int64_t r256 = (k * 512) % two_nt;  // phase index step between a lane's midpoints
+  double sr, cr;
+  sincospi(double(r256 < 0 ? r256 + two_nt : r256) * inv_nt, &sr, &cr);
+  double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0}, s = 0.0, c = 1.0;
+  int it = 0;
+  for (int64_t n = threadIdx.x; n < d.nt; n += 256, ++it) {
+    if ((it & 15) == 0) {
+      int64_t r = (k * (2 * n + 1 - d.nt)) % two_nt;
+      if (r < 0) r += two_nt;
+      sincospi(double(r) * inv_nt, &s, &c);
+    }
+    const double2 gv = g[n], ev = Et[n];
+    const double wc = k == 0 ? double(2 * n + 1 - two_nt) * (0.5 * d.dt) : s, ws = c - sgn;
+    acc[0] = fma(gv.x, wc, acc[0]);
+    acc[1] = fma(gv.x, ws, acc[1]);
+    acc[2] = fma(gv.y, wc, acc[2]);
+    acc[3] = fma(gv.y, ws, acc[3]);
+    acc[4] = fma(ev.x, c, acc[4]);
+    acc[5] = fma(ev.x, s, acc[5]);
+    acc[6] = fma(ev.y, c, acc[6]);
+    acc[7] = fma(ev.y, s, acc[7]);
+    const double cn = fma(c, cr, -(s * sr));
+    s = fma(s, cr, c * sr);
+    c = cn;
+  }
+  __shared__ double red[4][8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) acc[q] += __shfl_xor(acc[q], off, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][q] = acc[q];
+  }
+  __syncthreads();
+  if (threadIdx.x >= 8) return;
+  const int q = threadIdx.x;
+  double v = ((red[0][q] + red[1][q]) + red[2][q]) + red[3][q];
+  if (q < 4) {
+    const bool is_c = (q & 1) == 0;
+    if (k >= 1) {
+      v = (is_c ? -v : v) / (double(k) * d.dw);
+    } else if (k == 0 && is_c) {
+      v = -v;
+      if (gedge) v = fma(gedge[4 * blockIdx.y + q / 2], d.T, v);  // dJ/dA(t_i), components 0 and 1
     } else {
-      gv = gedge ? reinterpret_cast<const double2*>(gedge)[2 * blockIdx.y + (n - d.nt)] : make_double2(0.0, 0.0);
-      hh = (n == d.nt) ? 0 : 2 * int64_t(d.nt);
+      v = 0.0;
     }
-    double al, be, co, si;
-    line_terms(d, k, hh, al, be, co, si);
-    acc[0] -= gv.x * al;
-    acc[1] -= gv.x * be;
-    acc[2] -= gv.y * al;
-    acc[3] -= gv.y * be;
-    if (mid) {
-      const double gg = cospi(double(hh - d.nt) * (0.5 / double(d.nt)));
-      const double w = 2.0 * d.dt * gg * gg * inv_s;
-      const double2 ev = Et[n];
-      acc[4] += w * ev.x * co;
-      acc[5] += w * ev.x * si;
-      acc[6] += w * ev.y * co;
-      acc[7] += w * ev.y * si;
-    }
+  } else {
+    const double sc = scale[blockIdx.y];
+    v = k >= 0 && (k > 0 || (q & 1) == 0) && sc != 0.0 ? v * (2.0 * d.dt / sc) : 0.0;
   }
-  __shared__ double red[256];
-  double L[8];
-  for (int q = 0; q < 8; ++q) L[q] = block_sum(acc[q], red);
-  const int t = threadIdx.x;
-  if (t >= 4 * d.ns) return;
-  const int l = t / (2 * d.ns), kind = (t / d.ns) % 2, i = t % d.ns;
-  const double* a = coeff + d.coeff_off;
-  double b[2 * kMaxNs + 2];
-  const double w = fmin(fmax(double(k) * d.dw, d.wmin), d.wmax);
-  bspline_all(d.order, d.ns, d.wmin, d.wmax, w, b);
-  double Ev = 0.0, ph = 0.0;
-  for (int q = 0; q < d.ns; ++q) {
-    Ev += a[(l * 2 + 0) * d.ns + q] * b[q];
-    ph += M_PI * (a[(l * 2 + 1) * d.ns + q] + 1.0) * b[q];
-  }
-  double sp, cp;
-  sincos(ph, &sp, &cp);
-  const double Gc = L[2 * l], Gs = L[2 * l + 1], Uc = L[4 + 2 * l], Us = L[4 + 2 * l + 1];
-  double dJ, dU;
-  if (kind == 0) {  // amplitude: d(cE, sE)/dE = (cos Phi, sin Phi)
-    dJ = Gc * cp + Gs * sp;
-    dU = Uc * cp + Us * sp;
-  } else {          // phase: d(cE, sE)/dPhi = (-E sin Phi, E cos Phi), dPhi/dc = pi b_i
-    dJ = M_PI * Ev * (Gs * cp - Gc * sp);
-    dU = M_PI * Ev * (Us * cp - Uc * sp);
-  }
-  double* o = out + (d.spec_off / 4 + j) * stride;
-  o[t] = dJ * b[i];
-  o[4 * d.ns + t] = dU * b[i];
+  out[8 * (d.harm_off + i) + q] = v;
 }
 
-// One workgroup per pulse.  Fixed-order sums of g.A over the table and of |E|^2 (the energy),
-// then thread c < 4 n_s sums its line contributions in line order.
-__global__ void __launch_bounds__(256) k_adjoint_coeff(const PulseDev* __restrict__ desc, const double* __restrict__ lines,
+// One workgroup per pulse.  Fixed-order sums of g.A over the table and of |E|^2 (the energy); per line the
+// window's adjoint and the chain through cE = E cos Phi, sE = E sin Phi, values lines[line][q] = d/d(Ex,
+// Phix, Ey, Phiy) of J then U, and the basis values at the line; then thread c < 4 n_s sums its line
+// contributions in line order.
+__global__ void __launch_bounds__(256) k_adjoint_coeff(const PulseDev* __restrict__ desc, const double* __restrict__ coeff,
+                                                       const double* __restrict__ harm, double* __restrict__ lines,
                                                        const double* __restrict__ gA, const double* __restrict__ gedge,
                                                        const double* __restrict__ A, const double* __restrict__ Aedge,
                                                        const double* __restrict__ E, const double* __restrict__ scale,
@@ -567,6 +525,39 @@ __global__ void __launch_bounds__(256) k_adjoint_coeff(const PulseDev* __restric
   const double2* g = reinterpret_cast<const double2*>(gA) + d.tab_off;
   const double2* At = reinterpret_cast<const double2*>(A) + d.tab_off;
   const double2* Et = reinterpret_cast<const double2*>(E) + d.tab_off;
+  const double* a = coeff + d.coeff_off;
+  double* ln = lines + d.line_off * stride;
+  for (int j = threadIdx.x; j < d.nlines; j += 256) {
+    const double* h = harm + 8 * (d.harm_off + j);  // harmonic records of k - 1, k, k + 1, k = nmin + j
+    const bool zero = d.nmin + j == 0;
+    double E2[2], ph[2];
+    line_spectrum(d, a, j, E2, ph);
+    for (int half = 0; half < 2; ++half)
+      for (int l = 0; l < 2; ++l) {
+        const int q = 4 * half + 2 * l;
+        // k = 0: its lower side line k = -1 is cos(dw t), -sin(dw t)
+        const double Gc = 0.5 * h[8 + q] + 0.25 * (h[16 + q] + (zero ? h[16 + q] : h[q]));
+        const double Gs = zero ? 0.0 : 0.5 * h[8 + q + 1] + 0.25 * (h[16 + q + 1] + h[q + 1]);
+        double sp, cp;
+        sincos(ph[l], &sp, &cp);
+        ln[int64_t(j) * stride + q] = Gc * cp + Gs * sp;
+        ln[int64_t(j) * stride + q + 1] = M_PI * E2[l] * (Gs * cp - Gc * sp);
+      }
+    double* b = ln + int64_t(j) * stride + 8;
+    const double w = fmin(fmax(double(d.nmin + j) * d.dw, d.wmin), d.wmax);
+    if (d.order <= 4) {
+      double N[4];
+      const int i0 = bspline_local(d.order, d.ns, d.wmin, d.wmax, w, N);
+      for (int i = 0; i < d.ns; ++i) b[i] = 0.0;
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (r < d.order) b[i0 + r] = N[r];
+    } else {
+      double full[2 * kMaxNs + 2];
+      bspline_all(d.order, d.ns, d.wmin, d.wmax, w, full);
+      for (int i = 0; i < d.ns; ++i) b[i] = full[i];
+    }
+  }
   double ga = 0.0, uu = 0.0;
   for (int64_t n = threadIdx.x; n < d.nt; n += blockDim.x) {
     const double2 gv = g[n], av = At[n], ev = Et[n];
@@ -586,11 +577,14 @@ __global__ void __launch_bounds__(256) k_adjoint_coeff(const PulseDev* __restric
   if (threadIdx.x == 0 && Uout) Uout[blockIdx.x] = U;
   const int t = threadIdx.x;
   if (t >= 4 * d.ns) return;
-  const double* ln = lines + (d.spec_off / 4) * stride;
+  const int q = t / d.ns, i = t % d.ns;  // q = 2 component + kind: the column of lines
   double gj = 0.0, gu = 0.0;
+#pragma unroll 8
   for (int j = 0; j < d.nlines; ++j) {
-    gj += ln[int64_t(j) * stride + t];
-    gu += ln[int64_t(j) * stride + 4 * d.ns + t];
+    const double* l = ln + int64_t(j) * stride;
+    const double b = l[8 + i];
+    gj = fma(l[q], b, gj);
+    gu = fma(l[4 + q], b, gu);
   }
   // A = s A_raw: NORM_NONE has s = 1; NORM_ENERGY has s = sqrt(U0 / U_raw), so
   // dJ/dc = s dJ_raw/dc - (g.A) / (2 U_raw) dU_raw/dc and the energy stays U0.
@@ -600,11 +594,9 @@ __global__ void __launch_bounds__(256) k_adjoint_coeff(const PulseDev* __restric
   if (gU) gU[d.coeff_off + t] = energy ? 0.0 : gu;
 }
 
-}  // namespace
-
-po_status launch_synth(const Batch& b, const PulseDev* d_desc, const double* d_coeff, double* d_spec,
-                       double* d_part, double* d_scale_ws, double* d_A, double* d_E, double* d_A_edge,
-                       double* d_scale_out, hipStream_t s) {
+// Spectra and, where the batch has a normalisation, its partials; the scale kernel unless it is fused.
+po_status launch_spectra(const Batch& b, const PulseDev* d_desc, const double* d_coeff, double* d_spec, double* d_part,
+                         double* d_scale_ws, bool* fused, hipStream_t s) {
   const int P = b.n_pulses;
   hipLaunchKernelGGL(k_spectra, dim3(P), dim3(128), 0, s, d_desc, d_coeff, d_spec);
   PO_HIP(hipGetLastError());
@@ -613,24 +605,63 @@ po_status launch_synth(const Batch& b, const PulseDev* d_desc, const double* d_c
                        b.max_stat_blocks, d_part);
     PO_HIP(hipGetLastError());
   }
-  hipLaunchKernelGGL(k_scale, dim3(P), dim3(256), 0, s, d_desc, d_part, b.max_stat_blocks, d_scale_ws,
-                     d_scale_out);
-  PO_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_tables, dim3((b.max_nt + 255) / 256, P), dim3(256), 0, s, d_desc, d_spec, d_scale_ws,
-                     d_A, d_E, d_A_edge);
+  *fused = b.max_stat_blocks <= kFusedStats;
+  if (!*fused) {
+    hipLaunchKernelGGL(k_scale, dim3(P), dim3(256), 0, s, d_desc, d_part, b.max_stat_blocks, d_scale_ws);
+    PO_HIP(hipGetLastError());
+  }
+  return PO_OK;
+}
+
+template <bool FUSED, bool WE, bool WD, bool WA>
+void launch_samples_t(const Batch& b, const PulseDev* d_desc, const double* d_spec, const double* d_part,
+                      const double* d_scale_ws, int n_sub, const Offsets& off, int with_end, double* d_E, double* d_Ed,
+                      double* d_A, double* d_A_edge, double* d_scale_out, hipStream_t s) {
+  const int64_t rows = int64_t(b.max_nt) * n_sub + (with_end ? 1 : 0);
+  hipLaunchKernelGGL((k_samples<FUSED, WE, WD, WA>), dim3(unsigned((rows + 255) / 256), b.n_pulses), dim3(256), 0, s,
+                     d_desc, d_spec, d_part, b.max_stat_blocks, d_scale_ws, n_sub, off, with_end, d_E, d_Ed, d_A,
+                     d_A_edge, d_scale_out);
+}
+
+template <bool FUSED, bool... W, class... Args>
+void pick_samples(const bool* want, const Args&... args) {
+  if constexpr (sizeof...(W) == 3) {
+    launch_samples_t<FUSED, W...>(args...);
+  } else {
+    if (want[sizeof...(W)]) pick_samples<FUSED, W..., true>(want, args...);
+    else pick_samples<FUSED, W..., false>(want, args...);
+  }
+}
+
+}  // namespace
+
+po_status launch_synth(const Batch& b, const PulseDev* d_desc, const double* d_coeff, double* d_spec,
+                       double* d_part, double* d_scale_ws, double* d_A, double* d_E, double* d_A_edge,
+                       double* d_scale_out, double* d_ranges, hipStream_t s) {
+  bool fused = false;
+  PO_TRY(launch_spectra(b, d_desc, d_coeff, d_spec, d_part, d_scale_ws, &fused, s));
+  const dim3 grid((b.max_nt + 255) / 256, b.n_pulses);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, d_desc, d_spec, d_part, b.max_stat_blocks, d_scale_ws, d_A, d_E,
+                       d_A_edge, d_scale_out, d_ranges);
+  };
+  if (fused && d_E) launch(k_tables<true, true>);
+  else if (fused) launch(k_tables<true, false>);
+  else if (d_E) launch(k_tables<false, true>);
+  else launch(k_tables<false, false>);
   PO_HIP(hipGetLastError());
   return PO_OK;
 }
 
 po_status launch_synth_adjoint(const Batch& b, const PulseDev* d_desc, const double* d_coeff, const double* d_gA,
                                const double* d_gedge, const double* d_A, const double* d_A_edge, const double* d_E,
-                               const double* d_scale, double* d_lines, double* d_grad, double* d_U, double* d_gU,
-                               hipStream_t s) {
-  hipLaunchKernelGGL(k_adjoint_lines, dim3(b.max_lines, b.n_pulses), dim3(256), 0, s, d_desc, d_coeff, d_gA, d_gedge,
-                     d_E, d_scale, 8 * b.max_ns, d_lines);
+                               const double* d_scale, double* d_harm, double* d_lines, double* d_grad, double* d_U,
+                               double* d_gU, hipStream_t s) {
+  hipLaunchKernelGGL(k_adjoint_harmonics, dim3(b.max_lines + 2, b.n_pulses), dim3(256), 0, s, d_desc, d_gA, d_gedge,
+                     d_E, d_scale, d_harm);
   PO_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_adjoint_coeff, dim3(b.n_pulses), dim3(256), 0, s, d_desc, d_lines, d_gA, d_gedge, d_A, d_A_edge,
-                     d_E, d_scale, 8 * b.max_ns, d_grad, d_U, d_gU);
+  hipLaunchKernelGGL(k_adjoint_coeff, dim3(b.n_pulses), dim3(256), 0, s, d_desc, d_coeff, d_harm, d_lines, d_gA,
+                     d_gedge, d_A, d_A_edge, d_E, d_scale, 8 + b.max_ns, d_grad, d_U, d_gU);
   PO_HIP(hipGetLastError());
   return PO_OK;
 }
@@ -638,22 +669,13 @@ po_status launch_synth_adjoint(const Batch& b, const PulseDev* d_desc, const dou
 po_status launch_samples(const Batch& b, const PulseDev* d_desc, const double* d_coeff, double* d_spec, double* d_part,
                          double* d_scale_ws, int n_sub, const double* offsets, int with_end, double* d_E,
                          double* d_Ed, double* d_A, double* d_A_edge, double* d_scale_out, hipStream_t s) {
-  const int P = b.n_pulses;
   Offsets off{};
   for (int r = 0; r < n_sub; ++r) off.c[r] = offsets[r];
-  hipLaunchKernelGGL(k_spectra, dim3(P), dim3(128), 0, s, d_desc, d_coeff, d_spec);
-  PO_HIP(hipGetLastError());
-  if (b.max_stat_blocks > 0) {
-    hipLaunchKernelGGL(k_field_stats, dim3(b.max_stat_blocks, P), dim3(256), 0, s, d_desc, d_spec,
-                       b.max_stat_blocks, d_part);
-    PO_HIP(hipGetLastError());
-  }
-  hipLaunchKernelGGL(k_scale, dim3(P), dim3(256), 0, s, d_desc, d_part, b.max_stat_blocks, d_scale_ws,
-                     d_scale_out);
-  PO_HIP(hipGetLastError());
-  const int64_t rows = int64_t(b.max_nt) * n_sub + (with_end ? 1 : 0);
-  hipLaunchKernelGGL(k_samples, dim3(unsigned((rows + 255) / 256), P), dim3(256), 0, s, d_desc, d_spec, d_scale_ws,
-                     n_sub, off, with_end, d_E, d_Ed, d_A, d_A_edge);
+  bool fused = false;
+  PO_TRY(launch_spectra(b, d_desc, d_coeff, d_spec, d_part, d_scale_ws, &fused, s));
+  const bool want[3] = {d_E != nullptr, d_Ed != nullptr, d_A != nullptr};
+  if (fused) pick_samples<true>(want, b, d_desc, d_spec, d_part, d_scale_ws, n_sub, off, with_end, d_E, d_Ed, d_A, d_A_edge, d_scale_out, s);
+  else pick_samples<false>(want, b, d_desc, d_spec, d_part, d_scale_ws, n_sub, off, with_end, d_E, d_Ed, d_A, d_A_edge, d_scale_out, s);
   PO_HIP(hipGetLastError());
   return PO_OK;
 }
