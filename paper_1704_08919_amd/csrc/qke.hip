@@ -20,9 +20,14 @@
 //
 // Tables: E, dE/dt and A at the 2 nt + 1 half-step points t_i + h dt/2 of each pulse.  A
 // workgroup of 256 lanes owns 256 consecutive modes (one per lane); per chunk of 128 steps each
-// lane stages one point -- (A_x, A_y), (E_x, E_y), (|E|^2, (E x dE/dt)_z) -- into LDS
+// lane stages one point -- (A_x, A_y), (E_x, E_y), (|E|^2, (E x dE/dt)_z dt/2) -- into LDS
 // (double-buffered) and every lane reads the same record (broadcast).  The coefficients at
 // t_n + dt are carried to the next step, so each step evaluates them at two new points.
+//
+// Bound by FP64 issue: about 150 FP64 instructions and four reciprocal square roots per step, 4 cycles
+// each even with one wave per SIMD: 65536 modes x 12000 steps take 4.25 ms (5.8 ms with the math
+// library's rsqrt, which classifies its argument and scales the result; 4.5 ms with two steps per
+// loop iteration, and with the root of X taken whether or not X > 0).
 #include "reduce.hpp"
 
 #pragma clang fp contract(off)
@@ -48,16 +53,26 @@ struct Coef {
 };
 
 struct Point {
-  double2 a, e, s;  // (A_x, A_y), (E_x, E_y), (|E|^2, (E x dE/dt)_z)
+  double2 a, e, s;  // (A_x, A_y), (E_x, E_y), (|E|^2, (E x dE/dt)_z dt/2)
 };
 
+// 1/sqrt(x) for normal x > 0: the hardware estimate (23 bits or more) and one step of third order,
+// 1/sqrt(x) = y (1 + e/2 + 3 e^2/8 + ...), e = 1 - x y^2, whose remainder is below 2^-67.  (The math
+// library's function also sorts out special arguments, which the callers here do themselves.)
+__device__ __forceinline__ double rsqrt_pos(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-(x * y), y, 1.0);
+  return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
+// s.y of the point comes multiplied by dt/2.
 template <bool LINEAR>
 __device__ __forceinline__ Coef coef_at(const Point& pt, double px, double py, double e2, double ep, double dt,
                                         double hdt) {
   const double Px = px - pt.a.x, Py = py - pt.a.y;
   const double t2 = fma(Py, Py, e2);  // 1 + P_y^2 + p_z^2
   const double w2 = fma(Px, Px, t2);
-  const double rw = rsqrt(w2);
+  const double rw = rsqrt_pos(w2);
   const double w = w2 * rw;
   Coef c;
   c.W = w * dt;
@@ -67,14 +82,9 @@ __device__ __forceinline__ Coef coef_at(const Point& pt, double px, double py, d
   } else {
     const double EP = fma(pt.e.x, Px, pt.e.y * Py);
     const double X = fma(w2, pt.s.x, -(EP * EP));
-    if (X > 0.0) {
-      const double rX = rsqrt(X);
-      c.q = (X * rX) * (rw * rw) * hdt;
-      c.r = ((ep * w) * pt.s.y) * (rX * rX) * hdt;
-    } else {
-      c.q = 0.0;
-      c.r = 0.0;
-    }
+    const double rX = X > 0.0 ? rsqrt_pos(X) : 0.0;  // Q = R = 0 where X = 0
+    c.q = (X * rX) * ((rw * rw) * hdt);
+    c.r = ((ep * w) * pt.s.y) * (rX * rX);
   }
   return c;
 }
@@ -121,9 +131,9 @@ __device__ __forceinline__ void rk4_step(Y6& y, const Coef& k0, const Coef& k1, 
 }
 
 __device__ __forceinline__ Point load_point(const double2* __restrict__ E, const double2* __restrict__ Ed,
-                                            const double2* __restrict__ A, int64_t h) {
+                                            const double2* __restrict__ A, int64_t h, double hdt) {
   const double2 a = A[h], e = E[h], ed = Ed[h];
-  return Point{a, e, make_double2(fma(e.x, e.x, e.y * e.y), fma(e.x, ed.y, -(e.y * ed.x)))};
+  return Point{a, e, make_double2(fma(e.x, e.x, e.y * e.y), fma(e.x, ed.y, -(e.y * ed.x)) * hdt)};
 }
 
 template <bool LINEAR>
@@ -148,14 +158,14 @@ __global__ void __launch_bounds__(kQPoints) k_qke(QkeArgs a) {
   const int nchunks = (nt + kQChunk - 1) / kQChunk;
   {
     const int64_t h = 1 + threadIdx.x;
-    lds[0][threadIdx.x] = h < npts ? load_point(E, Ed, A, h) : Point{};
+    lds[0][threadIdx.x] = h < npts ? load_point(E, Ed, A, h, hdt) : Point{};
   }
-  Coef k0 = coef_at<LINEAR>(load_point(E, Ed, A, 0), px, py, e2, ep, dt, hdt);
+  Coef k0 = coef_at<LINEAR>(load_point(E, Ed, A, 0, hdt), px, py, e2, ep, dt, hdt);
   __syncthreads();
   Y6 y{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   for (int c = 0; c < nchunks; ++c) {
     const int64_t h = int64_t(c + 1) * kQPoints + 1 + threadIdx.x;
-    const Point pre = (c + 1 < nchunks && h < npts) ? load_point(E, Ed, A, h) : Point{};
+    const Point pre = (c + 1 < nchunks && h < npts) ? load_point(E, Ed, A, h, hdt) : Point{};
     const Point* buf = lds[c & 1];
     const int len = min(kQChunk, nt - c * kQChunk);
     for (int k = 0; k < len; ++k) {
