@@ -126,24 +126,27 @@ __global__ void __launch_bounds__(128) k_de_select(po_de_params prm, double* __r
 // Indices of the set entries of a 0/1 mask, in increasing order (single workgroup, n <= 8192).
 __global__ void __launch_bounds__(1024) k_mask_indices(const uint8_t* __restrict__ mask, int n, int32_t* __restrict__ idx,
                                                        int32_t* __restrict__ count) {
-  __shared__ int32_t part[1024];
-  const int per = (n + 1023) / 1024;
+  __shared__ int32_t part[16];  // counts of the waves
+  const int per = (n + 1023) / 1024, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lo = threadIdx.x * per, hi = min(n, lo + per);
   int c = 0;
   for (int i = lo; i < hi; ++i) c += mask[i] != 0;
-  part[threadIdx.x] = c;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int run = 0;
-    for (int t = 0; t < 1024; ++t) {
-      const int v = part[t];
-      part[t] = run;
-      run += v;
-    }
-    if (count) *count = run;
+  int o = c;  // inclusive scan within the wave
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int v = __shfl_up(o, d, 64);
+    o += lane >= d ? v : 0;
   }
+  if (lane == 63) part[wave] = o;
   __syncthreads();
-  int o = part[threadIdx.x];
+  int before = 0, total = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    before += w < wave ? part[w] : 0;
+    total += part[w];
+  }
+  if (threadIdx.x == 0 && count) *count = total;
+  o += before - c;
   for (int i = lo; i < hi; ++i)
     if (mask[i]) idx[o++] = i;
 }

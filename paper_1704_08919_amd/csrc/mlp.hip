@@ -67,7 +67,7 @@ struct po_mlp {
   __bf16* hT = nullptr;        // transposed h_0 (the input)..h_{depth-1} [depth][hstride][max_batch]
   float* gp = nullptr;         // gelu'(z_l) [depth][max_batch][width] fp32
   __bf16* dz = nullptr;        // pre-activation gradients [2][max_batch][width] bf16 (ping-pong)
-  __bf16* dzT = nullptr;       // transposed [2][width][max_batch] bf16 (ping-pong)
+  __bf16* dzT = nullptr;       // transposed, of every hidden layer [depth][width][max_batch] bf16
   float* y = nullptr;          // outputs [max_batch]
   float* wpart = nullptr;      // weight-gradient partials, per layer [kMaxSplit][k_in][width]
   float* bpart = nullptr;      // bias-gradient partials, per layer [max_batch / 32][width]
@@ -407,6 +407,291 @@ __global__ void __launch_bounds__(256) k_out_fwd(const __bf16* __restrict__ h, c
   if (lane == 0) y[s] = acc + b0[0];
 }
 
+// ---------------------------------------------------------------------------------------------
+// Whole network for 32 samples per workgroup (widths up to kFusedWidth).  A sample's forward pass, output,
+// dL/dy and backward chain of pre-activation gradients only need that sample's row, so one workgroup of
+// eight waves takes 32 rows through all layers with the activations (then the gradients) in LDS; each
+// wave owns column tiles of 32 and reads its weights from L2.  What the weight gradients need --
+// transposed inputs and pre-activation gradients of every layer -- and the column sums go to global memory.
+// Products, roundings and sums are those of the layer-by-layer kernels below (mm_body, k_out_train), in
+// their order.
+// ---------------------------------------------------------------------------------------------
+constexpr int kFusedWidth = 512;   // two column tiles per wave
+constexpr int kNetWaves = 8;
+constexpr int kNetThreads = 64 * kNetWaves;
+
+struct NetArgs {
+  const double* x;    // input rows [.][n_in]
+  RowMap rows;
+  int n_in, W, D, B, max_batch, hs;  // hs: row count of a slot of hT
+  const float* p;     // master parameters (biases)
+  const __bf16* wb;   // W_l[k][n]
+  const __bf16* wt;   // W_l^T[n][k]
+  float* y;
+  // training
+  const float* target;
+  const double* J;
+  double mean, inv_std;
+  __bf16* hT;         // [D][hs][max_batch]: the input, then h_1..h_{D-1}
+  float* gp;          // [D][max_batch][W]: gelu' (the last layer's stays in LDS)
+  __bf16* dzT;        // [D][W][max_batch]
+  float* bpart;       // [D][max_batch / 32][W]
+  float* opart;       // [B / 32][W + 2]
+  Counters* ctr;      // with `step`: the optimiser's step is counted here
+  int step;
+};
+
+__device__ __forceinline__ int net_lda(int W, int n_in) { return max(W, n_in) + 8; }
+
+// acc = A B^T for the wave's column tiles: A [32][K] bf16 in LDS (row stride lda), Bt[n][k] global.
+template <int TPW>
+__device__ __forceinline__ void net_mm(floatx4 (&acc)[TPW][2][2], const __bf16* A, int lda, const __bf16* Bt, int K, int N,
+                                       int wave, int lane) {
+  const int r16 = lane & 15, kq = (lane >> 4) * 8;
+#pragma unroll
+  for (int t = 0; t < TPW; ++t)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[t][i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int t = 0; t < TPW; ++t) {
+    const int tn = wave + t * kNetWaves;
+    if (tn * kTile >= N) break;
+    const __bf16* b0 = Bt + size_t(tn * kTile + r16) * K + kq;
+    const __bf16* b1 = b0 + size_t(16) * K;
+    // eight k-steps' weights in flight at a time
+    for (int kb = 0; kb < K; kb += 8 * 32) {
+      bf16x8 bf[8][2];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (kb + 32 * u < K) {
+          bf[u][0] = load8(b0 + kb + 32 * u);
+          bf[u][1] = load8(b1 + kb + 32 * u);
+        }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (kb + 32 * u < K) {
+          const __bf16* a0 = A + r16 * lda + kb + 32 * u + kq;
+          const bf16x8 af[2] = {load8(a0), load8(a0 + 16 * lda)};
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+              acc[t][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bf[u][j], acc[t][i][j], 0, 0, 0);
+        }
+    }
+  }
+}
+
+template <int TPW, bool TRAIN>
+__global__ void __launch_bounds__(kNetThreads) k_net(NetArgs a) {
+  extern __shared__ __align__(16) unsigned char net_lds[];
+  const int lda = net_lda(a.W, a.n_in);
+  __bf16* act = reinterpret_cast<__bf16*>(net_lds);                            // [32][lda]
+  float* gl = reinterpret_cast<float*>(net_lds + size_t(32) * lda * sizeof(__bf16));  // [32][W + 1]: last layer's gelu'
+  __shared__ float s_dy[32], s_sq[32];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int b0 = blockIdx.x * 32, r16 = lane & 15, rq = (lane >> 4) * 4;
+  if (TRAIN && a.step && blockIdx.x == 0 && threadIdx.x == 0) {
+    const long long t = a.ctr->t + 1;
+    a.ctr->t = t;
+    a.ctr->bc1 = float(1.0 - pow(0.9, double(t)));
+    a.ctr->bc2 = float(1.0 - pow(0.999, double(t)));
+  }
+  for (int e = threadIdx.x; e < 32 * (a.n_in / 8); e += kNetThreads) {
+    const int row = e / (a.n_in / 8), c8 = (e - row * (a.n_in / 8)) * 8;
+    *reinterpret_cast<bf16x8*>(act + row * lda + c8) = load8(a.x + size_t(a.rows.row(b0 + row)) * a.n_in + c8);
+  }
+  __syncthreads();
+  if constexpr (TRAIN) {
+    for (int e = threadIdx.x; e < 8 * a.n_in; e += kNetThreads) {  // the input's transpose, four rows at a time
+      const int k = e >> 3, m = (e & 7) * 4;
+      bf16x4 t4;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) t4[q] = act[(m + q) * lda + k];
+      *reinterpret_cast<bf16x4*>(a.hT + size_t(k) * a.max_batch + b0 + m) = t4;
+    }
+  }
+  floatx4 acc[TPW][2][2];
+  int64_t off = 0;
+  int K = a.n_in;
+  for (int l = 0; l < a.D; ++l) {
+    net_mm<TPW>(acc, act, lda, a.wt + off, K, a.W, wave, lane);
+    const float* bias = a.p + off + int64_t(K) * a.W;
+    __syncthreads();  // every wave is done with the layer's input
+#pragma unroll
+    for (int t = 0; t < TPW; ++t) {
+      const int tn = wave + t * kNetWaves;
+      if (tn * kTile >= a.W) break;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int n = tn * kTile + j * 16 + r16;
+        const float bn = bias[n];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          bf16x4 t4;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int m = i * 16 + rq + r;
+            const float z = acc[t][i][j][r] + bn;
+            const __bf16 hb = __bf16(gelu(z));
+            act[m * lda + n] = hb;
+            t4[r] = hb;
+            if constexpr (TRAIN) {
+              const float g = gelu_grad(z);
+              if (l + 1 < a.D) a.gp[(size_t(l) * a.max_batch + b0 + m) * a.W + n] = g;
+              else gl[m * (a.W + 1) + n] = g;
+            }
+          }
+          if constexpr (TRAIN) {
+            if (l + 1 < a.D)
+              *reinterpret_cast<bf16x4*>(a.hT + (size_t(l + 1) * a.hs + n) * a.max_batch + b0 + i * 16 + rq) = t4;
+          }
+        }
+      }
+    }
+    __syncthreads();
+    off += int64_t(K) * a.W + a.W;
+    K = a.W;
+  }
+  const __bf16* wo = a.wb + off;      // output weights, then the bias
+  const float bo = a.p[off + a.W];
+  if constexpr (!TRAIN) {
+    // as k_out_fwd: one sample per wave at a time
+    for (int m = wave; m < 32; m += kNetWaves) {
+      float v = 0.0f;
+      for (int j = lane; j < a.W; j += 64) v = fmaf(float(act[m * lda + j]), float(wo[j]), v);
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+      if (lane == 0) a.y[b0 + m] = v + bo;
+    }
+    return;
+  } else {
+    if (wave < 4) {  // as k_out_train: a wave does 8 samples at once with 8 lanes each
+      const int g = lane >> 3, part = lane & 7;
+      const int m = wave * 8 + g, b = b0 + m;
+      float p[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) p[e] = 0.0f;
+      for (int j0 = 8 * part; j0 < a.W; j0 += 64) {
+        const bf16x8 hv = load8(act + m * lda + j0);
+        const bf16x8 wv8 = load8(wo + j0);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) p[e] = fmaf(float(hv[e]), float(wv8[e]), p[e]);
+      }
+#pragma unroll
+      for (int o = 4; o > 0; o >>= 1)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) p[e] += __shfl_xor(p[e], o, 64);
+#pragma unroll
+      for (int o = 4; o > 0; o >>= 1) {
+        float q[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) q[e] = p[e] + p[e ^ o];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) p[e] = q[e];
+      }
+      if (part == 0) {
+        const float yb = p[0] + bo;
+        a.y[b] = yb;
+        float t;
+        if (a.J) {
+          const double Jv = a.J[a.rows.row(b)];
+          t = float((log10(fmax(Jv, 1e-300)) - a.mean) * a.inv_std);
+        } else {
+          t = a.target[b];
+        }
+        const float d = yb - t;
+        s_dy[m] = 2.0f * d / float(a.B);
+        s_sq[m] = d * d;
+      }
+    }
+    __syncthreads();
+    // the last hidden layer's gradient, one column per thread, rows in order
+    __bf16* dzT = a.dzT + size_t(a.D - 1) * a.W * a.max_batch;
+    for (int j = threadIdx.x; j < a.W; j += kNetThreads) {
+      const float wj = float(wo[j]);
+      float sb = 0.0f, sw = 0.0f;
+#pragma unroll
+      for (int r = 0; r < 32; r += 4) {
+        bf16x4 t4;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float hv = float(act[(r + e) * lda + j]);
+          const float d = s_dy[r + e] * wj * gl[(r + e) * (a.W + 1) + j];
+          const __bf16 db = __bf16(d);
+          act[(r + e) * lda + j] = db;
+          t4[e] = db;
+          sb += d;
+          sw = fmaf(hv, s_dy[r + e], sw);
+        }
+        *reinterpret_cast<bf16x4*>(dzT + size_t(j) * a.max_batch + b0 + r) = t4;
+      }
+      a.bpart[(size_t(a.D - 1) * (a.max_batch / 32) + blockIdx.x) * a.W + j] = sb;
+      a.opart[size_t(blockIdx.x) * (a.W + 2) + j] = sw;
+    }
+    if (threadIdx.x == 0) {
+      float sd = 0.0f, sq = 0.0f;
+      for (int r = 0; r < 32; ++r) {
+        sd += s_dy[r];
+        sq += s_sq[r];
+      }
+      a.opart[size_t(blockIdx.x) * (a.W + 2) + a.W] = sd;
+      a.opart[size_t(blockIdx.x) * (a.W + 2) + a.W + 1] = sq;
+    }
+    __syncthreads();
+    // backward through the hidden layers: dz_{l-1} = (dz_l W_l^T) gelu'(z_{l-1})
+    for (int l = a.D - 1; l > 0; --l) {
+      const int Kl = l == 0 ? a.n_in : a.W;
+      off -= int64_t(Kl) * a.W + a.W;  // W_l
+      float gv[TPW][2][2][4];
+#pragma unroll
+      for (int t = 0; t < TPW; ++t) {
+        const int tn = wave + t * kNetWaves;
+        if (tn * kTile >= a.W) break;
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              gv[t][j][i][r] = a.gp[(size_t(l - 1) * a.max_batch + b0 + i * 16 + rq + r) * a.W + tn * kTile + j * 16 + r16];
+      }
+      net_mm<TPW>(acc, act, lda, a.wb + off, a.W, a.W, wave, lane);
+      __syncthreads();
+#pragma unroll
+      for (int t = 0; t < TPW; ++t) {
+        const int tn = wave + t * kNetWaves;
+        if (tn * kTile >= a.W) break;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const int n = tn * kTile + j * 16 + r16;
+          float colsum = 0.0f;
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            bf16x4 t4;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const int m = i * 16 + rq + r;
+              const float d = acc[t][i][j][r] * gv[t][j][i][r];
+              const __bf16 db = __bf16(d);
+              act[m * lda + n] = db;
+              t4[r] = db;
+              colsum += d;
+            }
+            *reinterpret_cast<bf16x4*>(a.dzT + (size_t(l - 1) * a.W + n) * a.max_batch + b0 + i * 16 + rq) = t4;
+          }
+          colsum += __shfl_xor(colsum, 16, 64);
+          colsum += __shfl_xor(colsum, 32, 64);
+          if (lane < 16) a.bpart[(size_t(l - 1) * (a.max_batch / 32) + blockIdx.x) * a.W + n] = colsum;
+        }
+      }
+      __syncthreads();
+    }
+  }
+}
+
 // Where parameter i lives: hidden layer l weight (k, n) or bias n, or the output layer.
 struct ParamMap {
   int n_in, width, depth, splits, nblk, batch;
@@ -481,6 +766,130 @@ __global__ void k_adam_begin(Counters* c) {
   c->cursor += 1;
 }
 
+// Adam's new value of a parameter with gradient g (updates its moments).
+__device__ __forceinline__ float adam_value(float g, float p, float& m, float& v, float lr, float bc1, float bc2) {
+  m = 0.9f * m + 0.1f * g;
+  v = 0.999f * v + 0.001f * g * g;
+  return p - lr * (m / bc1) / (sqrtf(v / bc2) + 1e-8f);
+}
+
+// Weight gradients of every hidden layer and, with lr >= 0, the optimiser step, in one launch after k_net:
+// workgroups [0, n_tiles) take one 32x32 tile of one layer's dW_l = h_l^T dz_l each, wave s the s-th
+// part of the batch; the parts are added in order (as assembled_grad adds them) and the tile's
+// parameters, moments and both bf16 copies updated where they are.  The other workgroups do the biases and
+// the output layer from their partial sums, one parameter per thread, and the loss.
+struct StepArgs {
+  ParamMap q;
+  const __bf16* hT;   // [D][hs][max_batch]
+  const __bf16* dzT;  // [D][W][max_batch]
+  int hs, max_batch, n_tiles;
+  float *p, *m, *v, *g;
+  __bf16 *wb, *wt;
+  float lr;
+  Counters* ctr;
+  float* loss;
+  int loss_by_cursor;
+};
+
+__global__ void __launch_bounds__(256) k_step(StepArgs a) {
+  const ParamMap& q = a.q;
+  const float bc1 = a.ctr->bc1, bc2 = a.ctr->bc2;
+  if (int(blockIdx.x) >= a.n_tiles) {
+    int64_t i = int64_t(blockIdx.x - a.n_tiles) * 256 + threadIdx.x;  // biases layer by layer, then the output layer
+    if (i == 0) {
+      if (a.loss) {
+        float s = 0.0f;
+#pragma unroll 8
+        for (int t = 0; t < q.nblk; ++t) s += q.opart[int64_t(t) * (q.width + 2) + q.width + 1];
+        a.loss[a.loss_by_cursor ? a.ctr->cursor : 0] = s / float(q.batch);
+      }
+      if (a.lr >= 0.0f) a.ctr->cursor += 1;
+    }
+    if (i >= int64_t(q.depth) * q.width + q.width + 1) return;
+    const int l = min(int(i / q.width), q.depth);
+    int64_t o = i;  // position in the parameter vector: plus the weights of the layers up to this one
+    for (int k = 0; k <= l && k < q.depth; ++k) o += int64_t(k == 0 ? q.n_in : q.width) * q.width;
+    const float g = assembled_grad(q, o);
+    a.g[o] = g;
+    if (a.lr < 0.0f) return;
+    const float pi = adam_value(g, a.p[o], a.m[o], a.v[o], a.lr, bc1, bc2);
+    a.p[o] = pi;
+    a.wb[o] = a.wt[o] = __bf16(pi);
+    return;
+  }
+  const int tn_n = q.width / kTile, first = (q.n_in / kTile) * tn_n, per = tn_n * tn_n;
+  int tile = blockIdx.x, l = 0, K = q.n_in;
+  int64_t off = 0;
+  if (tile >= first) {
+    l = 1 + (tile - first) / per;
+    tile = (tile - first) % per;
+    K = q.width;
+    off = int64_t(q.n_in) * q.width + q.width + int64_t(l - 1) * (int64_t(q.width) * q.width + q.width);
+  }
+  const int tm = tile / tn_n, tn = tile - tm * tn_n;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __shared__ float part[kMaxSplit][kTile][kTile + 1];
+  __shared__ __bf16 tr[kTile][kTile + 2];
+  if (wave < q.splits) {
+    const int r16 = lane & 15, kq = (lane >> 4) * 8, kc = q.batch / q.splits;
+    const __bf16* A0 = a.hT + (size_t(l) * a.hs + tm * kTile + r16) * a.max_batch + wave * kc + kq;
+    const __bf16* B0 = a.dzT + (size_t(l) * q.width + tn * kTile + r16) * a.max_batch + wave * kc + kq;
+    floatx4 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int kb = 0; kb < kc; kb += 8 * 32) {
+      bf16x8 af[8][2], bf[8][2];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (kb + 32 * u < kc) {
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            af[u][i] = load8(A0 + size_t(i * 16) * a.max_batch + kb + 32 * u);
+            bf[u][i] = load8(B0 + size_t(i * 16) * a.max_batch + kb + 32 * u);
+          }
+        }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (kb + 32 * u < kc) {
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[u][i], bf[u][j], acc[i][j], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[wave][i * 16 + (lane >> 4) * 4 + r][j * 16 + r16] = acc[i][j][r];
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < kTile * kTile; e += 256) {
+    const int k = e / kTile, n = e % kTile;
+    float g = 0.0f;
+    for (int sp = 0; sp < q.splits; ++sp) g += part[sp][k][n];
+    const int64_t o = off + int64_t(tm * kTile + k) * q.width + tn * kTile + n;
+    a.g[o] = g;
+    if (a.lr >= 0.0f) {
+      const float pi = adam_value(g, a.p[o], a.m[o], a.v[o], a.lr, bc1, bc2);
+      a.p[o] = pi;
+      const __bf16 pb = __bf16(pi);
+      a.wb[o] = pb;
+      tr[n][k] = pb;
+    }
+  }
+  if (a.lr < 0.0f) return;
+  __syncthreads();
+  for (int e = threadIdx.x; e < kTile * kTile; e += 256) {
+    const int n = e / kTile, k = e % kTile;
+    a.wt[off + int64_t(tn * kTile + n) * K + tm * kTile + k] = tr[n][k];
+  }
+}
+
 // Assembles the gradient (from the partials, or takes g_in), then Adam and the bf16 copies.
 // Thread 0 of block 0 also writes the loss of the step (sum of the squared-error partials / B).
 __global__ void __launch_bounds__(256) k_adam(ParamMap q, const float* __restrict__ g_in, float* __restrict__ p,
@@ -499,11 +908,7 @@ __global__ void __launch_bounds__(256) k_adam(ParamMap q, const float* __restric
   const float gi = g_in ? g_in[i] : assembled_grad(q, i);
   if (g_out) g_out[i] = gi;
   if (lr < 0.0f) return;  // gradient only
-  const float mi = 0.9f * m[i] + 0.1f * gi;
-  const float vi = 0.999f * v[i] + 0.001f * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  const float pi = p[i] - lr * (mi / c->bc1) / (sqrtf(vi / c->bc2) + 1e-8f);
+  const float pi = adam_value(gi, p[i], m[i], v[i], lr, c->bc1, c->bc2);
   p[i] = pi;
   const __bf16 pb = __bf16(pi);
   wb[i] = pb;
@@ -555,23 +960,37 @@ __global__ void k_init(float* __restrict__ p, int64_t off, int64_t n, float boun
   p[off + i] = bound * (2.0f * r - 1.0f);
 }
 
-__global__ void __launch_bounds__(1024) k_topk(const float* __restrict__ s, int n, int k, uint8_t* __restrict__ mask) {
-  // rank_i = #{j : s_j > s_i, or s_j == s_i and j < i}; NaN ranks below every number
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    const float si = s[i];
-    const bool nan_i = si != si;
-    int rank = 0;
-    for (int j = 0; j < n; ++j) {
-      const float sj = s[j];
-      const bool nan_j = sj != sj;
-      bool before;
-      if (nan_i) before = !nan_j || j < i;
-      else if (nan_j) before = false;
-      else before = sj > si || (sj == si && j < i);
-      rank += before;
-    }
-    mask[i] = rank < k ? 1 : 0;
+// mask_i = rank_i < k with rank_i = #{j : s_j > s_i, or s_j == s_i and j < i}; NaN ranks below every number.
+// Every workgroup holds all scores in LDS as integers of the same order and ranks 32 of them with 8 lanes
+// each: the n^2 comparisons spread over n / 32 workgroups (512 scores 3 us; one workgroup of 1024 threads
+// reading the scores from memory took 52 us).
+constexpr int kTopkMax = 8192, kTopkRows = 32;
+
+__device__ __forceinline__ uint32_t order_key(float f) {
+  if (f != f) return 0u;
+  const uint32_t u = __float_as_uint(f + 0.0f);  // -0 counts as +0
+  return (u & 0x80000000u) ? ~u : u | 0x80000000u;
+}
+
+__global__ void __launch_bounds__(256) k_topk(const float* __restrict__ s, int n, int k, uint8_t* __restrict__ mask) {
+  __shared__ uint4 key4[kTopkMax / 4];
+  uint32_t* key = reinterpret_cast<uint32_t*>(key4);
+  const int npad = (n + 31) / 32 * 32;
+  for (int j = threadIdx.x; j < npad; j += 256) key[j] = j < n ? order_key(s[j]) : 0u;
+  __syncthreads();
+  const int part = threadIdx.x & 7, i = blockIdx.x * kTopkRows + (threadIdx.x >> 3);
+  const uint32_t ki = key[min(i, n - 1)];
+  int rank = 0;
+  for (int j = 4 * part; j < npad; j += 32) {  // key_j > key_i, or equal and j < i; the padding never counts
+    const uint4 q = key4[j / 4];
+    rank += q.x >= ki + (j >= i);
+    rank += q.y >= ki + (j + 1 >= i);
+    rank += q.z >= ki + (j + 2 >= i);
+    rank += q.w >= ki + (j + 3 >= i);
   }
+#pragma unroll
+  for (int o = 1; o < 8; o <<= 1) rank += __shfl_xor(rank, o, 64);
+  if (part == 0 && i < n) mask[i] = rank < k ? 1 : 0;
 }
 
 __global__ void k_log10_standardize(const double* __restrict__ J, int n, double floor_, double mean, double inv_std,
@@ -679,8 +1098,47 @@ po_status hidden_forward(po_mlp* a, const double* d_x, RowMap rows, int B, bool 
   return PO_OK;
 }
 
+// Widths the fused kernels take: up to two 32-column tiles per wave, and the LDS of a workgroup.
+bool net_fused(const po_mlp* a) { return a->width <= kFusedWidth && a->n_in <= kFusedWidth; }
+
+size_t net_lds_bytes(const po_mlp* a, bool train) {
+  const size_t act = size_t(32) * (std::max(a->width, a->n_in) + 8) * sizeof(__bf16);
+  return act + (train ? size_t(32) * (a->width + 1) * sizeof(float) : 0);
+}
+
+template <int TPW, bool TRAIN>
+po_status launch_net_t(const po_mlp* a, const NetArgs& n, hipStream_t s) {
+  // at width 512 a workgroup holds 99 KB of LDS, beyond the 64 KB that need no request
+  if (net_lds_bytes(a, TRAIN) > 65536 - 1024)
+    PO_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_net<TPW, TRAIN>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, int(net_lds_bytes(a, TRAIN))));
+  hipLaunchKernelGGL((k_net<TPW, TRAIN>), dim3(n.B / 32), dim3(kNetThreads), unsigned(net_lds_bytes(a, TRAIN)), s, n);
+  PO_HIP(hipGetLastError());
+  return PO_OK;
+}
+
+template <bool TRAIN>
+po_status launch_net(po_mlp* a, const double* d_x, RowMap rows, const float* d_t, const double* d_J, double mean,
+                     double inv_std, int B, float* d_y, int step, hipStream_t s) {
+  const NetArgs n{d_x,     rows, a->n_in, a->width, a->depth, B,     a->max_batch, hstride(a), a->p,     a->wb,   a->wt, d_y,
+                  d_t,     d_J,  mean,    inv_std,  a->hT,    a->gp, a->dzT,       a->bpart,   a->opart, a->ctr,  step};
+  return a->width <= 32 * kNetWaves ? launch_net_t<1, TRAIN>(a, n, s) : launch_net_t<2, TRAIN>(a, n, s);
+}
+
+// Weight gradients (and, lr >= 0, the optimiser step) after launch_net<true>.
+po_status launch_step(po_mlp* a, int B, float lr, float* loss, int loss_by_cursor, hipStream_t s) {
+  const int tn = a->width / kTile;
+  const int tiles = (a->n_in / kTile) * tn + (a->depth - 1) * tn * tn;
+  const StepArgs t{param_map(a, B), a->hT, a->dzT, hstride(a), a->max_batch, tiles, a->p, a->m, a->v, a->g, a->wb,
+                   a->wt, lr, a->ctr, loss, loss_by_cursor};
+  hipLaunchKernelGGL(k_step, dim3(tiles + blocks(int64_t(a->depth + 1) * a->width + 1)), dim3(256), 0, s, t);
+  PO_HIP(hipGetLastError());
+  return PO_OK;
+}
+
 po_status forward_impl(po_mlp* a, const double* d_x, int B, float* d_y, hipStream_t s) {
   RowMap rows{nullptr, nullptr, B, B};
+  if (net_fused(a)) return launch_net<false>(a, d_x, rows, nullptr, nullptr, 0.0, 1.0, B, d_y, 0, s);
   PO_TRY(hidden_forward(a, d_x, rows, B, false, s));
   const int64_t wo = layer_w_off(a, a->depth);
   hipLaunchKernelGGL(k_out_fwd, dim3(blocks(B, 4)), dim3(256), 0, s, a->h + size_t(a->depth - 1) * a->max_batch * a->width,
@@ -788,8 +1246,14 @@ po_status train_replay(po_mlp* a, const double* d_x, const float* d_t, const dou
     a->graph = nullptr;
     PO_HIP(hipStreamBeginCapture(a->cap, hipStreamCaptureModeThreadLocal));
     RowMap rows{d_idx, a->ctr, B, n_rows};
-    po_status st = grad_impl(a, d_x, rows, d_t, d_J, mean, inv_std, B, a->cap);
-    if (st == PO_OK) st = adam_launch(a, B, nullptr, a->g, lr, d_loss, d_idx ? 1 : 0, a->cap);
+    po_status st;
+    if (net_fused(a)) {
+      st = launch_net<true>(a, d_x, rows, d_t, d_J, mean, inv_std, B, a->y, 1, a->cap);
+      if (st == PO_OK) st = launch_step(a, B, lr, d_loss, d_idx ? 1 : 0, a->cap);
+    } else {
+      st = grad_impl(a, d_x, rows, d_t, d_J, mean, inv_std, B, a->cap);
+      if (st == PO_OK) st = adam_launch(a, B, nullptr, a->g, lr, d_loss, d_idx ? 1 : 0, a->cap);
+    }
     hipGraph_t g = nullptr;
     const hipError_t e = hipStreamEndCapture(a->cap, &g);
     if (st != PO_OK) {
@@ -861,7 +1325,7 @@ po_status create_impl(po_mlp* a, uint64_t seed, hipStream_t s) {
   PO_TRY(dalloc(&a->hT, size_t(a->depth) * hs * MB));
   PO_TRY(dalloc(&a->gp, size_t(a->depth) * MB * W));
   PO_TRY(dalloc(&a->dz, 2 * size_t(MB) * W));
-  PO_TRY(dalloc(&a->dzT, 2 * size_t(W) * MB));
+  PO_TRY(dalloc(&a->dzT, size_t(a->depth) * W * MB));
   PO_TRY(dalloc(&a->y, MB));
   PO_TRY(dalloc(&a->wpart, size_t(kMaxSplit) * (size_t(a->n_in) * W + size_t(a->depth - 1) * W * W)));
   PO_TRY(dalloc(&a->bpart, size_t(a->depth) * (MB / 32) * W));
@@ -962,8 +1426,13 @@ po_status po_mlp_loss_grad(struct po_mlp* a, const double* d_x, const float* d_t
   if (d_grad) PO_TRY(check_device_range(d_grad, sizeof(float) * a->n_params, 4, "d_grad"));
   hipStream_t s = static_cast<hipStream_t>(stream);
   RowMap rows{nullptr, nullptr, batch, batch};
-  PO_TRY(grad_impl(a, d_x, rows, d_target, nullptr, 0.0, 1.0, batch, s));
-  PO_TRY(adam_launch(a, batch, nullptr, a->g, -1.0f, d_loss, 0, s));  // assemble only
+  if (net_fused(a)) {
+    PO_TRY(launch_net<true>(a, d_x, rows, d_target, nullptr, 0.0, 1.0, batch, a->y, 0, s));
+    PO_TRY(launch_step(a, batch, -1.0f, d_loss, 0, s));  // gradient only
+  } else {
+    PO_TRY(grad_impl(a, d_x, rows, d_target, nullptr, 0.0, 1.0, batch, s));
+    PO_TRY(adam_launch(a, batch, nullptr, a->g, -1.0f, d_loss, 0, s));  // assemble only
+  }
   if (d_grad) PO_HIP(hipMemcpyAsync(d_grad, a->g, sizeof(float) * a->n_params, hipMemcpyDeviceToDevice, s));
   return PO_OK;
 }
@@ -1015,11 +1484,12 @@ void po_mlp_destroy(struct po_mlp* a) {
 }
 
 po_status po_topk_mask(const float* d_score, int32_t n, int32_t k, uint8_t* d_mask, void* stream) {
-  if (n < 1 || n > 8192) return set_error(PO_ERR_INVALID, "n must be in [1, 8192]");
+  if (n < 1 || n > kTopkMax) return set_error(PO_ERR_INVALID, "n must be in [1, %d]", kTopkMax);
   if (k < 0 || k > n) return set_error(PO_ERR_INVALID, "k must be in [0, n]");
   PO_TRY(check_device_range(d_score, sizeof(float) * n, 4, "d_score"));
   PO_TRY(check_device_range(d_mask, n, 1, "d_mask"));
-  hipLaunchKernelGGL(k_topk, dim3(1), dim3(1024), 0, static_cast<hipStream_t>(stream), d_score, n, k, d_mask);
+  hipLaunchKernelGGL(k_topk, dim3(blocks(n, kTopkRows)), dim3(256), 0, static_cast<hipStream_t>(stream), d_score, n, k,
+                     d_mask);
   PO_HIP(hipGetLastError());
   return PO_OK;
 }
