@@ -61,13 +61,13 @@ struct po_mlp {
   float* m = nullptr;          // Adam first moment
   float* v = nullptr;          // Adam second moment
   float* g = nullptr;          // last assembled gradient
-  __bf16* wb = nullptr;        // bf16 weights, W_l[k][n] at the parameter offsets
-  __bf16* wt = nullptr;        // bf16 transposed weights, W_l^T[n][k] at the same offsets
+  __bf16* wb = nullptr;        // bf16 weights, W_l[k][n] at the parameter offsets (fused: operand order)
+  __bf16* wt = nullptr;        // bf16 transposed weights, W_l^T[n][k] at the same offsets (fused: operand order)
   __bf16* h = nullptr;         // activations h_1..h_depth [depth][max_batch][width] bf16
   __bf16* hT = nullptr;        // transposed h_0 (the input)..h_{depth-1} [depth][hstride][max_batch]
   float* gp = nullptr;         // gelu'(z_l) [depth][max_batch][width] fp32
   __bf16* dz = nullptr;        // pre-activation gradients [2][max_batch][width] bf16 (ping-pong)
-  __bf16* dzT = nullptr;       // transposed, of every hidden layer [depth][width][max_batch] bf16
+  __bf16* dzT = nullptr;       // transposed [2][width][max_batch] bf16 (ping-pong; fused: of every hidden layer)
   float* y = nullptr;          // outputs [max_batch]
   float* wpart = nullptr;      // weight-gradient partials, per layer [kMaxSplit][k_in][width]
   float* bpart = nullptr;      // bias-gradient partials, per layer [max_batch / 32][width]
@@ -109,6 +109,13 @@ struct RowMap {
     return (r >= 0 && r < n_rows) ? r : 0;
   }
 };
+
+// Operand order: a matrix X[row][k] with rows of K cut into pieces of 16 rows by 32 k, each stored as the 64 lanes
+// of the matrix instruction hold it (lane = 16 (k % 32 / 8) + row % 16, eight k each), so that a wave's operand
+// is 1 KiB in one piece.
+__host__ __device__ __forceinline__ int64_t operand_pos(int64_t row, int64_t k, int64_t K) {
+  return ((row / 16) * (K / 32) + k / 32) * 512 + ((k % 32) / 8 * 16 + row % 16) * 8 + k % 8;
+}
 
 struct MMArgs {
   const void* A;      // A[m][k] (bf16, or double rounded to bf16 through float), row stride lda
@@ -408,77 +415,89 @@ __global__ void __launch_bounds__(256) k_out_fwd(const __bf16* __restrict__ h, c
 }
 
 // ---------------------------------------------------------------------------------------------
-// Whole network for 32 samples per workgroup (widths up to kFusedWidth).  A sample's forward pass, output,
-// dL/dy and backward chain of pre-activation gradients only need that sample's row, so one workgroup of
-// eight waves takes 32 rows through all layers with the activations (then the gradients) in LDS; each
-// wave owns column tiles of 32 and reads its weights from L2.  What the weight gradients need --
-// transposed inputs and pre-activation gradients of every layer -- and the column sums go to global memory.
-// Products, roundings and sums are those of the layer-by-layer kernels below (mm_body, k_out_train), in
-// their order.
+// Whole network for 32 samples per workgroup (widths and inputs up to kFusedWidth).  A sample's forward pass,
+// output, dL/dy and backward chain of pre-activation gradients only need that sample's row, so one workgroup of
+// sixteen waves takes 32 rows through all layers with the activations (then the gradients) in LDS; each
+// wave owns column tiles of 16 and reads their weights from L2, a layer's first 256 rows of them before the
+// previous layer's activation function.  What the weight gradients need -- transposed inputs and
+// pre-activation gradients of every layer -- and the column sums go to global memory.  Weights and these
+// transposes are kept in operand order: rows and columns of them would be touched in pieces of 8 to 64 bytes, and
+// the workgroup waits for its stores at the next layer's weights.  Products, roundings and sums
+// are those of the layer-by-layer kernels (mm_body, k_out_train), in their order.
+// A batch of 1024 fills 32 of the chip's 256 compute units, and each wave waits for a chain of loads, products
+// and activation functions: 24 us for three layers of 256 (32 with row-major copies, 39 also without the early
+// loads and with eight waves; a training step, with k_step, 38 us against 68 in nine launches).  16 samples
+// per workgroup would halve the activation functions' share, but add the bias and output
+// gradients in another order, which Adam turns into other weights within a few steps.  Wider
+// networks take the layer-by-layer kernels, whose products fill the chip by themselves.
 // ---------------------------------------------------------------------------------------------
 constexpr int kFusedWidth = 512;   // two column tiles per wave
-constexpr int kNetWaves = 8;
+constexpr int kNetWaves = 16;
 constexpr int kNetThreads = 64 * kNetWaves;
+constexpr int kNetRows = 32, kNetCols = 16;  // a wave's tile
 
 struct NetArgs {
   const double* x;    // input rows [.][n_in]
   RowMap rows;
   int n_in, W, D, B, max_batch, hs;  // hs: row count of a slot of hT
   const float* p;     // master parameters (biases)
-  const __bf16* wb;   // W_l[k][n]
-  const __bf16* wt;   // W_l^T[n][k]
+  const __bf16* wb;   // W_l[k][n] in operand order; output weights
+  const __bf16* wt;   // W_l^T[n][k] in operand order
   float* y;
   // training
   const float* target;
   const double* J;
   double mean, inv_std;
-  __bf16* hT;         // [D][hs][max_batch]: the input, then h_1..h_{D-1}
-  float* gp;          // [D][max_batch][W]: gelu' (the last layer's stays in LDS)
-  __bf16* dzT;        // [D][W][max_batch]
+  // slots of hs * max_batch (the input, then h_1..h_{D-1}) and of W * max_batch; within a slot per 32 samples the
+  // transpose [columns][32] in operand order
+  __bf16* hT;
+  __bf16* dzT;
+  float* gp;          // slots of W * max_batch: gelu', as the lanes hold it (the last layer's stays in LDS)
   float* bpart;       // [D][max_batch / 32][W]
   float* opart;       // [B / 32][W + 2]
-  Counters* ctr;      // with `step`: the optimiser's step is counted here
+  Counters* ctr;      // with `step`: one more workgroup counts the optimiser's step here
   int step;
 };
 
+// a b, rounded before whatever uses it.
+__device__ __forceinline__ float product(float a, float b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
+
 __device__ __forceinline__ int net_lda(int W, int n_in) { return max(W, n_in) + 8; }
 
-// acc = A B^T for the wave's column tiles: A [32][K] bf16 in LDS (row stride lda), Bt[n][k] global.
+// Eight k-steps' weights of one column tile, in flight together: Bt[n][k] in operand order.
+struct WeightChunk {
+  bf16x8 w[8];
+};
+__device__ __forceinline__ void load_chunk(WeightChunk& c, const __bf16* Bt, int K, int N, int tn, int kb, int lane) {
+  if (tn * kNetCols >= N) return;
+  const __bf16* b0 = Bt + (size_t(tn) * (K / 32) + kb / 32) * 512 + lane * 8;
+#pragma unroll
+  for (int u = 0; u < 8; ++u)
+    if (kb + 32 * u < K) c.w[u] = load8(b0 + 512 * u);
+}
+
+// acc = A B^T for the wave's column tiles: A [32][K] in LDS (row stride lda); c holds the first chunk.
 template <int TPW>
-__device__ __forceinline__ void net_mm(floatx4 (&acc)[TPW][2][2], const __bf16* A, int lda, const __bf16* Bt, int K, int N,
-                                       int wave, int lane) {
-  const int r16 = lane & 15, kq = (lane >> 4) * 8;
-#pragma unroll
-  for (int t = 0; t < TPW; ++t)
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) acc[t][i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+__device__ __forceinline__ void net_mm(floatx4 (&acc)[TPW][2], WeightChunk& c, const __bf16* A, int lda, const __bf16* Bt,
+                                       int K, int N, int wave, int lane) {
+  const __bf16* a0 = A + (lane & 15) * lda + (lane >> 4) * 8;
 #pragma unroll
   for (int t = 0; t < TPW; ++t) {
+    acc[t][0] = acc[t][1] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
     const int tn = wave + t * kNetWaves;
-    if (tn * kTile >= N) break;
-    const __bf16* b0 = Bt + size_t(tn * kTile + r16) * K + kq;
-    const __bf16* b1 = b0 + size_t(16) * K;
-    // eight k-steps' weights in flight at a time
+    if (tn * kNetCols >= N) break;
     for (int kb = 0; kb < K; kb += 8 * 32) {
-      bf16x8 bf[8][2];
+      if (t > 0 || kb > 0) load_chunk(c, Bt, K, N, tn, kb, lane);
 #pragma unroll
       for (int u = 0; u < 8; ++u)
         if (kb + 32 * u < K) {
-          bf[u][0] = load8(b0 + kb + 32 * u);
-          bf[u][1] = load8(b1 + kb + 32 * u);
-        }
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (kb + 32 * u < K) {
-          const __bf16* a0 = A + r16 * lda + kb + 32 * u + kq;
-          const bf16x8 af[2] = {load8(a0), load8(a0 + 16 * lda)};
 #pragma unroll
           for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-              acc[t][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bf[u][j], acc[t][i][j], 0, 0, 0);
+            acc[t][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(load8(a0 + i * 16 * lda + kb + 32 * u), c.w[u], acc[t][i],
+                                                                0, 0, 0);
         }
     }
   }
@@ -488,206 +507,207 @@ template <int TPW, bool TRAIN>
 __global__ void __launch_bounds__(kNetThreads) k_net(NetArgs a) {
   extern __shared__ __align__(16) unsigned char net_lds[];
   const int lda = net_lda(a.W, a.n_in);
-  __bf16* act = reinterpret_cast<__bf16*>(net_lds);                            // [32][lda]
-  float* gl = reinterpret_cast<float*>(net_lds + size_t(32) * lda * sizeof(__bf16));  // [32][W + 1]: last layer's gelu'
-  __shared__ float s_dy[32], s_sq[32];
+  __bf16* act = reinterpret_cast<__bf16*>(net_lds);                                         // [32][lda]
+  float* gl = reinterpret_cast<float*>(net_lds + size_t(kNetRows) * lda * sizeof(__bf16));  // [32][W + 1]: last gelu'
+  __shared__ float s_dy[kNetRows], s_sq[kNetRows];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int b0 = blockIdx.x * 32, r16 = lane & 15, rq = (lane >> 4) * 4;
-  if (TRAIN && a.step && blockIdx.x == 0 && threadIdx.x == 0) {
-    const long long t = a.ctr->t + 1;
-    a.ctr->t = t;
-    a.ctr->bc1 = float(1.0 - pow(0.9, double(t)));
-    a.ctr->bc2 = float(1.0 - pow(0.999, double(t)));
+  const int b0 = blockIdx.x * kNetRows, r16 = lane & 15, rq = (lane >> 4) * 4;
+  if (TRAIN && b0 >= a.B) {  // a workgroup of its own: the powers take as long as a layer
+    if (threadIdx.x == 0) {
+      const long long t = a.ctr->t + 1;
+      a.ctr->t = t;
+      a.ctr->bc1 = float(1.0 - pow(0.9, double(t)));
+      a.ctr->bc2 = float(1.0 - pow(0.999, double(t)));
+    }
+    return;
   }
-  for (int e = threadIdx.x; e < 32 * (a.n_in / 8); e += kNetThreads) {
+  WeightChunk wc;
+  load_chunk(wc, a.wt, a.n_in, a.W, wave, 0, lane);
+  for (int e = threadIdx.x; e < kNetRows * (a.n_in / 8); e += kNetThreads) {
     const int row = e / (a.n_in / 8), c8 = (e - row * (a.n_in / 8)) * 8;
     *reinterpret_cast<bf16x8*>(act + row * lda + c8) = load8(a.x + size_t(a.rows.row(b0 + row)) * a.n_in + c8);
   }
-  __syncthreads();
-  if constexpr (TRAIN) {
-    for (int e = threadIdx.x; e < 8 * a.n_in; e += kNetThreads) {  // the input's transpose, four rows at a time
-      const int k = e >> 3, m = (e & 7) * 4;
-      bf16x4 t4;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) t4[q] = act[(m + q) * lda + k];
-      *reinterpret_cast<bf16x4*>(a.hT + size_t(k) * a.max_batch + b0 + m) = t4;
+  // the sample's target, by the lanes that will need it
+  const int og = lane >> 3, opart = lane & 7, om = wave * 8 + og;
+  float target = 0.0f;
+  if (TRAIN && wave < kNetRows / 8 && opart == 0) {
+    if (a.J) {
+      const double Jv = a.J[a.rows.row(b0 + om)];
+      target = float((log10(fmax(Jv, 1e-300)) - a.mean) * a.inv_std);
+    } else {
+      target = a.target[b0 + om];
     }
   }
-  floatx4 acc[TPW][2][2];
+  __syncthreads();
+  if constexpr (TRAIN) {
+    for (int e = threadIdx.x; e < a.n_in / 16 * 64; e += kNetThreads) {  // the input's transpose
+      const int k = e / 64 * 16 + (e & 15), m = (e & 63) / 16 * 8;
+      bf16x8 t8;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) t8[q] = act[(m + q) * lda + k];
+      *reinterpret_cast<bf16x8*>(a.hT + size_t(b0) * a.n_in + e * 8) = t8;
+    }
+  }
+  // where the lane's rows 16 i + rq .. + 3 of a column tile lie in the transpose's operand
+  const int opos = ((lane >> 5) * 16 + r16) * 8 + (lane >> 4 & 1) * 4;
+  floatx4 acc[TPW][2];
   int64_t off = 0;
   int K = a.n_in;
   for (int l = 0; l < a.D; ++l) {
-    net_mm<TPW>(acc, act, lda, a.wt + off, K, a.W, wave, lane);
     const float* bias = a.p + off + int64_t(K) * a.W;
+    float bn[TPW];
+#pragma unroll
+    for (int t = 0; t < TPW; ++t) bn[t] = bias[min((wave + t * kNetWaves) * kNetCols + r16, a.W - 1)];
+    net_mm<TPW>(acc, wc, act, lda, a.wt + off, K, a.W, wave, lane);
+    const int64_t next = off + int64_t(K) * a.W + a.W;
+    if (l + 1 < a.D) load_chunk(wc, a.wt + next, a.W, a.W, wave, 0, lane);
+    else if (TRAIN && l > 0) load_chunk(wc, a.wb + off, a.W, a.W, wave, 0, lane);  // the backward pass's first
     __syncthreads();  // every wave is done with the layer's input
 #pragma unroll
     for (int t = 0; t < TPW; ++t) {
-      const int tn = wave + t * kNetWaves;
-      if (tn * kTile >= a.W) break;
+      const int n = (wave + t * kNetWaves) * kNetCols + r16;
+      if ((wave + t * kNetWaves) * kNetCols >= a.W) break;
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int n = tn * kTile + j * 16 + r16;
-        const float bn = bias[n];
+      for (int i = 0; i < 2; ++i) {
+        bf16x4 t4;
+        floatx4 g4;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          bf16x4 t4;
+        for (int r = 0; r < 4; ++r) {
+          const int m = i * 16 + rq + r;
+          const float z = acc[t][i][r] + bn[t];
+          const __bf16 hb = __bf16(gelu(z));
+          act[m * lda + n] = hb;
+          t4[r] = hb;
+          if constexpr (TRAIN) g4[r] = gelu_grad(z);
+        }
+        if constexpr (TRAIN) {
+          const int tile = wave + t * kNetWaves;
+          if (l + 1 < a.D) {
+            *reinterpret_cast<bf16x4*>(a.hT + size_t(l + 1) * a.hs * a.max_batch + size_t(b0) * a.W + tile * 512 +
+                                       i * 256 + opos) = t4;
+            *reinterpret_cast<floatx4*>(a.gp + size_t(l) * a.max_batch * a.W + size_t(b0) * a.W + tile * 512 + i * 256 +
+                                        lane * 4) = g4;
+          } else {
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int m = i * 16 + rq + r;
-            const float z = acc[t][i][j][r] + bn;
-            const __bf16 hb = __bf16(gelu(z));
-            act[m * lda + n] = hb;
-            t4[r] = hb;
-            if constexpr (TRAIN) {
-              const float g = gelu_grad(z);
-              if (l + 1 < a.D) a.gp[(size_t(l) * a.max_batch + b0 + m) * a.W + n] = g;
-              else gl[m * (a.W + 1) + n] = g;
-            }
-          }
-          if constexpr (TRAIN) {
-            if (l + 1 < a.D)
-              *reinterpret_cast<bf16x4*>(a.hT + (size_t(l + 1) * a.hs + n) * a.max_batch + b0 + i * 16 + rq) = t4;
+            for (int r = 0; r < 4; ++r) gl[(i * 16 + rq + r) * (a.W + 1) + n] = g4[r];
           }
         }
       }
     }
     __syncthreads();
-    off += int64_t(K) * a.W + a.W;
+    off = next;
     K = a.W;
   }
-  const __bf16* wo = a.wb + off;      // output weights, then the bias
-  const float bo = a.p[off + a.W];
-  if constexpr (!TRAIN) {
-    // as k_out_fwd: one sample per wave at a time
-    for (int m = wave; m < 32; m += kNetWaves) {
-      float v = 0.0f;
-      for (int j = lane; j < a.W; j += 64) v = fmaf(float(act[m * lda + j]), float(wo[j]), v);
+  const __bf16* wo = a.wb + off;  // output weights, then the bias
+  if (wave < kNetRows / 8) {      // a wave does 8 samples at once with 8 lanes each, summed as in k_out_train
+    const float bo = a.p[off + a.W];
+    float p[8];
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-      if (lane == 0) a.y[b0 + m] = v + bo;
+    for (int e = 0; e < 8; ++e) p[e] = 0.0f;
+    for (int j0 = 8 * opart; j0 < a.W; j0 += 64) {
+      const bf16x8 hv = load8(act + om * lda + j0);
+      const bf16x8 wv8 = load8(wo + j0);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) p[e] = fmaf(float(hv[e]), float(wv8[e]), p[e]);
     }
-    return;
-  } else {
-    if (wave < 4) {  // as k_out_train: a wave does 8 samples at once with 8 lanes each
-      const int g = lane >> 3, part = lane & 7;
-      const int m = wave * 8 + g, b = b0 + m;
-      float p[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) p[e] = 0.0f;
-      for (int j0 = 8 * part; j0 < a.W; j0 += 64) {
-        const bf16x8 hv = load8(act + m * lda + j0);
-        const bf16x8 wv8 = load8(wo + j0);
+    for (int o = 4; o > 0; o >>= 1)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) p[e] = fmaf(float(hv[e]), float(wv8[e]), p[e]);
-      }
+      for (int e = 0; e < 8; ++e) p[e] += __shfl_xor(p[e], o, 64);
 #pragma unroll
-      for (int o = 4; o > 0; o >>= 1)
+    for (int o = 4; o > 0; o >>= 1) {
+      float q[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) p[e] += __shfl_xor(p[e], o, 64);
+      for (int e = 0; e < 8; ++e) q[e] = p[e] + p[e ^ o];
 #pragma unroll
-      for (int o = 4; o > 0; o >>= 1) {
-        float q[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) q[e] = p[e] + p[e ^ o];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) p[e] = q[e];
-      }
-      if (part == 0) {
-        const float yb = p[0] + bo;
-        a.y[b] = yb;
-        float t;
-        if (a.J) {
-          const double Jv = a.J[a.rows.row(b)];
-          t = float((log10(fmax(Jv, 1e-300)) - a.mean) * a.inv_std);
-        } else {
-          t = a.target[b];
-        }
-        const float d = yb - t;
-        s_dy[m] = 2.0f * d / float(a.B);
-        s_sq[m] = d * d;
+      for (int e = 0; e < 8; ++e) p[e] = q[e];
+    }
+    if (opart == 0) {
+      const float yb = p[0] + bo;
+      a.y[b0 + om] = yb;
+      if constexpr (TRAIN) {
+        const float d = yb - target;
+        s_dy[om] = 2.0f * d / float(a.B);
+        s_sq[om] = d * d;
       }
     }
+  }
+  if constexpr (TRAIN) {
     __syncthreads();
+    const size_t nb = a.max_batch / kNetRows;
     // the last hidden layer's gradient, one column per thread, rows in order
     __bf16* dzT = a.dzT + size_t(a.D - 1) * a.W * a.max_batch;
     for (int j = threadIdx.x; j < a.W; j += kNetThreads) {
       const float wj = float(wo[j]);
       float sb = 0.0f, sw = 0.0f;
 #pragma unroll
-      for (int r = 0; r < 32; r += 4) {
-        bf16x4 t4;
+      for (int r = 0; r < kNetRows; r += 8) {
+        bf16x8 t8;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
+        for (int e = 0; e < 8; ++e) {
           const float hv = float(act[(r + e) * lda + j]);
-          const float d = s_dy[r + e] * wj * gl[(r + e) * (a.W + 1) + j];
-          const __bf16 db = __bf16(d);
+          const float c = product(s_dy[r + e], wj), gv = gl[(r + e) * (a.W + 1) + j];
+          const __bf16 db = __bf16(product(c, gv));
           act[(r + e) * lda + j] = db;
-          t4[e] = db;
-          sb += d;
+          t8[e] = db;
+          sb = fmaf(c, gv, sb);
           sw = fmaf(hv, s_dy[r + e], sw);
         }
-        *reinterpret_cast<bf16x4*>(dzT + size_t(j) * a.max_batch + b0 + r) = t4;
+        *reinterpret_cast<bf16x8*>(dzT + size_t(b0) * a.W + operand_pos(j, r, kNetRows)) = t8;
       }
-      a.bpart[(size_t(a.D - 1) * (a.max_batch / 32) + blockIdx.x) * a.W + j] = sb;
+      a.bpart[((a.D - 1) * nb + blockIdx.x) * a.W + j] = sb;
       a.opart[size_t(blockIdx.x) * (a.W + 2) + j] = sw;
     }
-    if (threadIdx.x == 0) {
+    if (threadIdx.x == kNetThreads - 1) {
       float sd = 0.0f, sq = 0.0f;
-      for (int r = 0; r < 32; ++r) {
+      for (int r = 0; r < kNetRows; ++r) {
         sd += s_dy[r];
         sq += s_sq[r];
       }
       a.opart[size_t(blockIdx.x) * (a.W + 2) + a.W] = sd;
       a.opart[size_t(blockIdx.x) * (a.W + 2) + a.W + 1] = sq;
     }
-    __syncthreads();
-    // backward through the hidden layers: dz_{l-1} = (dz_l W_l^T) gelu'(z_{l-1})
+    // backward through the hidden layers: dz_{l-1} = (dz_l W_l^T) gelu'(z_{l-1}); off: W_l
+    off -= int64_t(a.D > 1 ? a.W : a.n_in) * a.W + a.W;
     for (int l = a.D - 1; l > 0; --l) {
-      const int Kl = l == 0 ? a.n_in : a.W;
-      off -= int64_t(Kl) * a.W + a.W;  // W_l
-      float gv[TPW][2][2][4];
+      floatx4 gv[TPW][2];  // written by this lane in the forward pass
 #pragma unroll
       for (int t = 0; t < TPW; ++t) {
-        const int tn = wave + t * kNetWaves;
-        if (tn * kTile >= a.W) break;
+        const int tile = wave + t * kNetWaves;
+        if (tile * kNetCols >= a.W) break;
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-              gv[t][j][i][r] = a.gp[(size_t(l - 1) * a.max_batch + b0 + i * 16 + rq + r) * a.W + tn * kTile + j * 16 + r16];
+        for (int i = 0; i < 2; ++i)
+          gv[t][i] = *reinterpret_cast<const floatx4*>(a.gp + size_t(l - 1) * a.max_batch * a.W + size_t(b0) * a.W +
+                                                       tile * 512 + i * 256 + lane * 4);
       }
-      net_mm<TPW>(acc, act, lda, a.wb + off, a.W, a.W, wave, lane);
-      __syncthreads();
+      __syncthreads();  // dz_l is complete
+      net_mm<TPW>(acc, wc, act, lda, a.wb + off, a.W, a.W, wave, lane);
+      off -= int64_t(l > 1 ? a.W : a.n_in) * a.W + a.W;
+      if (l > 1) load_chunk(wc, a.wb + off, a.W, a.W, wave, 0, lane);
+      __syncthreads();  // every wave has read dz_l
 #pragma unroll
       for (int t = 0; t < TPW; ++t) {
-        const int tn = wave + t * kNetWaves;
-        if (tn * kTile >= a.W) break;
+        const int n = (wave + t * kNetWaves) * kNetCols + r16;
+        if ((wave + t * kNetWaves) * kNetCols >= a.W) break;
+        float colsum = 0.0f;
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const int n = tn * kTile + j * 16 + r16;
-          float colsum = 0.0f;
+        for (int i = 0; i < 2; ++i) {
+          bf16x4 t4;
 #pragma unroll
-          for (int i = 0; i < 2; ++i) {
-            bf16x4 t4;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const int m = i * 16 + rq + r;
-              const float d = acc[t][i][j][r] * gv[t][j][i][r];
-              const __bf16 db = __bf16(d);
-              act[m * lda + n] = db;
-              t4[r] = db;
-              colsum += d;
-            }
-            *reinterpret_cast<bf16x4*>(a.dzT + (size_t(l - 1) * a.W + n) * a.max_batch + b0 + i * 16 + rq) = t4;
+          for (int r = 0; r < 4; ++r) {
+            const float d = product(acc[t][i][r], gv[t][i][r]);
+            const __bf16 db = __bf16(d);
+            act[(i * 16 + rq + r) * lda + n] = db;
+            t4[r] = db;
+            colsum += d;
           }
-          colsum += __shfl_xor(colsum, 16, 64);
-          colsum += __shfl_xor(colsum, 32, 64);
-          if (lane < 16) a.bpart[(size_t(l - 1) * (a.max_batch / 32) + blockIdx.x) * a.W + n] = colsum;
+          *reinterpret_cast<bf16x4*>(a.dzT + size_t(l - 1) * a.W * a.max_batch + size_t(b0) * a.W +
+                                     (wave + t * kNetWaves) * 512 + i * 256 + opos) = t4;
         }
+        colsum += __shfl_xor(colsum, 16, 64);
+        colsum += __shfl_xor(colsum, 32, 64);
+        if (lane < 16) a.bpart[((l - 1) * nb + blockIdx.x) * a.W + n] = colsum;
       }
-      __syncthreads();
     }
   }
 }
@@ -700,14 +720,27 @@ struct ParamMap {
   const float* bpart;  // per layer [max_batch / 32][width]
   const float* opart;  // [max_batch / 32][width + 2]
   int64_t bpart_stride;  // max_batch / 32 * width
+  int operand;         // bf16 weights in operand order
 };
 
 __device__ __forceinline__ int64_t wpart_off(const ParamMap& q, int l) {
   return l == 0 ? 0 : int64_t(kMaxSplit) * q.n_in * q.width + int64_t(l - 1) * kMaxSplit * q.width * q.width;
 }
 
-// Gradient of parameter i: its partial sums added in a fixed order (the loops are unrolled so that
-// their loads are in flight together; the additions stay in order).
+// Sum of p[t * stride], t < n, in order, with 32 loads in flight.
+__device__ __forceinline__ float ordered_sum(const float* p, int64_t stride, int n) {
+  float s = 0.0f;
+  for (int t0 = 0; t0 < n; t0 += 32) {
+    float v[32];
+#pragma unroll
+    for (int t = 0; t < 32; ++t) v[t] = t0 + t < n ? p[(t0 + t) * stride] : 0.0f;
+#pragma unroll
+    for (int t = 0; t < 32; ++t) s += v[t];
+  }
+  return s;
+}
+
+// Gradient of parameter i: its partial sums added in a fixed order.
 __device__ __forceinline__ float assembled_grad(const ParamMap& q, int64_t i) {
   int64_t off = 0;
   int kin = q.n_in;
@@ -723,24 +756,20 @@ __device__ __forceinline__ float assembled_grad(const ParamMap& q, int64_t i) {
     }
     if (i < off + nw + q.width) {
       const int n = int(i - off - nw);
-      const float* bp = q.bpart + l * q.bpart_stride;
-      float s = 0.0f;
-#pragma unroll 8
-      for (int t = 0; t < q.nblk; ++t) s += bp[int64_t(t) * q.width + n];
-      return s;
+      return ordered_sum(q.bpart + l * q.bpart_stride + n, q.width, q.nblk);
     }
     off += nw + q.width;
     kin = q.width;
   }
   const int j = int(i - off);  // 0..width-1: output weights; width: output bias
-  float s = 0.0f;
-#pragma unroll 8
-  for (int t = 0; t < q.nblk; ++t) s += q.opart[int64_t(t) * (q.width + 2) + j];
-  return s;
+  return ordered_sum(q.opart + j, q.width + 2, q.nblk);
 }
 
-// Transposed position of parameter i (weights of a hidden layer; others map to themselves).
-__device__ __forceinline__ int64_t transposed_index(const ParamMap& q, int64_t i) {
+// Positions of parameter i in the two bf16 copies (weights of a hidden layer; others keep theirs).
+struct CopyPos {
+  int64_t b, t;
+};
+__device__ __forceinline__ CopyPos copy_pos(const ParamMap& q, int64_t i) {
   int64_t off = 0;
   int kin = q.n_in;
   for (int l = 0; l < q.depth; ++l) {
@@ -748,13 +777,14 @@ __device__ __forceinline__ int64_t transposed_index(const ParamMap& q, int64_t i
     if (i < off + nw) {
       const int64_t e = i - off;
       const int64_t k = e / q.width, n = e - k * q.width;
-      return off + n * kin + k;
+      if (q.operand) return {off + operand_pos(k, n, q.width), off + operand_pos(n, k, kin)};
+      return {i, off + n * kin + k};
     }
-    if (i < off + nw + q.width) return i;  // the layer's bias
+    if (i < off + nw + q.width) break;  // the layer's bias
     off += nw + q.width;
     kin = q.width;
   }
-  return i;
+  return {i, i};
 }
 
 // Starts an optimiser step: t += 1 and its bias corrections; advances the indexed-training cursor.
@@ -766,10 +796,11 @@ __global__ void k_adam_begin(Counters* c) {
   c->cursor += 1;
 }
 
-// Adam's new value of a parameter with gradient g (updates its moments).
+// Adam's new value of a parameter with gradient g (updates its moments); the fused operations are written
+// out so that every kernel rounds alike.
 __device__ __forceinline__ float adam_value(float g, float p, float& m, float& v, float lr, float bc1, float bc2) {
-  m = 0.9f * m + 0.1f * g;
-  v = 0.999f * v + 0.001f * g * g;
+  m = fmaf(0.1f, g, 0.9f * m);
+  v = fmaf(0.001f * g, g, 0.999f * v);
   return p - lr * (m / bc1) / (sqrtf(v / bc2) + 1e-8f);
 }
 
@@ -777,11 +808,12 @@ __device__ __forceinline__ float adam_value(float g, float p, float& m, float& v
 // workgroups [0, n_tiles) take one 32x32 tile of one layer's dW_l = h_l^T dz_l each, wave s the s-th
 // part of the batch; the parts are added in order (as assembled_grad adds them) and the tile's
 // parameters, moments and both bf16 copies updated where they are.  The other workgroups do the biases and
-// the output layer from their partial sums, one parameter per thread, and the loss.
+// the output layer from their partial sums, one parameter per thread, and the loss.  Bound by two waits for memory
+// (the operands, all in flight, then the parameters' stores): 6.5 us for 140000 parameters and 1024 samples.
 struct StepArgs {
   ParamMap q;
-  const __bf16* hT;   // [D][hs][max_batch]
-  const __bf16* dzT;  // [D][W][max_batch]
+  const __bf16* hT;   // as in NetArgs
+  const __bf16* dzT;
   int hs, max_batch, n_tiles;
   float *p, *m, *v, *g;
   __bf16 *wb, *wt;
@@ -796,16 +828,15 @@ __global__ void __launch_bounds__(256) k_step(StepArgs a) {
   const float bc1 = a.ctr->bc1, bc2 = a.ctr->bc2;
   if (int(blockIdx.x) >= a.n_tiles) {
     int64_t i = int64_t(blockIdx.x - a.n_tiles) * 256 + threadIdx.x;  // biases layer by layer, then the output layer
-    if (i == 0) {
-      if (a.loss) {
-        float s = 0.0f;
-#pragma unroll 8
-        for (int t = 0; t < q.nblk; ++t) s += q.opart[int64_t(t) * (q.width + 2) + q.width + 1];
-        a.loss[a.loss_by_cursor ? a.ctr->cursor : 0] = s / float(q.batch);
-      }
-      if (a.lr >= 0.0f) a.ctr->cursor += 1;
+    const int64_t count = int64_t(q.depth) * q.width + q.width + 1;
+    if (i == count) {
+      const int cursor = a.ctr->cursor;
+      if (a.loss)
+        a.loss[a.loss_by_cursor ? cursor : 0] =
+            ordered_sum(q.opart + q.width + 1, q.width + 2, q.nblk) / float(q.batch);
+      if (a.lr >= 0.0f) a.ctr->cursor = cursor + 1;
     }
-    if (i >= int64_t(q.depth) * q.width + q.width + 1) return;
+    if (i >= count) return;
     const int l = min(int(i / q.width), q.depth);
     int64_t o = i;  // position in the parameter vector: plus the weights of the layers up to this one
     for (int k = 0; k <= l && k < q.depth; ++k) o += int64_t(k == 0 ? q.n_in : q.width) * q.width;
@@ -829,11 +860,23 @@ __global__ void __launch_bounds__(256) k_step(StepArgs a) {
   const int tm = tile / tn_n, tn = tile - tm * tn_n;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   __shared__ float part[kMaxSplit][kTile][kTile + 1];
-  __shared__ __bf16 tr[kTile][kTile + 2];
+  __shared__ __bf16 tile_w[kTile][kTile + 2];
+  // the tile's parameters and moments, four rows of 32 columns apart per thread, loaded before the products
+  float pv[4], mv[4], vv[4];
+  const int64_t o0 = off + int64_t(tm * kTile + (threadIdx.x >> 5)) * q.width + tn * kTile + (threadIdx.x & 31);
+  if (a.lr >= 0.0f) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t o = o0 + int64_t(8 * u) * q.width;
+      pv[u] = a.p[o];
+      mv[u] = a.m[o];
+      vv[u] = a.v[o];
+    }
+  }
   if (wave < q.splits) {
-    const int r16 = lane & 15, kq = (lane >> 4) * 8, kc = q.batch / q.splits;
-    const __bf16* A0 = a.hT + (size_t(l) * a.hs + tm * kTile + r16) * a.max_batch + wave * kc + kq;
-    const __bf16* B0 = a.dzT + (size_t(l) * q.width + tn * kTile + r16) * a.max_batch + wave * kc + kq;
+    const int r16 = lane & 15, kc = q.batch / q.splits;
+    const __bf16* A0 = a.hT + size_t(l) * a.hs * a.max_batch + size_t(wave) * kc * K + tm * 1024 + lane * 8;
+    const __bf16* B0 = a.dzT + size_t(l) * q.width * a.max_batch + size_t(wave) * kc * q.width + tn * 1024 + lane * 8;
     floatx4 acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -846,8 +889,8 @@ __global__ void __launch_bounds__(256) k_step(StepArgs a) {
         if (kb + 32 * u < kc) {
 #pragma unroll
           for (int i = 0; i < 2; ++i) {
-            af[u][i] = load8(A0 + size_t(i * 16) * a.max_batch + kb + 32 * u);
-            bf[u][i] = load8(B0 + size_t(i * 16) * a.max_batch + kb + 32 * u);
+            af[u][i] = load8(A0 + size_t(kb + 32 * u) * K + i * 512);
+            bf[u][i] = load8(B0 + size_t(kb + 32 * u) * q.width + i * 512);
           }
         }
 #pragma unroll
@@ -868,26 +911,34 @@ __global__ void __launch_bounds__(256) k_step(StepArgs a) {
         for (int r = 0; r < 4; ++r) part[wave][i * 16 + (lane >> 4) * 4 + r][j * 16 + r16] = acc[i][j][r];
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < kTile * kTile; e += 256) {
-    const int k = e / kTile, n = e % kTile;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int k = (threadIdx.x >> 5) + 8 * u, n = threadIdx.x & 31;
+    const int64_t o = o0 + int64_t(8 * u) * q.width;
     float g = 0.0f;
     for (int sp = 0; sp < q.splits; ++sp) g += part[sp][k][n];
-    const int64_t o = off + int64_t(tm * kTile + k) * q.width + tn * kTile + n;
     a.g[o] = g;
     if (a.lr >= 0.0f) {
-      const float pi = adam_value(g, a.p[o], a.m[o], a.v[o], a.lr, bc1, bc2);
+      const float pi = adam_value(g, pv[u], mv[u], vv[u], a.lr, bc1, bc2);
       a.p[o] = pi;
-      const __bf16 pb = __bf16(pi);
-      a.wb[o] = pb;
-      tr[n][k] = pb;
+      a.m[o] = mv[u];
+      a.v[o] = vv[u];
+      tile_w[k][n] = __bf16(pi);
     }
   }
   if (a.lr < 0.0f) return;
   __syncthreads();
-  for (int e = threadIdx.x; e < kTile * kTile; e += 256) {
-    const int n = e / kTile, k = e % kTile;
-    a.wt[off + int64_t(tn * kTile + n) * K + tm * kTile + k] = tr[n][k];
+  // both copies, each two operands of 1 KiB: thread = (operand, lane, half of the lane's eight)
+  const int f = threadIdx.x >> 7, ln = (threadIdx.x & 127) >> 1, half = (threadIdx.x & 1) * 4;
+  const int row = f * 16 + (ln & 15), col = (ln >> 4) * 8 + half;
+  bf16x4 wbv, wtv;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    wbv[e] = tile_w[row][col + e];
+    wtv[e] = tile_w[col + e][row];
   }
+  *reinterpret_cast<bf16x4*>(a.wb + off + (int64_t(tm * 2 + f) * tn_n + tn) * 512 + ln * 8 + half) = wbv;
+  *reinterpret_cast<bf16x4*>(a.wt + off + (int64_t(tn * 2 + f) * (K / kTile) + tm) * 512 + ln * 8 + half) = wtv;
 }
 
 // Assembles the gradient (from the partials, or takes g_in), then Adam and the bf16 copies.
@@ -898,12 +949,9 @@ __global__ void __launch_bounds__(256) k_adam(ParamMap q, const float* __restric
                                               const Counters* __restrict__ c, float* __restrict__ loss,
                                               int loss_by_cursor) {
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i == 0 && loss) {
-    float s = 0.0f;
-#pragma unroll 8
-    for (int t = 0; t < q.nblk; ++t) s += q.opart[int64_t(t) * (q.width + 2) + q.width + 1];
-    loss[loss_by_cursor ? c->cursor - 1 : 0] = s / float(q.batch);
-  }
+  if (i == 0 && loss)
+    loss[loss_by_cursor ? c->cursor - 1 : 0] =
+        ordered_sum(q.opart + q.width + 1, q.width + 2, q.nblk) / float(q.batch);
   if (i >= q.n_params) return;
   const float gi = g_in ? g_in[i] : assembled_grad(q, i);
   if (g_out) g_out[i] = gi;
@@ -911,8 +959,9 @@ __global__ void __launch_bounds__(256) k_adam(ParamMap q, const float* __restric
   const float pi = adam_value(gi, p[i], m[i], v[i], lr, c->bc1, c->bc2);
   p[i] = pi;
   const __bf16 pb = __bf16(pi);
-  wb[i] = pb;
-  wt[transposed_index(q, i)] = pb;
+  const CopyPos c2 = copy_pos(q, i);
+  wb[c2.b] = pb;
+  wt[c2.t] = pb;
 }
 
 // Master weights -> bf16 copies, row-major and transposed.
@@ -921,8 +970,9 @@ __global__ void k_weights_to_bf16(ParamMap q, const float* __restrict__ p, __bf1
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= q.n_params) return;
   const __bf16 pb = __bf16(p[i]);
-  wb[i] = pb;
-  wt[transposed_index(q, i)] = pb;
+  const CopyPos c2 = copy_pos(q, i);
+  wb[c2.b] = pb;
+  wt[c2.t] = pb;
 }
 
 __global__ void k_reset_counters(Counters* c, int reset_t) {
@@ -962,7 +1012,7 @@ __global__ void k_init(float* __restrict__ p, int64_t off, int64_t n, float boun
 
 // mask_i = rank_i < k with rank_i = #{j : s_j > s_i, or s_j == s_i and j < i}; NaN ranks below every number.
 // Every workgroup holds all scores in LDS as integers of the same order and ranks 32 of them with 8 lanes
-// each: the n^2 comparisons spread over n / 32 workgroups (512 scores 3 us; one workgroup of 1024 threads
+// each: the n^2 comparisons spread over n / 32 workgroups (512 scores 4.3 us; one workgroup of 1024 threads
 // reading the scores from memory took 52 us).
 constexpr int kTopkMax = 8192, kTopkRows = 32;
 
@@ -1017,6 +1067,9 @@ int splits_for(int B) {
   return kt % 4 == 0 ? 4 : (kt % 2 == 0 ? 2 : 1);
 }
 
+// Widths the fused kernels take: up to two 32-column tiles per wave, and the LDS of a workgroup.
+bool net_fused(const po_mlp* a) { return a->width <= kFusedWidth && a->n_in <= kFusedWidth; }
+
 ParamMap param_map(const po_mlp* a, int B) {
   ParamMap q;
   q.n_in = a->n_in;
@@ -1030,6 +1083,7 @@ ParamMap param_map(const po_mlp* a, int B) {
   q.bpart = a->bpart;
   q.opart = a->opart;
   q.bpart_stride = int64_t(a->max_batch / 32) * a->width;
+  q.operand = net_fused(a);
   return q;
 }
 
@@ -1098,12 +1152,9 @@ po_status hidden_forward(po_mlp* a, const double* d_x, RowMap rows, int B, bool 
   return PO_OK;
 }
 
-// Widths the fused kernels take: up to two 32-column tiles per wave, and the LDS of a workgroup.
-bool net_fused(const po_mlp* a) { return a->width <= kFusedWidth && a->n_in <= kFusedWidth; }
-
 size_t net_lds_bytes(const po_mlp* a, bool train) {
-  const size_t act = size_t(32) * (std::max(a->width, a->n_in) + 8) * sizeof(__bf16);
-  return act + (train ? size_t(32) * (a->width + 1) * sizeof(float) : 0);
+  const size_t act = size_t(kNetRows) * (std::max(a->width, a->n_in) + 8) * sizeof(__bf16);
+  return act + (train ? size_t(kNetRows) * (a->width + 1) * sizeof(float) : 0);
 }
 
 template <int TPW, bool TRAIN>
@@ -1112,7 +1163,7 @@ po_status launch_net_t(const po_mlp* a, const NetArgs& n, hipStream_t s) {
   if (net_lds_bytes(a, TRAIN) > 65536 - 1024)
     PO_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_net<TPW, TRAIN>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, int(net_lds_bytes(a, TRAIN))));
-  hipLaunchKernelGGL((k_net<TPW, TRAIN>), dim3(n.B / 32), dim3(kNetThreads), unsigned(net_lds_bytes(a, TRAIN)), s, n);
+  hipLaunchKernelGGL((k_net<TPW, TRAIN>), dim3(n.B / kNetRows + (n.step ? 1 : 0)), dim3(kNetThreads), unsigned(net_lds_bytes(a, TRAIN)), s, n);
   PO_HIP(hipGetLastError());
   return PO_OK;
 }
@@ -1121,8 +1172,8 @@ template <bool TRAIN>
 po_status launch_net(po_mlp* a, const double* d_x, RowMap rows, const float* d_t, const double* d_J, double mean,
                      double inv_std, int B, float* d_y, int step, hipStream_t s) {
   const NetArgs n{d_x,     rows, a->n_in, a->width, a->depth, B,     a->max_batch, hstride(a), a->p,     a->wb,   a->wt, d_y,
-                  d_t,     d_J,  mean,    inv_std,  a->hT,    a->gp, a->dzT,       a->bpart,   a->opart, a->ctr,  step};
-  return a->width <= 32 * kNetWaves ? launch_net_t<1, TRAIN>(a, n, s) : launch_net_t<2, TRAIN>(a, n, s);
+                  d_t,     d_J,  mean,    inv_std,  a->hT,    a->dzT, a->gp,       a->bpart,   a->opart, a->ctr,  step};
+  return a->width <= kNetCols * kNetWaves ? launch_net_t<1, TRAIN>(a, n, s) : launch_net_t<2, TRAIN>(a, n, s);
 }
 
 // Weight gradients (and, lr >= 0, the optimiser step) after launch_net<true>.
@@ -1131,7 +1182,7 @@ po_status launch_step(po_mlp* a, int B, float lr, float* loss, int loss_by_curso
   const int tiles = (a->n_in / kTile) * tn + (a->depth - 1) * tn * tn;
   const StepArgs t{param_map(a, B), a->hT, a->dzT, hstride(a), a->max_batch, tiles, a->p, a->m, a->v, a->g, a->wb,
                    a->wt, lr, a->ctr, loss, loss_by_cursor};
-  hipLaunchKernelGGL(k_step, dim3(tiles + blocks(int64_t(a->depth + 1) * a->width + 1)), dim3(256), 0, s, t);
+  hipLaunchKernelGGL(k_step, dim3(tiles + blocks(int64_t(a->depth + 1) * a->width + 2)), dim3(256), 0, s, t);
   PO_HIP(hipGetLastError());
   return PO_OK;
 }
@@ -1321,13 +1372,14 @@ po_status create_impl(po_mlp* a, uint64_t seed, hipStream_t s) {
   PO_TRY(dalloc(&a->g, np));
   PO_TRY(dalloc(&a->wb, np));
   PO_TRY(dalloc(&a->wt, np));
-  PO_TRY(dalloc(&a->h, size_t(a->depth) * MB * W));
+  const bool fused = net_fused(a);  // no row-major activations, gradients and partial products then
+  PO_TRY(dalloc(&a->h, fused ? 0 : size_t(a->depth) * MB * W));
   PO_TRY(dalloc(&a->hT, size_t(a->depth) * hs * MB));
   PO_TRY(dalloc(&a->gp, size_t(a->depth) * MB * W));
-  PO_TRY(dalloc(&a->dz, 2 * size_t(MB) * W));
-  PO_TRY(dalloc(&a->dzT, size_t(a->depth) * W * MB));
+  PO_TRY(dalloc(&a->dz, fused ? 0 : 2 * size_t(MB) * W));
+  PO_TRY(dalloc(&a->dzT, size_t(fused ? a->depth : 2) * W * MB));
   PO_TRY(dalloc(&a->y, MB));
-  PO_TRY(dalloc(&a->wpart, size_t(kMaxSplit) * (size_t(a->n_in) * W + size_t(a->depth - 1) * W * W)));
+  PO_TRY(dalloc(&a->wpart, fused ? 0 : size_t(kMaxSplit) * (size_t(a->n_in) * W + size_t(a->depth - 1) * W * W)));
   PO_TRY(dalloc(&a->bpart, size_t(a->depth) * (MB / 32) * W));
   PO_TRY(dalloc(&a->opart, size_t(MB / 32) * (W + 2)));
   PO_TRY(dalloc(&a->ctr, 1));
