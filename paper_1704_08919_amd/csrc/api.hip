@@ -747,14 +747,13 @@ po_status po_evolve_modes_m4(int32_t n, const po_pulse_spec* specs, const po_gri
   hipStream_t s = static_cast<hipStream_t>(stream);
   Work w;
   const DescWork dw(w, n);
-  const size_t o_units = w.add(sizeof(double) * size_t(b.total_units));
-  const size_t o_ranges = w.add(sizeof(double) * 4 * size_t(b.total_chunks));
+  const EvolveWork z(w, b);
   PO_TRY(w.alloc(s));
   PulseDev* d_desc = w.at<PulseDev>(dw.desc);
   PO_TRY(put_desc(h, d_desc, s));
-  double *d_units = d_J ? w.at<double>(o_units) : nullptr, *d_ranges = w.at<double>(o_ranges);
-  PO_TRY(launch_chunk_ranges4(b, d_desc, d_Ag, d_ranges, s));
-  PO_TRY(launch_evolve4_grid(b, d_desc, d_Ag, d_A_edge, d_ranges, d_f, d_units, s));
+  double* d_units = d_J ? w.at<double>(z.units) : nullptr;
+  PO_TRY(launch_evolve4(b, d_desc, d_Ag, d_A_edge, w.at<double>(z.ranges),
+          z.split ? w.at<double>(z.prop) : nullptr, d_f, d_units, s));
   if (d_J) PO_TRY(launch_yield_from_units(b, d_desc, d_units, d_J, s));
   return PO_OK;
 }
@@ -777,13 +776,13 @@ po_status po_evolve_modes_split(int32_t n, const po_pulse_spec* specs, const po_
   hipStream_t s = static_cast<hipStream_t>(stream);
   Work w;
   const DescWork dw(w, n);
-  const size_t o_units = w.add(sizeof(double) * size_t(b.total_units));
-  const size_t o_ranges = w.add(sizeof(double) * 4 * size_t(b.total_chunks));
+  const EvolveWork z(w, b);
   PO_TRY(w.alloc(s));
   PulseDev* d_desc = w.at<PulseDev>(dw.desc);
   PO_TRY(put_desc(h, d_desc, s));
-  double *d_units = d_J ? w.at<double>(o_units) : nullptr, *d_ranges = w.at<double>(o_ranges);
-  PO_TRY(launch_evolve_split_grid(b, order, d_desc, d_At, d_A_edge, d_ranges, d_f, d_units, s));
+  double* d_units = d_J ? w.at<double>(z.units) : nullptr;
+  PO_TRY(launch_evolve_split(b, order, d_desc, d_At, d_A_edge, w.at<double>(z.ranges),
+          z.split ? w.at<double>(z.prop) : nullptr, d_f, d_units, s));
   if (d_J) PO_TRY(launch_yield_from_units(b, d_desc, d_units, d_J, s));
   return PO_OK;
 }

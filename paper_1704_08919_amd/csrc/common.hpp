@@ -183,15 +183,12 @@ int evolve_workgroups_per_cu(const EvolveConfig& cfg);
 // Fourth-order (Magnus) evolution: table ranges over both nodes of every step per chunk
 // (d_ranges [total_chunks][4]) and one workgroup per 256 modes; d_Ag is [sum nt][2 nodes][2] with
 // desc.tab_off counted in steps.
-po_status launch_chunk_ranges4(const Batch& b, const PulseDev* d_desc, const double* d_Ag, double* d_ranges,
-                               hipStream_t s);
-po_status launch_evolve4_grid(const Batch& b, const PulseDev* d_desc, const double* d_Ag, const double* d_A_edge,
-                              const double* d_ranges, double* d_f, double* d_units, hipStream_t s);
-// Split-operator evolution (order 2: Strang, order 4: triple jump): table ranges into d_ranges
-// [total_chunks][4], then one workgroup per 256 modes; d_At is [sum nt][1 or 3][2], desc.tab_off in steps.
-po_status launch_evolve_split_grid(const Batch& b, int order, const PulseDev* d_desc, const double* d_At,
-                                   const double* d_A_edge, double* d_ranges, double* d_f, double* d_units,
-                                   hipStream_t s);
+// Fourth-order and split-operator schemes.  d_prop: propagators of the batch's slots, or NULL for the form without.
+po_status launch_evolve4(const Batch& b, const PulseDev* d_desc, const double* d_Ag, const double* d_A_edge,
+                         double* d_ranges, double* d_prop, double* d_f, double* d_units, hipStream_t s);
+po_status launch_evolve_split(const Batch& b, int order, const PulseDev* d_desc, const double* d_At,
+                              const double* d_A_edge, double* d_ranges, double* d_prop, double* d_f, double* d_units,
+                              hipStream_t s);
 // Kinetic equation (qke.hip): tables at the 2 nt + 1 half-step points, desc.tab_off in points.
 po_status launch_qke_grid(const Batch& b, const PulseDev* d_desc, const double* d_E, const double* d_Ed,
                           const double* d_A, int linear, double* d_f, double* d_units, hipStream_t s);

@@ -107,29 +107,6 @@ __device__ __forceinline__ void rotate(State& v, double C, double S, double qx, 
   v = State{ar, ai, br, bi, cr, ci, dr, di};
 }
 
-// psi <- (1 - i T Q_s) psi for both blocks: the rotation above with C -> 1 and S -> T.
-__device__ __forceinline__ void rotate_tan(State& v, double T, double qx, double qy, double qz) {
-  const double tx = T * qx, ty = T * qy, tz = T * qz;
-  const double ar = fma(tx, v.bi, fma(-ty, v.br, fma(tz, v.ai, v.ar)));
-  const double ai = fma(-tx, v.br, fma(-ty, v.bi, fma(-tz, v.ar, v.ai)));
-  const double br = fma(-tz, v.bi, fma(tx, v.ai, fma(ty, v.ar, v.br)));
-  const double bi = fma(tz, v.br, fma(-tx, v.ar, fma(ty, v.ai, v.bi)));
-  const double cr = fma(tx, v.di, fma(ty, v.dr, fma(tz, v.ci, v.cr)));
-  const double ci = fma(-tx, v.dr, fma(ty, v.di, fma(-tz, v.cr, v.ci)));
-  const double dr = fma(-tz, v.di, fma(tx, v.ci, fma(-ty, v.cr, v.dr)));
-  const double di = fma(tz, v.dr, fma(-tx, v.cr, fma(-ty, v.ci, v.di)));
-  v = State{ar, ai, br, bi, cr, ci, dr, di};
-}
-
-template <int V>  // series variant
-__device__ __forceinline__ void step_tan(State& v, double2 rec, double pxdt, double pydt, double qz, double qz2,
-                                         const Fit<V>& f) {
-  const double qx = pxdt + rec.x;  // rec = -A dt
-  const double qy = pydt + rec.y;
-  const double x = fma(qx, qx, fma(qy, qy, qz2));
-  rotate_tan(v, tan_ratio<V>(x, f), qx, qy, qz);
-}
-
 // ---------------------------------------------------------------------------------------------
 // Cotangent form of the step.  With everything in units of e = e_perp, q' = (p - A)/e, y = |q'|^2
 // and z = (e dt)^2, x = (omega dt)^2 = z (1 + y), the step is a multiple of
@@ -273,24 +250,6 @@ __device__ __forceinline__ void apply_propagator(State& s, const State& p) {
   s = State{ar, ai, br, bi, cr, ci, dr, di};
 }
 
-// Large-step path: C, S at x / 4^h, then h double-angle steps; the step stays unitary.
-__device__ __forceinline__ void step_halving(State& v, double2 rec, double pxdt, double pydt, double qz, double qz2,
-                                             int h, double inv4h) {
-  const double qx = pxdt + rec.x;
-  const double qy = pydt + rec.y;
-  const double x = fma(qx, qx, fma(qy, qy, qz2));
-  double xs = x * inv4h;
-  double C, S;
-  cos_sinc<7>(xs, C, S);  // xs <= kCosSinXmax
-  for (int i = 0; i < h; ++i) {
-    const double c2 = fma(C, C, -(xs * S) * S);  // cos 2t = cos^2 t - t^2 (sin t / t)^2
-    S = S * C;                                 // sin 2t / 2t = (sin t / t) cos t
-    C = c2;
-    xs *= 4.0;
-  }
-  rotate(v, C, S, qx, qy, qz);
-}
-
 // C = cos sqrt x, S = sin sqrt x / sqrt x from the degree-7 series at x / 4^h and h double-angle steps.
 __device__ __forceinline__ void cos_sinc_halved(double x, int h, double inv4h, double& C, double& S) {
   double xs = x * inv4h;
@@ -303,16 +262,6 @@ __device__ __forceinline__ void cos_sinc_halved(double x, int h, double inv4h, d
   }
 }
 
-// psi <- (1 - i t . tau) psi for one block (a, b).
-__device__ __forceinline__ void rotate_block_tan(double& ar, double& ai, double& br, double& bi, double tx, double ty,
-                                                 double tz) {
-  const double nar = fma(tx, bi, fma(-ty, br, fma(tz, ai, ar)));
-  const double nai = fma(-tx, br, fma(-ty, bi, fma(-tz, ar, ai)));
-  const double nbr = fma(-tz, bi, fma(tx, ai, fma(ty, ar, br)));
-  const double nbi = fma(tz, br, fma(-tx, ar, fma(ty, ai, bi)));
-  ar = nar; ai = nai; br = nbr; bi = nbi;
-}
-
 // psi <- (C - i s . tau) psi for one block (a, b).
 __device__ __forceinline__ void rotate_block(double& ar, double& ai, double& br, double& bi, double C, double sx,
                                              double sy, double sz) {
@@ -321,14 +270,6 @@ __device__ __forceinline__ void rotate_block(double& ar, double& ai, double& br,
   const double nbr = fma(-sz, bi, fma(C, br, fma(sx, ai, sy * ar)));
   const double nbi = fma(sz, br, fma(C, bi, fma(-sx, ar, sy * ai)));
   ar = nar; ai = nai; br = nbr; bi = nbi;
-}
-
-// Rescales the state by an exact power of two (no rounding) so that |psi_{+1}|^2 is O(1).
-__device__ __forceinline__ void renormalise(State& v) {
-  const double n2 = fma(v.bi, v.bi, fma(v.br, v.br, fma(v.ai, v.ai, v.ar * v.ar)));
-  const int e = -(ilogb(n2) >> 1);
-  v.ar = ldexp(v.ar, e); v.ai = ldexp(v.ai, e); v.br = ldexp(v.br, e); v.bi = ldexp(v.bi, e);
-  v.cr = ldexp(v.cr, e); v.ci = ldexp(v.ci, e); v.dr = ldexp(v.dr, e); v.di = ldexp(v.di, e);
 }
 
 // A lane's state in slot `slot` of a propagator buffer [slot][8 components][256 lanes].

@@ -61,42 +61,6 @@
 namespace po {
 namespace {
 
-// NODES = 1: the second-order step's angle.  NODES = 2: the fourth-order step's, from theta^2 the
-// bound above over both Gauss nodes, |w_s| <= theta + (sqrt3/6) theta^2.
-template <int NODES>
-__device__ __forceinline__ int2 choose_variant(const BlockBox& bb, double lx, double hx, double ly, double hy,
-                                               double dt) {
-  double xb = x_bound(bb, lx, hx, ly, hy, dt);
-  if constexpr (NODES == 2) {
-    const double th = sqrt(xb);
-    xb = (th + kSqrt3Over6 * th * th) * (th + kSqrt3Over6 * th * th) * (1.0 + 1e-6);
-  }
-  return variant_for_x(xb);
-}
-
-// Variant of a block for the whole table (the union of its nchunks chunk ranges rg[c][4]).
-template <int NODES = 1>
-__device__ __forceinline__ int2 block_variant(const BlockBox& bb, const double* rg, int nchunks, double dt) {
-  double lx = rg[0], hx = rg[1], ly = rg[2], hy = rg[3];
-  for (int c = 1; c < nchunks; ++c) {
-    lx = fmin(lx, rg[4 * c]); hx = fmax(hx, rg[4 * c + 1]);
-    ly = fmin(ly, rg[4 * c + 2]); hy = fmax(hy, rg[4 * c + 3]);
-  }
-  return choose_variant<NODES>(bb, lx, hx, ly, hy, dt);
-}
-
-// Variant of chunk c given the block's (bmode).  A block within the T-series range: the lower of
-// the block's variant and the one for the chunk's own range (both cover the chunk's steps).  A
-// block on the angle-halving path: its chunks take that path with their own number of halvings,
-// or, when their own range allows any T fit, the degree-11 one (two code paths only, so the
-// loop keeps to its register budget).
-template <int NODES = 1>
-__device__ __forceinline__ int2 chunk_variant(const BlockBox& bb, const double* rg, int c, int bmode, double dt) {
-  const int2 own = choose_variant<NODES>(bb, rg[4 * c], rg[4 * c + 1], rg[4 * c + 2], rg[4 * c + 3], dt);
-  if (bmode == kFineHalving) return own.x == kFineHalving ? own : make_int2(kNumFine - 1, 0);
-  return make_int2(min(own.x, bmode), 0);
-}
-
 // Range (min A_x, max A_x, min A_y, max A_y) of the table over chunk blockIdx.x of pulse blockIdx.y
 // (NODES = 2: over both Gauss-node values of every step).
 template <int NODES>
@@ -142,17 +106,22 @@ struct EvolveArgs {
   double* units;
 };
 
-// Variant of the cotangent form for a bound xb on x = (omega dt)^2: the lowest fit that covers it
-// (compared by the upper words, so a bound within 2^-20 of a fit's end takes the next one; NaN and
-// infinity compare above all), kCotHalving beyond, and for steps so small that even the short group
-// would overflow (dt < 2^-59), which need no halvings there.
-__device__ __forceinline__ int cot_variant(double xb, double dt) {
+// Fit of sqrt(x) cot(sqrt x) for a bound xb on the squared step angle: the lowest that covers it (compared by the
+// upper words, so a bound within 2^-20 of a fit's end takes the next one; NaN and infinity compare above all),
+// kCotHalving beyond.
+__device__ __forceinline__ int cot_fit(double xb) {
   const uint32_t hi = __builtin_amdgcn_readfirstlane(__double2hiint(xb));
   int mode = kCotHalving;
 #pragma unroll
   for (int k = kNumCot - 1; k >= 0; --k)
     if (hi < high_word(kCotXmax[k])) mode = k;
-  return dt < kGroupShortMinDt ? kCotHalving : mode;
+  return mode;
+}
+
+// Variant of the cotangent form: kCotHalving also for steps so small that even the short group would
+// overflow (dt < 2^-59), which need no halvings there.
+__device__ __forceinline__ int cot_variant(double xb, double dt) {
+  return dt < kGroupShortMinDt ? kCotHalving : cot_fit(xb);
 }
 
 // The steps of one chunk (len table records of buf) for the MPL modes of a lane in fit variant V,
@@ -187,16 +156,43 @@ __constant__ double2 kHalvingCoef[8] = {
     {cos_coef(0), sinc_coef(0)}, {cos_coef(1), sinc_coef(1)}, {cos_coef(2), sinc_coef(2)}, {cos_coef(3), sinc_coef(3)},
     {cos_coef(4), sinc_coef(4)}, {cos_coef(5), sinc_coef(5)}, {cos_coef(6), sinc_coef(6)}, {cos_coef(7), sinc_coef(7)}};
 
+// Halvings that bring the bound xb into the degree-7 series' range (at most kMaxHalvings), uniform.
+__device__ __forceinline__ int halvings(double xb) {
+  int h = 0;
+  for (double x = xb; x > kCosSinXmax && h < kMaxHalvings; x *= 0.25) ++h;
+  return __builtin_amdgcn_readfirstlane(h);
+}
+
+// C = cos sqrt x, S = sin sqrt x / sqrt x from the series (coefficients cs) at xs = x / 4^h and h doublings.
+__device__ __forceinline__ void halved_cos_sinc(double xs, int h, const double2* cs, double& C, double& S) {
+  C = cs[7].x;
+  S = cs[7].y;
+#pragma unroll
+  for (int k = 6; k >= 0; --k) {
+    C = fma(C, xs, cs[k].x);
+    S = fma(S, xs, cs[k].y);
+  }
+  for (int i = 0; i < h; ++i) {
+    const double c2 = fma(C, C, -(xs * S) * S);
+    S = S * C;
+    C = c2;
+    xs *= 4.0;
+  }
+}
+
+__device__ __forceinline__ const double2* halving_coef() {
+  const double2* cs = kHalvingCoef;
+  asm volatile("" : "+s"(cs));
+  return cs;
+}
+
 // The chunk beyond the fits: C and S of degree 7 with angle halvings.
 template <int MPL>
 __device__ __forceinline__ void run_halving(State (&v)[MPL], const double2* buf, int len, double xb, double dt,
                                             const CotMode (&m)[MPL]) {
-  int h = 0;
-  for (double x = xb; x > kCosSinXmax && h < kMaxHalvings; x *= 0.25) ++h;
-  h = __builtin_amdgcn_readfirstlane(h);
+  const int h = halvings(xb);
   const double inv4h = ldexp(1.0, -2 * h);
-  const double2* cs = kHalvingCoef;
-  asm volatile("" : "+s"(cs));
+  const double2* cs = halving_coef();
 #pragma unroll 1
   for (int n = 0; n < len; ++n) {
     const double2 rec = buf[n];
@@ -205,19 +201,8 @@ __device__ __forceinline__ void run_halving(State (&v)[MPL], const double2* buf,
       // back to units of 1/dt: q = e dt q'
       const double qz = m[j].e * dt;
       const double qx = qz * fma(rec.x, m[j].nie, m[j].px), qy = qz * fma(rec.y, m[j].nie, m[j].py);
-      double xs = fma(qx, qx, fma(qy, qy, qz * qz)) * inv4h;
-      double C = cs[7].x, S = cs[7].y;
-#pragma unroll
-      for (int k = 6; k >= 0; --k) {
-        C = fma(C, xs, cs[k].x);
-        S = fma(S, xs, cs[k].y);
-      }
-      for (int i = 0; i < h; ++i) {
-        const double c2 = fma(C, C, -(xs * S) * S);
-        S = S * C;
-        C = c2;
-        xs *= 4.0;
-      }
+      double C, S;
+      halved_cos_sinc(fma(qx, qx, fma(qy, qy, qz * qz)) * inv4h, h, cs, C, S);
       rotate(v[j], C, S, qx, qy, qz);
     }
   }
@@ -408,9 +393,17 @@ __global__ void __launch_bounds__(256) k_yield(const PulseDev* __restrict__ desc
   if (threadIdx.x == 0) J[blockIdx.x] = s * d.dv;
 }
 
+__device__ __forceinline__ int size_class(double xb) {
+  int mode = kFineHalving;
+  for (int k = kNumFine - 1; k >= 0; --k)
+    if (xb <= kFitXmax[k]) mode = k;
+  return mode;
+}
+
 // Diagnostics: adds modes x steps of every (selection block, chunk) of every pulse to the count
-// of its step-size class (the ranges of the tangent fits, by block_variant and chunk_variant); the
-// blocks here run over all modes of the grid, mirror images included.
+// of its step-size class (the ranges of the tangent fits, kFineHalving beyond: the lower of the block's class over
+// the whole table and the chunk's own, but of a block beyond the fits only the last); the blocks here run
+// over all modes of the grid, mirror images included.
 // One workgroup per pulse, one thread per block.
 __global__ void __launch_bounds__(256) k_count_mode_steps(const PulseDev* __restrict__ desc,
                                                           const double* __restrict__ ranges,
@@ -424,9 +417,15 @@ __global__ void __launch_bounds__(256) k_count_mode_steps(const PulseDev* __rest
     const BlockBox bb = block_box(d, b, nmodes);
     const unsigned long long mb = (unsigned long long)min(int64_t(kSelBlock), nmodes - int64_t(b) * kSelBlock);
     unsigned long long local[kSeriesVariants] = {};
-    const int bmode = block_variant(bb, rg, nch, d.dt).x;
+    double lx = rg[0], hx = rg[1], ly = rg[2], hy = rg[3];
+    for (int c = 1; c < nch; ++c) {
+      lx = fmin(lx, rg[4 * c]); hx = fmax(hx, rg[4 * c + 1]);
+      ly = fmin(ly, rg[4 * c + 2]); hy = fmax(hy, rg[4 * c + 3]);
+    }
+    const int bmode = size_class(x_bound(bb, lx, hx, ly, hy, d.dt));
     for (int c = 0; c < nch; ++c) {
-      const int mode = chunk_variant(bb, rg, c, bmode, d.dt).x;
+      const int own = size_class(x_bound(bb, rg[4 * c], rg[4 * c + 1], rg[4 * c + 2], rg[4 * c + 3], d.dt));
+      const int mode = bmode != kFineHalving ? min(own, bmode) : (own == kFineHalving ? own : kNumFine - 1);
       local[min(max(mode, 0), kSeriesVariants - 1)] += mb * (unsigned long long)min(kChunk, d.nt - c * kChunk);
     }
     for (int k = 0; k < kSeriesVariants; ++k)
@@ -446,8 +445,8 @@ void launch_persistent_t(EvolveArgs a, const int2* q, int n_items, int nwg, int*
 // v_s = (P_x, s P_y, e_perp), [h_2, h_1] = 2i (v_2 x v_1) . tau, so the Magnus exponent of a step
 // is -i w_s . tau with
 //     w_s = dt (v_1 + v_2)/2 + (sqrt3/6) dt^2 (v_2 x v_1),
-// and the step is again U = C [1 - i T(|w_s|^2) w_s . tau], now with one w_s (and one T) per
-// block.  With a_k = (p_x - A_x(t_k)) dt, b_k likewise, e = e_perp dt, abar = (a_1 + a_2)/2 and
+// and the step is a multiple of K(|w_s|^2) - i w_s . tau, K = sqrt(x) cot(sqrt x), now with one w_s (and one K)
+// per block.  With a_k = (p_x - A_x(t_k)) dt, b_k likewise, e = e_perp dt, abar = (a_1 + a_2)/2 and
 // g = (sqrt3/6) (a_1 - a_2, b_1 - b_2):
 //     w_s = (abar - s e g_y,  s (bbar + s e g_x),  e + s (abar g_y - bbar g_x)).
 // The record staged per step is (-(A_1 + A_2) dt/2, (sqrt3/6)(A_2 - A_1) dt): abar and g cost one
@@ -465,148 +464,145 @@ __device__ __forceinline__ Magnus4 magnus4(double4 rec, double pxdt, double pydt
   return Magnus4{ab - egy, bb + egx, e + g, ab + egy, bb - egx, e - g};
 }
 
-template <int V>  // series variant
-__device__ __forceinline__ void step4_tan(State& v, double4 rec, double pxdt, double pydt, double e, const Fit<V>& f) {
-  const Magnus4 w = magnus4(rec, pxdt, pydt, e);
-  const double xp = fma(w.Xp, w.Xp, fma(w.Yp, w.Yp, w.Zp * w.Zp));
-  const double xm = fma(w.Xm, w.Xm, fma(w.Ym, w.Ym, w.Zm * w.Zm));
-  const double Tp = tan_ratio<V>(xp, f), Tm = tan_ratio<V>(xm, f);
-  rotate_block_tan(v.ar, v.ai, v.br, v.bi, Tp * w.Xp, Tp * w.Yp, Tp * w.Zp);
-  rotate_block_tan(v.cr, v.ci, v.dr, v.di, Tm * w.Xm, -(Tm * w.Ym), Tm * w.Zm);
+// Coefficients of the fit of variant V in scalar registers, read from memory where they are used (the variants share
+// some: as literals the compiler keeps them all from the kernel's entry on).
+struct CotRows {
+  double c[kNumCot][kCotMaxTerms];
+};
+constexpr CotRows cot_rows() {
+  CotRows t{};
+  for (int v = 0; v < kNumCot; ++v)
+    for (int k = 0; k < kCotMaxTerms; ++k) t.c[v][k] = kCotCoef[v][k];
+  return t;
+}
+__constant__ const CotRows kCotTable = cot_rows();
+
+template <int V>
+struct CotFit {
+  double r[kCotDegree[V]];
+};
+template <int V>
+__device__ __forceinline__ CotFit<V> load_cot_fit() {
+  const double* p = kCotTable.c[V];
+  asm volatile("" : "+s"(p));
+  CotFit<V> f;
+#pragma unroll
+  for (int k = 0; k < kCotDegree[V]; ++k) f.r[k] = p[k];
+  return f;
 }
 
-__device__ __forceinline__ void step4_halving(State& v, double4 rec, double pxdt, double pydt, double e, int h,
-                                              double inv4h) {
-  const Magnus4 w = magnus4(rec, pxdt, pydt, e);
-  const double xp = fma(w.Xp, w.Xp, fma(w.Yp, w.Yp, w.Zp * w.Zp));
-  const double xm = fma(w.Xm, w.Xm, fma(w.Ym, w.Ym, w.Zm * w.Zm));
-  double Cp, Sp, Cm, Sm;
-  cos_sinc_halved(xp, h, inv4h, Cp, Sp);
-  cos_sinc_halved(xm, h, inv4h, Cm, Sm);
-  rotate_block(v.ar, v.ai, v.br, v.bi, Cp, Sp * w.Xp, Sp * w.Yp, Sp * w.Zp);
-  rotate_block(v.cr, v.ci, v.dr, v.di, Cm, Sm * w.Xm, -(Sm * w.Ym), Sm * w.Zm);
+// K(x) = sqrt(x) cot(sqrt x): kCotDegree[V] fused multiply-adds.
+template <int V>
+__device__ __forceinline__ double cot_value(double x, const CotFit<V>& f) {
+  constexpr int n = kCotDegree[V];
+  double R = f.r[n - 1];
+#pragma unroll
+  for (int k = n - 2; k >= 0; --k) R = fma(R, x, f.r[k]);
+  return fma(R, x, 1.0);
 }
 
-// Rescales each block by its own exact power of two.
-__device__ __forceinline__ void renormalise_blocks(State& v) {
-  const double n1 = fma(v.bi, v.bi, fma(v.br, v.br, fma(v.ai, v.ai, v.ar * v.ar)));
-  const double n2 = fma(v.di, v.di, fma(v.dr, v.dr, fma(v.ci, v.ci, v.cr * v.cr)));
-  const int e1 = -(ilogb(n1) >> 1), e2 = -(ilogb(n2) >> 1);
+// Rescales each block by its own exact power of two so that its largest component lies in [1/2, 1).
+__device__ __forceinline__ void rescale_blocks(State& v) {
+  const int e1 = -__builtin_amdgcn_frexp_exp(fmax(fmax(fabs(v.ar), fabs(v.ai)), fmax(fabs(v.br), fabs(v.bi))));
+  const int e2 = -__builtin_amdgcn_frexp_exp(fmax(fmax(fabs(v.cr), fabs(v.ci)), fmax(fabs(v.dr), fabs(v.di))));
   v.ar = ldexp(v.ar, e1); v.ai = ldexp(v.ai, e1); v.br = ldexp(v.br, e1); v.bi = ldexp(v.bi, e1);
   v.cr = ldexp(v.cr, e2); v.ci = ldexp(v.ci, e2); v.dr = ldexp(v.dr, e2); v.di = ldexp(v.di, e2);
 }
 
-// Steps of one chunk in variant MODE; the tangent form then rescales each block.
-template <int MODE>
-__device__ __forceinline__ void run_chunk4(State& v, const double4* buf, int len, double pxdt, double pydt, double e,
-                                           int h) {
-  if constexpr (MODE < kFineHalving) {
-    const Fit<MODE> f = load_fit<MODE>();
-    if (len == kChunk) {
-#pragma unroll 2
-      for (int k = 0; k < kChunk; ++k) step4_tan<MODE>(v, buf[k], pxdt, pydt, e, f);
-    } else {
-      for (int k = 0; k < len; ++k) step4_tan<MODE>(v, buf[k], pxdt, pydt, e, f);
-    }
-    renormalise_blocks(v);
-  } else {
-    const double inv4h = ldexp(1.0, -2 * h);
-    if (len == kChunk) {
-#pragma unroll 2
-      for (int k = 0; k < kChunk; ++k) step4_halving(v, buf[k], pxdt, pydt, e, h, inv4h);
-    } else {
-      for (int k = 0; k < len; ++k) step4_halving(v, buf[k], pxdt, pydt, e, h, inv4h);
-    }
-  }
-}
-
-struct Evolve4Args {
+struct SchemeArgs {
   const PulseDev* desc;
   int n_pulses;
-  const double* Ag;  // [sum nt][2 nodes][2] A at the Gauss-Legendre nodes
+  const double* tab;     // [sum nt][kRec][2] A at the scheme's points of every step
   const double* Aedge;
-  const double* ranges;  // [total_chunks][4] range of the node values per chunk (k_chunk_ranges<2>)
+  const double* ranges;  // [total_chunks][4] range of the table per chunk (k_chunk_ranges<kRec>)
   double* f;
   double* units;
 };
 
-// The chunks of a fourth-order item, as chunk_loop: the record staged per step is
-// (-(A_1 + A_2) dt/2, (sqrt3/6)(A_2 - A_1) dt); each chunk in its variant (chunk_variant<2>).
-template <bool HALVING>
-__device__ __forceinline__ void chunk_loop4(State& v, const double4* tab, int nt, double dt, const double* rg,
-                                            const BlockBox& bb, int bmode, double pxdt, double pydt, double e,
-                                            double4 (*lds)[kChunk]) {
-  const double hdt = -0.5 * dt, kdt = kSqrt3Over6 * dt;
-  const int nchunks = (nt + kChunk - 1) / kChunk;
-  {
-    const double4 t = int(threadIdx.x) < nt ? tab[threadIdx.x] : make_double4(0.0, 0.0, 0.0, 0.0);
-    lds[0][threadIdx.x] = make_double4(hdt * (t.x + t.z), hdt * (t.y + t.w), kdt * (t.z - t.x), kdt * (t.w - t.y));
+__device__ __forceinline__ BlockBox uniform_box(const PulseDev& d, int first) {
+  const BlockBox bb = block_box(d, first / kSelBlock, d.ndist);
+  return BlockBox{uniform(bb.pxl), uniform(bb.pxh), uniform(bb.pyl), uniform(bb.pyh), uniform(bb.pz2)};
+}
+
+// The fourth-order scheme for one lane's mode.  Step s: exp(-i w_s . tau), a multiple of K(|w_s|^2) - i w_s . tau
+// with K = sqrt(x) cot(sqrt x): 50 + 2n instructions for the two blocks (56 + 2n in the tangent form, whose
+// fits need a larger n and end at x = 0.26; 110 and more beyond).  The norm grows by at most 1.58 per step
+// for x <= 2.5, 2^168 over a chunk.  Bound by FP64 issue: 40000 modes x 10000 steps of 0.2 in 1.45 ms (3.2 ms in the
+// tangent form with one workgroup per item, which took 157 of 256 CUs).
+struct Magnus4Scheme {
+  static constexpr int kRec = 2;    // table points per step
+  static constexpr int kWaves = 4;  // per SIMD; 3 would take no spills but 4% longer
+  const double2* tab;
+  double dt, pxdt, pydt, e;
+  BlockBox bb;
+  __device__ __forceinline__ Magnus4Scheme(const SchemeArgs& a, const PulseDev& d, int first, int lane)
+      : tab(reinterpret_cast<const double2*>(a.tab) + 2 * d.tab_off), dt(d.dt), bb(uniform_box(d, first)) {
+    double px, py;
+    e = lane_mode(d, int64_t(first) + lane, px, py) * dt;
+    pxdt = px * dt;
+    pydt = py * dt;
   }
-  __syncthreads();
-  for (int c = 0; c < nchunks; ++c) {
-    const int n = (c + 1) * kChunk + threadIdx.x;
-    const double4 pre = (c + 1 < nchunks && n < nt) ? tab[n] : make_double4(0.0, 0.0, 0.0, 0.0);
-    const double4* buf = lds[c & 1];
-    const int len = min(kChunk, nt - c * kChunk);
-    const int2 cv = chunk_variant<2>(bb, rg, c, bmode, dt);
-    const int mode = __builtin_amdgcn_readfirstlane(cv.x);
-    if constexpr (HALVING) {
-      if (mode == kFineHalving)
-        run_chunk4<kFineHalving>(v, buf, len, pxdt, pydt, e, __builtin_amdgcn_readfirstlane(cv.y));
-      else
-        run_chunk4<kNumFine - 1>(v, buf, len, pxdt, pydt, e, 0);
-    } else {
-      switch (mode) {
-        case 0: run_chunk4<0>(v, buf, len, pxdt, pydt, e, 0); break;
-        case 1: run_chunk4<1>(v, buf, len, pxdt, pydt, e, 0); break;
-        case 2: run_chunk4<2>(v, buf, len, pxdt, pydt, e, 0); break;
-        case 3: run_chunk4<3>(v, buf, len, pxdt, pydt, e, 0); break;
-        case 4: run_chunk4<4>(v, buf, len, pxdt, pydt, e, 0); break;
-        case 5: run_chunk4<5>(v, buf, len, pxdt, pydt, e, 0); break;
-        case 6: run_chunk4<6>(v, buf, len, pxdt, pydt, e, 0); break;
-        default: run_chunk4<7>(v, buf, len, pxdt, pydt, e, 0); break;
+  __device__ __forceinline__ void enter(State&) const {}
+  __device__ __forceinline__ void leave(State&) const {}
+  // the staged record of step n: (-(A_1 + A_2) dt/2, (sqrt3/6)(A_2 - A_1) dt)
+  __device__ __forceinline__ void stage(double2* lds, int n) const {
+    const double hdt = -0.5 * dt, kdt = kSqrt3Over6 * dt;
+    const double2 a1 = tab[2 * int64_t(n)], a2 = tab[2 * int64_t(n) + 1];
+    lds[0] = make_double2(hdt * (a1.x + a2.x), hdt * (a1.y + a2.y));
+    lds[1] = make_double2(kdt * (a2.x - a1.x), kdt * (a2.y - a1.y));
+  }
+  // bound on |w_s|^2 over a chunk's table range
+  __device__ __forceinline__ double bound(const double* rg) const {
+    const double th = sqrt(x_bound(bb, rg[0], rg[1], rg[2], rg[3], dt));
+    return (th + kSqrt3Over6 * th * th) * (th + kSqrt3Over6 * th * th) * (1.0 + 1e-6);
+  }
+  __device__ __forceinline__ Magnus4 angles(const double2* rec, double& xp, double& xm) const {
+    const Magnus4 w = magnus4(make_double4(rec[0].x, rec[0].y, rec[1].x, rec[1].y), pxdt, pydt, e);
+    xp = fma(w.Xp, w.Xp, fma(w.Yp, w.Yp, w.Zp * w.Zp));
+    xm = fma(w.Xm, w.Xm, fma(w.Ym, w.Ym, w.Zm * w.Zm));
+    return w;
+  }
+  template <int V>
+  __device__ __forceinline__ void run_fit(State& v, const double2* buf, int len) const {
+    const CotFit<V> f = load_cot_fit<V>();
+#pragma unroll 2
+    for (int k = 0; k < len; ++k) {
+      double xp, xm;
+      const Magnus4 w = angles(buf + 2 * k, xp, xm);
+      const double Kp = cot_value<V>(xp, f), Km = cot_value<V>(xm, f);
+      rotate_block(v.ar, v.ai, v.br, v.bi, Kp, w.Xp, w.Yp, w.Zp);
+      rotate_block(v.cr, v.ci, v.dr, v.di, Km, w.Xm, -w.Ym, w.Zm);
+    }
+    rescale_blocks(v);
+  }
+  __device__ __forceinline__ void run(State& v, const double2* buf, int len, double xb) const {
+    switch (cot_fit(xb)) {
+      case 0: run_fit<0>(v, buf, len); break;
+      case 1: run_fit<1>(v, buf, len); break;
+      case 2: run_fit<2>(v, buf, len); break;
+      case 3: run_fit<3>(v, buf, len); break;
+      case 4: run_fit<4>(v, buf, len); break;
+      case 5: run_fit<5>(v, buf, len); break;
+      case 6: run_fit<6>(v, buf, len); break;
+      case 7: run_fit<7>(v, buf, len); break;
+      case 8: run_fit<8>(v, buf, len); break;
+      default: {
+        const int h = halvings(xb);
+        const double inv4h = ldexp(1.0, -2 * h);
+        const double2* cs = halving_coef();
+#pragma unroll 1
+        for (int k = 0; k < len; ++k) {
+          double xp, xm, Cp, Sp, Cm, Sm;
+          const Magnus4 w = angles(buf + 2 * k, xp, xm);
+          halved_cos_sinc(xp * inv4h, h, cs, Cp, Sp);
+          halved_cos_sinc(xm * inv4h, h, cs, Cm, Sm);
+          rotate_block(v.ar, v.ai, v.br, v.bi, Cp, Sp * w.Xp, Sp * w.Yp, Sp * w.Zp);
+          rotate_block(v.cr, v.ci, v.dr, v.di, Cm, Sm * w.Xm, -(Sm * w.Ym), Sm * w.Zm);
+        }
       }
     }
-    lds[(c + 1) & 1][threadIdx.x] =
-        make_double4(hdt * (pre.x + pre.z), hdt * (pre.y + pre.w), kdt * (pre.z - pre.x), kdt * (pre.w - pre.y));
-    __syncthreads();
   }
-}
-
-// One 256-mode item of pulse pi, one mode per lane; the structure of process_item, with the
-// series variant per (selection block, chunk) from the range of both node values.
-__device__ __forceinline__ void process_item4(const Evolve4Args& a, int pi, int first, double4 (*lds)[kChunk]) {
-  const PulseDev& d = a.desc[pi];
-  const int nt = d.nt;
-  const double dt = d.dt;
-  const double4* tab = reinterpret_cast<const double4*>(a.Ag) + d.tab_off;
-  const double2* edge = reinterpret_cast<const double2*>(a.Aedge) + 2 * pi;
-  const int64_t m = int64_t(first) + threadIdx.x;
-  double px, py, pz;
-  mode_momentum(d, m < d.ndist ? m : 0, px, py, pz);
-  const double ep = sqrt(fma(pz, pz, 1.0));
-  State v;
-  const double2 ain = edge[0];
-  init_state(v, px - ain.x, py - ain.y, ep);
-  const double pxdt = px * dt, pydt = py * dt, e = ep * dt;
-  const BlockBox bb = block_box(d, first / kSelBlock, d.ndist);
-  const double* rg = a.ranges + 4 * int64_t(d.chk_off);
-  const int bmode = __builtin_amdgcn_readfirstlane(block_variant<2>(bb, rg, (nt + kChunk - 1) / kChunk, dt).x);
-  if (bmode == kFineHalving)
-    chunk_loop4<true>(v, tab, nt, dt, rg, bb, bmode, pxdt, pydt, e, lds);
-  else
-    chunk_loop4<false>(v, tab, nt, dt, rg, bb, bmode, pxdt, pydt, e, lds);
-
-  const double2 aout = edge[1];
-  write_density(d, a.f, a.units, m, m < d.ndist ? project(v, px - aout.x, py - aout.y, ep) : 0.0);
-}
-
-__global__ void __launch_bounds__(kItem) __attribute__((amdgpu_waves_per_eu(4))) k_evolve4(Evolve4Args a) {
-  __shared__ double4 lds[2][kChunk];
-  const int item = xcd_item(blockIdx.x, gridDim.x);
-  const int pi = find_pulse_item(a.desc, a.n_pulses, item);
-  process_item4(a, pi, (item - a.desc[pi].item_off) * kItem, lds);
-}
+};
 
 // ---------------------------------------------------------------------------------------------
 // Split-operator steps: the frozen Hamiltonian splits into the part the field does not touch,
@@ -622,12 +618,11 @@ __global__ void __launch_bounds__(kItem) __attribute__((amdgpu_waves_per_eu(4)))
 //     R(-theta_0) [prod over steps, substeps i: R(theta_i) K_i] R(theta_0),
 // theta_0 = e dt/2 (Strang) or w1 e dt/2, theta_i = e dt (Strang) or ((w1 + w0)/2, (w1 + w0)/2,
 // w1) e dt.  In tangent form R(theta) = cos(theta) (1 - i a tau_z), a = tan(theta), and
-// K = C (1 - i T Q_s) with T = tan|q| / |q| (the evolution's polynomial fits, x = |q|^2); since
-// tau_z Q_s = i (q_x tau_y - s q_y tau_x), the product is 1 - i w_s . tau with
-//     w_s = (u - s a v, s v + a u, a),   u = T q_x, v = T q_y,
-// again a scalar multiple of a unitary matrix, of the same norm for both blocks: one rescaling per
-// chunk, as in the midpoint step (34 + n VALU instructions per substep against 31 + n).  Beyond
-// the fits' range the exact C, S (angle halving) and c = cos(theta), s = sin(theta) give
+// K = C (1 - i T Q_s) with T = tan|q| / |q| (polynomial fits, x = |q|^2); the two factors are applied one
+// after the other: 30 + n instructions per substep.  (Multiplied out, 34 + n.)  Beyond the tangent
+// fits, up to x = 1.6, K is a multiple of |q| cot|q| - i Q_s: 36 + n.  Both are scalar multiples
+// of a unitary matrix, of the same norm for both blocks.  Beyond that the exact C, S (angle halving) and
+// c = cos(theta), s = sin(theta) give
 //     R K = c C - i (S (c q_x - s_b s q_y), S (s_b c q_y + s q_x), s C) . tau,   s_b = +-1.
 // ---------------------------------------------------------------------------------------------
 constexpr double kTripleW1 = 1.3512071919596576;   // 1 / (2 - 2^(1/3))
@@ -652,171 +647,249 @@ __device__ __forceinline__ void phase_z(State& v, double cp, double sp) {
   r = fma(-v.di, sp, v.dr * cp); i = fma(v.dr, sp, v.di * cp); v.dr = r; v.di = i;
 }
 
-template <int V>
-__device__ __forceinline__ void substep_split_tan(State& v, double2 rec, double pxw, double pyw, double a,
-                                                  const Fit<V>& f) {
-  const double qx = pxw + rec.x, qy = pyw + rec.y;  // rec = -A w dt
-  const double x = fma(qx, qx, qy * qy);
-  const double T = tan_ratio<V>(x, f);
-  const double u = T * qx, w = T * qy;
-  rotate_block_tan(v.ar, v.ai, v.br, v.bi, fma(-a, w, u), fma(a, u, w), a);
-  rotate_block_tan(v.cr, v.ci, v.dr, v.di, fma(a, w, u), fma(a, u, -w), a);
+// psi <- (k - i Q_s) psi for both blocks, Q_s = x tau_x + s y tau_y (k = 1 is not multiplied).
+template <bool ONE>
+__device__ __forceinline__ void rotate_xy(State& v, double k, double x, double y) {
+  const auto m = [&](double c) { return ONE ? c : k * c; };
+  const double ar = fma(x, v.bi, fma(-y, v.br, m(v.ar))), ai = fma(-x, v.br, fma(-y, v.bi, m(v.ai)));
+  const double br = fma(x, v.ai, fma(y, v.ar, m(v.br))), bi = fma(-x, v.ar, fma(y, v.ai, m(v.bi)));
+  const double cr = fma(x, v.di, fma(y, v.dr, m(v.cr))), ci = fma(-x, v.dr, fma(y, v.di, m(v.ci)));
+  const double dr = fma(x, v.ci, fma(-y, v.cr, m(v.dr))), di = fma(-x, v.cr, fma(-y, v.ci, m(v.di)));
+  v = State{ar, ai, br, bi, cr, ci, dr, di};
 }
 
-__device__ __forceinline__ void substep_split_halving(State& v, double2 rec, double pxw, double pyw, double c,
-                                                      double s, int h, double inv4h) {
-  const double qx = pxw + rec.x, qy = pyw + rec.y;
-  const double x = fma(qx, qx, qy * qy);
-  double C, S;
-  cos_sinc_halved(x, h, inv4h, C, S);
-  const double cC = c * C, sz = s * C;
-  const double cx = c * qx, cy = c * qy, sx = s * qx, sy = s * qy;
-  rotate_block(v.ar, v.ai, v.br, v.bi, cC, S * (cx - sy), S * (cy + sx), sz);
-  rotate_block(v.cr, v.ci, v.dr, v.di, cC, S * (cx + sy), S * (sx - cy), sz);
+// psi <- (1 - i a tau_z) psi for both blocks.
+__device__ __forceinline__ void tilt_z(State& v, double a) {
+  v = State{fma(a, v.ai, v.ar), fma(-a, v.ar, v.ai), fma(-a, v.bi, v.br), fma(a, v.br, v.bi),
+            fma(a, v.ci, v.cr), fma(-a, v.cr, v.ci), fma(-a, v.di, v.dr), fma(a, v.dr, v.di)};
 }
 
-template <int NSUB, int MODE>
-__device__ __forceinline__ void run_chunk_split(State& v, const double2* buf, int len, const SplitMode<NSUB>& k,
-                                                int h) {
-  if constexpr (MODE < kFineHalving) {
-    const Fit<MODE> f = load_fit<MODE>();
-    if (len == kChunk) {
-#pragma unroll(NSUB == 1 ? 4 : 1)
-      for (int n = 0; n < kChunk; ++n)
-#pragma unroll
-        for (int i = 0; i < NSUB; ++i)
-          substep_split_tan<MODE>(v, buf[n * NSUB + i], k.pxw[split_w(i)], k.pyw[split_w(i)], k.a[split_t(i)], f);
+// The split-operator schemes for one lane's mode.  The series of a chunk bounds |q|^2 <= |p - A|^2
+// (w_max dt)^2 through the second-order bound at step w_max dt, which also counts
+// (1 + p_z^2)(w_max dt)^2 >= theta_i^2: the tangents a stay below 3.3 for the fits in use (x <= 1.61), and
+// the norm below 2^420 over the 64 steps between two rescalings.  Bound by FP64 issue: 40000 modes x 4000 steps of
+// 0.2 in 0.46 (Strang) and 1.40 ms (fourth order); 1.06 and 2.69 ms multiplied out, with angle halving
+// beyond x = 0.26 and one workgroup per item.
+template <int NSUB>
+struct SplitScheme {
+  static constexpr int kRec = NSUB;
+  static constexpr int kWaves = 3;  // 4 would take spills and 2% longer
+  static constexpr int kAngles = NSUB == 1 ? 1 : 2;
+  static constexpr int kFirstCot = 5, kLastCot = 7;  // cotangent fits in use: x <= 0.35, 0.94, 1.61
+  const double2* tab;
+  double dt;
+  double pxw[kAngles], pyw[kAngles];                  // p w dt for the distinct weights
+  double a[kAngles], c[kAngles], s[kAngles];          // tan, cos, sin of theta_i
+  double c0, s0;                                      // of theta_0
+  BlockBox bb;
+  __device__ __forceinline__ static constexpr int weight(int i) { return i == 1 ? 1 : 0; }
+  __device__ __forceinline__ static constexpr int angle(int i) { return i == 2 ? 1 : 0; }
+  __device__ __forceinline__ static constexpr double step(int i) {
+    return NSUB == 1 ? 1.0 : (i == 1 ? kTripleW0 : kTripleW1);
+  }
+  __device__ __forceinline__ SplitScheme(const SchemeArgs& arg, const PulseDev& d, int first, int lane)
+      : tab(reinterpret_cast<const double2*>(arg.tab) + NSUB * d.tab_off), dt(d.dt), bb(uniform_box(d, first)) {
+    double px, py;
+    const double ep = lane_mode(d, int64_t(first) + lane, px, py);
+    double th0;
+    if constexpr (NSUB == 1) {
+      pxw[0] = px * dt;
+      pyw[0] = py * dt;
+      sincos(ep * dt, &s[0], &c[0]);
+      th0 = 0.5 * ep * dt;
     } else {
-      for (int n = 0; n < len; ++n)
-#pragma unroll
-        for (int i = 0; i < NSUB; ++i)
-          substep_split_tan<MODE>(v, buf[n * NSUB + i], k.pxw[split_w(i)], k.pyw[split_w(i)], k.a[split_t(i)], f);
+      pxw[0] = px * (kTripleW1 * dt); pyw[0] = py * (kTripleW1 * dt);
+      pxw[1] = px * (kTripleW0 * dt); pyw[1] = py * (kTripleW0 * dt);
+      sincos(0.5 * (kTripleW1 + kTripleW0) * ep * dt, &s[0], &c[0]);
+      sincos(kTripleW1 * ep * dt, &s[1], &c[1]);
+      th0 = 0.5 * kTripleW1 * ep * dt;
     }
-    renormalise(v);
-  } else {
-    const double inv4h = ldexp(1.0, -2 * h);
-    for (int n = 0; n < len; ++n)
 #pragma unroll
-      for (int i = 0; i < NSUB; ++i)
-        substep_split_halving(v, buf[n * NSUB + i], k.pxw[split_w(i)], k.pyw[split_w(i)], k.c[split_t(i)],
-                              k.s[split_t(i)], h, inv4h);
+    for (int j = 0; j < kAngles; ++j) a[j] = s[j] / c[j];
+    sincos(th0, &s0, &c0);
   }
-}
-
-struct SplitArgs {
-  const PulseDev* desc;
-  int n_pulses;
-  const double* At;  // [sum nt][NSUB][2] A at the substep midpoints
-  const double* Aedge;
-  const double* ranges;  // [total_chunks][4] range of the table per chunk (k_chunk_ranges<NSUB>)
-  double* f;
-  double* units;
-};
-
-// The chunks of an item: NSUB records per step staged through LDS as -A w_i dt (double-buffered,
-// one barrier per chunk), each chunk in its variant for steps of size w_max dt.
-template <int NSUB, bool HALVING>
-__device__ __forceinline__ void chunk_loop_split(State& v, const double2* tab, int nt, double dt, double dtw,
-                                                 const double* rg, const BlockBox& bb, int bmode,
-                                                 const SplitMode<NSUB>& k, double2 (*lds)[NSUB * kChunk]) {
-  const double wdt[3] = {NSUB == 1 ? -dt : -kTripleW1 * dt, -kTripleW0 * dt, -kTripleW1 * dt};
-  const int nchunks = (nt + kChunk - 1) / kChunk;
+  __device__ __forceinline__ void enter(State& v) const { phase_z(v, c0, s0); }
+  __device__ __forceinline__ void leave(State& v) const { phase_z(v, c0, -s0); }
+  __device__ __forceinline__ void stage(double2* lds, int n) const {  // -A w_i dt
 #pragma unroll
-  for (int i = 0; i < NSUB; ++i) {
-    const double2 t = int(threadIdx.x) < nt ? tab[NSUB * threadIdx.x + i] : make_double2(0.0, 0.0);
-    lds[0][NSUB * threadIdx.x + i] = make_double2(t.x * wdt[i], t.y * wdt[i]);
+    for (int i = 0; i < NSUB; ++i) {
+      const double2 t = tab[NSUB * int64_t(n) + i];
+      const double w = -step(i) * dt;
+      lds[i] = make_double2(t.x * w, t.y * w);
+    }
   }
-  __syncthreads();
-  for (int c = 0; c < nchunks; ++c) {
-    double2 pre[NSUB];
-    const int n = (c + 1) * kChunk + threadIdx.x;
+  __device__ __forceinline__ double bound(const double* rg) const {
+    return x_bound(bb, rg[0], rg[1], rg[2], rg[3], NSUB == 1 ? dt : -kTripleW0 * dt);
+  }
+  // V < kNumFine: tangent fit V; else the cotangent fit V - kNumFine
+  template <int V>
+  __device__ __forceinline__ void run_fit(State& v, const double2* buf, int len) const {
+    constexpr bool kTan = V < kNumFine;
+    const auto f = [] {
+      if constexpr (kTan) return load_fit<V>();
+      else return load_cot_fit<V - kNumFine>();
+    }();
+    for (int n0 = 0; n0 < len; n0 += kGroupLong) {
+      const int end = min(n0 + kGroupLong, len);
+#pragma unroll(NSUB == 1 ? 4 : 1)
+      for (int n = n0; n < end; ++n)
 #pragma unroll
-    for (int i = 0; i < NSUB; ++i) pre[i] = (c + 1 < nchunks && n < nt) ? tab[NSUB * n + i] : make_double2(0.0, 0.0);
-    const double2* buf = lds[c & 1];
-    const int len = min(kChunk, nt - c * kChunk);
-    const int2 cv = chunk_variant<1>(bb, rg, c, bmode, dtw);
-    const int mode = __builtin_amdgcn_readfirstlane(cv.x);
-    if constexpr (HALVING) {
-      if (mode == kFineHalving)
-        run_chunk_split<NSUB, kFineHalving>(v, buf, len, k, __builtin_amdgcn_readfirstlane(cv.y));
-      else
-        run_chunk_split<NSUB, kNumFine - 1>(v, buf, len, k, 0);
-    } else {
-      switch (mode) {
-        case 0: run_chunk_split<NSUB, 0>(v, buf, len, k, 0); break;
-        case 1: run_chunk_split<NSUB, 1>(v, buf, len, k, 0); break;
-        case 2: run_chunk_split<NSUB, 2>(v, buf, len, k, 0); break;
-        case 3: run_chunk_split<NSUB, 3>(v, buf, len, k, 0); break;
-        case 4: run_chunk_split<NSUB, 4>(v, buf, len, k, 0); break;
-        case 5: run_chunk_split<NSUB, 5>(v, buf, len, k, 0); break;
-        case 6: run_chunk_split<NSUB, 6>(v, buf, len, k, 0); break;
-        default: run_chunk_split<NSUB, 7>(v, buf, len, k, 0); break;
+        for (int i = 0; i < NSUB; ++i) {
+          const double2 rec = buf[n * NSUB + i];
+          const double qx = pxw[weight(i)] + rec.x, qy = pyw[weight(i)] + rec.y;
+          const double x = fma(qx, qx, qy * qy);
+          if constexpr (kTan) {
+            const double T = tan_ratio<V>(x, f);
+            rotate_xy<true>(v, 1.0, T * qx, T * qy);
+          } else {
+            rotate_xy<false>(v, cot_value<V - kNumFine>(x, f), qx, qy);
+          }
+          tilt_z(v, a[angle(i)]);
+        }
+      rescale(v);
+    }
+  }
+  __device__ __forceinline__ void run(State& v, const double2* buf, int len, double xb) const {
+    const uint32_t hi = __builtin_amdgcn_readfirstlane(__double2hiint(xb));
+    int mode = kNumFine + kCotHalving;
+#pragma unroll
+    for (int k = kLastCot; k >= kFirstCot; --k)
+      if (hi < high_word(kCotXmax[k])) mode = kNumFine + k;
+#pragma unroll
+    for (int k = kNumFine - 1; k >= 0; --k)
+      if (hi < high_word(kFitXmax[k])) mode = k;
+    switch (mode) {
+      case 0: run_fit<0>(v, buf, len); break;
+      case 1: run_fit<1>(v, buf, len); break;
+      case 2: run_fit<2>(v, buf, len); break;
+      case 3: run_fit<3>(v, buf, len); break;
+      case 4: run_fit<4>(v, buf, len); break;
+      case 5: run_fit<5>(v, buf, len); break;
+      case 6: run_fit<6>(v, buf, len); break;
+      case 7: run_fit<7>(v, buf, len); break;
+      case kNumFine + 5: run_fit<kNumFine + 5>(v, buf, len); break;
+      case kNumFine + 6: run_fit<kNumFine + 6>(v, buf, len); break;
+      case kNumFine + 7: run_fit<kNumFine + 7>(v, buf, len); break;
+      default: {
+        const int h = halvings(xb);
+        const double inv4h = ldexp(1.0, -2 * h);
+        const double2* cs = halving_coef();
+#pragma unroll 1
+        for (int n = 0; n < len; ++n)
+#pragma unroll
+          for (int i = 0; i < NSUB; ++i) {
+            const double2 rec = buf[n * NSUB + i];
+            const double qx = pxw[weight(i)] + rec.x, qy = pyw[weight(i)] + rec.y;
+            const double ci = c[angle(i)], si = s[angle(i)];
+            double C, S;
+            halved_cos_sinc(fma(qx, qx, qy * qy) * inv4h, h, cs, C, S);
+            const double cC = ci * C, sz = si * C;
+            const double cx = ci * qx, cy = ci * qy, sx = si * qx, sy = si * qy;
+            rotate_block(v.ar, v.ai, v.br, v.bi, cC, S * (cx - sy), S * (cy + sx), sz);
+            rotate_block(v.cr, v.ci, v.dr, v.di, cC, S * (cx + sy), S * (sx - cy), sz);
+          }
       }
     }
-#pragma unroll
-    for (int i = 0; i < NSUB; ++i)
-      lds[(c + 1) & 1][NSUB * threadIdx.x + i] = make_double2(pre[i].x * wdt[i], pre[i].y * wdt[i]);
+  }
+};
+
+// ---------------------------------------------------------------------------------------------
+// The same launch forms as the midpoint step's for the schemes above: segments of the pulse's own lengths, each
+// evolved from the identity and applied to the state, by one workgroup per item or, where split_in_time
+// says so, one per (item, segment) and a second kernel.
+// ---------------------------------------------------------------------------------------------
+template <class S>
+__device__ __forceinline__ State propagate_scheme(const S& sch, const double* rg, int n0, int n1, double2* lds) {
+  State v{1.0, 0.0, 0.0, 0.0, 1.0, 0.0, 0.0, 0.0};
+  for (int n = n0; n < n1;) {
+    const int c = n / kChunk, len = min((c + 1) * kChunk, n1) - n;
     __syncthreads();
+    for (int i = threadIdx.x; i < len; i += kItem) sch.stage(lds + S::kRec * i, n + i);
+    __syncthreads();
+    sch.run(v, lds, len, sch.bound(rg + 4 * c));
+    n += len;
   }
+  rescale_blocks(v);  // the angle-halving path leaves the norm alone
+  return v;
 }
 
-// One 256-mode item of pulse pi, one mode per lane, the structure of process_item4.  The series
-// variant per (selection block, chunk) bounds |q|^2 <= |p - A|^2 (w_max dt)^2 through the
-// second-order bound at step w_max dt (which also counts (1 + p_z^2)(w_max dt)^2: conservative).
-template <int NSUB>
-__device__ __forceinline__ void process_item_split(const SplitArgs& a, int pi, int first,
-                                                   double2 (*lds)[NSUB * kChunk]) {
-  const PulseDev& d = a.desc[pi];
-  const int nt = d.nt;
-  const double dt = d.dt;
-  const double dtw = NSUB == 1 ? dt : -kTripleW0 * dt;  // the largest substep
-  const double2* tab = reinterpret_cast<const double2*>(a.At) + NSUB * d.tab_off;
-  const double2* edge = reinterpret_cast<const double2*>(a.Aedge) + 2 * pi;
-  const int64_t m = int64_t(first) + threadIdx.x;
-  double px, py, pz;
-  mode_momentum(d, m < d.ndist ? m : 0, px, py, pz);
-  const double ep = sqrt(fma(pz, pz, 1.0));
-  SplitMode<NSUB> k;
-  double th0;
-  if constexpr (NSUB == 1) {
-    k.pxw[0] = px * dt;
-    k.pyw[0] = py * dt;
-    sincos(ep * dt, &k.s[0], &k.c[0]);
-    th0 = 0.5 * ep * dt;
-  } else {
-    k.pxw[0] = px * (kTripleW1 * dt); k.pyw[0] = py * (kTripleW1 * dt);
-    k.pxw[1] = px * (kTripleW0 * dt); k.pyw[1] = py * (kTripleW0 * dt);
-    sincos(0.5 * (kTripleW1 + kTripleW0) * ep * dt, &k.s[0], &k.c[0]);
-    sincos(kTripleW1 * ep * dt, &k.s[1], &k.c[1]);
-    th0 = 0.5 * kTripleW1 * ep * dt;
-  }
-#pragma unroll
-  for (int j = 0; j < (NSUB == 1 ? 1 : 2); ++j) k.a[j] = k.s[j] / k.c[j];
-  double s0, c0;
-  sincos(th0, &s0, &c0);
-  State v;
-  const double2 ain = edge[0];
-  init_state(v, px - ain.x, py - ain.y, ep);
-  phase_z(v, c0, s0);
-  const BlockBox bb = block_box(d, first / kSelBlock, d.ndist);
-  const double* rg = a.ranges + 4 * int64_t(d.chk_off);
-  const int bmode = __builtin_amdgcn_readfirstlane(block_variant<1>(bb, rg, (nt + kChunk - 1) / kChunk, dtw).x);
-  if (bmode == kFineHalving)
-    chunk_loop_split<NSUB, true>(v, tab, nt, dt, dtw, rg, bb, bmode, k, lds);
-  else
-    chunk_loop_split<NSUB, false>(v, tab, nt, dt, dtw, rg, bb, bmode, k, lds);
-  phase_z(v, c0, -s0);
-
-  const double2 aout = edge[1];
-  write_density(d, a.f, a.units, m, m < d.ndist ? project(v, px - aout.x, py - aout.y, ep) : 0.0);
-}
-
-template <int NSUB>
-__global__ void __launch_bounds__(kItem) k_evolve_split(SplitArgs a) {
-  __shared__ double2 lds[2][NSUB * kChunk];
+template <class S>
+__global__ void __launch_bounds__(kItem) k_scheme(SchemeArgs a) {
+  __shared__ double2 lds[S::kRec * kChunk];
   const int item = xcd_item(blockIdx.x, gridDim.x);
   const int pi = find_pulse_item(a.desc, a.n_pulses, item);
-  process_item_split<NSUB>(a, pi, (item - a.desc[pi].item_off) * kItem, lds);
+  const PulseDev& d = a.desc[pi];
+  const int first = (item - d.item_off) * kItem;
+  const int64_t m = int64_t(first) + threadIdx.x;
+  const double2* edge = reinterpret_cast<const double2*>(a.Aedge) + 2 * pi;
+  const double* rg = a.ranges + 4 * int64_t(d.chk_off);
+  const double2 ain = edge[0], aout = edge[1];
+  const S sch(a, d, first, threadIdx.x);
+  double px, py;
+  double e = lane_mode(d, m, px, py);
+  State psi;
+  init_state(psi, px - ain.x, py - ain.y, e);
+  sch.enter(psi);
+  for (int n0 = 0; n0 < d.nt; n0 += d.seg_len) {
+    const State v = propagate_scheme(sch, rg, n0, min(n0 + d.seg_len, d.nt), lds);
+    apply_propagator(psi, v);
+    rescale(psi);
+  }
+  sch.leave(psi);
+  e = lane_mode(d, m, px, py);
+  write_density(d, a.f, a.units, m, m < d.ndist ? project(psi, px - aout.x, py - aout.y, e) : 0.0);
+}
+
+template <class S>
+__global__ void __launch_bounds__(kItem) __attribute__((amdgpu_waves_per_eu(S::kWaves)))
+k_scheme_segments(SchemeArgs a, double* __restrict__ prop) {
+  __shared__ double2 lds[S::kRec * kChunk];
+  const int64_t slot = blockIdx.x;
+  const int pi = find_pulse_slot(a.desc, a.n_pulses, slot);
+  const PulseDev& d = a.desc[pi];
+  const int rel = int(slot - d.slot_off), li = rel / d.nseg, seg = rel - li * d.nseg;
+  const S sch(a, d, li * kItem, threadIdx.x);
+  store_state(prop, slot, propagate_scheme(sch, a.ranges + 4 * int64_t(d.chk_off), seg * d.seg_len,
+                                           min((seg + 1) * d.seg_len, d.nt), lds));
+}
+
+template <class S>
+__global__ void __launch_bounds__(64) k_scheme_join(SchemeArgs a, const double* __restrict__ prop) {
+  const int item = blockIdx.x / (kItem / 64), lane = (blockIdx.x % (kItem / 64)) * 64 + threadIdx.x;
+  const int pi = find_pulse_item(a.desc, a.n_pulses, item);
+  const PulseDev& d = a.desc[pi];
+  const int li = item - d.item_off;
+  const int64_t m = int64_t(li) * kItem + lane;
+  const double2* edge = reinterpret_cast<const double2*>(a.Aedge) + 2 * pi;
+  const double2 ain = edge[0], aout = edge[1];
+  const S sch(a, d, li * kItem, lane);
+  double px, py;
+  const double e = lane_mode(d, m, px, py);
+  State psi;
+  init_state(psi, px - ain.x, py - ain.y, e);
+  sch.enter(psi);
+  apply_segments(psi, prop, d.slot_off + int64_t(li) * d.nseg, d.nseg, lane);
+  sch.leave(psi);
+  write_density(d, a.f, a.units, m, m < d.ndist ? project(psi, px - aout.x, py - aout.y, e) : 0.0);
+}
+
+// d_prop: propagators of the batch's slots, or NULL for the form without.
+template <class S>
+po_status launch_scheme(const Batch& b, const PulseDev* d_desc, const double* d_tab, const double* d_A_edge,
+                        double* d_ranges, double* d_prop, double* d_f, double* d_units, hipStream_t s) {
+  const int max_chunks = (b.max_nt + kChunk - 1) / kChunk;
+  const SchemeArgs a{d_desc, b.n_pulses, d_tab, d_A_edge, d_ranges, d_f, d_units};
+  hipLaunchKernelGGL(k_chunk_ranges<S::kRec>, dim3(max_chunks, b.n_pulses), dim3(256), 0, s, d_desc, d_tab, d_ranges);
+  PO_HIP(hipGetLastError());
+  if (d_prop) {
+    hipLaunchKernelGGL(k_scheme_segments<S>, dim3(unsigned(b.total_slots)), dim3(kItem), 0, s, a, d_prop);
+    PO_HIP(hipGetLastError());
+    hipLaunchKernelGGL(k_scheme_join<S>, dim3(unsigned(b.total_items) * (kItem / 64)), dim3(64), 0, s, a, d_prop);
+  } else {
+    hipLaunchKernelGGL(k_scheme<S>, dim3(b.total_items), dim3(kItem), 0, s, a);
+  }
+  PO_HIP(hipGetLastError());
+  return PO_OK;
 }
 
 }  // namespace
@@ -934,38 +1007,16 @@ po_status launch_yield_from_units(const Batch& b, const PulseDev* d_desc, const 
   return PO_OK;
 }
 
-po_status launch_chunk_ranges4(const Batch& b, const PulseDev* d_desc, const double* d_Ag, double* d_ranges,
-                               hipStream_t s) {
-  const int max_chunks = (b.max_nt + kChunk - 1) / kChunk;
-  hipLaunchKernelGGL(k_chunk_ranges<2>, dim3(max_chunks, b.n_pulses), dim3(256), 0, s, d_desc, d_Ag, d_ranges);
-  PO_HIP(hipGetLastError());
-  return PO_OK;
+po_status launch_evolve4(const Batch& b, const PulseDev* d_desc, const double* d_Ag, const double* d_A_edge,
+                         double* d_ranges, double* d_prop, double* d_f, double* d_units, hipStream_t s) {
+  return launch_scheme<Magnus4Scheme>(b, d_desc, d_Ag, d_A_edge, d_ranges, d_prop, d_f, d_units, s);
 }
 
-po_status launch_evolve4_grid(const Batch& b, const PulseDev* d_desc, const double* d_Ag, const double* d_A_edge,
-                              const double* d_ranges, double* d_f, double* d_units, hipStream_t s) {
-  Evolve4Args a{d_desc, b.n_pulses, d_Ag, d_A_edge, d_ranges, d_f, d_units};
-  hipLaunchKernelGGL(k_evolve4, dim3(b.total_items), dim3(kItem), 0, s, a);
-  PO_HIP(hipGetLastError());
-  return PO_OK;
-}
-
-po_status launch_evolve_split_grid(const Batch& b, int order, const PulseDev* d_desc, const double* d_At,
-                                   const double* d_A_edge, double* d_ranges, double* d_f, double* d_units,
-                                   hipStream_t s) {
-  const int max_chunks = (b.max_nt + kChunk - 1) / kChunk;
-  SplitArgs a{d_desc, b.n_pulses, d_At, d_A_edge, d_ranges, d_f, d_units};
-  if (order == 2) {
-    hipLaunchKernelGGL(k_chunk_ranges<1>, dim3(max_chunks, b.n_pulses), dim3(256), 0, s, d_desc, d_At, d_ranges);
-    PO_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_evolve_split<1>, dim3(b.total_items), dim3(kItem), 0, s, a);
-  } else {
-    hipLaunchKernelGGL(k_chunk_ranges<3>, dim3(max_chunks, b.n_pulses), dim3(256), 0, s, d_desc, d_At, d_ranges);
-    PO_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_evolve_split<3>, dim3(b.total_items), dim3(kItem), 0, s, a);
-  }
-  PO_HIP(hipGetLastError());
-  return PO_OK;
+po_status launch_evolve_split(const Batch& b, int order, const PulseDev* d_desc, const double* d_At,
+                              const double* d_A_edge, double* d_ranges, double* d_prop, double* d_f, double* d_units,
+                              hipStream_t s) {
+  return order == 2 ? launch_scheme<SplitScheme<1>>(b, d_desc, d_At, d_A_edge, d_ranges, d_prop, d_f, d_units, s)
+                    : launch_scheme<SplitScheme<3>>(b, d_desc, d_At, d_A_edge, d_ranges, d_prop, d_f, d_units, s);
 }
 
 }  // namespace po

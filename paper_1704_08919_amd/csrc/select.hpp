@@ -29,25 +29,8 @@ __device__ __forceinline__ BlockBox block_box(const PulseDev& d, int b, int64_t 
   return BlockBox{fmin(px0, px1), fmax(px0, px1), fmin(py0, py1), fmax(py0, py1), fmax(pz0 * pz0, pz1 * pz1)};
 }
 
-// Series variant (x: index of the T fits or kFineHalving; y: angle halvings) for a bound xb on
-// the step angle squared.  For a block box against a range [lx, hx] x [ly, hy] of table values,
-// with the largest |p - A| per component,
-//   x = (omega dt)^2 <= dt^2 [ max|p_x - A_x|^2 + max|p_y - A_y|^2 + 1 + max p_z^2 ].
-__device__ __forceinline__ int2 variant_for_x(double xb) {
-  int mode = kFineHalving, h = 0;
-  for (int k = kNumFine - 1; k >= 0; --k)
-    if (xb <= kFitXmax[k]) mode = k;
-  if (mode == kFineHalving) {
-    double x = xb;
-    while (x > kCosSinXmax && h < kMaxHalvings) {
-      x *= 0.25;
-      ++h;
-    }
-  }
-  return make_int2(mode, h);
-}
-
-// Bound on (omega dt)^2 for a block box against a range [lx, hx] x [ly, hy] of table values.
+// Bound on x = (omega dt)^2 for a block box against a range [lx, hx] x [ly, hy] of table values, with the largest
+// |p - A| per component: dt^2 [ max|p_x - A_x|^2 + max|p_y - A_y|^2 + 1 + max p_z^2 ].
 __device__ __forceinline__ double x_bound(const BlockBox& bb, double lx, double hx, double ly, double hy, double dt) {
   const double X = fmax(fmax(bb.pxh - lx, hx - bb.pxl), 0.0);
   const double Y = fmax(fmax(bb.pyh - ly, hy - bb.pyl), 0.0);
