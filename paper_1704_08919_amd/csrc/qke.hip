@@ -20,14 +20,15 @@
 //
 // Tables: E, dE/dt and A at the 2 nt + 1 half-step points t_i + h dt/2 of each pulse.  A
 // workgroup of 256 lanes owns 256 consecutive modes (one per lane); per chunk of 128 steps each
-// lane stages one point -- (A_x, A_y), (E_x, E_y), (|E|^2, (E x dE/dt)_z dt/2) -- into LDS
-// (double-buffered) and every lane reads the same record (broadcast).  The coefficients at
-// t_n + dt are carried to the next step, so each step evaluates them at two new points.
+// lane stages one point into LDS (a ring of two chunks) and every lane reads the same record
+// (broadcast).  The coefficients at t_n + dt are carried to the next step, so each step evaluates them
+// at two new points.
 //
-// Bound by FP64 issue: about 150 FP64 instructions and four reciprocal square roots per step, 4 cycles
-// each even with one wave per SIMD: 65536 modes x 12000 steps take 4.25 ms (5.8 ms with the math
-// library's rsqrt, which classifies its argument and scales the result; 4.5 ms with two steps per
-// loop iteration, and with the root of X taken whether or not X > 0).
+// Bound by FP64 issue, 141 FP64 instructions and four reciprocal square roots per step, with one wave per SIMD at
+// 65536 modes: 12000 steps take 4.0 ms.  The next step's coefficients are formed alongside this step's
+// stages, which do not depend on them: 4.25 ms when formed at the step's start, where the wave
+// waits for them.  (5.8 ms with the math library's rsqrt, which classifies its argument and scales the
+// result, and a test of X per lane.)
 #include "reduce.hpp"
 
 #pragma clang fp contract(off)
@@ -52,8 +53,11 @@ struct Coef {
   double q, W, r;
 };
 
+// (A_x, A_y), (E_x, E_y), (|E|^2, (E x dE/dt)_z dt/2), and dt/2.  Where E = 0, |E|^2 is replaced by a tiny number
+// and dt/2 by 0: then X > 0 always and Q = R = 0 come out without a test per lane.
 struct Point {
-  double2 a, e, s;  // (A_x, A_y), (E_x, E_y), (|E|^2, (E x dE/dt)_z dt/2)
+  double2 a, e, s;
+  double hdt;
 };
 
 // 1/sqrt(x) for normal x > 0: the hardware estimate (23 bits or more) and one step of third order,
@@ -65,10 +69,9 @@ __device__ __forceinline__ double rsqrt_pos(double x) {
   return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
-// s.y of the point comes multiplied by dt/2.
+// X as e_perp^2 |E|^2 + (E x P)_z^2, which is the same without the difference.
 template <bool LINEAR>
-__device__ __forceinline__ Coef coef_at(const Point& pt, double px, double py, double e2, double ep, double dt,
-                                        double hdt) {
+__device__ __forceinline__ Coef coef_at(const Point& pt, double px, double py, double e2, double ep, double dt) {
   const double Px = px - pt.a.x, Py = py - pt.a.y;
   const double t2 = fma(Py, Py, e2);  // 1 + P_y^2 + p_z^2
   const double w2 = fma(Px, Px, t2);
@@ -77,13 +80,13 @@ __device__ __forceinline__ Coef coef_at(const Point& pt, double px, double py, d
   Coef c;
   c.W = w * dt;
   if constexpr (LINEAR) {
-    c.q = (pt.e.x * sqrt(t2)) * (rw * rw) * hdt;
+    c.q = (pt.e.x * sqrt(t2)) * (rw * rw) * pt.hdt;
     c.r = 0.0;
   } else {
-    const double EP = fma(pt.e.x, Px, pt.e.y * Py);
-    const double X = fma(w2, pt.s.x, -(EP * EP));
-    const double rX = X > 0.0 ? rsqrt_pos(X) : 0.0;  // Q = R = 0 where X = 0
-    c.q = (X * rX) * ((rw * rw) * hdt);
+    const double cross = fma(pt.e.x, Py, -(pt.e.y * Px));
+    const double X = fma(cross, cross, e2 * pt.s.x);
+    const double rX = rsqrt_pos(X);
+    c.q = (X * rX) * ((rw * rw) * pt.hdt);
     c.r = ((ep * w) * pt.s.y) * (rX * rX);
   }
   return c;
@@ -93,20 +96,23 @@ struct Y6 {
   double f, c2, c3, c4, c5, c6;
 };
 
-template <bool LINEAR>
-__device__ __forceinline__ Y6 rhs(const Y6& y, const Coef& k) {
+// K(y) + add (ADD) or K(y).
+template <bool LINEAR, bool ADD = false>
+__device__ __forceinline__ Y6 rhs(const Y6& y, const Coef& k, const Y6& add = Y6{}) {
+  const auto first = [](double a, double b, double c) { return ADD ? fma(a, b, c) : a * b; };
   Y6 o;
-  o.f = k.q * y.c2;
+  o.f = first(k.q, y.c2, add.f);
+  const double q = ADD ? k.q + add.c2 : k.q;
   if constexpr (LINEAR) {
-    o.c2 = fma(-k.W, y.c3, fma(-k.q, y.f, k.q));
-    o.c3 = k.W * y.c2;
+    o.c2 = fma(-k.W, y.c3, fma(-k.q, y.f, q));
+    o.c3 = first(k.W, y.c2, add.c3);
     o.c4 = o.c5 = o.c6 = 0.0;
   } else {
-    o.c2 = fma(k.r, y.c4, fma(-k.W, y.c3, fma(-k.q, y.f, k.q)));
-    o.c3 = fma(-k.r, y.c5, k.W * y.c2);
-    o.c4 = fma(k.W, y.c5, -(k.r * y.c2));
-    o.c5 = fma(k.q, y.c6, fma(-k.W, y.c4, k.r * y.c3));
-    o.c6 = -(k.q * y.c5);
+    o.c2 = fma(k.r, y.c4, fma(-k.W, y.c3, fma(-k.q, y.f, q)));
+    o.c3 = fma(-k.r, y.c5, first(k.W, y.c2, add.c3));
+    o.c4 = fma(k.W, y.c5, first(-k.r, y.c2, add.c4));
+    o.c5 = fma(k.q, y.c6, fma(-k.W, y.c4, first(k.r, y.c3, add.c5)));
+    o.c6 = first(-k.q, y.c5, add.c6);
   }
   return o;
 }
@@ -125,20 +131,20 @@ __device__ __forceinline__ void rk4_step(Y6& y, const Coef& k0, const Coef& k1, 
   const Y6 K1 = rhs<LINEAR>(y, k0);
   const Y6 K2 = rhs<LINEAR>(add(y, K1), k1);
   const Y6 K3 = rhs<LINEAR>(add(y, K2), k1);
-  const Y6 K4 = rhs<LINEAR>(axpy(y, 2.0, K3), k2);
-  const Y6 s = add(axpy(axpy(K1, 2.0, K2), 2.0, K3), K4);
+  const Y6 s = rhs<LINEAR, true>(axpy(y, 2.0, K3), k2, axpy(axpy(K1, 2.0, K2), 2.0, K3));
   y = axpy(y, 1.0 / 3.0, s);
 }
 
 __device__ __forceinline__ Point load_point(const double2* __restrict__ E, const double2* __restrict__ Ed,
                                             const double2* __restrict__ A, int64_t h, double hdt) {
   const double2 a = A[h], e = E[h], ed = Ed[h];
-  return Point{a, e, make_double2(fma(e.x, e.x, e.y * e.y), fma(e.x, ed.y, -(e.y * ed.x)) * hdt)};
+  const double e2 = fma(e.x, e.x, e.y * e.y);
+  return Point{a, e, make_double2(e2 > 0.0 ? e2 : 1e-290, fma(e.x, ed.y, -(e.y * ed.x)) * hdt), e2 > 0.0 ? hdt : 0.0};
 }
 
 template <bool LINEAR>
 __global__ void __launch_bounds__(kQPoints) k_qke(QkeArgs a) {
-  __shared__ Point lds[2][kQPoints];
+  __shared__ Point lds[2 * kQPoints];  // points of two chunks, a ring
   const int item = xcd_item(blockIdx.x, gridDim.x);
   const int pi = find_pulse_item(a.desc, a.n_pulses, item);
   const PulseDev& d = a.desc[pi];
@@ -154,27 +160,32 @@ __global__ void __launch_bounds__(kQPoints) k_qke(QkeArgs a) {
   mode_momentum(d, m < d.ndist ? m : 0, px, py, pz);
   const double e2 = fma(pz, pz, 1.0), ep = sqrt(e2);
 
-  // chunk c holds the points h = 2 c kQChunk + 1 + i, i < kQPoints
+  // chunk c holds the points h = 2 c kQChunk + 1 + i, i < kQPoints, in half c & 1 of the ring
   const int nchunks = (nt + kQChunk - 1) / kQChunk;
-  {
-    const int64_t h = 1 + threadIdx.x;
-    lds[0][threadIdx.x] = h < npts ? load_point(E, Ed, A, h, hdt) : Point{};
-  }
-  Coef k0 = coef_at<LINEAR>(load_point(E, Ed, A, 0, hdt), px, py, e2, ep, dt, hdt);
+  const auto fetch = [&](int c) {
+    const int64_t h = int64_t(c) * kQPoints + 1 + threadIdx.x;
+    return h < npts ? load_point(E, Ed, A, h, hdt) : Point{};
+  };
+  lds[threadIdx.x] = fetch(0);
+  Point next = fetch(1);
+  Coef k0 = coef_at<LINEAR>(load_point(E, Ed, A, 0, hdt), px, py, e2, ep, dt);
   __syncthreads();
+  Coef k1 = coef_at<LINEAR>(lds[0], px, py, e2, ep, dt), k2 = coef_at<LINEAR>(lds[1], px, py, e2, ep, dt);
   Y6 y{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   for (int c = 0; c < nchunks; ++c) {
-    const int64_t h = int64_t(c + 1) * kQPoints + 1 + threadIdx.x;
-    const Point pre = (c + 1 < nchunks && h < npts) ? load_point(E, Ed, A, h, hdt) : Point{};
-    const Point* buf = lds[c & 1];
+    const int half = (c & 1) * kQPoints;
+    lds[(half + kQPoints + threadIdx.x) & (2 * kQPoints - 1)] = next;
+    __syncthreads();
+    next = fetch(c + 2);
     const int len = min(kQChunk, nt - c * kQChunk);
     for (int k = 0; k < len; ++k) {
-      const Coef k1 = coef_at<LINEAR>(buf[2 * k], px, py, e2, ep, dt, hdt);
-      const Coef k2 = coef_at<LINEAR>(buf[2 * k + 1], px, py, e2, ep, dt, hdt);
+      const Point* pt = lds + ((half + 2 * k + 2) & (2 * kQPoints - 1));
+      const Coef n1 = coef_at<LINEAR>(pt[0], px, py, e2, ep, dt), n2 = coef_at<LINEAR>(pt[1], px, py, e2, ep, dt);
       rk4_step<LINEAR>(y, k0, k1, k2);
       k0 = k2;
+      k1 = n1;
+      k2 = n2;
     }
-    lds[(c + 1) & 1][threadIdx.x] = pre;
     __syncthreads();
   }
 
