@@ -426,7 +426,7 @@ __global__ void __launch_bounds__(256) k_out_fwd(const __bf16* __restrict__ h, c
 // are those of the layer-by-layer kernels (mm_body, k_out_train), in their order.
 // A batch of 1024 fills 32 of the chip's 256 compute units, and each wave waits for a chain of loads, products
 // and activation functions: 24 us for three layers of 256 (32 with row-major copies, 39 also without the early
-// loads and with eight waves; a training step, with k_step, 38 us against 68 in nine launches).  16 samples
+// loads and with eight waves; a training step, with k_step, 33 us against 68 in nine launches).  16 samples
 // per workgroup would halve the activation functions' share, but add the bias and output
 // gradients in another order, which Adam turns into other weights within a few steps.  Wider
 // networks take the layer-by-layer kernels, whose products fill the chip by themselves.
@@ -1287,6 +1287,14 @@ po_status adam_launch(po_mlp* a, int B, const float* g_in, float* g_out, float l
 // graph already holds them, then replays it `steps` times on stream s.
 po_status train_replay(po_mlp* a, const double* d_x, const float* d_t, const double* d_J, const int* d_idx, int n_rows,
                        double mean, double inv_std, int B, float lr, float* d_loss, int steps, hipStream_t s) {
+  if (net_fused(a)) {  // two launches per 30 us of work: the host keeps ahead (a step 33 us, 38 as a graph of them)
+    const RowMap rows{d_idx, a->ctr, B, n_rows};
+    for (int i = 0; i < steps; ++i) {
+      PO_TRY(launch_net<true>(a, d_x, rows, d_t, d_J, mean, inv_std, B, a->y, 1, s));
+      PO_TRY(launch_step(a, B, lr, d_loss, d_idx ? 1 : 0, s));
+    }
+    return PO_OK;
+  }
   const bool same = a->exec && a->key_x == d_x && a->key_t == d_t && a->key_J == d_J && a->key_idx == d_idx &&
                     a->key_loss == d_loss && a->key_batch == B && a->key_rows == n_rows && a->key_lr == lr &&
                     a->key_mean == mean && a->key_istd == inv_std;
@@ -1297,14 +1305,8 @@ po_status train_replay(po_mlp* a, const double* d_x, const float* d_t, const dou
     a->graph = nullptr;
     PO_HIP(hipStreamBeginCapture(a->cap, hipStreamCaptureModeThreadLocal));
     RowMap rows{d_idx, a->ctr, B, n_rows};
-    po_status st;
-    if (net_fused(a)) {
-      st = launch_net<true>(a, d_x, rows, d_t, d_J, mean, inv_std, B, a->y, 1, a->cap);
-      if (st == PO_OK) st = launch_step(a, B, lr, d_loss, d_idx ? 1 : 0, a->cap);
-    } else {
-      st = grad_impl(a, d_x, rows, d_t, d_J, mean, inv_std, B, a->cap);
-      if (st == PO_OK) st = adam_launch(a, B, nullptr, a->g, lr, d_loss, d_idx ? 1 : 0, a->cap);
-    }
+    po_status st = grad_impl(a, d_x, rows, d_t, d_J, mean, inv_std, B, a->cap);
+    if (st == PO_OK) st = adam_launch(a, B, nullptr, a->g, lr, d_loss, d_idx ? 1 : 0, a->cap);
     hipGraph_t g = nullptr;
     const hipError_t e = hipStreamEndCapture(a->cap, &g);
     if (st != PO_OK) {
