@@ -452,18 +452,18 @@ po_status po_mlp_loss_grad(struct po_mlp* net, const double* d_x, const float* d
                            float* d_loss, float* d_grad, void* stream);
 /* One Adam step with d_grad (NULL = the network's last gradient). */
 po_status po_mlp_adam_step(struct po_mlp* net, const float* d_grad, float lr, void* stream);
-/* po_mlp_loss_grad followed by po_mlp_adam_step (bitwise the same result).  The step's launches
- * are captured into a HIP graph on the first call with a given set of pointers, batch and lr, and
- * the graph is replayed by later calls with the same arguments. */
+/* po_mlp_loss_grad followed by po_mlp_adam_step (bitwise the same result).  Networks with width and
+ * n_in up to 512 take two launches; the launches of wider ones are captured into a HIP graph on the first
+ * call with a given set of pointers, batch and lr, and the graph is replayed by later calls with
+ * the same arguments. */
 po_status po_mlp_train_step(struct po_mlp* net, const double* d_x, const float* d_target, int32_t batch,
                             float lr, float* d_loss, void* stream);
 /* `steps` training steps on minibatches drawn from a data set held on the device:
  *  d_X [n_rows][n_in] double (16-byte aligned) and d_J [n_rows] double (yields); step s uses the
  *  rows d_idx[s batch .. s batch + batch - 1] (int32; entries outside [0, n_rows) read row 0) with
  *  targets (log10(max(J, 1e-300)) - mean) * inv_std, the standardisation of po_log10_standardize;
- *  d_losses [steps] float or NULL receives each step's loss.  Each step is the graph of
- *  po_mlp_train_step (captured once per set of arguments), replayed without host work between
- *  steps. */
+ *  d_losses [steps] float or NULL receives each step's loss.  Each step is that of
+ *  po_mlp_train_step, without host work between steps. */
 po_status po_mlp_train_indexed(struct po_mlp* net, const double* d_X, const double* d_J, int32_t n_rows,
                                const int32_t* d_idx, int32_t steps, int32_t batch, double mean,
                                double inv_std, float lr, float* d_losses, void* stream);

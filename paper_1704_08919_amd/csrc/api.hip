@@ -181,7 +181,9 @@ po_status build_batch(int32_t n, const po_pulse_spec* specs, const po_grid* grid
       d.nlines = int32_t(std::floor((s.omega_max - s.omega_min) / d.dw + 1e-9)) + 1;
       d.norm = s.norm;
       d.norm_value = s.norm_value;
-      d.stat_blocks = s.norm == PO_NORM_NONE ? 0 : (s.nt + 1 + 255) / 256;
+      d.stat_blocks =
+          s.norm == PO_NORM_NONE ? 0 : (image_bases(s.nt, s.norm == PO_NORM_PEAK ? s.nt : s.nt - 1) + 255) / 256;
+      b->max_bases = std::max(b->max_bases, image_bases(s.nt, s.nt - 1));
       tab += s.nt;
       chunks += (s.nt + kChunkSteps - 1) / kChunkSteps;
       coeff += 4 * int64_t(s.n_s);

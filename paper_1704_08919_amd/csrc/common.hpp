@@ -76,6 +76,12 @@ struct PulseDev {
   double lo[3], dp[3];  // p_d = lo_d + (i + 1/2) dp_d; dp_d = 0 for a sheet (then p_d = lo_d)
 };
 
+// Base points whose images (t -> -t and, for even nt, t -> t + T/2) cover points 0..last of a pulse; last is
+// nt - 1 for step midpoints, nt for nodes.
+__host__ __device__ inline int image_bases(int nt, int last) {
+  return nt % 2 ? last / 2 + 1 : (last - nt / 2) / 2 + 1;
+}
+
 struct Batch {
   int32_t n_pulses = 0;
   int64_t total_rows = 0, total_modes = 0, total_coeff = 0, total_spec = 0;
@@ -85,6 +91,7 @@ struct Batch {
   int32_t total_items = 0;     // workgroups of the default evolution launch
   int64_t total_slots = 0;     // (256-mode item, time segment) pairs of all pulses
   int32_t total_chunks = 0;    // kChunkSteps-step chunks of all pulses
+  int32_t max_bases = 0;       // largest per-pulse count of base points of the table synthesis (image_bases)
   int32_t max_stat_blocks = 0; // largest per-pulse block count of the field statistics pass
   int32_t max_nt = 0;
   int32_t max_lines = 0;       // most spectral lines of any pulse

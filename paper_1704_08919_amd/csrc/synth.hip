@@ -18,11 +18,12 @@
 // FMAs per wanted component, E from the raw lines (times the window, so that it vanishes at the ends
 // to relative precision) and A from P and Q: 12 operations for E and A, against about 120 when the
 // three frequencies of every line are summed separately.  The records are equal for all lanes and come
-// through scalar loads, four records in flight.  Bound by FP64 issue on large batches: 256 pulses x
-// 16384 steps x 128 lines take 0.36 ms for A and E and 0.27 ms for the peak (2.06 and 0.47 ms when each
-// line's three frequencies and the divisions by them were formed per step; 134 MB of tables are 0.03
-// ms).  A single pulse (16 workgroups) is a chain of rotations and exact phases: 9 and 13 us for 66
-// harmonics, 72 and 11 us before.
+// through scalar loads, four records in flight.  The tables and the statistics take a point together with
+// its images in time (ImageSums), a quarter of that per point.  Bound by FP64 issue on large batches, with
+// the exact phases a third of it: 256 pulses x 16384 steps x 128 lines take 0.12 ms for A and E and 0.09 ms for the peak
+// (0.36 and 0.27 ms point by point; 2.06 and 0.47 ms when each line's three frequencies and the
+// divisions by them were formed per step; 134 MB of tables are 0.03 ms).  A single pulse is a chain of
+// rotations and exact phases: 11 and 12 us for 66 harmonics, 72 and 11 us before.
 #include "common.hpp"
 
 namespace po {
@@ -125,12 +126,17 @@ __device__ void line_spectrum(const PulseDev& d, const double* __restrict__ a, i
 // Harmonic records of a pulse, kSpecRec doubles each for k = nmin - 1 + i, i = 0..nlines + 1 (padded with
 // zero records to a multiple of kSpecPad): the raw line
 // (cEx, sEx, cEy, sEy) (cE = E cos Phi, sE = E sin Phi; 0 for the two outer records) and (Px, Qx, Py,
-// Qy); then (A_0x, A_0y, C_0x, C_0y).  One workgroup per pulse, in tiles of kSpecTile harmonics.
+// Qy); then (A_0x, A_0y, C_0x, C_0y).  One workgroup per pulse, in tiles of kSpecTile harmonics.  It also
+// empties the chunk ranges that k_tables fills.
 constexpr int kSpecTile = 126;
 
 __global__ void __launch_bounds__(128) k_spectra(const PulseDev* __restrict__ desc,
-                                                 const double* __restrict__ coeff, double* __restrict__ spec) {
+                                                 const double* __restrict__ coeff, double* __restrict__ spec,
+                                                 double* __restrict__ ranges) {
   const PulseDev d = desc[blockIdx.x];
+  if (ranges)
+    for (int i = threadIdx.x; i < 4 * ((d.nt + kChunkSteps - 1) / kChunkSteps); i += 128)
+      ranges[4 * int64_t(d.chk_off) + i] = (i & 1) ? -INFINITY : INFINITY;
   const double* a = coeff + d.coeff_off;
   __shared__ double4 raw[128];
   __shared__ double red[4][128];
@@ -247,11 +253,11 @@ __device__ __forceinline__ FieldSums field_sums(const PulseDev& d, const double*
   return o;
 }
 
-// A(t) from the sums, t - t_f = tmf.
-__device__ __forceinline__ double2 potential(const PulseDev& d, const double* __restrict__ rec, const FieldSums& o,
+// A(t) from its sums over the harmonics, t - t_f = tmf.
+__device__ __forceinline__ double2 potential(const PulseDev& d, const double* __restrict__ rec, double ax, double ay,
                                              double tmf) {
   const double* e = rec + int64_t(kSpecRec) * spec_records(d.nlines);
-  return make_double2(e[0] - (e[2] * tmf + o.ax), e[1] - (e[3] * tmf + o.ay));
+  return make_double2(e[0] - (e[2] * tmf + ax), e[1] - (e[3] * tmf + ay));
 }
 
 // A(t_i) = C_0 T and A(t_f) = 0: all harmonics return to their values at t_f.
@@ -262,6 +268,91 @@ __device__ __forceinline__ void write_edges(const PulseDev& d, const double* __r
   edge[1] = make_double2(0.0, 0.0);
 }
 
+// Times come in images of one another: -theta changes the sign of the sines, theta + pi that of the odd harmonics.  So
+// one walk over the harmonics with the sums kept apart by cos or sin and by parity gives the field at theta,
+// -theta, theta + pi and -(theta + pi), which are four grid points where nt is even (two where it is odd): a
+// quarter of the rotations and products per point.
+template <bool WA>
+struct ImageSums {
+  double c[WA ? 4 : 2][2], s[WA ? 4 : 2][2];  // [E_x, E_y, A_x, A_y][parity of the record]
+};
+
+constexpr int kImages = 4;
+
+// First double of every record, one per thread: asks for the pulse's records as a whole, so that the walk's scalar
+// loads, four records at a time, find them in its L2 (k_spectra wrote them elsewhere): 12 us instead of 16 for one
+// pulse, in the kernel that reads them first.  The value is
+// used (keep) after the walk, which does not wait for it.
+__device__ __forceinline__ double warm_records(const PulseDev& d, const double* __restrict__ rec) {
+  double w = 0.0;
+  for (int i = threadIdx.x; i < min(spec_records(d.nlines), 1024); i += 256) w += rec[int64_t(kSpecRec) * i];
+  return w;
+}
+__device__ __forceinline__ void keep(double w) { asm volatile("" ::"v"(w)); }
+
+template <bool WE, bool WA>
+__device__ __forceinline__ ImageSums<WA> image_sums(const PulseDev& d, const double* __restrict__ rec, int64_t hm) {
+  const int64_t two_nt = 2 * int64_t(d.nt);
+  const double inv_nt = 1.0 / double(d.nt);
+  const int nh = spec_records(d.nlines), k0 = d.nmin - 1;
+  int64_t r = (int64_t(k0) * hm) % two_nt, r16 = (kSpecPad * hm) % two_nt;
+  if (r < 0) r += two_nt;
+  if (r16 < 0) r16 += two_nt;
+  double sr, cr;  // rotation by one harmonic
+  sincospi(double(hm < 0 ? hm + two_nt : hm) * inv_nt, &sr, &cr);
+  ImageSums<WA> o{};
+  for (int i0 = 0; i0 < nh; i0 += kSpecPad) {
+    double s, c;
+    sincospi(double(r) * inv_nt, &s, &c);
+    r += r16;
+    if (r >= two_nt) r -= two_nt;
+#pragma unroll 2
+    for (int i = i0; i < i0 + kSpecPad; i += 2) {  // (four records' scalar loads in flight)
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const double* q = rec + int64_t(kSpecRec) * (i + p);
+        if (WE) {
+          o.c[0][p] = fma(q[0], c, o.c[0][p]);
+          o.s[0][p] = fma(q[1], s, o.s[0][p]);
+          o.c[1][p] = fma(q[2], c, o.c[1][p]);
+          o.s[1][p] = fma(q[3], s, o.s[1][p]);
+        }
+        if constexpr (WA) {
+          o.s[2][p] = fma(q[4], s, o.s[2][p]);
+          o.c[2][p] = fma(-q[5], c, o.c[2][p]);
+          o.s[3][p] = fma(q[6], s, o.s[3][p]);
+          o.c[3][p] = fma(-q[7], c, o.c[3][p]);
+        }
+        const double cn = fma(c, cr, -(s * sr));
+        s = fma(s, cr, c * sr);
+        c = cn;
+      }
+    }
+  }
+  return o;
+}
+
+// Component j at image m (bit 0: -theta, bit 1: + pi).  odd0: whether record 0's harmonic is odd.
+template <bool WA>
+__device__ __forceinline__ double image_value(const ImageSums<WA>& o, int j, int m, bool odd0) {
+  double c = o.c[j][0], s = o.s[j][0], c1 = o.c[j][1], s1 = o.s[j][1];
+  if (m & 2) {
+    c1 = -c1;
+    s1 = -s1;
+  }
+  c += c1;
+  s += s1;
+  const double v = (m & 1) ? c - s : c + s;
+  return (m & 2) && odd0 ? -v : v;
+}
+
+// Points 0..last of a pulse (last = nt - 1 for midpoints, nt for nodes) and their images: point n has
+// the images last - n, n + nt/2 and last - nt/2 - n; base points n < image_bases cover them all.
+__device__ __forceinline__ int image_point(int n, int m, int nt, int last) {
+  const int k = (m & 2) ? n + nt / 2 : n;
+  return (m & 1) ? last - k : k;
+}
+
 // Per block: max |E| over step nodes (PEAK) or sum |E|^2 over midpoints (ENERGY) -> part[pulse][block].
 __global__ void __launch_bounds__(256) k_field_stats(const PulseDev* __restrict__ desc,
                                                      const double* __restrict__ spec, int stride,
@@ -269,17 +360,31 @@ __global__ void __launch_bounds__(256) k_field_stats(const PulseDev* __restrict_
   const PulseDev d = desc[blockIdx.y];
   if (d.norm == PO_NORM_NONE || int(blockIdx.x) >= d.stat_blocks) return;
   __shared__ double red[256];
-  const int64_t n = int64_t(blockIdx.x) * 256 + threadIdx.x;
   const bool peak = d.norm == PO_NORM_PEAK;
   // nodes 0..nt (PEAK) or midpoints 0..nt-1 (ENERGY)
+  const int n = blockIdx.x * 256 + threadIdx.x, last = peak ? d.nt : d.nt - 1;
+  const double warm = warm_records(d, spec + d.spec_off);
   double v = 0.0;
-  if (peak ? n <= d.nt : n < d.nt) {
-    const int64_t hm = (peak ? 2 * n : 2 * n + 1) - d.nt;
-    const FieldSums o = field_sums<true, false, false>(d, spec + d.spec_off, hm, 0.0);
-    const double g = cospi(double(hm) * (0.5 / double(d.nt)));  // cos(pi t / T)
-    const double ex = g * g * o.ex, ey = g * g * o.ey;
-    v = peak ? sqrt(ex * ex + ey * ey) : ex * ex + ey * ey;
+  if (n < image_bases(d.nt, last)) {
+    const int64_t hm = (peak ? 2 * int64_t(n) : 2 * int64_t(n) + 1) - d.nt;
+    const ImageSums<false> o = image_sums<true, false>(d, spec + d.spec_off, hm);
+    double gs, gc;  // the window's root at the images: |cos(pi t / T)| = gc or gs
+    sincospi(double(hm) * (0.5 / double(d.nt)), &gs, &gc);
+    const bool odd0 = (d.nmin - 1) & 1;
+    const int images = d.nt % 2 ? 2 : kImages;
+#pragma unroll
+    for (int m = 0; m < kImages; ++m) {
+      if (m >= images) break;
+      bool again = false;  // the same point as an earlier image
+#pragma unroll
+      for (int q = 0; q < kImages; ++q) again = again || (q < m && image_point(n, q, d.nt, last) == image_point(n, m, d.nt, last));
+      if (again) continue;
+      const double g = (m & 2) ? gs : gc;
+      const double ex = g * g * image_value(o, 0, m, odd0), ey = g * g * image_value(o, 1, m, odd0);
+      v = peak ? fmax(v, sqrt(ex * ex + ey * ey)) : v + (ex * ex + ey * ey);
+    }
   }
+  keep(warm);
   red[threadIdx.x] = v;
   __syncthreads();
   for (int w = 128; w > 0; w >>= 1) {
@@ -333,33 +438,46 @@ __device__ __forceinline__ double block_scale(const PulseDev& d, int pulse, cons
   else return scale_ws[pulse];
 }
 
-// Scaled A (and E) at every step midpoint, the table's range over the workgroup's 256 steps (one chunk of
-// the per-mode kernels; NULL to skip); block (0, pulse) also writes A(t_i), A(t_f) and the scale.
+// Scaled A (and E) at every step midpoint and, where `ranges` is given, the table's range per chunk; workgroup = 256
+// base points and their images, each of the four runs contiguous.  A run's part of a chunk is merged into
+// the chunk's range (set to (inf, -inf) by k_spectra) by atomic minima and maxima; at most two chunks per
+// run.
 template <bool FUSED, bool WE>
 __global__ void __launch_bounds__(256) k_tables(const PulseDev* __restrict__ desc, const double* __restrict__ spec,
                                                 const double* __restrict__ part, int stride,
                                                 const double* __restrict__ scale_ws, double* __restrict__ Aout,
                                                 double* __restrict__ Eout, double* __restrict__ Aedge,
                                                 double* __restrict__ scale_out, double* __restrict__ ranges) {
-  static_assert(kChunkSteps == 256, "one workgroup per chunk");
+  static_assert(kChunkSteps == 256, "a run covers at most two chunks");
   const PulseDev d = desc[blockIdx.y];
-  if (int64_t(blockIdx.x) * 256 >= d.nt) return;  // whole workgroup: beyond this pulse's steps
+  const int last = d.nt - 1, bases = image_bases(d.nt, last), n0 = int(blockIdx.x) * 256;
+  if (n0 >= bases) return;  // whole workgroup
   __shared__ double red[256];
-  const int64_t n = int64_t(blockIdx.x) * 256 + threadIdx.x;
+  __shared__ double2 run[kImages][256];
+  const int n = n0 + threadIdx.x;
   const double* rec = spec + d.spec_off;
   const double s = block_scale<FUSED>(d, blockIdx.y, part, stride, scale_ws, red);
-  double lx = INFINITY, hx = -INFINITY, ly = INFINITY, hy = -INFINITY;
-  if (n < d.nt) {
-    const int64_t hm = 2 * n + 1 - d.nt;
-    const FieldSums o = field_sums<WE, false, true>(d, rec, hm, 0.0);
-    const double2 A = potential(d, rec, o, double(2 * n + 1 - 2 * int64_t(d.nt)) * (0.5 * d.dt));
-    const double ax = s * A.x, ay = s * A.y;
-    lx = hx = ax;
-    ly = hy = ay;
-    reinterpret_cast<double2*>(Aout)[d.tab_off + n] = make_double2(ax, ay);
-    if constexpr (WE) {
-      const double g = cospi(double(hm) * (0.5 / double(d.nt)));  // cos(pi t / T)
-      reinterpret_cast<double2*>(Eout)[d.tab_off + n] = make_double2(s * (g * g * o.ex), s * (g * g * o.ey));
+  const int images = d.nt % 2 ? 2 : kImages;
+  if (n < bases) {
+    const int64_t hm = 2 * int64_t(n) + 1 - d.nt;
+    const ImageSums<true> o = image_sums<WE, true>(d, rec, hm);
+    double gs = 0.0, gc = 0.0;  // the window's root at the images: |cos(pi t / T)| = gc or gs
+    if constexpr (WE) sincospi(double(hm) * (0.5 / double(d.nt)), &gs, &gc);
+    const bool odd0 = (d.nmin - 1) & 1;
+#pragma unroll
+    for (int m = 0; m < kImages; ++m) {
+      if (m >= images) break;
+      const int k = image_point(n, m, d.nt, last);
+      const double2 A = potential(d, rec, image_value(o, 2, m, odd0), image_value(o, 3, m, odd0),
+                                  double(2 * k + 1 - 2 * int64_t(d.nt)) * (0.5 * d.dt));
+      const double2 sa = make_double2(s * A.x, s * A.y);
+      reinterpret_cast<double2*>(Aout)[d.tab_off + k] = sa;
+      run[m][threadIdx.x] = sa;
+      if constexpr (WE) {
+        const double g = (m & 2) ? gs : gc;
+        reinterpret_cast<double2*>(Eout)[d.tab_off + k] =
+            make_double2(s * (g * g * image_value(o, 0, m, odd0)), s * (g * g * image_value(o, 1, m, odd0)));
+      }
     }
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -367,20 +485,34 @@ __global__ void __launch_bounds__(256) k_tables(const PulseDev* __restrict__ des
     if (scale_out) scale_out[blockIdx.y] = s;
   }
   if (ranges) {
-    // NaN entries drop out of the range, as in k_chunk_ranges
-    double v[4] = {-lx, hx, -ly, hy};
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) v[k] = fmax(v[k], __shfl_xor(v[k], off, 64));
     __syncthreads();
-    if ((threadIdx.x & 63) == 0)
-      for (int k = 0; k < 4; ++k) red[(threadIdx.x >> 6) * 4 + k] = v[k];
-    __syncthreads();
-    if (threadIdx.x < 4) {
-      const int k = threadIdx.x;
-      const double m = fmax(fmax(red[k], red[4 + k]), fmax(red[8 + k], red[12 + k]));
-      ranges[4 * int64_t(d.chk_off + int(blockIdx.x)) + k] = (k % 2 == 0) ? -m : m;
+    const int m = threadIdx.x >> 6, lane = threadIdx.x & 63, len = min(256, bases - n0);  // a run per wave
+    if (m >= images) return;
+    const int ka = image_point(n0, m, d.nt, last), kb = image_point(n0 + len - 1, m, d.nt, last);
+    for (int c = min(ka, kb) / kChunkSteps; c <= max(ka, kb) / kChunkSteps; ++c) {
+      // NaN entries drop out of the range, as in k_chunk_ranges
+      double v[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int i = lane + 64 * e;
+        if (i < len && image_point(n0 + i, m, d.nt, last) / kChunkSteps == c) {
+          const double2 a = run[m][i];
+          v[0] = fmax(v[0], -a.x);
+          v[1] = fmax(v[1], a.x);
+          v[2] = fmax(v[2], -a.y);
+          v[3] = fmax(v[3], a.y);
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v[k] = fmax(v[k], __shfl_xor(v[k], off, 64));
+      if (lane < 4) {
+        double* p = ranges + 4 * int64_t(d.chk_off + c) + lane;
+        const double x = lane < 2 ? (lane ? v[1] : -v[0]) : (lane == 3 ? v[3] : -v[2]);
+        if (lane & 1) unsafeAtomicMax(p, x);
+        else unsafeAtomicMin(p, x);
+      }
     }
   }
 }
@@ -421,7 +553,7 @@ __global__ void __launch_bounds__(256) k_samples(const PulseDev* __restrict__ de
       reinterpret_cast<double2*>(Edout)[row] = make_double2(s * (g2d * o.ex + g * g * o.dx), s * (g2d * o.ey + g * g * o.dy));
     }
     if constexpr (WA) {
-      const double2 A = potential(d, rec, o, (double(n - d.nt) + c) * d.dt);
+      const double2 A = potential(d, rec, o.ax, o.ay, (double(n - d.nt) + c) * d.dt);
       reinterpret_cast<double2*>(Aout)[row] = make_double2(s * A.x, s * A.y);
     }
   }
@@ -596,9 +728,9 @@ __global__ void __launch_bounds__(256) k_adjoint_coeff(const PulseDev* __restric
 
 // Spectra and, where the batch has a normalisation, its partials; the scale kernel unless it is fused.
 po_status launch_spectra(const Batch& b, const PulseDev* d_desc, const double* d_coeff, double* d_spec, double* d_part,
-                         double* d_scale_ws, bool* fused, hipStream_t s) {
+                         double* d_scale_ws, double* d_ranges, bool* fused, hipStream_t s) {
   const int P = b.n_pulses;
-  hipLaunchKernelGGL(k_spectra, dim3(P), dim3(128), 0, s, d_desc, d_coeff, d_spec);
+  hipLaunchKernelGGL(k_spectra, dim3(P), dim3(128), 0, s, d_desc, d_coeff, d_spec, d_ranges);
   PO_HIP(hipGetLastError());
   if (b.max_stat_blocks > 0) {
     hipLaunchKernelGGL(k_field_stats, dim3(b.max_stat_blocks, P), dim3(256), 0, s, d_desc, d_spec,
@@ -639,8 +771,8 @@ po_status launch_synth(const Batch& b, const PulseDev* d_desc, const double* d_c
                        double* d_part, double* d_scale_ws, double* d_A, double* d_E, double* d_A_edge,
                        double* d_scale_out, double* d_ranges, hipStream_t s) {
   bool fused = false;
-  PO_TRY(launch_spectra(b, d_desc, d_coeff, d_spec, d_part, d_scale_ws, &fused, s));
-  const dim3 grid((b.max_nt + 255) / 256, b.n_pulses);
+  PO_TRY(launch_spectra(b, d_desc, d_coeff, d_spec, d_part, d_scale_ws, d_ranges, &fused, s));
+  const dim3 grid((b.max_bases + 255) / 256, b.n_pulses);
   auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, d_desc, d_spec, d_part, b.max_stat_blocks, d_scale_ws, d_A, d_E,
                        d_A_edge, d_scale_out, d_ranges);
@@ -672,7 +804,7 @@ po_status launch_samples(const Batch& b, const PulseDev* d_desc, const double* d
   Offsets off{};
   for (int r = 0; r < n_sub; ++r) off.c[r] = offsets[r];
   bool fused = false;
-  PO_TRY(launch_spectra(b, d_desc, d_coeff, d_spec, d_part, d_scale_ws, &fused, s));
+  PO_TRY(launch_spectra(b, d_desc, d_coeff, d_spec, d_part, d_scale_ws, nullptr, &fused, s));
   const bool want[3] = {d_E != nullptr, d_Ed != nullptr, d_A != nullptr};
   if (fused) pick_samples<true>(want, b, d_desc, d_spec, d_part, d_scale_ws, n_sub, off, with_end, d_E, d_Ed, d_A, d_A_edge, d_scale_out, s);
   else pick_samples<false>(want, b, d_desc, d_spec, d_part, d_scale_ws, n_sub, off, with_end, d_E, d_Ed, d_A, d_A_edge, d_scale_out, s);
