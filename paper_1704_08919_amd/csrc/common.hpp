@@ -66,7 +66,7 @@ struct PulseDev {
   int32_t nunits;     // 64-mode units, 256-mode items and selection blocks of the distinct modes
   int32_t item_off;   // first workgroup item of this pulse in the default evolution launch
   int32_t nitems;
-  // Time segments of the second-order evolution: nseg of seg_len steps (the last may be shorter),
+  // Time segments of the evolution: nseg of seg_len steps (the last may be shorter),
   // each evolved from the identity and then applied to the state.  slot_off: first (item, segment)
   // slot of the pulse in the batch, slots in the order item * nseg + segment.
   int32_t nseg, seg_len;

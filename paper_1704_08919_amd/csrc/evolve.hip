@@ -24,16 +24,16 @@
 // the item belongs to in the 256-step chunk (a box of momenta against the range of the table in the
 // chunk); beyond the fits' range (x > 2.48) the large-step path halves the angle and takes C and S
 // from truncated Maclaurin series (remainder below 2^-56).  Either is shared by both blocks, because
-// omega does not depend on s.  The fourth-order and split-operator kernels below keep the multiple
-// 1 - i T Q_s with fits of T.
+// omega does not depend on s.
 //
 // What bounds it: FP64 issue, at the clock the power limit leaves (a chain of v_fma_f64 on distinct
 // registers runs at 1.85-1.95 GHz on this card, 0.73 of the 2.4 GHz peak at four waves per SIMD and
 // 0.77 at eight), so the time follows the number of FP64 instructions: 28 + n per mode-step with n =
 // 5.2 on average on the 64-pulse 64x64x16 nt = 16384 workload, against 31 + 6.2 for the tangent form
-// that this replaced there: 73.6 ms per generation against 80.9 (A/B on one card).  Five or six waves
+// that this replaced there: 73.6 ms per generation against 80.9 (A/B on one card) when every mode was
+// stepped, 36.8 ms with the distinct modes of the mirror-symmetric grid alone.  Five or six waves
 // per SIMD (96 or 80 VGPRs) measured 74.5 and 75.5 ms, two or one steps per loop iteration at four
-// waves 74.0 ms and slower.
+// waves 74.0 ms and slower (every mode stepped).
 //
 // Work decomposition: a workgroup of THREADS lanes (64-wide waves) owns an item of
 // THREADS x MPL consecutive modes of one pulse, MPL modes per lane.  The pulse's table of A

@@ -3,22 +3,20 @@
 // vector, the output a standardised log10 pair yield.
 //
 // Every matrix product is C[m][n] = sum_k A[m][k] Bt[n][k] with both operands contiguous in k, so
-// each lane of a v_mfma_f32_16x16x32_bf16 fetches its 8 consecutive-k values of one A row and one
-// B column with one 16-byte load, straight from L2 (every operand of a step, ~1 MB, stays there).
-// One wave owns a 32x32 tile of C (2 x 2 MFMA tiles: each fragment feeds two instructions); four
-// independent waves per workgroup.  The layouts that make k contiguous are produced by the
-// epilogues that write the operands: the forward pass writes every hidden activation both
-// row-major ([batch][width], the next layer's A) and transposed ([width][batch], the A of the
-// weight gradient); the backward pass writes each pre-activation gradient row-major (A of the
-// next input gradient) and transposed (Bt of the weight gradient); the optimiser keeps every
-// weight matrix in bf16 both as W[k_in][width] (Bt of the input gradient) and as W^T (Bt of the
-// forward product).  Weight gradients (k = batch) are split over k into fixed partial sums that
-// the optimiser adds in order, bias gradients are column sums per 32-row tile fused into the
-// epilogue that produces the pre-activation gradient, and the output layer (a dot product per
-// sample), the loss, dL/dy and the last hidden layer's gradient are one kernel, and the weight
-// gradient of a layer shares a launch with the input gradient of the layer below (the transposed
-// gradients alternate between two buffers).  A training step is 9 launches, captured once into a
-// HIP graph and replayed; every reduction has a fixed order, so a step is bitwise reproducible.
+// each lane of a v_mfma_f32_16x16x32_bf16 holds 8 consecutive-k values of one A row and one
+// B column, straight from L2 or LDS.  Weight gradients (k = batch) are split over k into fixed partial
+// sums that are added in order, bias gradients are column sums per 32-row tile; every reduction has a fixed
+// order, so a step is bitwise reproducible.
+//
+// Networks with width and input up to 512: k_net takes 32 samples through all layers, the loss and the
+// backward chain, k_step sums the weight gradients and applies the optimiser; weights and transposed operands
+// are kept in operand order.  Wider ones go layer by layer: one wave owns a 32x32 tile of C (2 x 2 MFMA
+// tiles), four independent waves per workgroup; the epilogues write what the next products read, every hidden
+// activation and pre-activation gradient row-major and transposed, and the optimiser keeps every weight
+// matrix in bf16 as W[k_in][width] and as W^T; the output layer, the loss, dL/dy and the last hidden layer's
+// gradient are one kernel, and the weight gradient of a layer shares a launch with the input gradient of
+// the layer below (the transposed gradients alternate between two buffers); those launches are captured once
+// into a HIP graph and replayed.
 //
 // Rounding points (the oracle emulates them): the input is rounded to bf16 through float, every
 // weight matrix used as an operand, every hidden activation gelu(z) and every pre-activation
