@@ -210,6 +210,7 @@ po_status build_batch(int32_t n, const po_pulse_spec* specs, const po_grid* grid
       const int64_t m = int64_t(g.n[0]) * g.n[1] * g.n[2];
       d.mirror = g.n[2] > 1 && g.lo[2] == -g.hi[2] ? 1 : 0;
       d.ndist = d.mirror ? int64_t(g.n[0]) * g.n[1] * ((g.n[2] + 1) / 2) : m;
+      if (kItem % g.n[0] != 0 || int64_t(g.n[0]) * g.n[1] % (2 * kItem) != 0) b->row_pairs = false;
       d.nunits = int32_t((d.ndist + kUnit - 1) / kUnit);
       d.nitems = int32_t((d.ndist + kItem - 1) / kItem);
       b->total_units_all += (m + kUnit - 1) / kUnit;

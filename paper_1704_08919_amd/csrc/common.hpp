@@ -91,6 +91,7 @@ struct Batch {
   int32_t total_items = 0;     // workgroups of the default evolution launch
   int64_t total_slots = 0;     // (256-mode item, time segment) pairs of all pulses
   int32_t total_chunks = 0;    // kChunkSteps-step chunks of all pulses
+  bool row_pairs = true;       // in every pulse's grid, modes m and m + 256 share p_x and p_z for m % 512 < 256
   int32_t max_bases = 0;       // largest per-pulse count of base points of the table synthesis (image_bases)
   int32_t max_stat_blocks = 0; // largest per-pulse block count of the field statistics pass
   int32_t max_nt = 0;

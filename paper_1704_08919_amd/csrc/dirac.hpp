@@ -211,10 +211,10 @@ __device__ __forceinline__ double cot_K(double y, const CotCoef<V>& k) {
   }
 }
 
+// One step with q'_x, q'_y given and xx = q'_x^2.
 template <int V>
-__device__ __forceinline__ void step_cot(State& v, double2 A, const CotMode& m, const CotCoef<V>& k) {
-  const double qx = fma(A.x, m.nie, m.px), qy = fma(A.y, m.nie, m.py);
-  const double K = cot_K<V>(fma(qx, qx, qy * qy), k);
+__device__ __forceinline__ void step_cot_q(State& v, double qx, double qy, double xx, const CotCoef<V>& k) {
+  const double K = cot_K<V>(fma(qy, qy, xx), k);
   const double ar = fma(qx, v.bi, fma(-qy, v.br, fma(K, v.ar, v.ai)));
   const double ai = fma(-qx, v.br, fma(-qy, v.bi, fma(K, v.ai, -v.ar)));
   const double br = fma(qx, v.ai, fma(qy, v.ar, fma(K, v.br, -v.bi)));
@@ -224,6 +224,12 @@ __device__ __forceinline__ void step_cot(State& v, double2 A, const CotMode& m, 
   const double dr = fma(qx, v.ci, fma(-qy, v.cr, fma(K, v.dr, -v.di)));
   const double di = fma(-qx, v.cr, fma(-qy, v.ci, fma(K, v.di, v.dr)));
   v = State{ar, ai, br, bi, cr, ci, dr, di};
+}
+
+template <int V>
+__device__ __forceinline__ void step_cot(State& v, double2 A, const CotMode& m, const CotCoef<V>& k) {
+  const double qx = fma(A.x, m.nie, m.px), qy = fma(A.y, m.nie, m.py);
+  step_cot_q<V>(v, qx, qy, qx * qx, k);
 }
 
 // Rescales both blocks by one exact power of two so that the largest component of the first lies

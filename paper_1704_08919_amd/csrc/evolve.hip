@@ -126,13 +126,14 @@ __device__ __forceinline__ int cot_variant(double xb, double dt) {
 
 // The steps of one chunk (len table records of buf) for the MPL modes of a lane in fit variant V,
 // rescaled every `group` steps.
-template <int V, int MPL>
+template <int V, int MPL, bool ROW>
 __device__ __forceinline__ void run_cot(State (&v)[MPL], const double2* buf, int len, double dt,
                                         const CotMode (&m)[MPL]) {
   const int group = dt >= kGroupLongMinDt ? kGroupLong : kGroupShort;
-  CotCoef<V> k[MPL];
+  constexpr int kDistinct = ROW ? 1 : MPL;  // ROW: the modes share e and p_x, so K's coefficients, q'_x and its square
+  CotCoef<V> k[kDistinct];
 #pragma unroll
-  for (int j = 0; j < MPL; ++j) {
+  for (int j = 0; j < kDistinct; ++j) {
     double e = m[j].e;
     asm volatile("" : "+v"(e));  // keeps this set-up inside the chunk loop, out of long-lived registers
     k[j] = cot_coef<V>(cot_step_size(e, dt));
@@ -142,8 +143,14 @@ __device__ __forceinline__ void run_cot(State (&v)[MPL], const double2* buf, int
 #pragma unroll kCotUnroll
     for (int n = n0; n < end; ++n) {
       const double2 rec = buf[n];
+      if constexpr (ROW) {
+        const double qx = fma(rec.x, m[0].nie, m[0].px), xx = qx * qx;
 #pragma unroll
-      for (int j = 0; j < MPL; ++j) step_cot<V>(v[j], rec, m[j], k[j]);
+        for (int j = 0; j < MPL; ++j) step_cot_q<V>(v[j], qx, fma(rec.y, m[0].nie, m[j].py), xx, k[0]);
+      } else {
+#pragma unroll
+        for (int j = 0; j < MPL; ++j) step_cot<V>(v[j], rec, m[j], k[j]);
+      }
     }
 #pragma unroll
     for (int j = 0; j < MPL; ++j) rescale(v[j]);
@@ -209,19 +216,19 @@ __device__ __forceinline__ void run_halving(State (&v)[MPL], const double2* buf,
 }
 
 // The steps of one chunk, in the variant that the bound xb on its (omega dt)^2 selects.
-template <int MPL>
+template <int MPL, bool ROW>
 __device__ __forceinline__ void run_chunk(State (&v)[MPL], const double2* buf, int len, double xb, double dt,
                                           const CotMode (&m)[MPL]) {
   switch (cot_variant(xb, dt)) {
-    case 0: run_cot<0, MPL>(v, buf, len, dt, m); break;
-    case 1: run_cot<1, MPL>(v, buf, len, dt, m); break;
-    case 2: run_cot<2, MPL>(v, buf, len, dt, m); break;
-    case 3: run_cot<3, MPL>(v, buf, len, dt, m); break;
-    case 4: run_cot<4, MPL>(v, buf, len, dt, m); break;
-    case 5: run_cot<5, MPL>(v, buf, len, dt, m); break;
-    case 6: run_cot<6, MPL>(v, buf, len, dt, m); break;
-    case 7: run_cot<7, MPL>(v, buf, len, dt, m); break;
-    case 8: run_cot<8, MPL>(v, buf, len, dt, m); break;
+    case 0: run_cot<0, MPL, ROW>(v, buf, len, dt, m); break;
+    case 1: run_cot<1, MPL, ROW>(v, buf, len, dt, m); break;
+    case 2: run_cot<2, MPL, ROW>(v, buf, len, dt, m); break;
+    case 3: run_cot<3, MPL, ROW>(v, buf, len, dt, m); break;
+    case 4: run_cot<4, MPL, ROW>(v, buf, len, dt, m); break;
+    case 5: run_cot<5, MPL, ROW>(v, buf, len, dt, m); break;
+    case 6: run_cot<6, MPL, ROW>(v, buf, len, dt, m); break;
+    case 7: run_cot<7, MPL, ROW>(v, buf, len, dt, m); break;
+    case 8: run_cot<8, MPL, ROW>(v, buf, len, dt, m); break;
     default: run_halving<MPL>(v, buf, len, xb, dt, m); break;
   }
 }
@@ -245,7 +252,7 @@ __device__ __forceinline__ ItemTab item_tab(const EvolveArgs& a, const PulseDev&
 // through LDS chunk by chunk; the series variant of each piece is chosen from the item's selection
 // block (items never straddle blocks) and the chunk's table range, so it depends only on the pulse,
 // the block and the chunk, never on the launch.
-template <int THREADS, int MPL>
+template <int THREADS, int MPL, bool ROW = false>
 __device__ __forceinline__ void propagate(State (&v)[MPL], const ItemTab& t, int n0, int n1, const CotMode (&mode)[MPL],
                                           double2* lds) {
 #pragma unroll
@@ -256,7 +263,7 @@ __device__ __forceinline__ void propagate(State (&v)[MPL], const ItemTab& t, int
     for (int i = threadIdx.x; i < len; i += THREADS) lds[i] = t.tab[n + i];
     __syncthreads();
     const double* rg = t.rg + 4 * c;
-    run_chunk<MPL>(v, lds, len, x_bound(t.bb, rg[0], rg[1], rg[2], rg[3], t.dt), t.dt, mode);
+    run_chunk<MPL, ROW>(v, lds, len, x_bound(t.bb, rg[0], rg[1], rg[2], rg[3], t.dt), t.dt, mode);
     n += len;
   }
 }
@@ -283,7 +290,7 @@ struct ItemLds {
 
 // Evolves the item of THREADS * MPL modes of pulse pi starting at mode `first`, writes f and the
 // 64-mode unit sums.  Every lane of the workgroup must call it (it contains barriers).
-template <int THREADS, int MPL>
+template <int THREADS, int MPL, bool ROW = false>
 __device__ __forceinline__ void process_item(const EvolveArgs& a, int pi, int first, ItemLds<THREADS, MPL>& lds) {
   const PulseDev& d = a.desc[pi];
   const double2* edge = reinterpret_cast<const double2*>(a.Aedge) + 2 * pi;
@@ -302,7 +309,7 @@ __device__ __forceinline__ void process_item(const EvolveArgs& a, int pi, int fi
   }
   for (int n0 = 0; n0 < d.nt; n0 += d.seg_len) {
     State v[MPL];
-    propagate<THREADS, MPL>(v, t, n0, min(n0 + d.seg_len, d.nt), mode, lds.tab);
+    propagate<THREADS, MPL, ROW>(v, t, n0, min(n0 + d.seg_len, d.nt), mode, lds.tab);
 #pragma unroll
     for (int j = 0; j < MPL; ++j) {
       State psi = lds.get(j);
@@ -329,6 +336,16 @@ __global__ void __launch_bounds__(kItem) __attribute__((amdgpu_waves_per_eu(4)))
   const int item = xcd_item(blockIdx.x, gridDim.x);
   const int pi = find_pulse_item(a.desc, a.n_pulses, item);
   process_item<kItem, 1>(a, pi, (item - a.desc[pi].item_off) * kItem, lds);
+}
+
+// Two items per workgroup, two modes per lane, where pair_rows says so: the modes m and m + 256 of a lane then lie in
+// the same column p_x of the same plane p_z and share q'_x, its square and the coefficients of K: 2 of 66 operations.
+// 182 VGPRs, two waves per SIMD (three, with spills around the step loops, measured the same).
+__global__ void __launch_bounds__(kItem) __attribute__((amdgpu_waves_per_eu(2))) k_evolve_rows(EvolveArgs a) {
+  __shared__ ItemLds<kItem, 2> lds;
+  const int item = 2 * xcd_item(blockIdx.x, gridDim.x);
+  const int pi = find_pulse_item(a.desc, a.n_pulses, item);
+  process_item<kItem, 2, true>(a, pi, (item - a.desc[pi].item_off) * kItem, lds);
 }
 
 // Time-split form, first kernel: one workgroup per (item, segment) slot; the segment's propagators go to
@@ -925,10 +942,21 @@ po_status launch_chunk_ranges(const Batch& b, const PulseDev* d_desc, const doub
   return PO_OK;
 }
 
+// Two items per workgroup where every pulse's grid allows it (row_pairs) and whole rounds of 256 CUs lose no more than
+// the 3% that the shared operations save: 2 ceil(items / 512) of its items against ceil(items / 256).
+// Measured, 64x64x16 modes at nt = 4096, us per call paired / single: 512 items 804 / 814, 640 items 1202 / 1024,
+// 1024 items 1288 / 1323, 1152 items 1756 / 1565, 2048 items 2461 / 2520, 2304 items 2961 / 2811, 3072 items
+// 3632 / 3737; and 8192 items at nt = 16384 35.5 / 36.6 ms.
+bool pair_rows(const Batch& b) {
+  const int64_t single = (int64_t(b.total_items) + 255) / 256, paired = 2 * ((int64_t(b.total_items) + 511) / 512);
+  return b.row_pairs && 100 * single >= 97 * paired;
+}
+
 po_status launch_evolve_grid(const Batch& b, const PulseDev* d_desc, const double* d_A, const double* d_A_edge,
                              const double* d_ranges, double* d_f, double* d_units, hipStream_t s) {
   EvolveArgs a{d_desc, b.n_pulses, d_A, d_A_edge, d_ranges, d_f, d_units};
-  hipLaunchKernelGGL(k_evolve, dim3(b.total_items), dim3(kItem), 0, s, a);
+  if (pair_rows(b)) hipLaunchKernelGGL(k_evolve_rows, dim3(b.total_items / 2), dim3(kItem), 0, s, a);
+  else hipLaunchKernelGGL(k_evolve, dim3(b.total_items), dim3(kItem), 0, s, a);
   PO_HIP(hipGetLastError());
   return PO_OK;
 }
