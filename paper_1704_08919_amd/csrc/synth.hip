@@ -201,6 +201,22 @@ __global__ void __launch_bounds__(128) k_spectra(const PulseDev* __restrict__ de
     *reinterpret_cast<double4*>(out + int64_t(kSpecRec) * nh) = make_double4(red[0][0], red[1][0], c0[0], c0[1]);
 }
 
+// sin and cos of pi (u + lo), lo small.
+__device__ __forceinline__ void sincos_turn(double u, double lo, double* s, double* c) {
+  double s0, c0;
+  sincospi(u, &s0, &c0);
+  lo *= M_PI;
+  *s = fma(lo, c0, s0);
+  *c = fma(-lo, s0, c0);
+}
+
+// sin and cos of pi r / n with inv = 1 / n: the rounding of the quotient, the largest error of a phase for n that is no
+// power of two (and carried on by every rotation), is put back to first order.
+__device__ __forceinline__ void sincos_ratio(double r, double n, double inv, double* s, double* c) {
+  const double u = r * inv;
+  sincos_turn(u, fma(-u, n, r) * inv, s, c);
+}
+
 // Sums over the harmonics of a pulse at phase index hm = h - nt plus a fraction cf (in half-steps): the
 // raw field e (without its window), its derivative ed, and sum [P sin - Q cos] in a.  The phase is
 // evaluated exactly (sincospi of the reduced index) at every 16th harmonic and carried to the next 15
@@ -212,21 +228,23 @@ struct FieldSums {
 template <bool WE, bool WD, bool WA>
 __device__ __forceinline__ FieldSums field_sums(const PulseDev& d, const double* __restrict__ rec, int64_t hm, double cf) {
   const int64_t two_nt = 2 * int64_t(d.nt);
-  const double inv_nt = 1.0 / double(d.nt);
+  const double nt = double(d.nt), inv_nt = 1.0 / nt;
   const int nh = spec_records(d.nlines), k0 = d.nmin - 1;
   int64_t r = (int64_t(k0) * hm) % two_nt, r16 = (kSpecPad * hm) % two_nt;
   if (r < 0) r += two_nt;
   if (r16 < 0) r16 += two_nt;
   double sr, cr;  // rotation by one harmonic
-  sincospi((double(hm < 0 ? hm + two_nt : hm) + cf) * inv_nt, &sr, &cr);
+  const double ur = (double(hm) + cf) * inv_nt;
+  sincos_turn(ur, (fma(-ur, nt, double(hm)) + cf) * inv_nt, &sr, &cr);
   FieldSums o{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   for (int i0 = 0; i0 < nh; i0 += kSpecPad) {
     double s, c, u = double(r) * inv_nt;
+    const double lo = fma(-u, nt, double(r)) * inv_nt;
     if (cf != 0.0) {
       u = fma(double(k0 + i0), cf * inv_nt, u);
       u -= 2.0 * floor(0.5 * u);
     }
-    sincospi(u, &s, &c);
+    sincos_turn(u, lo, &s, &c);
     r += r16;
     if (r >= two_nt) r -= two_nt;
 #pragma unroll 4
@@ -293,17 +311,17 @@ __device__ __forceinline__ void keep(double w) { asm volatile("" ::"v"(w)); }
 template <bool WE, bool WA>
 __device__ __forceinline__ ImageSums<WA> image_sums(const PulseDev& d, const double* __restrict__ rec, int64_t hm) {
   const int64_t two_nt = 2 * int64_t(d.nt);
-  const double inv_nt = 1.0 / double(d.nt);
+  const double nt = double(d.nt), inv_nt = 1.0 / nt;
   const int nh = spec_records(d.nlines), k0 = d.nmin - 1;
   int64_t r = (int64_t(k0) * hm) % two_nt, r16 = (kSpecPad * hm) % two_nt;
   if (r < 0) r += two_nt;
   if (r16 < 0) r16 += two_nt;
   double sr, cr;  // rotation by one harmonic
-  sincospi(double(hm < 0 ? hm + two_nt : hm) * inv_nt, &sr, &cr);
+  sincos_ratio(double(hm), nt, inv_nt, &sr, &cr);
   ImageSums<WA> o{};
   for (int i0 = 0; i0 < nh; i0 += kSpecPad) {
     double s, c;
-    sincospi(double(r) * inv_nt, &s, &c);
+    sincos_ratio(double(r), nt, inv_nt, &s, &c);
     r += r16;
     if (r >= two_nt) r -= two_nt;
 #pragma unroll 2
@@ -369,7 +387,7 @@ __global__ void __launch_bounds__(256) k_field_stats(const PulseDev* __restrict_
     const int64_t hm = (peak ? 2 * int64_t(n) : 2 * int64_t(n) + 1) - d.nt;
     const ImageSums<false> o = image_sums<true, false>(d, spec + d.spec_off, hm);
     double gs, gc;  // the window's root at the images: |cos(pi t / T)| = gc or gs
-    sincospi(double(hm) * (0.5 / double(d.nt)), &gs, &gc);
+    sincos_ratio(double(hm), 2.0 * double(d.nt), 0.5 / double(d.nt), &gs, &gc);
     const bool odd0 = (d.nmin - 1) & 1;
     const int images = d.nt % 2 ? 2 : kImages;
 #pragma unroll
@@ -462,7 +480,7 @@ __global__ void __launch_bounds__(256) k_tables(const PulseDev* __restrict__ des
     const int64_t hm = 2 * int64_t(n) + 1 - d.nt;
     const ImageSums<true> o = image_sums<WE, true>(d, rec, hm);
     double gs = 0.0, gc = 0.0;  // the window's root at the images: |cos(pi t / T)| = gc or gs
-    if constexpr (WE) sincospi(double(hm) * (0.5 / double(d.nt)), &gs, &gc);
+    if constexpr (WE) sincos_ratio(double(hm), 2.0 * double(d.nt), 0.5 / double(d.nt), &gs, &gc);
     const bool odd0 = (d.nmin - 1) & 1;
 #pragma unroll
     for (int m = 0; m < kImages; ++m) {
@@ -585,19 +603,19 @@ __global__ void __launch_bounds__(256) k_adjoint_harmonics(const PulseDev* __res
   const int i = blockIdx.x;
   if (i >= d.nlines + 2) return;
   const int64_t k = int64_t(d.nmin) - 1 + i, two_nt = 2 * int64_t(d.nt);
-  const double inv_nt = 1.0 / double(d.nt), sgn = (k & 1) ? -1.0 : 1.0;
+  const double nt = double(d.nt), inv_nt = 1.0 / nt, sgn = (k & 1) ? -1.0 : 1.0;
   const double2* g = reinterpret_cast<const double2*>(gA) + d.tab_off;
   const double2* Et = reinterpret_cast<const double2*>(E) + d.tab_off;
   const int64_t r256 = (k * 512) % two_nt;  // phase index step between a lane's midpoints
   double sr, cr;
-  sincospi(double(r256 < 0 ? r256 + two_nt : r256) * inv_nt, &sr, &cr);
+  sincos_ratio(double(r256), nt, inv_nt, &sr, &cr);
   double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0}, s = 0.0, c = 1.0;
   int it = 0;
   for (int64_t n = threadIdx.x; n < d.nt; n += 256, ++it) {
     if ((it & 15) == 0) {
       int64_t r = (k * (2 * n + 1 - d.nt)) % two_nt;
       if (r < 0) r += two_nt;
-      sincospi(double(r) * inv_nt, &s, &c);
+      sincos_ratio(double(r), nt, inv_nt, &s, &c);
     }
     const double2 gv = g[n], ev = Et[n];
     const double wc = k == 0 ? double(2 * n + 1 - two_nt) * (0.5 * d.dt) : s, ws = c - sgn;
