@@ -211,18 +211,19 @@ __device__ __forceinline__ double cot_K(double y, const CotCoef<V>& k) {
   }
 }
 
-// One step with q'_x, q'_y given and xx = q'_x^2.
+// One step with q'_x, q'_y given and xx = q'_x^2.  K times the component comes last: K is 1/(e dt) times the other
+// terms, whose sum is then rounded at their own size, so a component takes one large rounding per step, not three.
 template <int V>
 __device__ __forceinline__ void step_cot_q(State& v, double qx, double qy, double xx, const CotCoef<V>& k) {
   const double K = cot_K<V>(fma(qy, qy, xx), k);
-  const double ar = fma(qx, v.bi, fma(-qy, v.br, fma(K, v.ar, v.ai)));
-  const double ai = fma(-qx, v.br, fma(-qy, v.bi, fma(K, v.ai, -v.ar)));
-  const double br = fma(qx, v.ai, fma(qy, v.ar, fma(K, v.br, -v.bi)));
-  const double bi = fma(-qx, v.ar, fma(qy, v.ai, fma(K, v.bi, v.br)));
-  const double cr = fma(qx, v.di, fma(qy, v.dr, fma(K, v.cr, v.ci)));
-  const double ci = fma(-qx, v.dr, fma(qy, v.di, fma(K, v.ci, -v.cr)));
-  const double dr = fma(qx, v.ci, fma(-qy, v.cr, fma(K, v.dr, -v.di)));
-  const double di = fma(-qx, v.cr, fma(-qy, v.ci, fma(K, v.di, v.dr)));
+  const double ar = fma(K, v.ar, fma(qx, v.bi, fma(-qy, v.br, v.ai)));
+  const double ai = fma(K, v.ai, fma(-qx, v.br, fma(-qy, v.bi, -v.ar)));
+  const double br = fma(K, v.br, fma(qx, v.ai, fma(qy, v.ar, -v.bi)));
+  const double bi = fma(K, v.bi, fma(-qx, v.ar, fma(qy, v.ai, v.br)));
+  const double cr = fma(K, v.cr, fma(qx, v.di, fma(qy, v.dr, v.ci)));
+  const double ci = fma(K, v.ci, fma(-qx, v.dr, fma(qy, v.di, -v.cr)));
+  const double dr = fma(K, v.dr, fma(qx, v.ci, fma(-qy, v.cr, -v.di)));
+  const double di = fma(K, v.di, fma(-qx, v.cr, fma(-qy, v.ci, v.dr)));
   v = State{ar, ai, br, bi, cr, ci, dr, di};
 }
 
@@ -268,13 +269,13 @@ __device__ __forceinline__ void cos_sinc_halved(double x, int h, double inv4h, d
   }
 }
 
-// psi <- (C - i s . tau) psi for one block (a, b).
+// psi <- (C - i s . tau) psi for one block (a, b); the term with C, the largest for small steps, last.
 __device__ __forceinline__ void rotate_block(double& ar, double& ai, double& br, double& bi, double C, double sx,
                                              double sy, double sz) {
-  const double nar = fma(sx, bi, fma(-sy, br, fma(sz, ai, C * ar)));
-  const double nai = fma(-sx, br, fma(-sy, bi, fma(-sz, ar, C * ai)));
-  const double nbr = fma(-sz, bi, fma(C, br, fma(sx, ai, sy * ar)));
-  const double nbi = fma(sz, br, fma(C, bi, fma(-sx, ar, sy * ai)));
+  const double nar = fma(C, ar, fma(sx, bi, fma(-sy, br, sz * ai)));
+  const double nai = fma(C, ai, fma(-sx, br, fma(-sy, bi, -(sz * ar))));
+  const double nbr = fma(C, br, fma(-sz, bi, fma(sx, ai, sy * ar)));
+  const double nbi = fma(C, bi, fma(sz, br, fma(-sx, ar, sy * ai)));
   ar = nar; ai = nai; br = nbr; bi = nbi;
 }
 

@@ -687,14 +687,21 @@ __device__ __forceinline__ void phase_z(State& v, double cp, double sp) {
   r = fma(-v.di, sp, v.dr * cp); i = fma(v.dr, sp, v.di * cp); v.dr = r; v.di = i;
 }
 
-// psi <- (k - i Q_s) psi for both blocks, Q_s = x tau_x + s y tau_y (k = 1 is not multiplied).
-template <bool ONE>
+// psi <- (1 - i Q_s) psi for both blocks, Q_s = x tau_x + s y tau_y.
+__device__ __forceinline__ void rotate_xy(State& v, double x, double y) {
+  const double ar = fma(x, v.bi, fma(-y, v.br, v.ar)), ai = fma(-x, v.br, fma(-y, v.bi, v.ai));
+  const double br = fma(x, v.ai, fma(y, v.ar, v.br)), bi = fma(-x, v.ar, fma(y, v.ai, v.bi));
+  const double cr = fma(x, v.di, fma(y, v.dr, v.cr)), ci = fma(-x, v.dr, fma(y, v.di, v.ci));
+  const double dr = fma(x, v.ci, fma(-y, v.cr, v.dr)), di = fma(-x, v.cr, fma(-y, v.ci, v.di));
+  v = State{ar, ai, br, bi, cr, ci, dr, di};
+}
+
+// psi <- (k - i Q_s) psi for both blocks.
 __device__ __forceinline__ void rotate_xy(State& v, double k, double x, double y) {
-  const auto m = [&](double c) { return ONE ? c : k * c; };
-  const double ar = fma(x, v.bi, fma(-y, v.br, m(v.ar))), ai = fma(-x, v.br, fma(-y, v.bi, m(v.ai)));
-  const double br = fma(x, v.ai, fma(y, v.ar, m(v.br))), bi = fma(-x, v.ar, fma(y, v.ai, m(v.bi)));
-  const double cr = fma(x, v.di, fma(y, v.dr, m(v.cr))), ci = fma(-x, v.dr, fma(y, v.di, m(v.ci)));
-  const double dr = fma(x, v.ci, fma(-y, v.cr, m(v.dr))), di = fma(-x, v.cr, fma(-y, v.ci, m(v.di)));
+  const double ar = fma(k, v.ar, fma(x, v.bi, -(y * v.br))), ai = fma(k, v.ai, fma(-x, v.br, -(y * v.bi)));
+  const double br = fma(k, v.br, fma(x, v.ai, y * v.ar)), bi = fma(k, v.bi, fma(-x, v.ar, y * v.ai));
+  const double cr = fma(k, v.cr, fma(x, v.di, y * v.dr)), ci = fma(k, v.ci, fma(-x, v.dr, y * v.di));
+  const double dr = fma(k, v.dr, fma(x, v.ci, -(y * v.cr))), di = fma(k, v.di, fma(-x, v.cr, -(y * v.ci)));
   v = State{ar, ai, br, bi, cr, ci, dr, di};
 }
 
@@ -780,9 +787,9 @@ struct SplitScheme {
           const double x = fma(qx, qx, qy * qy);
           if constexpr (kTan) {
             const double T = tan_ratio<V>(x, f);
-            rotate_xy<true>(v, 1.0, T * qx, T * qy);
+            rotate_xy(v, T * qx, T * qy);
           } else {
-            rotate_xy<false>(v, cot_value<V - kNumFine>(x, f), qx, qy);
+            rotate_xy(v, cot_value<V - kNumFine>(x, f), qx, qy);
           }
           tilt_z(v, a[angle(i)]);
         }
