@@ -46,10 +46,12 @@ __device__ __forceinline__ double uniform(double v) {
 // Upper 32 bits of a positive double (ordered as the doubles are).
 constexpr uint32_t high_word(double v) { return uint32_t(__builtin_bit_cast(uint64_t, v) >> 32); }
 
-// Momentum of distinct mode m (mode 0 for lanes beyond them), its e_perp.
+// Momentum of distinct mode m, its e_perp; lanes beyond the last one take the last one's, which lies in the box their
+// block's series is chosen for (another mode's step angle may be far outside the fit's range, where the
+// state overflows).
 __device__ __forceinline__ double lane_mode(const PulseDev& d, int64_t m, double& px, double& py) {
   double pz;
-  mode_momentum(d, m < d.ndist ? m : 0, px, py, pz);
+  mode_momentum(d, min(m, d.ndist - 1), px, py, pz);
   return sqrt(fma(pz, pz, 1.0));
 }
 
