@@ -20,7 +20,8 @@
  *    asynchronous on that stream; results are valid once the stream reaches them.
  *  - Work buffers that a call needs beyond its arguments are taken, stream-ordered on `stream`, from
  *    a memory pool of the library's own (one per device; it keeps up to 512 MiB between calls), so
- *    calls on different streams never share scratch memory.
+ *    calls on different streams never share scratch memory.  (The device's default pool as long as the
+ *    first call comes while a stream is being captured.)
  *  - Errors: every argument is validated before anything is enqueued.  Invalid arguments
  *    return PO_ERR_INVALID, HIP failures PO_ERR_DEVICE; in both cases po_last_error() gives a
  *    message (thread-local).  No C++ exception crosses the ABI.  Nothing is enqueued when a

@@ -74,21 +74,34 @@ constexpr int kMaxDevices = 64;
 std::mutex g_pool_mu;
 hipMemPool_t g_pool[kMaxDevices] = {};
 
-po_status scratch_pool(hipMemPool_t* out) {
+// The pool cannot be created while a stream of the process is being captured (in the global mode): a call
+// that comes first at that time takes its scratch from the device's default pool.
+po_status scratch_pool(hipStream_t s, hipMemPool_t* out) {
   int dev = -1;
   PO_HIP(hipGetDevice(&dev));
   if (dev < 0 || dev >= kMaxDevices) return set_error(PO_ERR_UNSUPPORTED, "device %d out of range", dev);
   std::lock_guard<std::mutex> lk(g_pool_mu);
   if (!g_pool[dev]) {
-    hipMemPoolProps props;
-    std::memset(&props, 0, sizeof props);
-    props.allocType = hipMemAllocationTypePinned;
-    props.location.type = hipMemLocationTypeDevice;
-    props.location.id = dev;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    PO_HIP(hipStreamIsCapturing(s, &cap));
     hipMemPool_t pool = nullptr;
-    PO_HIP(hipMemPoolCreate(&pool, &props));
+    hipError_t e = hipErrorStreamCaptureUnsupported;
+    if (cap == hipStreamCaptureStatusNone) {
+      hipMemPoolProps props;
+      std::memset(&props, 0, sizeof props);
+      props.allocType = hipMemAllocationTypePinned;
+      props.location.type = hipMemLocationTypeDevice;
+      props.location.id = dev;
+      e = hipMemPoolCreate(&pool, &props);
+    }
+    if (e == hipErrorStreamCaptureUnsupported) {
+      (void)hipGetLastError();
+      PO_HIP(hipDeviceGetDefaultMemPool(out, dev));
+      return PO_OK;
+    }
+    if (e != hipSuccess) return device_error(e, "hipMemPoolCreate");
     uint64_t keep = kPoolKeep;
-    const hipError_t e = hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep);
+    e = hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &keep);
     if (e != hipSuccess) {
       (void)hipMemPoolDestroy(pool);
       return device_error(e, "hipMemPoolSetAttribute");
@@ -105,7 +118,7 @@ po_status Scratch::alloc(size_t bytes, hipStream_t s) {
   stream = s;
   if (bytes == 0) bytes = 8;
   hipMemPool_t pool = nullptr;
-  PO_TRY(scratch_pool(&pool));
+  PO_TRY(scratch_pool(s, &pool));
   hipError_t e = hipMallocFromPoolAsync(&ptr, bytes, pool, s);
   if (e == hipErrorOutOfMemory) {
     (void)hipGetLastError();
