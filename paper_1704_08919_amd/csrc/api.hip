@@ -310,18 +310,21 @@ __global__ void __launch_bounds__(64) k_fill_desc(PulseDev d, PulseDev step, int
 
 // Puts the descriptors into device memory: by kernel arguments where they fit (a few pulses, or pulses
 // alike), which spares the copy from pageable host memory (it takes longer than these kernels, and
-// the host waits for it), else by that copy.
+// the host waits for it), else by that copy.  Under capture always by kernel arguments, a few at a time: a recorded copy
+// would read the host's array at the replay, when it is gone.
 po_status put_desc(const std::vector<PulseDev>& h, PulseDev* d_desc, hipStream_t s) {
   static_assert(sizeof(DescPack) <= 3840, "kernel arguments are limited to 4 KiB");
   const int n = int(h.size());
-  if (n <= kArgPulses) {
+  const auto put_few = [&](int first) -> po_status {
+    const int few = std::min(kArgPulses, n - first);
     DescPack p;
-    std::memcpy(p.d, h.data(), sizeof(PulseDev) * h.size());
-    for (int i = n; i < kArgPulses; ++i) std::memset(&p.d[i], 0, sizeof(PulseDev));
-    hipLaunchKernelGGL(k_put_desc, dim3(1), dim3(64), 0, s, p, n, d_desc);
+    std::memcpy(p.d, h.data() + first, sizeof(PulseDev) * size_t(few));
+    for (int i = few; i < kArgPulses; ++i) std::memset(&p.d[i], 0, sizeof(PulseDev));
+    hipLaunchKernelGGL(k_put_desc, dim3(1), dim3(64), 0, s, p, few, d_desc + first);
     PO_HIP(hipGetLastError());
     return PO_OK;
-  }
+  };
+  if (n <= kArgPulses) return put_few(0);
   bool alike = true;
   for (int i = 2; i < n && alike; ++i) {
     PulseDev e;
@@ -350,6 +353,12 @@ po_status put_desc(const std::vector<PulseDev>& h, PulseDev* d_desc, hipStream_t
   if (alike) {
     hipLaunchKernelGGL(k_fill_desc, dim3((n + 63) / 64), dim3(64), 0, s, h[0], h[1], n, d_desc);
     PO_HIP(hipGetLastError());
+    return PO_OK;
+  }
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  PO_HIP(hipStreamIsCapturing(s, &cap));
+  if (cap != hipStreamCaptureStatusNone) {
+    for (int i = 0; i < n; i += kArgPulses) PO_TRY(put_few(i));
     return PO_OK;
   }
   PO_HIP(hipMemcpyAsync(d_desc, h.data(), sizeof(PulseDev) * h.size(), hipMemcpyHostToDevice, s));
