@@ -256,9 +256,10 @@ po_status po_evolve_modes_split(int32_t n_pulses, const po_pulse_spec* specs, co
  * Work buffers of ceil(distinct modes / 256) x (nt x 16 bytes + segments x 16 KiB) per pulse (the per-step
  * partial sums of each 256-mode item and the propagators of its 8 to 32 time segments) come from the
  * scratch pool: 48 MiB for a 64x64x16 pulse symmetric in p_z at nt = 16384, 640 MiB for a 128x128x32
- * one at nt = 32768.  A batch that would need more than 2 GiB is worked through in groups of pulses,
- * one after the other in the same buffers; a pulse whose buffers do not fit in device memory returns
- * PO_ERR_NOMEM before the gradient kernels are enqueued.
+ * one at nt = 32768.  A batch that would need more than 2 GiB is worked through in groups of pulses or,
+ * within a pulse, of 256-mode items, one after the other in the same buffers (the results do not depend
+ * on it); buffers that device memory does not hold return PO_ERR_NOMEM before the gradient kernels are
+ * enqueued.
  *
  * po_synth_gradient -- chain rule through the synthesis (Sec. III) of po_pulse_synth:
  *  d_gA, d_gedge  as produced above (d_gedge may be NULL: no end-point terms).

@@ -452,8 +452,8 @@ po_status evolve_impl(const Work& w, const EvolveWork& z, const Batch& b, const 
 }
 
 // Gradient of J with respect to the tables (forward and adjoint sweeps per mode, fixed-order sums).
-// The pulses are taken in groups whose segment propagators and partial sums stay within kGradGroup
-// bytes (a single pulse may need more), one group after the other in the same buffers.
+// The items are taken in groups whose segment propagators and partial sums stay within kGradGroup bytes, one
+// after the other in the same buffers: as many whole pulses as fit, or a part of one that does not.
 constexpr int64_t kGradGroup = int64_t(2) << 30;
 
 struct GradWork {
@@ -461,23 +461,32 @@ struct GradWork {
   std::vector<GradRange> groups;
   GradWork(Work& w, const std::vector<PulseDev>& h, const Batch& b) {
     int64_t max_slots = 0, max_rows = 0, max_items = 0;
-    for (int i = 0; i < b.n_pulses;) {
-      GradRange r{i, i, h[i].slot_off, 0, h[i].part_off, h[i].item_off, 0, 0};
-      int64_t rows = 0;
-      for (; r.i1 < b.n_pulses; ++r.i1) {
+    const auto item_bytes = [](const PulseDev& d) {
+      return d.nseg * int64_t(sizeof(double)) * kSlotDoubles + 16 * int64_t(d.nt) + 128;
+    };
+    for (int i = 0, li = 0; i < b.n_pulses;) {  // next item: li of pulse i
+      const PulseDev& f = h[i];
+      GradRange r{i, i, f.slot_off + int64_t(li) * f.nseg, 0, f.part_off + 2 * int64_t(li) * f.nt, f.item_off + li, 0, 0};
+      int64_t rows = 0, left = kGradGroup;
+      while (r.i1 < b.n_pulses) {
         const PulseDev& d = h[r.i1];
-        const int64_t ds = int64_t(d.nitems) * d.nseg, dr = int64_t(d.nitems) * d.nt;
-        if (r.i1 > i && (r.slots + ds) * kSlotDoubles * 8 + (rows + dr) * 16 > kGradGroup) break;
-        r.slots += ds;
-        rows += dr;
-        r.items += d.nitems;
+        const int64_t fit = left / item_bytes(d), rest = d.nitems - li;
+        if (r.items > 0 && rest > fit) break;
+        const int64_t take = std::min(rest, std::max<int64_t>(fit, 1));
+        left -= take * item_bytes(d);
+        r.slots += take * d.nseg;
+        rows += take * d.nt;
+        r.items += int(take);
         r.max_nt = std::max(r.max_nt, d.nt);
+        ++r.i1;
+        li = take < rest ? li + int(take) : 0;
+        if (li > 0) break;
       }
       max_slots = std::max(max_slots, r.slots);
       max_rows = std::max(max_rows, rows);
       max_items = std::max<int64_t>(max_items, r.items);
       groups.push_back(r);
-      i = r.i1;
+      i = li > 0 ? r.i1 - 1 : r.i1;
     }
     prop = w.add(sizeof(double) * kSlotDoubles * size_t(max_slots));
     part = w.add(sizeof(double) * 2 * size_t(max_rows));

@@ -148,8 +148,9 @@ po_status launch_synth_adjoint(const Batch& b, const PulseDev* d_desc, const dou
                                const double* d_gedge, const double* d_A, const double* d_A_edge, const double* d_E,
                                const double* d_scale, double* d_harm, double* d_lines, double* d_grad, double* d_U, double* d_gU,
                                hipStream_t s);
-// Yield gradient (grad.hip) of pulses [i0, i1) of the batch: d_prop holds their slots, d_part their item
-// partials [items][nt][2], d_epart 4 x [4] doubles per item of them.
+// Yield gradient (grad.hip) of the items [item0, item0 + items) of the batch, which belong to the pulses [i0, i1):
+// d_prop holds their slots, d_part their item partials [items][nt][2], d_epart 4 x [4] doubles per item of
+// them.  A pulse's sums over its items go on from one range to the next in d_gA and d_gedge (if not NULL).
 struct GradRange {
   int i0, i1;
   int64_t slot0, slots, part0;

@@ -283,7 +283,7 @@ struct GradArgs {
   const PulseDev* desc;  // of the group's pulses
   int n_pulses;
   int64_t slot0, part0;  // first slot, first partial and first item of the group in the batch
-  int item0;
+  int item0, items;
   const double* A;
   const double* Aedge;
   const double* ranges;
@@ -514,23 +514,27 @@ __global__ void __launch_bounds__(kItem) __attribute__((amdgpu_waves_per_eu(3)))
 }
 
 // dJ/dA[n] = -dt dV sum over the pulse's items (in order) of the partials (the edge partials carry
-// their factors); one thread per (n, component).
+// their factors); one thread per (n, component).  Of a pulse that goes on in the next group the sums so far are
+// kept where the results will be, so they are added in the same order whatever the groups.
 __global__ void __launch_bounds__(256) k_grad_reduce(GradArgs a, double* __restrict__ gA, double* __restrict__ gedge) {
   const PulseDev& d = a.desc[blockIdx.y];
+  const int first = max(a.item0 - d.item_off, 0), last = min(a.item0 + a.items - d.item_off, d.nitems);
   const int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x;
   const int64_t per = 2 * int64_t(d.nt);
   if (e < per) {
     const double* p = a.part + (d.part_off - a.part0) + e;
-    double v = 0.0;
+    double* out = gA + 2 * d.tab_off + e;
+    double v = first > 0 ? *out : 0.0;
 #pragma unroll 8
-    for (int i = 0; i < d.nitems; ++i) v += p[int64_t(i) * per];
-    gA[2 * d.tab_off + e] = v * -d.dt * d.dv;  // dq_x/dA_x = -dt; the partials hold 2 Re[...]
+    for (int i = first; i < last; ++i) v += p[int64_t(i) * per];
+    *out = last < d.nitems ? v : v * -d.dt * d.dv;  // dq_x/dA_x = -dt; the partials hold 2 Re[...]
   }
   if (gedge && blockIdx.x == 0 && threadIdx.x < 4) {
     const double* p = a.epart + int64_t(d.item_off - a.item0) * kWaves * 4 + threadIdx.x;
-    double v = 0.0;
-    for (int i = 0; i < d.nitems * kWaves; ++i) v += p[int64_t(i) * 4];
-    gedge[4 * blockIdx.y + threadIdx.x] = v * d.dv;
+    double* out = gedge + 4 * blockIdx.y + threadIdx.x;
+    double v = first > 0 ? *out : 0.0;
+    for (int i = first * kWaves; i < last * kWaves; ++i) v += p[int64_t(i) * 4];
+    *out = last < d.nitems ? v : v * d.dv;
   }
 }
 
@@ -541,8 +545,8 @@ po_status launch_yield_grad(const PulseDev* d_desc, const GradRange& r, const do
                             double* d_gA, double* d_gedge, hipStream_t s) {
   const int n = r.i1 - r.i0;
   const PulseDev* desc = d_desc + r.i0;
-  GradArgs a{desc,     n,      r.slot0, r.part0, r.item0, d_A,    d_A_edge + 4 * int64_t(r.i0),
-             d_ranges, d_prop, d_part,  d_epart, d_units};
+  GradArgs a{desc, n, r.slot0, r.part0, r.item0, r.items, d_A, d_A_edge + 4 * int64_t(r.i0), d_ranges, d_prop, d_part,
+             d_epart, d_units};
   PO_TRY(launch_segments(desc, n, r.slot0, r.slots, d_A, d_ranges, d_prop, s));
   hipLaunchKernelGGL(k_grad_join, dim3(unsigned(r.items) * kWaves), dim3(64), 0, s, a);
   PO_HIP(hipGetLastError());
