@@ -132,8 +132,8 @@ po_status po_pulse_synth(int32_t n_pulses, const po_pulse_spec* specs, const dou
  *  d_f       out [sum M] double or NULL: f(t_f, p) per mode.
  *  d_J       out [n_pulses] double or NULL: J = Delta V sum_p f (Sec. IV A, Eq. opt_prob).
  *            At least one of d_f, d_J must be non-NULL.
- *  plan      NULL (one workgroup per 256 modes) or a plan created for the same specs and
- *            grids, whose launch shape and queue are then used.
+ *  plan      NULL (one workgroup per 256 modes, or per 512, or per 256 modes and time segment) or a
+ *            plan created for the same specs and grids, whose launch shape and queue are then used.
  * --------------------------------------------------------------------------------------- */
 struct po_plan;
 po_status po_evolve_modes(int32_t n_pulses, const po_pulse_spec* specs, const po_grid* grids,
@@ -397,7 +397,9 @@ po_status po_de_generation(const po_de_params* prm, int64_t generation, const po
  * per-pulse descriptors and a device work queue of (pulse, block of modes) items ordered by
  * decreasing cost (nt), so persistent workgroups take the longest work first.  The launch
  * shape is given or chosen by timing the candidates on the plan's own batch (autotuning); the
- * choice can be cached in a text file.  The first po_plan_evaluate with a given set of
+ * choice can be cached in a text file.  A batch so small that it is evolved with one workgroup per
+ * 256 distinct modes and time segment (up to 448 times 256 distinct modes) is evolved in that form
+ * whatever its launch shape, which is then not timed.  The first po_plan_evaluate with a given set of
  * pointers captures synthesis -> series selection -> evolution -> yield into a HIP graph, later
  * calls with the same pointers replay it.  Results do not depend on the launch shape: J is
  * bitwise identical to po_evaluate's.  Calls on one plan must not overlap (they share its
@@ -413,8 +415,8 @@ typedef struct {
 
 /* cfg NULL = autotune everything.  cache_path NULL = no cache; otherwise a text file read before
  * and appended after autotuning, keyed by the device and the batch shape.  Allocates device
- * memory (sum nt x 32 bytes + modes / 8 bytes + small); runs and synchronises `stream` while
- * autotuning. */
+ * memory (sum nt x 32 bytes + modes / 8 bytes + small; for a small batch up to 128 MiB for its
+ * segments); runs and synchronises `stream` while autotuning. */
 po_status po_plan_create(int32_t n_pulses, const po_pulse_spec* specs, const po_grid* grids,
                          const po_plan_config* cfg, const char* cache_path, void* stream,
                          struct po_plan** out);

@@ -27,7 +27,7 @@ struct po_plan {
   int* d_counter = nullptr;
   double* d_ranges = nullptr;  // table range per chunk
   double* d_units = nullptr;
-  double* d_prop = nullptr;    // segment propagators of a batch that is split in time (any launch shape)
+  double* d_prop = nullptr;    // segment propagators of a batch that is split in time (whatever the launch shape)
   double* d_A = nullptr;
   double* d_edge = nullptr;
   double* d_spec = nullptr;
@@ -130,9 +130,10 @@ std::string cache_key(const po_plan* p) {
   for (int i = 0; i < p->n; ++i) {
     h = fnv(h, &p->specs[i].nt, sizeof(int32_t));
     h = fnv(h, p->grids[i].n, sizeof(p->grids[i].n));
+    h = fnv(h, &p->h_desc[i].mirror, sizeof(int32_t));  // half the modes, and perhaps the time-split form
   }
-  std::ostringstream os;
-  os << arch << ":" << p->n << ":" << std::hex << h;
+  std::ostringstream os;  // "2": entries of shapes timed on the kernels that evolved every mode do not match
+  os << arch << ":2:" << p->n << ":" << std::hex << h;
   return os.str();
 }
 
@@ -180,20 +181,30 @@ po_status time_config(po_plan* p, hipStream_t s, float* ms) {
   return st;
 }
 
-po_status autotune(po_plan* p, const po_plan_config* req, hipStream_t s) {
+// Launch shapes that satisfy a request.
+std::vector<EvolveConfig> candidates(const po_plan_config& req) {
   std::vector<EvolveConfig> cands;
   const int ths[3] = {256, 128, 64};
   for (int pers = 0; pers <= 1; ++pers)
     for (int t : ths)
       for (int m = 1; m <= 2; ++m) {
-        EvolveConfig c{t, m, pers};
+        const EvolveConfig c{t, m, pers};
         if (!valid_config(c)) continue;
-        if (req->threads && req->threads != t) continue;
-        if (req->modes_per_lane && req->modes_per_lane != m) continue;
-        if (req->persistent >= 0 && req->persistent != pers) continue;
+        if (req.threads && req.threads != t) continue;
+        if (req.modes_per_lane && req.modes_per_lane != m) continue;
+        if (req.persistent >= 0 && req.persistent != pers) continue;
         cands.push_back(c);
       }
+  return cands;
+}
+
+po_status autotune(po_plan* p, const po_plan_config* req, hipStream_t s) {
+  const std::vector<EvolveConfig> cands = candidates(*req);
   if (cands.empty()) return set_error(PO_ERR_INVALID, "no launch shape satisfies the requested config");
+  if (p->d_prop) {  // the shape is not used: nothing to time
+    p->cfg = cands[0];
+    return build_queue(p, s);
+  }
   float best = 1e30f;
   EvolveConfig pick = cands[0];
   const int wg_req = p->workgroups;
