@@ -143,6 +143,11 @@ __global__ void __launch_bounds__(128) k_spectra(const PulseDev* __restrict__ de
   __shared__ double c0[2];
   const int t = threadIdx.x, nh = spec_records(d.nlines);
   double* out = spec + d.spec_off;
+  // A line's sums over all basis functions hold 0 times every coefficient outside its own few, which line_spectrum
+  // leaves out: a coefficient that is not finite spoils its component here, through the first line.
+  bool odd = false;
+  for (int i = t; i < 4 * d.ns; i += 128) odd = odd || !isfinite(a[i]);
+  const bool spoilt = __syncthreads_or(odd);
   double a0x = 0.0, a0y = 0.0;
   if (t < 2) c0[t] = 0.0;
   for (int i0 = 0; i0 < nh; i0 += kSpecTile) {
@@ -151,6 +156,8 @@ __global__ void __launch_bounds__(128) k_spectra(const PulseDev* __restrict__ de
     if (j >= 0 && j < d.nlines) {
       double E[2], ph[2], sp, cp;
       line_spectrum(d, a, j, E, ph);
+      if (spoilt && j == 0)
+        for (int i = 0; i < 4 * d.ns; ++i) E[i / (2 * d.ns)] += 0.0 * a[i];
       sincos(ph[0], &sp, &cp);
       q.x = E[0] * cp;
       q.y = E[0] * sp;
