@@ -165,7 +165,8 @@ po_status po_evaluate(int32_t n_pulses, const po_pulse_spec* specs, const po_gri
  * table ranges) lives in one file-scope device array of 133 MiB that each device holds from
  * the library's first use there until the process ends; the caller passes inputs and outputs as
  * for po_evaluate.  Limits: at most 4096 pulses, and a batch whose scratch (about
- * 8 (sum 4 lines + pulses (statistic blocks + 1) + sum modes / 64 + 4 sum ceil(nt/256)) bytes
+ * 8 (sum 4 lines + pulses (statistic blocks + 1) + sum modes / 64 + 4 sum ceil(nt/256)) bytes,
+ * statistic blocks = ceil((nt + 1)/256) of the longest normalised pulse, at least 1,
  * plus descriptors, each part rounded up to 256 bytes) exceeds 64 MiB is rejected with
  * PO_ERR_INVALID before anything is enqueued.  Every call on a device shares that device's
  * array: calls that overlap on one device (on different streams, or from several threads) race

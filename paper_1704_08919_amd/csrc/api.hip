@@ -976,10 +976,13 @@ po_status po_evaluate_noalloc(int32_t n, const po_pulse_spec* specs, const po_gr
   Batch b;
   PO_TRY(build_batch(n, specs, grids, g_noalloc_desc, &b));
   const EvalSizes z = eval_sizes(n, b);
-  // the documented limit: descriptors (208 bytes a pulse), 4 doubles a line, partials, scales, unit sums and
-  // ranges; the array also has room for the larger records that are laid out in it
+  // the documented limit: descriptors (208 bytes a pulse), 4 doubles a line, a partial per 256 nodes of the longest
+  // normalised pulse, scales, unit sums and ranges; the array also has room for what is larger in it
+  int64_t blocks = 1;
+  for (int i = 0; i < n; ++i)
+    if (specs[i].norm != PO_NORM_NONE) blocks = std::max<int64_t>(blocks, (int64_t(specs[i].nt) + 1 + 255) / 256);
   const size_t limit = align256(208 * size_t(n)) + align256(32 * size_t(b.total_lines)) +
-                       align256(sizeof(double) * z.part) + align256(sizeof(double) * z.scl) +
+                       align256(sizeof(double) * size_t(blocks) * size_t(n)) + align256(sizeof(double) * z.scl) +
                        align256(sizeof(double) * z.units) + align256(sizeof(double) * z.ranges);
   if (limit > kNoAllocLimitBytes)
     return set_error(PO_ERR_INVALID, "batch needs %zu bytes of scratch, the allocation-free path holds %zu", limit,
