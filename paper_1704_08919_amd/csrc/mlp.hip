@@ -725,20 +725,29 @@ __device__ __forceinline__ int64_t wpart_off(const ParamMap& q, int l) {
   return l == 0 ? 0 : int64_t(kMaxSplit) * q.n_in * q.width + int64_t(l - 1) * kMaxSplit * q.width * q.width;
 }
 
-// Sum of p[t * stride], t < n, in order, with 32 loads in flight.
+// Sum of p[t * stride], t < n, in order.  LONG: 32 loads in flight, for k_step, whose few threads of this kind wait for
+// nothing else; k_adam, one thread per parameter, is twice as long with it and waits for its own
+// instructions (320000 parameters, 13.3 us against 8.5).
+template <bool LONG>
 __device__ __forceinline__ float ordered_sum(const float* p, int64_t stride, int n) {
   float s = 0.0f;
-  for (int t0 = 0; t0 < n; t0 += 32) {
-    float v[32];
+  if constexpr (LONG) {
+    for (int t0 = 0; t0 < n; t0 += 32) {
+      float v[32];
 #pragma unroll
-    for (int t = 0; t < 32; ++t) v[t] = t0 + t < n ? p[(t0 + t) * stride] : 0.0f;
+      for (int t = 0; t < 32; ++t) v[t] = t0 + t < n ? p[(t0 + t) * stride] : 0.0f;
 #pragma unroll
-    for (int t = 0; t < 32; ++t) s += v[t];
+      for (int t = 0; t < 32; ++t) s += v[t];
+    }
+  } else {
+#pragma unroll 8
+    for (int t = 0; t < n; ++t) s += p[t * stride];
   }
   return s;
 }
 
 // Gradient of parameter i: its partial sums added in a fixed order.
+template <bool LONG>
 __device__ __forceinline__ float assembled_grad(const ParamMap& q, int64_t i) {
   int64_t off = 0;
   int kin = q.n_in;
@@ -754,13 +763,13 @@ __device__ __forceinline__ float assembled_grad(const ParamMap& q, int64_t i) {
     }
     if (i < off + nw + q.width) {
       const int n = int(i - off - nw);
-      return ordered_sum(q.bpart + l * q.bpart_stride + n, q.width, q.nblk);
+      return ordered_sum<LONG>(q.bpart + l * q.bpart_stride + n, q.width, q.nblk);
     }
     off += nw + q.width;
     kin = q.width;
   }
   const int j = int(i - off);  // 0..width-1: output weights; width: output bias
-  return ordered_sum(q.opart + j, q.width + 2, q.nblk);
+  return ordered_sum<LONG>(q.opart + j, q.width + 2, q.nblk);
 }
 
 // Positions of parameter i in the two bf16 copies (weights of a hidden layer; others keep theirs).
@@ -831,14 +840,14 @@ __global__ void __launch_bounds__(256) k_step(StepArgs a) {
       const int cursor = a.ctr->cursor;
       if (a.loss)
         a.loss[a.loss_by_cursor ? cursor : 0] =
-            ordered_sum(q.opart + q.width + 1, q.width + 2, q.nblk) / float(q.batch);
+            ordered_sum<true>(q.opart + q.width + 1, q.width + 2, q.nblk) / float(q.batch);
       if (a.lr >= 0.0f) a.ctr->cursor = cursor + 1;
     }
     if (i >= count) return;
     const int l = min(int(i / q.width), q.depth);
     int64_t o = i;  // position in the parameter vector: plus the weights of the layers up to this one
     for (int k = 0; k <= l && k < q.depth; ++k) o += int64_t(k == 0 ? q.n_in : q.width) * q.width;
-    const float g = assembled_grad(q, o);
+    const float g = assembled_grad<true>(q, o);
     a.g[o] = g;
     if (a.lr < 0.0f) return;
     const float pi = adam_value(g, a.p[o], a.m[o], a.v[o], a.lr, bc1, bc2);
@@ -949,9 +958,9 @@ __global__ void __launch_bounds__(256) k_adam(ParamMap q, const float* __restric
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i == 0 && loss)
     loss[loss_by_cursor ? c->cursor - 1 : 0] =
-        ordered_sum(q.opart + q.width + 1, q.width + 2, q.nblk) / float(q.batch);
+        ordered_sum<false>(q.opart + q.width + 1, q.width + 2, q.nblk) / float(q.batch);
   if (i >= q.n_params) return;
-  const float gi = g_in ? g_in[i] : assembled_grad(q, i);
+  const float gi = g_in ? g_in[i] : assembled_grad<false>(q, i);
   if (g_out) g_out[i] = gi;
   if (lr < 0.0f) return;  // gradient only
   const float pi = adam_value(gi, p[i], m[i], v[i], lr, c->bc1, c->bc2);
