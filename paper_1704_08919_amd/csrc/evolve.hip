@@ -193,21 +193,25 @@ __device__ __forceinline__ const double2* halving_coef() {
   return cs;
 }
 
-// The chunk beyond the fits: C and S of degree 7 with angle halvings.
-template <int MPL>
+// The chunk beyond the fits: C and S of degree 7 with angle halvings.  q is formed from p - A: from (p - A) / e its
+// relative error would be twice as large, the same in every step, and the angle is large here.  momentum(j, px,
+// py) gives the momentum of the lane's mode j, which only these chunks need.
+template <int MPL, class Momentum>
 __device__ __forceinline__ void run_halving(State (&v)[MPL], const double2* buf, int len, double xb, double dt,
-                                            const CotMode (&m)[MPL]) {
+                                            const CotMode (&m)[MPL], const Momentum& momentum) {
   const int h = halvings(xb);
   const double inv4h = ldexp(1.0, -2 * h);
   const double2* cs = halving_coef();
+  double px[MPL], py[MPL];
+#pragma unroll
+  for (int j = 0; j < MPL; ++j) momentum(j, px[j], py[j]);
 #pragma unroll 1
   for (int n = 0; n < len; ++n) {
     const double2 rec = buf[n];
 #pragma unroll
     for (int j = 0; j < MPL; ++j) {
-      // back to units of 1/dt: q = e dt q'
       const double qz = m[j].e * dt;
-      const double qx = qz * fma(rec.x, m[j].nie, m[j].px), qy = qz * fma(rec.y, m[j].nie, m[j].py);
+      const double qx = (px[j] - rec.x) * dt, qy = (py[j] - rec.y) * dt;
       double C, S;
       halved_cos_sinc(fma(qx, qx, fma(qy, qy, qz * qz)) * inv4h, h, cs, C, S);
       rotate(v[j], C, S, qx, qy, qz);
@@ -216,9 +220,9 @@ __device__ __forceinline__ void run_halving(State (&v)[MPL], const double2* buf,
 }
 
 // The steps of one chunk, in the variant that the bound xb on its (omega dt)^2 selects.
-template <int MPL, bool ROW>
+template <int MPL, bool ROW, class Momentum>
 __device__ __forceinline__ void run_chunk(State (&v)[MPL], const double2* buf, int len, double xb, double dt,
-                                          const CotMode (&m)[MPL]) {
+                                          const CotMode (&m)[MPL], const Momentum& momentum) {
   switch (cot_variant(xb, dt)) {
     case 0: run_cot<0, MPL, ROW>(v, buf, len, dt, m); break;
     case 1: run_cot<1, MPL, ROW>(v, buf, len, dt, m); break;
@@ -229,7 +233,7 @@ __device__ __forceinline__ void run_chunk(State (&v)[MPL], const double2* buf, i
     case 6: run_cot<6, MPL, ROW>(v, buf, len, dt, m); break;
     case 7: run_cot<7, MPL, ROW>(v, buf, len, dt, m); break;
     case 8: run_cot<8, MPL, ROW>(v, buf, len, dt, m); break;
-    default: run_halving<MPL>(v, buf, len, xb, dt, m); break;
+    default: run_halving<MPL>(v, buf, len, xb, dt, m, momentum); break;
   }
 }
 
@@ -252,9 +256,9 @@ __device__ __forceinline__ ItemTab item_tab(const EvolveArgs& a, const PulseDev&
 // through LDS chunk by chunk; the series variant of each piece is chosen from the item's selection
 // block (items never straddle blocks) and the chunk's table range, so it depends only on the pulse,
 // the block and the chunk, never on the launch.
-template <int THREADS, int MPL, bool ROW = false>
+template <int THREADS, int MPL, bool ROW = false, class Momentum>
 __device__ __forceinline__ void propagate(State (&v)[MPL], const ItemTab& t, int n0, int n1, const CotMode (&mode)[MPL],
-                                          double2* lds) {
+                                          const Momentum& momentum, double2* lds) {
 #pragma unroll
   for (int j = 0; j < MPL; ++j) v[j] = State{1.0, 0.0, 0.0, 0.0, 1.0, 0.0, 0.0, 0.0};
   for (int n = n0; n < n1;) {
@@ -263,7 +267,7 @@ __device__ __forceinline__ void propagate(State (&v)[MPL], const ItemTab& t, int
     for (int i = threadIdx.x; i < len; i += THREADS) lds[i] = t.tab[n + i];
     __syncthreads();
     const double* rg = t.rg + 4 * c;
-    run_chunk<MPL, ROW>(v, lds, len, x_bound(t.bb, rg[0], rg[1], rg[2], rg[3], t.dt), t.dt, mode);
+    run_chunk<MPL, ROW>(v, lds, len, x_bound(t.bb, rg[0], rg[1], rg[2], rg[3], t.dt), t.dt, mode, momentum);
     n += len;
   }
 }
@@ -307,9 +311,12 @@ __device__ __forceinline__ void process_item(const EvolveArgs& a, int pi, int fi
     lds.put(j, psi);
     mode[j] = cot_mode(px, py, e);
   }
+  const auto momentum = [&](int j, double& px, double& py) {
+    (void)lane_mode(d, int64_t(first) + j * THREADS + threadIdx.x, px, py);
+  };
   for (int n0 = 0; n0 < d.nt; n0 += d.seg_len) {
     State v[MPL];
-    propagate<THREADS, MPL, ROW>(v, t, n0, min(n0 + d.seg_len, d.nt), mode, lds.tab);
+    propagate<THREADS, MPL, ROW>(v, t, n0, min(n0 + d.seg_len, d.nt), mode, momentum, lds.tab);
 #pragma unroll
     for (int j = 0; j < MPL; ++j) {
       State psi = lds.get(j);
@@ -340,7 +347,7 @@ __global__ void __launch_bounds__(kItem) __attribute__((amdgpu_waves_per_eu(4)))
 
 // Two items per workgroup, two modes per lane, where pair_rows says so: the modes m and m + 256 of a lane then lie in
 // the same column p_x of the same plane p_z and share q'_x, its square and the coefficients of K: 2 of 66 operations.
-// 182 VGPRs, two waves per SIMD (three, with spills around the step loops, measured the same).
+// 185 VGPRs, two waves per SIMD (three, with spills around the step loops, measured the same).
 __global__ void __launch_bounds__(kItem) __attribute__((amdgpu_waves_per_eu(2))) k_evolve_rows(EvolveArgs a) {
   __shared__ ItemLds<kItem, 2> lds;
   const int item = 2 * xcd_item(blockIdx.x, gridDim.x);
@@ -360,8 +367,9 @@ k_segments(EvolveArgs a, int64_t slot0, double* __restrict__ prop) {
   double px, py;
   const double e = lane_mode(d, int64_t(li) * kItem + threadIdx.x, px, py);
   const CotMode mode[1] = {cot_mode(px, py, e)};
+  const auto momentum = [&](int, double& x, double& y) { (void)lane_mode(d, int64_t(li) * kItem + threadIdx.x, x, y); };
   State v[1];
-  propagate<kItem, 1>(v, item_tab(a, d, li * kItem), seg * d.seg_len, min((seg + 1) * d.seg_len, d.nt), mode, lds);
+  propagate<kItem, 1>(v, item_tab(a, d, li * kItem), seg * d.seg_len, min((seg + 1) * d.seg_len, d.nt), mode, momentum, lds);
   store_state(prop, slot - slot0, v[0]);
 }
 

@@ -403,9 +403,9 @@ __global__ void __launch_bounds__(64) k_grad_join(GradArgs a) {
 
 // Backward steps of a piece (len records of tab, last first) in fit variant MODE, kGroup steps at a time
 // (a short group first), with the per-wave step sums in red[wave].
-template <int MODE>
+template <int MODE, class Momentum>
 __device__ __forceinline__ void back_piece(WPair& w, const double2* tab, int len, const BackMode& m, double xb,
-                                           double2 (*buf)[64], double2* red, int lane) {
+                                           double2 (*buf)[64], double2* red, int lane, const Momentum& momentum) {
   int top = len - 1;
   const int r = len % kGroup;
   if constexpr (MODE < kFineHalving) {
@@ -426,11 +426,13 @@ __device__ __forceinline__ void back_piece(WPair& w, const double2* tab, int len
     int h = 0;
     for (double x = xb; x > kCosSinXmax && h < kMaxHalvings; x *= 0.25) ++h;
     const double inv4h = ldexp(1.0, -2 * h);
+    double px, py, dt;  // q from p - A, as the evolution's angle-halving path
+    momentum(px, py, dt);
     for (int n = r != 0 ? r : kGroup; top >= 0; top -= n, n = kGroup) {
 #pragma unroll 1
       for (int j = 0; j < n; ++j) {
         const double2 A = tab[top - j];
-        const double2 g = back_w_exact(w, fma(A.x, m.nie, m.px) * m.qz, fma(A.y, m.nie, m.py) * m.qz, m.qz, h, inv4h);
+        const double2 g = back_w_exact(w, (px - A.x) * dt, (py - A.y) * dt, m.qz, h, inv4h);
         buf[j][lane] = make_double2(g.x + g.x, g.y + g.y);
       }
       group_store(buf, red, lane, top, n);
@@ -481,6 +483,10 @@ __global__ void __launch_bounds__(kItem) __attribute__((amdgpu_waves_per_eu(3)))
   const BlockBox bb{uniform(b0.pxl), uniform(b0.pxh), uniform(b0.pyl), uniform(b0.pyh), uniform(b0.pz2)};
   const double* rg = a.ranges + 4 * int64_t(d.chk_off);
   double2* part = reinterpret_cast<double2*>(a.part + (d.part_off - a.part0) + int64_t(li) * d.nt * 2);
+  const auto momentum = [&](double& x, double& y, double& step) {
+    (void)lane_mode(d, int64_t(li) * kItem + threadIdx.x, x, y);
+    step = d.dt;
+  };
   const int n0 = seg * d.seg_len;
   for (int n1 = min(n0 + d.seg_len, d.nt); n1 > n0;) {
     const int c = (n1 - 1) / kChunk, beg = max(n0, c * kChunk), len = n1 - beg;
@@ -489,15 +495,15 @@ __global__ void __launch_bounds__(kItem) __attribute__((amdgpu_waves_per_eu(3)))
     __syncthreads();
     const double xb = x_bound(bb, rg[4 * c], rg[4 * c + 1], rg[4 * c + 2], rg[4 * c + 3], dt);
     switch (tan_variant(xb)) {
-      case 0: back_piece<0>(w, tab, len, m, xb, bufs[wave], red[wave], lane); break;
-      case 1: back_piece<1>(w, tab, len, m, xb, bufs[wave], red[wave], lane); break;
-      case 2: back_piece<2>(w, tab, len, m, xb, bufs[wave], red[wave], lane); break;
-      case 3: back_piece<3>(w, tab, len, m, xb, bufs[wave], red[wave], lane); break;
-      case 4: back_piece<4>(w, tab, len, m, xb, bufs[wave], red[wave], lane); break;
-      case 5: back_piece<5>(w, tab, len, m, xb, bufs[wave], red[wave], lane); break;
-      case 6: back_piece<6>(w, tab, len, m, xb, bufs[wave], red[wave], lane); break;
-      case 7: back_piece<7>(w, tab, len, m, xb, bufs[wave], red[wave], lane); break;
-      default: back_piece<kFineHalving>(w, tab, len, m, xb, bufs[wave], red[wave], lane); break;
+      case 0: back_piece<0>(w, tab, len, m, xb, bufs[wave], red[wave], lane, momentum); break;
+      case 1: back_piece<1>(w, tab, len, m, xb, bufs[wave], red[wave], lane, momentum); break;
+      case 2: back_piece<2>(w, tab, len, m, xb, bufs[wave], red[wave], lane, momentum); break;
+      case 3: back_piece<3>(w, tab, len, m, xb, bufs[wave], red[wave], lane, momentum); break;
+      case 4: back_piece<4>(w, tab, len, m, xb, bufs[wave], red[wave], lane, momentum); break;
+      case 5: back_piece<5>(w, tab, len, m, xb, bufs[wave], red[wave], lane, momentum); break;
+      case 6: back_piece<6>(w, tab, len, m, xb, bufs[wave], red[wave], lane, momentum); break;
+      case 7: back_piece<7>(w, tab, len, m, xb, bufs[wave], red[wave], lane, momentum); break;
+      default: back_piece<kFineHalving>(w, tab, len, m, xb, bufs[wave], red[wave], lane, momentum); break;
     }
     __syncthreads();
     if (int(threadIdx.x) < len) {
