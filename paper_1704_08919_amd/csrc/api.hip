@@ -207,7 +207,6 @@ po_status build_batch(int32_t n, const po_pulse_spec* specs, const po_grid* grid
       b->max_lines = std::max(b->max_lines, d.nlines);
       b->max_ns = std::max(b->max_ns, d.ns);
       b->max_stat_blocks = std::max(b->max_stat_blocks, d.stat_blocks);
-      if (i > 0 && (s.nt != specs[0].nt || s.T != specs[0].T)) b->uniform = false;
     }
     if (grids) {
       const po_grid& g = grids[i];
@@ -230,7 +229,6 @@ po_status build_batch(int32_t n, const po_pulse_spec* specs, const po_grid* grid
       modes += m;
       units += d.nunits;
       items += d.nitems;
-      if (i > 0 && std::memcmp(&g, &grids[0], sizeof g) != 0) b->uniform = false;
     }
     out[i] = d;
   }

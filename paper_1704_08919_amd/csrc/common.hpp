@@ -97,7 +97,6 @@ struct Batch {
   int32_t max_nt = 0;
   int32_t max_lines = 0;       // most spectral lines of any pulse
   int32_t max_ns = 0;          // most B-spline coefficients per spectral function of any pulse
-  bool uniform = true;         // all pulses share nt/grid (lets kernels skip the binary search)
 };
 
 po_status validate_spec(const po_pulse_spec& s, int i);

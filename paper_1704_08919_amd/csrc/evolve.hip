@@ -246,9 +246,8 @@ struct ItemTab {
 };
 
 __device__ __forceinline__ ItemTab item_tab(const EvolveArgs& a, const PulseDev& d, int first) {
-  const BlockBox bb = block_box(d, first / kSelBlock, d.ndist);
   return ItemTab{reinterpret_cast<const double2*>(a.A) + d.tab_off, a.ranges + 4 * int64_t(d.chk_off),
-                 BlockBox{uniform(bb.pxl), uniform(bb.pxh), uniform(bb.pyl), uniform(bb.pyh), uniform(bb.pz2)}, d.dt};
+                 uniform_box(d, first), d.dt};
 }
 
 // Propagators of steps [n0, n1) for the MPL modes of a lane: the first column per block of a multiple of
@@ -567,11 +566,6 @@ struct SchemeArgs {
   double* units;
 };
 
-__device__ __forceinline__ BlockBox uniform_box(const PulseDev& d, int first) {
-  const BlockBox bb = block_box(d, first / kSelBlock, d.ndist);
-  return BlockBox{uniform(bb.pxl), uniform(bb.pxh), uniform(bb.pyl), uniform(bb.pyh), uniform(bb.pz2)};
-}
-
 // The fourth-order scheme for one lane's mode.  Step s: exp(-i w_s . tau), a multiple of K(|w_s|^2) - i w_s . tau
 // with K = sqrt(x) cot(sqrt x): 50 + 2n instructions for the two blocks (56 + 2n in the tangent form, whose
 // fits need a larger n and end at x = 0.26; 110 and more beyond).  The norm grows by at most 1.58 per step
@@ -675,16 +669,6 @@ struct Magnus4Scheme {
 // ---------------------------------------------------------------------------------------------
 constexpr double kTripleW1 = 1.3512071919596576;   // 1 / (2 - 2^(1/3))
 constexpr double kTripleW0 = -1.7024143839193153;  // 1 - 2 w1
-
-template <int NSUB>
-struct SplitMode {
-  double pxw[NSUB == 1 ? 1 : 2], pyw[NSUB == 1 ? 1 : 2];  // p w dt for the distinct weights
-  double a[NSUB == 1 ? 1 : 2], c[NSUB == 1 ? 1 : 2], s[NSUB == 1 ? 1 : 2];  // tan, cos, sin of theta_i
-};
-
-// Weight index (into pxw, pyw) and angle index (into a, c, s) of substep i.
-__device__ __forceinline__ constexpr int split_w(int i) { return i == 1 ? 1 : 0; }
-__device__ __forceinline__ constexpr int split_t(int i) { return i == 2 ? 1 : 0; }
 
 // psi <- R(phi) psi for both blocks: a <- a e^{-i phi}, b <- b e^{i phi}.
 __device__ __forceinline__ void phase_z(State& v, double cp, double sp) {
@@ -961,7 +945,8 @@ po_status launch_chunk_ranges(const Batch& b, const PulseDev* d_desc, const doub
 // the 3% that the shared operations save: 2 ceil(items / 512) of its items against ceil(items / 256).
 // Measured, 64x64x16 modes at nt = 4096, us per call paired / single: 512 items 804 / 814, 640 items 1202 / 1024,
 // 1024 items 1288 / 1323, 1152 items 1756 / 1565, 2048 items 2461 / 2520, 2304 items 2961 / 2811, 3072 items
-// 3632 / 3737; and 8192 items at nt = 16384 35.5 / 36.6 ms.
+// 3632 / 3737; and 8192 items at nt = 16384 35.5 / 36.6 ms.  Other grids, nt = 2048: 16x64x128 (512 items) 314 / 321,
+// 128x128x32 (2048) 1159 / 1202, 256x256x8 1156 / 1203, 32x32x512 1177 / 1222.
 bool pair_rows(const Batch& b) {
   const int64_t single = (int64_t(b.total_items) + 255) / 256, paired = 2 * ((int64_t(b.total_items) + 511) / 512);
   return b.row_pairs && 100 * single >= 97 * paired;
@@ -980,7 +965,11 @@ po_status launch_evolve_grid(const Batch& b, const PulseDev* d_desc, const doubl
 // pulse at nt = 4096, us per call split / not split: 16 items 75 / 357, 128 items 190 / 344, 256 items
 // 329 / 352, 320 items 402 / 581 (some CUs then hold two workgroups, the others one), 384 items
 // 480 / 594, 512 items 619 / 626 and, at nt = 1024, 194 / 177.  At most 8192 slots (128 MiB of
-// propagators).
+// propagators).  Short tables pay for the second kernel: at nt = 256, 256 items 48 / 48, 448 items 65 / 59.  The line
+// is the same for the schemes, whose steps cost more.  Fourth-order Magnus: nt = 4096, 256 items 541 / 618,
+// 384 items 794 / 1049, 448 items 918 / 1069, 512 items 1041 / 1103; nt = 1024, 448 items 259 / 289; nt = 256, 87 / 88.
+// Strang, nt = 4096: 448 items 592 / 656, 512 items 671 / 673; nt = 256: 448 items 68 / 62.  Its composition, nt = 4096:
+// 448 items 1761 / 2036, 512 items 2003 / 2091; nt = 256: 448 items 140 / 148.
 bool split_in_time(const Batch& b) {
   return b.total_items <= 448 && b.total_slots > b.total_items && b.total_slots <= 8192;
 }

@@ -479,8 +479,7 @@ __global__ void __launch_bounds__(kItem) __attribute__((amdgpu_waves_per_eu(3)))
   m.z2 = m.z + m.z;
   const double* wp = a.prop + int64_t(blockIdx.x) * kSlotDoubles + threadIdx.x;
   WPair w{wp[0], wp[kItem], wp[2 * kItem], wp[3 * kItem], wp[4 * kItem], wp[5 * kItem]};
-  const BlockBox b0 = block_box(d, li * kItem / kSelBlock, d.ndist);
-  const BlockBox bb{uniform(b0.pxl), uniform(b0.pxh), uniform(b0.pyl), uniform(b0.pyh), uniform(b0.pz2)};
+  const BlockBox bb = uniform_box(d, li * kItem);
   const double* rg = a.ranges + 4 * int64_t(d.chk_off);
   double2* part = reinterpret_cast<double2*>(a.part + (d.part_off - a.part0) + int64_t(li) * d.nt * 2);
   const auto momentum = [&](double& x, double& y, double& step) {

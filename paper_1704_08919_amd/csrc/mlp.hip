@@ -1074,7 +1074,7 @@ int splits_for(int B) {
   return kt % 4 == 0 ? 4 : (kt % 2 == 0 ? 2 : 1);
 }
 
-// Widths the fused kernels take: up to two 32-column tiles per wave, and the LDS of a workgroup.
+// Widths the fused kernels take: up to two 16-column tiles per wave, and the LDS of a workgroup.
 bool net_fused(const po_mlp* a) { return a->width <= kFusedWidth && a->n_in <= kFusedWidth; }
 
 ParamMap param_map(const po_mlp* a, int B) {

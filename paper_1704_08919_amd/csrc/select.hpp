@@ -43,6 +43,12 @@ __device__ __forceinline__ double uniform(double v) {
                           __builtin_amdgcn_readfirstlane(__double2loint(v)));
 }
 
+// Box of the selection block that distinct mode `first` (the same in all lanes) lies in, in scalar registers.
+__device__ __forceinline__ BlockBox uniform_box(const PulseDev& d, int first) {
+  const BlockBox bb = block_box(d, first / kSelBlock, d.ndist);
+  return BlockBox{uniform(bb.pxl), uniform(bb.pxh), uniform(bb.pyl), uniform(bb.pyh), uniform(bb.pz2)};
+}
+
 // Upper 32 bits of a positive double (ordered as the doubles are).
 constexpr uint32_t high_word(double v) { return uint32_t(__builtin_bit_cast(uint64_t, v) >> 32); }
 
