@@ -147,7 +147,6 @@ __global__ void __launch_bounds__(128) k_spectra(const PulseDev* __restrict__ de
   // leaves out: a coefficient that is not finite spoils its component here, through the first line.
   bool odd = false;
   for (int i = t; i < 4 * d.ns; i += 128) odd = odd || !isfinite(a[i]);
-  const bool spoilt = __syncthreads_or(odd);
   double a0x = 0.0, a0y = 0.0;
   if (t < 2) c0[t] = 0.0;
   for (int i0 = 0; i0 < nh; i0 += kSpecTile) {
@@ -156,8 +155,6 @@ __global__ void __launch_bounds__(128) k_spectra(const PulseDev* __restrict__ de
     if (j >= 0 && j < d.nlines) {
       double E[2], ph[2], sp, cp;
       line_spectrum(d, a, j, E, ph);
-      if (spoilt && j == 0)
-        for (int i = 0; i < 4 * d.ns; ++i) E[i / (2 * d.ns)] += 0.0 * a[i];
       sincos(ph[0], &sp, &cp);
       q.x = E[0] * cp;
       q.y = E[0] * sp;
@@ -165,7 +162,13 @@ __global__ void __launch_bounds__(128) k_spectra(const PulseDev* __restrict__ de
       q.z = E[1] * cp;
       q.w = E[1] * sp;
     }
-    __syncthreads();
+    if (i0 > 0) {
+      __syncthreads();
+    } else if (__syncthreads_or(odd) && j == 0) {
+      double zero[2] = {0.0, 0.0};
+      for (int i = 0; i < 4 * d.ns; ++i) zero[i / (2 * d.ns)] += 0.0 * a[i];
+      q = make_double4(q.x + zero[0], q.y + zero[0], q.z + zero[1], q.w + zero[1]);
+    }
     raw[t] = q;
     __syncthreads();
     const int i = i0 + t;
