@@ -278,6 +278,7 @@ template <int THREADS, int MPL>
 struct ItemLds {
   double2 tab[kChunk];
   double psi[MPL][8][THREADS];
+  double2 mom[MPL][THREADS];  // p_x, p_y of the lane's modes, for chunks beyond the fits
   __device__ __forceinline__ void put(int j, const State& v) {
     double(*p)[THREADS] = psi[j];
     const int t = threadIdx.x;
@@ -308,10 +309,13 @@ __device__ __forceinline__ void process_item(const EvolveArgs& a, int pi, int fi
     State psi;
     init_state(psi, px - ain.x, py - ain.y, e);
     lds.put(j, psi);
+    lds.mom[j][threadIdx.x] = make_double2(px, py);
     mode[j] = cot_mode(px, py, e);
   }
   const auto momentum = [&](int j, double& px, double& py) {
-    (void)lane_mode(d, int64_t(first) + j * THREADS + threadIdx.x, px, py);
+    const double2 p = lds.mom[j][threadIdx.x];
+    px = p.x;
+    py = p.y;
   };
   for (int n0 = 0; n0 < d.nt; n0 += d.seg_len) {
     State v[MPL];
@@ -346,7 +350,7 @@ __global__ void __launch_bounds__(kItem) __attribute__((amdgpu_waves_per_eu(4)))
 
 // Two items per workgroup, two modes per lane, where pair_rows says so: the modes m and m + 256 of a lane then lie in
 // the same column p_x of the same plane p_z and share q'_x, its square and the coefficients of K: 2 of 66 operations.
-// 185 VGPRs, two waves per SIMD (three, with spills around the step loops, measured the same).
+// 184 VGPRs, two waves per SIMD (three, with spills around the step loops, measured the same).
 __global__ void __launch_bounds__(kItem) __attribute__((amdgpu_waves_per_eu(2))) k_evolve_rows(EvolveArgs a) {
   __shared__ ItemLds<kItem, 2> lds;
   const int item = 2 * xcd_item(blockIdx.x, gridDim.x);
