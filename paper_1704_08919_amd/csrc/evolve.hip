@@ -26,14 +26,13 @@
 // from truncated Maclaurin series (remainder below 2^-56).  Either is shared by both blocks, because
 // omega does not depend on s.
 //
-// What bounds it: FP64 issue, at the clock the power limit leaves (a chain of v_fma_f64 on distinct
-// registers runs at 1.85-1.95 GHz on this card, 0.73 of the 2.4 GHz peak at four waves per SIMD and
-// 0.77 at eight), so the time follows the number of FP64 instructions: 28 + n per mode-step with n =
-// 5.2 on average on the 64-pulse 64x64x16 nt = 16384 workload, against 31 + 6.2 for the tangent form
-// that this replaced there: 73.6 ms per generation against 80.9 (A/B on one card) when every mode was
-// stepped, 36.8 ms with the distinct modes of the mirror-symmetric grid alone.  Five or six waves
-// per SIMD (96 or 80 VGPRs) measured 74.5 and 75.5 ms, two or one steps per loop iteration at four
-// waves 74.0 ms and slower (every mode stepped).
+// What bounds it: FP64 issue (an FP64 instruction in 0.78-0.81 of the cycles at the 2.4 GHz peak clock; a loop of nothing
+// but v_fma_f64 chains issues at 0.78-0.80 at four waves per SIMD and at 0.89-0.91 at eight), so the time
+// follows the number of FP64 instructions: 28 + n per mode-step with n = 5.2 on average on the 64-pulse
+// 64x64x16 nt = 16384 workload, against 31 + 6.2 for the tangent form that this replaced there: 73.6 ms per
+// generation against 80.9 (A/B on one card) when every mode was stepped, 36.8 ms with the distinct modes
+// of the mirror-symmetric grid alone.  Five or six waves per SIMD (96 or 80 VGPRs) measured 74.5 and
+// 75.5 ms, two or one steps per loop iteration at four waves 74.0 ms and slower (every mode stepped).
 //
 // Work decomposition: a workgroup of THREADS lanes (64-wide waves) owns an item of
 // THREADS x MPL consecutive modes of one pulse, MPL modes per lane.  The pulse's table of A

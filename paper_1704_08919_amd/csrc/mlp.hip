@@ -424,7 +424,8 @@ __global__ void __launch_bounds__(256) k_out_fwd(const __bf16* __restrict__ h, c
 // are those of the layer-by-layer kernels (mm_body, k_out_train), in their order.
 // A batch of 1024 fills 32 of the chip's 256 compute units, and each wave waits for a chain of loads, products
 // and activation functions: 24 us for three layers of 256 (32 with row-major copies, 39 also without the early
-// loads and with eight waves; a training step, with k_step, 33 us against 68 in nine launches).  16 samples
+// loads and with eight waves; a training step, with k_step, 33 us against 68 in nine launches).  With sixteen waves
+// the training form spills between the layers: 9 VGPRs, 34 with two column tiles per wave.  16 samples
 // per workgroup would halve the activation functions' share, but add the bias and output
 // gradients in another order, which Adam turns into other weights within a few steps.  Wider
 // networks take the layer-by-layer kernels, whose products fill the chip by themselves.

@@ -25,8 +25,9 @@
 // at two new points.
 //
 // Bound by FP64 issue, 141 FP64 instructions and four reciprocal square roots per step, with one wave per SIMD at
-// 65536 modes: 12000 steps take 4.0 ms.  The next step's coefficients are formed alongside this step's
-// stages, which do not depend on them: 4.25 ms when formed at the step's start, where the wave
+// 65536 modes: 12000 steps take 4.0-4.3 ms on the cards measured.  The next step's coefficients are formed
+// alongside this step's stages, which do not depend on them: 3.99 ms against 4.26 ms, in turn on one
+// card, when they were formed at the step's start, where the wave
 // waits for them.  (5.8 ms with the math library's rsqrt, which classifies its argument and scales the
 // result, and a test of X per lane.)
 #include "reduce.hpp"
